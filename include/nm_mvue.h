@@ -324,7 +324,7 @@ int nm_rw_mix_probe(const void *src, void *dst, int64_t n_blocks, void *hip_stre
  *     rec[1] = 1/s  rec[2] = the bit pattern of max|t|   rec[3] = 0 (scratch of the record's consumer, see below)
  * t: [R x C] of NM_F32 or NM_BF16, row stride ld, C % 8 == 0.  top: the largest magnitude the 8-bit format is to
  * hold: 448 for e4m3 activations; 57344/4 for e5m2 gradients pruned 2:4 and 57344/2 for 1:2 (a kept value is at most
- * the sum of its block's magnitudes).  Three small kernels on the stream; the maximum is an order-independent atomic,
+ * the sum of its block's magnitudes).  Two kernels on the stream; the maximum is an order-independent atomic,
  * so the record is reproducible.
  *
  * nm_cast_e4m3: h8[r][c] = e4m3(h[r][c] * rec[0]) -- one binary32 product, round to nearest even, magnitudes beyond
