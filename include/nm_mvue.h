@@ -366,6 +366,22 @@ int nm_update_gemm_q8_shifted_ds(const uint8_t *vals8, const uint32_t *meta32, c
                                  const float *scale_rec_g, float *scale_rec_x, float beta,
                                  void *workspace, size_t workspace_bytes, void *hip_stream);
 
+/*
+ * Weight gradient of a k x k, stride-1, "same"-padded convolution in one call (bf16 tensors): the update phase above --
+ * padded grid, 2:4 prune, update GEMM on shifted views -- straight from the tensors a layer holds, without the grid of
+ * the gradient and with the result in the weight's own layout and type.
+ *   gy [N, O, H, W], x [N, C, H, W]   bf16, contiguous as channel planes, or (channels_last != 0) as [N, H, W, channels]
+ *   dW [O, C, k, k]                   bf16, contiguous
+ * Masks and kept values are those of mvue_prune_2of4 (q8 != 0: mvue_prune_2of4_q8_ds with nm_q8_scale's record) on the
+ * gradient's zero-padded channels-last grid, rows rounded up to a multiple of 16 (32); same mode, seed, stream_id.
+ * q8: scales, the e4m3 cast and the 8-bit product are part of the call.  k odd, k*k <= 32; O % 8 == 0, C % 8 == 0
+ * (q8: C % 16 == 0).  workspace: nm_conv_update_workspace(...) bytes (0 for sizes the call does not take).
+ */
+int nm_conv_update(const void *gy, int gy_channels_last, const void *x, int x_channels_last, int64_t N, int64_t C, int64_t O,
+                   int64_t H, int64_t W, int k, int q8, int mode, uint64_t seed, uint32_t stream_id, void *dW,
+                   void *workspace, size_t workspace_bytes, void *hip_stream);
+size_t nm_conv_update_workspace(int64_t N, int64_t C, int64_t O, int64_t H, int64_t W, int k, int q8);
+
 /* Message of the last error on this thread ("" if none).  Static storage; do not free. */
 const char *nm_last_error(void);
 

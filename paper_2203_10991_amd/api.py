@@ -88,6 +88,10 @@ def load():
     lib.nm_update_gemm_q8_ds.restype = i32
     lib.nm_update_gemm_q8_shifted_ds.argtypes = [vp, vp, vp, i64, i64, vp, i32, vp, i64, i64, i64, vp, vp, f32, vp, sz, vp]
     lib.nm_update_gemm_q8_shifted_ds.restype = i32
+    lib.nm_conv_update.argtypes = [vp, i32, vp, i32, i64, i64, i64, i64, i64, i32, i32, i32, u64, u32, vp, vp, sz, vp]
+    lib.nm_conv_update.restype = i32
+    lib.nm_conv_update_workspace.argtypes = [i64, i64, i64, i64, i64, i32, i32]
+    lib.nm_conv_update_workspace.restype = sz
     for f in (lib.mvue_prune_1of2, lib.mvue_prune_2of4, lib.nm_compress, lib.nm_update_gemm, lib.mvue_prune_2of4_q8,
               lib.nm_update_gemm_q8):
         f.restype = i32
@@ -522,4 +526,42 @@ def nm_update_gemm_q8_shifted(vals8: torch.Tensor, meta32: torch.Tensor, x8_full
     else:
         _check(lib.nm_update_gemm_q8_shifted(_ptr(vals8), _ptr(meta32), xp, ldx, Cb, sh, n, _ptr(dW), lddw, T, O, float(alpha),
                                              float(beta), _ptr(workspace), wbytes, _stream(x8_full)))
+    return dW
+
+
+# ---- layers: one call per weight gradient
+
+def _image_layout(t: torch.Tensor):
+    """(tensor, channels_last) of a 4-D tensor as nm_conv_update takes it: contiguous in one of the two layouts."""
+    if t.is_contiguous():
+        return t, 0
+    if t.is_contiguous(memory_format=torch.channels_last):
+        return t, 1
+    return t.contiguous(), 0
+
+
+def nm_conv_update_workspace(N: int, C: int, O: int, H: int, W: int, k: int, q8: bool = False) -> int:
+    """Bytes of workspace of nm_conv_update; 0 where it does not take the sizes."""
+    return int(load().nm_conv_update_workspace(N, C, O, H, W, k, int(q8)))
+
+
+def nm_conv_update(gy: torch.Tensor, x: torch.Tensor, k: int, q8: bool = False, mode: int = 0, seed: int = 0, stream_id: int = 0,
+                   workspace: Optional[torch.Tensor] = None) -> torch.Tensor:
+    """Weight gradient [O, C, k, k] (bf16) of a k x k, stride-1, "same" convolution from gy [N, O, H, W] and x [N, C, H, W] (bf16):
+    2:4 prune of gy on the zero-padded channels-last grid and the update GEMM on shifted views, in one library call."""
+    lib = load()
+    if gy.dtype != torch.bfloat16 or x.dtype != torch.bfloat16 or not (gy.is_cuda and x.is_cuda):
+        raise TypeError("nm_conv_update takes bfloat16 tensors on the GPU")
+    N, O, H, W = gy.shape
+    C = x.shape[1]
+    if tuple(x.shape) != (N, C, H, W):
+        raise ValueError(f"x {tuple(x.shape)} does not fit gy {tuple(gy.shape)}")
+    need = nm_conv_update_workspace(N, C, O, H, W, k, q8)
+    gy, g_cl = _image_layout(gy)
+    x, x_cl = _image_layout(x)
+    if workspace is None or workspace.numel() * workspace.element_size() < need:
+        workspace = torch.empty(max(need, 1), dtype=torch.uint8, device=gy.device)
+    dW = torch.empty((O, C, k, k), dtype=torch.bfloat16, device=gy.device)
+    _check(lib.nm_conv_update(_ptr(gy), g_cl, _ptr(x), x_cl, N, C, O, H, W, k, int(q8), mode, seed, stream_id, _ptr(dW), _ptr(workspace),
+                              workspace.numel() * workspace.element_size(), _stream(gy)))
     return dW

@@ -97,12 +97,15 @@ def _conv_update_shifted(gy: torch.Tensor, x: torch.Tensor, k: int, cfg: NMConfi
     activation rows (nm_update_gemm_shifted).  The N:M blocks run along the rows of that padded grid."""
     if not (gy.is_cuda and x.is_cuda):
         raise RuntimeError("the N:M update phase runs on the GPU only (no CPU fallback)")
+    q8 = cfg.precision == "q8"
+    N, O, H, W = gy.shape
+    if gy.dtype == torch.bfloat16 and api.nm_conv_update_workspace(N, x.shape[1], O, H, W, k, q8):
+        return api.nm_conv_update(gy, x, k, q8=q8, mode=cfg.mode, seed=cfg.current_seed(), stream_id=cfg.stream_id)
+    # sizes beyond the one-call form (grids of 2^31 rows): the same steps as tensor operations and separate library calls
     pad = k // 2
     xr, wp = padded_rows(x, pad)
     gr, _ = padded_rows(gy, pad)
     rows, C = xr.shape
-    O = gr.shape[1]
-    q8 = cfg.precision == "q8"
     T = (rows + 31) // 32 * 32 if q8 else (rows + 15) // 16 * 16
     margin = pad * wp + pad
     x_full = torch.zeros((T + 2 * margin, C), dtype=x.dtype, device=x.device)

@@ -786,8 +786,27 @@ hipError_t launch_update_gemm_smfmac(const void *vals, const uint16_t *meta, con
     return e;
 }
 
+// The kernels of a plan on the shift table (no 384-row tiles there), into `tg`
+static hipError_t run_shifted(const Plan &p, const OutTarget &tg, const void *vals, const uint16_t *meta, const void *x, int64_t ldx,
+                              int64_t cb, const int64_t *rows, int n, int64_t T, int64_t O, hipStream_t st)
+{
+    const int64_t I = cb * n;
+    const ShiftArg sh = make_shift_arg(cb, rows, n);
+    dim3 grid((unsigned)(p.tiles_m * p.tiles_n), 1, (unsigned)p.slabs);
+#define NM_LAUNCH(WM, WN, AB, BB)                                                                                     \
+    hipLaunchKernelGGL((update_gemm_smfmac_kernel<WM, WN, AB, BB, true>), grid, dim3(WM * WN * 64), 0, st,              \
+                       (const uint16_t *)vals, meta, (const uint16_t *)x, ldx, tg.out, tg.ldo, tg.slab_stride, T / 16,   \
+                       p.groups_per_slab, O, I, p.tiles_m, p.tiles_n, tg.accumulate, (int64_t)0, O, sh)
+    if (p.shape == 0) NM_LAUNCH(2, 4, 4, 2);
+    else if (p.shape == 1) NM_LAUNCH(2, 2, 2, 2);
+    else if (p.shape == 3) NM_LAUNCH(4, 2, 2, 2);
+    else NM_LAUNCH(1, 4, 2, 2);
+#undef NM_LAUNCH
+    return hipGetLastError();
+}
+
 // dW = beta*dW + decompress(vals, meta)^T [x shifted by rows[0] | x shifted by rows[1] | ...]  (I = n * cb columns).
-// Same plan as the plain GEMM of that size, on the kernels that take the shift table (no 384-row tiles).
+// Same plan as the plain GEMM of that size, on the kernels that take the shift table.
 hipError_t launch_update_gemm_smfmac_shifted(const void *vals, const uint16_t *meta, const void *x, int64_t ldx, int64_t cb,
                                              const int64_t *rows, int n, float *dW, int64_t lddw, int64_t T, int64_t O,
                                              float beta, void *workspace, hipStream_t st)
@@ -795,26 +814,26 @@ hipError_t launch_update_gemm_smfmac_shifted(const void *vals, const uint16_t *m
     const int64_t I = cb * n;
     if (O == 0 || I == 0) return hipSuccess;
     const Plan p = make_plan(T, O, I, true);
-    const ShiftArg sh = make_shift_arg(cb, rows, n);
     const int accumulate = beta != 0.f;
     const OutTarget tg = splitk_target(p.slabs, dW, lddw, workspace, O, I, accumulate);
-    float *out = tg.out;
-    const int64_t ldo = tg.ldo, slab_stride = tg.slab_stride;
-    const int acc_flag = tg.accumulate;
-    dim3 grid((unsigned)(p.tiles_m * p.tiles_n), 1, (unsigned)p.slabs);
-#define NM_LAUNCH(WM, WN, AB, BB)                                                                                     \
-    hipLaunchKernelGGL((update_gemm_smfmac_kernel<WM, WN, AB, BB, true>), grid, dim3(WM * WN * 64), 0, st,              \
-                       (const uint16_t *)vals, meta, (const uint16_t *)x, ldx, out, ldo, slab_stride, T / 16,            \
-                       p.groups_per_slab, O, I, p.tiles_m, p.tiles_n, acc_flag, (int64_t)0, O, sh)
-    if (p.shape == 0) NM_LAUNCH(2, 4, 4, 2);
-    else if (p.shape == 1) NM_LAUNCH(2, 2, 2, 2);
-    else if (p.shape == 3) NM_LAUNCH(4, 2, 2, 2);
-    else NM_LAUNCH(1, 4, 2, 2);
-#undef NM_LAUNCH
-    hipError_t e = hipGetLastError();
+    hipError_t e = run_shifted(p, tg, vals, meta, x, ldx, cb, rows, n, T, O, st);
     if (e != hipSuccess) return e;
     if (p.slabs > 1) e = launch_splitk_reduce((const float *)workspace, p.slabs, dW, lddw, O, I, accumulate, 1.0f, st);
     return e;
+}
+
+size_t update_gemm_smfmac_shifted_parts_bytes(int64_t T, int64_t O, int64_t I)
+{
+    return (size_t)make_plan(T, O, I, true).slabs * (size_t)O * (size_t)I * sizeof(float);
+}
+
+hipError_t launch_update_gemm_smfmac_shifted_parts(const void *vals, const uint16_t *meta, const void *x, int64_t ldx, int64_t cb,
+                                                   const int64_t *rows, int n, int64_t T, int64_t O, float *part, int *slabs, hipStream_t st)
+{
+    const int64_t I = cb * n;
+    const Plan p = make_plan(T, O, I, true);
+    *slabs = p.slabs;
+    return run_shifted(p, OutTarget{part, I, O * I, 0}, vals, meta, x, ldx, cb, rows, n, T, O, st);
 }
 
 }  // namespace nm

@@ -705,6 +705,24 @@ size_t update_gemm_q8_shifted_workspace(int64_t T, int64_t O, int64_t I)
     return splitk_workspace_bytes(make_plan_q8(T, O, I, true).slabs, O, I);
 }
 
+// The kernels of a plan on the shift table, into `tg`, scaled by `ap`
+static hipError_t run_q8_shifted(const PlanQ8 &p, const OutTarget &tg, const AlphaPair &ap, const uint8_t *vals8, const uint32_t *meta32,
+                                 const uint8_t *x8, int64_t ldx, int64_t cb, const int64_t *rows, int n, int64_t T, int64_t O, hipStream_t st)
+{
+    const int64_t I = cb * n;
+    const ShiftArg sh = make_shift_arg(cb, rows, n);
+    dim3 grid((unsigned)(p.tiles_m * p.tiles_n), 1, (unsigned)p.slabs);
+#define NM_LAUNCH(WM, WN, AB, BB)                                                                                     \
+    hipLaunchKernelGGL((update_gemm_smfmac_q8_kernel<WM, WN, AB, BB, true>), grid, dim3(WM * WN * 64), 0, st, vals8, meta32, x8, \
+                       ldx, tg.out, tg.ldo, tg.slab_stride, T / 32, p.groups_per_slab, O, I, p.tiles_m, p.tiles_n, ap.acc, ap.alpha,   \
+                       (int64_t)0, sh)
+    if (p.shape == 0) NM_LAUNCH(2, 4, 4, 2);
+    else if (p.shape == 1) NM_LAUNCH(2, 4, 2, 2);
+    else NM_LAUNCH(1, 4, 2, 2);
+#undef NM_LAUNCH
+    return hipGetLastError();
+}
+
 // dW = beta*dW + alpha * decompress(vals8, meta32)^T [x8 shifted by rows[0] | x8 shifted by rows[1] | ...]
 hipError_t launch_update_gemm_q8_shifted(const uint8_t *vals8, const uint32_t *meta32, const uint8_t *x8, int64_t ldx, int64_t cb,
                                          const int64_t *rows, int n, float *dW, int64_t lddw, int64_t T, int64_t O,
@@ -713,28 +731,28 @@ hipError_t launch_update_gemm_q8_shifted(const uint8_t *vals8, const uint32_t *m
     const int64_t I = cb * n;
     if (O == 0 || I == 0) return hipSuccess;
     const PlanQ8 p = make_plan_q8(T, O, I, true);
-    const ShiftArg sh = make_shift_arg(cb, rows, n);
     const int accumulate = beta != 0.f;
     const OutTarget tg = splitk_target(p.slabs, dW, lddw, workspace, O, I, accumulate);
-    float *out = tg.out;
-    const int64_t ldo = tg.ldo, slab_stride = tg.slab_stride;
     // partial sums are scaled once, in the second pass; otherwise the kernels scale, by a host or a device value
     const AlphaPair ap = p.slabs > 1 ? AlphaPair{tg.accumulate, 1.0f} : encode_alpha(tg.accumulate, alpha, st);
-    const int acc_flag = ap.acc;
-    const float k_alpha = ap.alpha;
-    dim3 grid((unsigned)(p.tiles_m * p.tiles_n), 1, (unsigned)p.slabs);
-#define NM_LAUNCH(WM, WN, AB, BB)                                                                                     \
-    hipLaunchKernelGGL((update_gemm_smfmac_q8_kernel<WM, WN, AB, BB, true>), grid, dim3(WM * WN * 64), 0, st, vals8, meta32, x8, \
-                       ldx, out, ldo, slab_stride, T / 32, p.groups_per_slab, O, I, p.tiles_m, p.tiles_n, acc_flag, k_alpha,   \
-                       (int64_t)0, sh)
-    if (p.shape == 0) NM_LAUNCH(2, 4, 4, 2);
-    else if (p.shape == 1) NM_LAUNCH(2, 4, 2, 2);
-    else NM_LAUNCH(1, 4, 2, 2);
-#undef NM_LAUNCH
-    hipError_t e = hipGetLastError();
+    hipError_t e = run_q8_shifted(p, tg, ap, vals8, meta32, x8, ldx, cb, rows, n, T, O, st);
     if (e != hipSuccess) return e;
     if (p.slabs > 1) e = launch_splitk_reduce((const float *)workspace, p.slabs, dW, lddw, O, I, accumulate, alpha, st);
     return e;
+}
+
+size_t update_gemm_q8_shifted_parts_bytes(int64_t T, int64_t O, int64_t I)
+{
+    return (size_t)make_plan_q8(T, O, I, true).slabs * (size_t)O * (size_t)I * sizeof(float);
+}
+
+hipError_t launch_update_gemm_q8_shifted_parts(const uint8_t *vals8, const uint32_t *meta32, const uint8_t *x8, int64_t ldx, int64_t cb,
+                                               const int64_t *rows, int n, int64_t T, int64_t O, float *part, int *slabs, hipStream_t st)
+{
+    const int64_t I = cb * n;
+    const PlanQ8 p = make_plan_q8(T, O, I, true);
+    *slabs = p.slabs;
+    return run_q8_shifted(p, OutTarget{part, I, O * I, 0}, AlphaPair{0, 1.0f}, vals8, meta32, x8, ldx, cb, rows, n, T, O, st);
 }
 
 }  // namespace nm

@@ -100,6 +100,12 @@ int launched(const char *fn, hipError_t e)
 
 }  // namespace
 
+// nm_last_error()'s slot for the other translation units of the ABI
+namespace nm {
+int abi_fail(int code, const char *message) { return fail(code, "%s", message); }
+void abi_clear() { g_err[0] = 0; }
+}  // namespace nm
+
 extern "C" {
 
 int mvue_prune_1of2(const void *g, int64_t T, int64_t O, int64_t ldg, int dtype, uint64_t seed, uint32_t stream_id,

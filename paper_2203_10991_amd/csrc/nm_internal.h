@@ -89,11 +89,35 @@ size_t update_gemm_q8_shifted_workspace(int64_t T, int64_t O, int64_t I);
 // 8-bit path, per-tensor scale and activation cast (q8_scale.hip).  rec: device float[4] = {s, 1/s, bits of max|t|, 0}
 // with s the largest power of two such that s * max|t| <= top (1 for an all-zero or non-finite tensor).
 hipError_t launch_q8_scale(int dt, const void *t, int64_t R, int64_t C, int64_t ld, float top, float *rec, hipStream_t st);
+// the scales of a layer's two bf16 tensors (R x C, row stride ld; not empty) in one pass of launches
+hipError_t launch_q8_scale_pair(const void *t0, int64_t R0, int64_t C0, int64_t ld0, float top0, float *rec0,
+                                const void *t1, int64_t R1, int64_t C1, int64_t ld1, float top1, float *rec1, hipStream_t st);
 // h8 = e4m3(h * rec[0]), round to nearest even, magnitudes beyond 448 saturate
 hipError_t launch_cast_e4m3(int dt, const void *h, int64_t R, int64_t C, int64_t ld, const float *rec, uint8_t *h8, int64_t ld8,
                             hipStream_t st);
 // measurement aid: streams 64 KB in and 36 KB out per block (the 16-bit prune's read:write mix)
 hipError_t launch_rw_mix_probe(const void *src, void *dst, int64_t n_blocks, hipStream_t st);
+
+// ---- layers (nm_layers.hip): a k x k, stride-1, "same" convolution on bf16 tensors [N, C, H, W] / [N, O, H, W], each stored
+// as channel planes or channels last
+struct ConvShape { int N, C, O, H, W, k; bool x_channels_last, g_channels_last; };
+// rows [-margin, out_rows - margin) of the zero-padded channels-last grid of the activations, as bf16 (rec == nullptr) or
+// e4m3(x * rec[0])
+hipError_t launch_grid_pack(const ConvShape &cs, const void *x, int64_t margin, int64_t out_rows, const float *rec, void *out, hipStream_t st);
+// 2:4 prune (est 0 optimal, 1 approx-MVUE) of the gradient on that grid, T rows; rec: 8-bit output in 32-token groups
+hipError_t launch_prune_grid(const ConvShape &cs, int est, const void *gy, int64_t T, uint64_t seed, uint32_t stream_id, const float *rec,
+                             void *vals, void *meta, hipStream_t st);
+
+// The update GEMMs without their second pass: binary32 partial sums part[slabs][O][I], at most parts_bytes of them (one
+// slab where the plan has no split); the caller sums them with launch_finish.
+size_t update_gemm_smfmac_shifted_parts_bytes(int64_t T, int64_t O, int64_t I);
+hipError_t launch_update_gemm_smfmac_shifted_parts(const void *vals, const uint16_t *meta, const void *x, int64_t ldx, int64_t cb,
+                                                   const int64_t *rows, int n, int64_t T, int64_t O, float *part, int *slabs, hipStream_t st);
+size_t update_gemm_q8_shifted_parts_bytes(int64_t T, int64_t O, int64_t I);
+hipError_t launch_update_gemm_q8_shifted_parts(const uint8_t *vals8, const uint32_t *meta32, const uint8_t *x8, int64_t ldx, int64_t cb,
+                                               const int64_t *rows, int n, int64_t T, int64_t O, float *part, int *slabs, hipStream_t st);
+// conv weight gradient, bf16 [O][C][taps] = alpha * sum over the slabs of part[slabs][O][taps][C]
+hipError_t launch_finish_conv(const float *part, int slabs, void *dW, int64_t O, int C, int taps, AlphaArg alpha, hipStream_t st);
 
 // The library's static device scratch array (nm_static.hip): its size, and its address on the current device
 // (looked up once per device; no allocation).

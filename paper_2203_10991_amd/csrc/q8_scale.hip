@@ -16,9 +16,10 @@ namespace nm {
 typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 
 // (a fill kernel, not a memset: safe to record into a HIP graph)
-__global__ void q8_scale_begin_kernel(float *rec)
+__global__ void q8_scale_begin_kernel(float *rec0, float *rec1)
 {
-    if (threadIdx.x < 4) ((uint32_t *)rec)[threadIdx.x] = 0u;
+    if (threadIdx.x < 4) ((uint32_t *)rec0)[threadIdx.x] = 0u;
+    if (rec1 && threadIdx.x < 4) ((uint32_t *)rec1)[threadIdx.x] = 0u;
 }
 
 // The largest power-of-two scale of a maximum (bit pattern mb): s = 2^e with s * max <= top, e in [-126, 126]
@@ -60,16 +61,26 @@ template <int DT> __device__ __forceinline__ uint32_t amax_piece(uint32_t m, con
     return m;
 }
 
+// one tensor of a launch: R rows of C elements at a stride of ld, handled by `blocks` workgroups
+struct AmaxArg { const void *t; int64_t R, C, ld; float top; float *rec; int blocks; };
+
+// (a launch takes one tensor, or the two of a layer: workgroups [0, a.blocks) the first, the others the second)
 template <int DT>
-__global__ __launch_bounds__(AMAX_THREADS) void q8_amax_kernel(const void *__restrict__ t_, int64_t R, int64_t C, int64_t ld, float top, float *rec)
+__global__ __launch_bounds__(AMAX_THREADS) void q8_amax_kernel(AmaxArg a, AmaxArg b)
 {
+    const bool second = (int)blockIdx.x >= a.blocks;
+    const int64_t bid = second ? blockIdx.x - a.blocks : blockIdx.x, n_blocks = second ? b.blocks : a.blocks;
+    const void *t_ = second ? b.t : a.t;
+    const int64_t R = second ? b.R : a.R, C = second ? b.C : a.C, ld = second ? b.ld : a.ld;
+    const float top = second ? b.top : a.top;
+    float *rec = second ? b.rec : a.rec;
     constexpr int VEC = DT == NM_DT_F32 ? 4 : 8, ESZ = DT == NM_DT_F32 ? 4 : 2;
     const int64_t cpr = C / VEC;
     uint32_t m = 0;
-    // rows blockIdx.x / (workgroups per row) ...: `split` workgroups share a row when there are fewer rows than workgroups
-    const int64_t split = R >= gridDim.x ? 1 : gridDim.x / R;
-    const int64_t part = (int64_t)blockIdx.x % split;
-    for (int64_t r = (int64_t)blockIdx.x / split; r < R; r += gridDim.x / split) {
+    // `split` workgroups share a row when there are fewer rows than workgroups
+    const int64_t split = R >= n_blocks ? 1 : n_blocks / R;
+    const int64_t part = bid % split;
+    for (int64_t r = bid / split; r < R; r += n_blocks / split) {
         const u32x4_t *row = (const u32x4_t *)((const char *)t_ + r * ld * ESZ);
         int64_t i = part * AMAX_THREADS + threadIdx.x;
         const int64_t step = split * AMAX_THREADS;
@@ -94,7 +105,7 @@ __global__ __launch_bounds__(AMAX_THREADS) void q8_amax_kernel(const void *__res
     if (m > __hip_atomic_load(top_bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
         __hip_atomic_fetch_max(top_bits, m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     // (release: this workgroup's maximum is in place before its ticket; acquire: the last one sees every maximum)
-    if (__hip_atomic_fetch_add(ticket, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) != gridDim.x - 1) return;
+    if (__hip_atomic_fetch_add(ticket, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) != (uint32_t)n_blocks - 1) return;
     write_scale(rec, __hip_atomic_load(top_bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), top);
     *ticket = 0;
 }
@@ -105,19 +116,38 @@ __global__ void q8_scale_empty_kernel(float *rec)
     if (threadIdx.x < 4) rec[threadIdx.x] = threadIdx.x < 2 ? 1.0f : 0.0f;
 }
 
+static AmaxArg amax_arg(int dt, const void *t, int64_t R, int64_t C, int64_t ld, float top, float *rec, int most_blocks)
+{
+    if (ld == C) { C *= R; ld = C; R = 1; }
+    const int vec = dt == NM_DT_F32 ? 4 : 8;
+    const int64_t per_row = (C / vec + AMAX_THREADS - 1) / AMAX_THREADS;      // workgroups that a row's pieces fill
+    const int64_t blocks = R >= most_blocks ? most_blocks : R * std::min<int64_t>(per_row, most_blocks / R);
+    return AmaxArg{t, R, C, ld, top, rec, (int)blocks};
+}
+
 hipError_t launch_q8_scale(int dt, const void *t, int64_t R, int64_t C, int64_t ld, float top, float *rec, hipStream_t st)
 {
     if (R == 0 || C == 0) {
         hipLaunchKernelGGL(q8_scale_empty_kernel, dim3(1), dim3(64), 0, st, rec);
         return hipGetLastError();
     }
-    if (ld == C) { C *= R; ld = C; R = 1; }
-    const int vec = dt == NM_DT_F32 ? 4 : 8;
-    const int64_t per_row = (C / vec + AMAX_THREADS - 1) / AMAX_THREADS;      // workgroups that a row's pieces fill
-    const int64_t blocks = R >= AMAX_BLOCKS ? AMAX_BLOCKS : R * std::min<int64_t>(per_row, AMAX_BLOCKS / R);
-    hipLaunchKernelGGL(q8_scale_begin_kernel, dim3(1), dim3(64), 0, st, rec);
-    if (dt == NM_DT_F32) hipLaunchKernelGGL(q8_amax_kernel<NM_DT_F32>, dim3((unsigned)blocks), dim3(AMAX_THREADS), 0, st, t, R, C, ld, top, rec);
-    else hipLaunchKernelGGL(q8_amax_kernel<NM_DT_BF16>, dim3((unsigned)blocks), dim3(AMAX_THREADS), 0, st, t, R, C, ld, top, rec);
+    const AmaxArg a = amax_arg(dt, t, R, C, ld, top, rec, AMAX_BLOCKS);
+    hipLaunchKernelGGL(q8_scale_begin_kernel, dim3(1), dim3(64), 0, st, rec, (float *)nullptr);
+    if (dt == NM_DT_F32) hipLaunchKernelGGL(q8_amax_kernel<NM_DT_F32>, dim3((unsigned)a.blocks), dim3(AMAX_THREADS), 0, st, a, AmaxArg{});
+    else hipLaunchKernelGGL(q8_amax_kernel<NM_DT_BF16>, dim3((unsigned)a.blocks), dim3(AMAX_THREADS), 0, st, a, AmaxArg{});
+    return hipGetLastError();
+}
+
+// the scales of a layer's two bf16 tensors in one pass of launches (neither is empty)
+hipError_t launch_q8_scale_pair(const void *t0, int64_t R0, int64_t C0, int64_t ld0, float top0, float *rec0,
+                                const void *t1, int64_t R1, int64_t C1, int64_t ld1, float top1, float *rec1, hipStream_t st)
+{
+    const int64_t n0 = R0 * C0, n1 = R1 * C1;                    // the workgroups are dealt by size
+    const int most0 = (int)std::max<int64_t>(1, std::min<int64_t>(AMAX_BLOCKS - 1, (int64_t)((double)AMAX_BLOCKS * (double)n0 / (double)(n0 + n1))));
+    const AmaxArg a = amax_arg(NM_DT_BF16, t0, R0, C0, ld0, top0, rec0, most0);
+    const AmaxArg b = amax_arg(NM_DT_BF16, t1, R1, C1, ld1, top1, rec1, AMAX_BLOCKS - most0);
+    hipLaunchKernelGGL(q8_scale_begin_kernel, dim3(1), dim3(64), 0, st, rec0, rec1);
+    hipLaunchKernelGGL(q8_amax_kernel<NM_DT_BF16>, dim3((unsigned)(a.blocks + b.blocks)), dim3(AMAX_THREADS), 0, st, a, b);
     return hipGetLastError();
 }
 
