@@ -40,16 +40,18 @@ __device__ __forceinline__ void write_scale(float *rec, uint32_t mb, float top)
 
 // max over the bit patterns of |t|: they order like the magnitudes, with infinity and every NaN on top (the maximum does
 // not depend on the order of the atomics: the result is reproducible), and the scale from it, in one launch.
-// Bound: HBM, one read of the tensor.  What it took instead was the atomics: one per wave on a single address, 9.5 ns
-// each one after the other (16384 of them: 155 us for a 20 MB tensor that streams in 4 us).  So at most AMAX_BLOCKS
-// workgroups of 1024 threads (two per CU: every wave slot) walk the tensor with four independent 16-byte loads in flight
-// per thread, reduce through LDS, and a workgroup touches the record only when its maximum is above what is there; a
-// ticket in rec[3] lets the last workgroup write the scale, which a launch of its own did before.
+// Bound: HBM, one read of the tensor.  What it took instead was the atomics: one per wave on a single address, about 10 ns
+// each one after the other (16384 of them: 155 us for a 20 MB tensor that streams in 4 us).  So a workgroup of 1024 threads
+// takes 128 KB or more with four independent 16-byte loads in flight per thread, reduces through LDS, and touches the record
+// only when its maximum is above what is there; a ticket in rec[3] lets the last workgroup write the scale, which a launch of
+// its own did before.  At most one workgroup per CU: the tickets queue up on one address as well (a sweep with 128 / 256 / 512 /
+// 1024 workgroups: 12608 x 3072 22 / 22 / 36 / 50 us, 32768 x 28672 350 / 311 / 322 / 343 us; and with 16 instead of 128 KB per
+// workgroup 4096 x 1024 takes 12-17 us instead of 10).
 // A contiguous tensor is one row of R * C elements: the 64-bit division of a piece's number by the row length, once per
 // 16 bytes, cost more instructions than everything else in the loop.
-// Measured, both scales of a call before -> after: 12608 x (768 + 3072) bf16 380 -> 55 us, 32768 x (28672 + 8192) bf16
-// 650 -> 450 us (5.4 TB/s); the 8-bit layers of those sizes take half their former time.
-constexpr int AMAX_THREADS = 1024, AMAX_BLOCKS = 512, AMAX_UNROLL = 4;
+// Measured, launches included, before -> after: 12608 x 768 bf16 192 -> 11 us, 32768 x 28672 398 -> 312 us (6.0 TB/s).
+constexpr int AMAX_THREADS = 1024, AMAX_BLOCKS = 256, AMAX_UNROLL = 4;
+constexpr int AMAX_PIECES = 8 * AMAX_THREADS;         // 16-byte pieces a workgroup takes at least: 128 KB
 
 template <int DT> __device__ __forceinline__ uint32_t amax_piece(uint32_t m, const u32x4_t &v)
 {
@@ -102,10 +104,15 @@ __global__ __launch_bounds__(AMAX_THREADS) void q8_amax_kernel(AmaxArg a, AmaxAr
 #pragma unroll
     for (int w = 1; w < AMAX_THREADS / 64; ++w) m = max(m, wave_max[w]);
     uint32_t *top_bits = (uint32_t *)rec + 2, *ticket = (uint32_t *)rec + 3;
-    if (m > __hip_atomic_load(top_bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-        __hip_atomic_fetch_max(top_bits, m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    // (release: this workgroup's maximum is in place before its ticket; acquire: the last one sees every maximum)
-    if (__hip_atomic_fetch_add(ticket, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) != (uint32_t)n_blocks - 1) return;
+    if (m > __hip_atomic_load(top_bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
+        const uint32_t before = __hip_atomic_fetch_max(top_bits, m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("" : : "v"(before));                        // (returning form: the wait below covers it)
+    }
+    // Every access to the record is a device-scope atomic, done where all XCDs meet, so it is enough that this workgroup's
+    // maximum has been performed (the wait) before its ticket: a release or acquire at this scope would write back and
+    // invalidate the XCD's L2, once per workgroup.
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (__hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != (uint32_t)n_blocks - 1) return;
     write_scale(rec, __hip_atomic_load(top_bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), top);
     *ticket = 0;
 }
@@ -120,7 +127,7 @@ static AmaxArg amax_arg(int dt, const void *t, int64_t R, int64_t C, int64_t ld,
 {
     if (ld == C) { C *= R; ld = C; R = 1; }
     const int vec = dt == NM_DT_F32 ? 4 : 8;
-    const int64_t per_row = (C / vec + AMAX_THREADS - 1) / AMAX_THREADS;      // workgroups that a row's pieces fill
+    const int64_t per_row = (C / vec + AMAX_PIECES - 1) / AMAX_PIECES;        // workgroups that a row's pieces fill
     const int64_t blocks = R >= most_blocks ? most_blocks : R * std::min<int64_t>(per_row, most_blocks / R);
     return AmaxArg{t, R, C, ld, top, rec, (int)blocks};
 }

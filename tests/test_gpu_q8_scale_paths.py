@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("R,C,ld", [(1, 8, 8), (1, 16, 16), (3, 8, 24), (511, 16, 24), (512, 16, 24), (513, 16, 16), (700, 8, 16), (1300, 40, 48),
-                                    (2, 8192 * 4 + 8, 8192 * 4 + 16), (7, 8192 * 9, 8192 * 9 + 8), (300, 8192 + 8, 8192 + 16), (4096, 1032, 1032)])
+                                    (2, 8192 * 4 + 8, 8192 * 4 + 16), (7, 8192 * 9, 8192 * 9 + 8), (1, 8 * 8192 * 8 + 8, 8 * 8192 * 8 + 8), (3, 8 * 8192 * 8, 8 * 8192 * 8 + 16), (300, 8192 + 8, 8192 + 16), (4096, 1032, 1032)])
 def test_scale_record_over_the_launch_forms(oracle, dtype, R, C, ld):
     import paper_2203_10991_amd as nm
     rng = np.random.default_rng(R * 131 + C)
