@@ -31,19 +31,26 @@ namespace nm {
 // u = W^T g_{l+1} (the dense backward GEMM's output) and dense_ / ldd the derivative factor d = f'(z_l); each row of
 // g_l = u * d (one binary32 product per element, rounded to the storage type) is formed in registers, written once to
 // gout_ -- the next layer's backward GEMM needs it dense -- and pruned from there: g_l is never read back.
+// PROD = 2: the factor is a ReLU's derivative, and d is the layer's OUTPUT y: d = 1 where y > 0, else 0 (nothing writes the factor out).
 struct ProdArg { const void *d; int64_t ldd; void *gout; int64_t ldgo; };
+// LAYER: the form a layer's backward pass calls (nm_linear_update).  T need not be a multiple of 16: rows past the last token read
+// as zeros through the bounds of buffer descriptors (and are not written to gout), so nothing is copied to pad them.  csum (may
+// be null): the sum of every column over the thread's 16 rows, csum[G][o], the first half of the bias gradient -- a pass over g
+// of its own otherwise.
+struct LayerArg { int64_t T; float *csum; };
 
-template <int DT>
+template <int DT, int PROD>
 __device__ __forceinline__ uint4 producer_row(const uint4 &u, const uint4 &d)
 {
     uint4 r;
+    auto factor = [](float f) { return PROD == 2 ? (f > 0.0f ? 1.0f : 0.0f) : f; };
     if constexpr (DT == NM_DT_F32) {
-        r.x = __float_as_uint(__uint_as_float(u.x) * __uint_as_float(d.x)); r.y = __float_as_uint(__uint_as_float(u.y) * __uint_as_float(d.y));
-        r.z = __float_as_uint(__uint_as_float(u.z) * __uint_as_float(d.z)); r.w = __float_as_uint(__uint_as_float(u.w) * __uint_as_float(d.w));
+        auto mul = [&](uint32_t a, uint32_t b) { return __float_as_uint(__uint_as_float(a) * factor(__uint_as_float(b))); };
+        r.x = mul(u.x, d.x); r.y = mul(u.y, d.y); r.z = mul(u.z, d.z); r.w = mul(u.w, d.w);
     } else {
-        auto mul2 = [](uint32_t a, uint32_t b) {
-            return pack_bf16_rne(__uint_as_float(a << 16) * __uint_as_float(b << 16),
-                                 __uint_as_float(a & 0xffff0000u) * __uint_as_float(b & 0xffff0000u));
+        auto mul2 = [&](uint32_t a, uint32_t b) {
+            return pack_bf16_rne(__uint_as_float(a << 16) * factor(__uint_as_float(b << 16)),
+                                 __uint_as_float(a & 0xffff0000u) * factor(__uint_as_float(b & 0xffff0000u)));
         };
         r.x = mul2(u.x, d.x); r.y = mul2(u.y, d.y); r.z = mul2(u.z, d.z); r.w = mul2(u.w, d.w);
     }
@@ -52,15 +59,16 @@ __device__ __forceinline__ uint4 producer_row(const uint4 &u, const uint4 &d)
 
 // HI0: the caller guarantees that every Philox call index of the launch is below 2^32 (the launcher checks the
 // tensor's size): counter words 1-3 are then wave-uniform and the generator's first rounds run partly on the scalar unit.
-template <int DT, int M, int EST, bool DENSE, bool PROD = false, bool HI0 = false, bool NT = false>
+// VEC: columns per thread: one 16-byte load, or half of it (bf16, for launches that would leave SIMDs without work)
+template <int DT, int M, int EST, bool DENSE, int PROD = 0, bool HI0 = false, bool NT = false, int VEC = Row<DT>::VEC, bool LAYER = false>
 __device__ __forceinline__ void prune_compress_body(
     const void *__restrict__ g_, int64_t n_groups, int64_t O, int64_t ldg,
     uint32_t key0, uint32_t key1, uint32_t stream_id,
-    void *__restrict__ vals_, uint16_t *__restrict__ meta_, void *__restrict__ dense_, int64_t ldd, ProdArg pa = ProdArg{})
+    void *__restrict__ vals_, uint16_t *__restrict__ meta_, void *__restrict__ dense_, int64_t ldd, ProdArg pa = ProdArg{}, LayerArg la = LayerArg{})
 {
     static_assert(!(PROD && DENSE), "the producer form writes g_l, not theta(g_l)");
-    constexpr int VEC = Row<DT>::VEC;
     constexpr int ESZ = DT == NM_DT_F32 ? 4 : 2;
+    constexpr int RB = VEC * ESZ;                     // bytes of a thread's piece of a row: 16 or 8
     const int64_t ncg = O / VEC;
     const int64_t n = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (n >= n_groups * ncg) return;                 // (NT: the launcher has checked that the thread count is a multiple of 64: whole waves leave)
@@ -74,27 +82,67 @@ __device__ __forceinline__ void prune_compress_body(
     uint4 rows[16];
     const char *dp_in = nullptr;
     char *gop = nullptr;
-    if constexpr (PROD) {
+    if constexpr (PROD != 0) {
         dp_in = (const char *)pa.d + ((G * 16) * pa.ldd + col0) * ESZ;
         gop = (char *)pa.gout + ((G * 16) * pa.ldgo + col0) * ESZ;
     }
+    auto load_piece = [&](const char *p) -> uint4 {
+        if constexpr (RB == 16) return NT ? load_stream(p) : load_global(p);
+        else return NT ? load_stream8(p) : load_global8(p);
+    };
+    [[maybe_unused]] float cs[VEC];
+    auto add_columns = [&](const uint4 &v, bool first) {
+#pragma unroll
+        for (int c = 0; c < VEC; ++c) cs[c] = first ? Row<DT>::get(v, c) : cs[c] + Row<DT>::get(v, c);
+    };
     auto fetch_rows = [&](const char *base, const char *dbase, int first) {
 #pragma unroll
         for (int r = first; r < first + 8; ++r) {
-            if constexpr (NT) rows[r] = load_stream(base + (int64_t)r * ldg * ESZ);
-            else rows[r] = load_global(base + (int64_t)r * ldg * ESZ);
-            if constexpr (PROD) {
-                if constexpr (NT) {
-                    rows[r] = producer_row<DT>(rows[r], load_stream(dbase + (int64_t)r * pa.ldd * ESZ));
-                    store_stream(gop + (int64_t)r * pa.ldgo * ESZ, rows[r]);
-                } else {
-                    rows[r] = producer_row<DT>(rows[r], load_global(dbase + (int64_t)r * pa.ldd * ESZ));
-                    *(uint4 *)(gop + (int64_t)r * pa.ldgo * ESZ) = rows[r];
-                }
+            rows[r] = load_piece(base + (int64_t)r * ldg * ESZ);
+            if constexpr (PROD != 0) {
+                rows[r] = producer_row<DT, PROD>(rows[r], load_piece(dbase + (int64_t)r * pa.ldd * ESZ));
+                if constexpr (NT) store_stream(gop + (int64_t)r * pa.ldgo * ESZ, rows[r]);
+                else *(uint4 *)(gop + (int64_t)r * pa.ldgo * ESZ) = rows[r];
             }
         }
     };
-    fetch_rows(gp, dp_in, 0);
+    // LAYER: everything through descriptors based at the workgroup's first token group, with the bytes up to the last token as bound
+    // (rows and columns stay below 2^21 elements and T rows: a workgroup's offsets fit 32 bits; the caller checks)
+    [[maybe_unused]] const int64_t t0 = ((int64_t)blockIdx.x * 256 / ncg) * 16;
+    auto rows_rsrc = [&](const void *p, int64_t ld) {
+        const int64_t bytes = (la.T - t0) * ld * ESZ;
+        return __builtin_amdgcn_make_buffer_rsrc((char *)p + t0 * ld * ESZ, 0, (int)(uint32_t)(bytes > 0xffffffffll ? 0xffffffffll : bytes), 0x00020000);
+    };
+    auto fetch_rows_layer = [&](uint32_t token, int first) {         // token: G * 16 - t0, through an opaque copy for the second half
+        const auto rg = rows_rsrc(g_, ldg);
+        const uint32_t og = (token * (uint32_t)ldg + (uint32_t)col0) * ESZ;
+#pragma unroll
+        for (int r = first; r < first + 8; ++r) rows[r] = buffer_piece<RB>(rg, og + (uint32_t)r * (uint32_t)ldg * ESZ);
+        if constexpr (PROD != 0) {
+            const auto rd = rows_rsrc(pa.d, pa.ldd), ro = rows_rsrc(pa.gout, pa.ldgo);
+            const uint32_t od = (token * (uint32_t)pa.ldd + (uint32_t)col0) * ESZ, oo = (token * (uint32_t)pa.ldgo + (uint32_t)col0) * ESZ;
+            uint4 f[8];
+#pragma unroll
+            for (int r = 0; r < 8; ++r) f[r] = buffer_piece<RB>(rd, od + (uint32_t)(first + r) * (uint32_t)pa.ldd * ESZ);
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {
+                rows[first + r] = producer_row<DT, PROD>(rows[first + r], f[r]);
+                buffer_put_piece<RB>(ro, oo + (uint32_t)(first + r) * (uint32_t)pa.ldgo * ESZ, rows[first + r]);
+            }
+        }
+        if (la.csum) {
+#pragma unroll
+            for (int r = first; r < first + 8; ++r) add_columns(rows[r], r == 0);
+            if (first == 8) {
+                float *cp = la.csum + G * O + col0;
+#pragma unroll
+                for (int c = 0; c < VEC; c += 4) *(float4 *)(cp + c) = make_float4(cs[c], cs[c + 1], cs[c + 2], cs[c + 3]);
+            }
+        }
+    };
+    [[maybe_unused]] const uint32_t token0 = (uint32_t)(G * 16 - t0);
+    if constexpr (LAYER) fetch_rows_layer(token0, 0);
+    else fetch_rows(gp, dp_in, 0);
 
     // kept values per column in the slot order of the group format, as stored: binary32 words, or bf16 pairs
     // (slots 2i, 2i+1) packed as soon as a block row is decided, which keeps the live registers low
@@ -119,9 +167,15 @@ __device__ __forceinline__ void prune_compress_body(
 #pragma unroll
     for (int b = 0; b < BLOCK_ROWS; ++b) {
         if (b == 1) {
-            const char *gp2 = gp, *dp2 = dp_in;
-            asm volatile("" : "+v"(gp2));               // an address the compiler cannot see through
-            fetch_rows(gp2, dp2, 8);
+            if constexpr (LAYER) {
+                uint32_t token2 = token0;
+                asm volatile("" : "+v"(token2));        // (as below)
+                fetch_rows_layer(token2, 8);
+            } else {
+                const char *gp2 = gp, *dp2 = dp_in;
+                asm volatile("" : "+v"(gp2));           // an address the compiler cannot see through
+                fetch_rows(gp2, dp2, 8);
+            }
         }
         const uint64_t blk0 = (uint64_t)(G * BLOCK_ROWS + b) * (uint64_t)O + (uint64_t)col0;
         uint32_t words[VEC * WPB];
@@ -169,22 +223,23 @@ __device__ __forceinline__ void prune_compress_body(
         }
     }
 
-    // ---- kept values: 8 per column, VEC columns contiguous = 128 bytes per thread
-    char *vp = (char *)vals_ + ((G * O + col0) * 8) * ESZ;            // = vals_ + 128 n: a wave's 64 threads own 8 KB in a row
+    // ---- kept values: 8 per column, VEC columns contiguous
+    [[maybe_unused]] char *vp = (char *)vals_ + ((G * O + col0) * 8) * ESZ;            // = vals_ + 16 PC n (below): a wave's 64 threads own one run of it
     [[maybe_unused]] uint16_t *mp_late = nullptr;
-    // Streaming stores want whole lines per instruction: the wave's 8 KB go through its own 8 KB of LDS, written as
-    // each thread holds them (eight 16-byte pieces at a stride of 128 bytes; piece c of lane l at slot 8l + (c ^ l%8),
-    // which spreads the lanes over the banks) and read back so that store k covers bytes [1024 k, 1024 k + 1024).
+    // Streaming stores want whole lines per instruction: the wave's pieces (8 KB at eight columns per thread) go through LDS of
+    // its own, written as each thread holds them (PC 16-byte pieces; piece c of lane l at slot PC l + (c ^ l%PC), which spreads the
+    // lanes over the banks) and read back so that store k covers bytes [1024 k, 1024 k + 1024).
     // Every lane of the wave is here (the launcher sends only launches made of whole waves to the streaming kernels), and
     // a wave's LDS operations execute in order, so the reads below see the writes above without a workgroup barrier.
+    constexpr int PC = VEC * KW / 4;                                     // 16-byte pieces per thread
     if constexpr (NT) {
-        __shared__ __attribute__((aligned(1024))) char xs[4 * 8192];
+        __shared__ __attribute__((aligned(1024))) char xs[4 * 1024 * PC];
         uint32_t tid = threadIdx.x;
         asm volatile("" : "+v"(tid) : "v"(kept[VEC - 1][KW - 1]));       // (the addresses below are formed here, after the last block, not carried through the kernel)
-        const uint32_t lane = tid & 63u, wave_lds = (tid >> 6) * 8192;
+        const uint32_t lane = tid & 63u, wave_lds = (tid >> 6) * (1024 * PC);
         const int64_t n_late = (int64_t)blockIdx.x * 256 + tid;          // = n
-        // byte address of piece p of this lane: 128 lane + 16 (p ^ lane%8) = (128 lane + 16 (lane%8)) ^ 16 p
-        const uint32_t wr = wave_lds + lane * 128 + (lane & 7) * 16;
+        // byte address of piece p of this lane: 16 PC lane + 16 (p ^ lane%PC) = (16 PC lane + 16 (lane%PC)) ^ 16 p
+        const uint32_t wr = wave_lds + lane * (16 * PC) + (lane % PC) * 16;
 #pragma unroll
         for (int c = 0; c < VEC; ++c)
 #pragma unroll
@@ -193,12 +248,12 @@ __device__ __forceinline__ void prune_compress_body(
                 *(uint4 *)(xs + (wr ^ (uint32_t)(piece * 16))) = make_uint4(kept[c][4 * j], kept[c][4 * j + 1], kept[c][4 * j + 2], kept[c][4 * j + 3]);
             }
         __builtin_amdgcn_wave_barrier();
-        // store k, lane l: piece l%8 of the wave's thread 8k + l/8, which sits at slot 8 (8k + l/8) + (l%8 ^ l/8)
-        char *wave_base = (char *)vals_ + (n_late - lane) * 128;
+        // store k, lane l: piece l%PC of the wave's thread (64/PC) k + l/PC, which sits at slot 64 k + PC (l/PC) + (l%PC ^ (l/PC)%PC)
+        char *wave_base = (char *)vals_ + (n_late - lane) * (16 * PC);
         mp_late = meta_ + n_late * VEC;                                   // (G O + col0 = n VEC)
-        const uint32_t rd = wave_lds + (8 * (lane >> 3) + ((lane & 7) ^ (lane >> 3))) * 16;
+        const uint32_t rd = wave_lds + (PC * (lane / PC) + ((lane % PC) ^ ((lane / PC) % PC))) * 16;
 #pragma unroll
-        for (int k = 0; k < 8; ++k) store_stream(wave_base + (1024 * k + 16 * lane), *(const uint4 *)(xs + rd + 1024 * k));
+        for (int k = 0; k < PC; ++k) store_stream(wave_base + (1024 * k + 16 * lane), *(const uint4 *)(xs + rd + 1024 * k));
     } else {
 #pragma unroll
     for (int c = 0; c < VEC; ++c)
@@ -218,7 +273,6 @@ __device__ __forceinline__ void prune_compress_body(
         uint2 o;
         o.x = md[0] | (md[1] << 16); o.y = md[2] | (md[3] << 16);
         if constexpr (NT) {
-            typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
             const u32x2_t t = {o.x, o.y};
             __builtin_nontemporal_store(t, (u32x2_t *)mp);
         } else *(uint2 *)mp = o;
@@ -261,18 +315,33 @@ __global__ __launch_bounds__(256) void prune_compress_kernel(
 // what the registers are budgeted for (four for the instances that need more than 96).
 // HI0: every Philox call index of the launch is below 2^32, which the launcher has checked.
 template <int DT, int M, int EST, bool HI0>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((DT == NM_DT_BF16 && (EST == 1 || (M == 2 && EST == 0))) ? 4 : 5, 5))) void prune_compress_stream_kernel(
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((DT == NM_DT_BF16 && EST == 1) ? 4 : 5, 5))) void prune_compress_stream_kernel(
     const void *__restrict__ g, int64_t n_groups, int64_t O, int64_t ldg, uint32_t key0, uint32_t key1, uint32_t stream_id,
     void *__restrict__ vals, uint16_t *__restrict__ meta)
 {
-    prune_compress_body<DT, M, EST, false, false, HI0, true>(g, n_groups, O, ldg, key0, key1, stream_id, vals, meta, nullptr, 0);
+    prune_compress_body<DT, M, EST, false, 0, HI0, true>(g, n_groups, O, ldg, key0, key1, stream_id, vals, meta, nullptr, 0);
+}
+// Four bf16 columns per thread instead of eight: half the registers and LDS (seven or eight waves per SIMD instead of four or
+// five), twice the waves, half the chain of instructions between a wave's loads and its stores.  MVUE 1:2, whose arithmetic is
+// light, takes it at every size (32768 x 28672: 495 -> 463 us, 6.3 TB/s; 12608 x 2304: 18.3 -> 16.7; 512 x 512: 5.7 -> 4.0).
+// The two 2:4 estimators are bound by their arithmetic on large tensors, where the address and index work that two threads do
+// instead of one costs 1-2 % (32768 x 28672 optimal 530 -> 541 us); on small ones the launch is a wave or two deep per SIMD and
+// what counts is how long one wave takes: optimal 512 x 512 8.3 -> 5.3 us, 12608 x 768 12.7 -> 9.8, 12608 x 2304 22.3 -> 19.8,
+// 16384 x 4096 41.6 -> 41.0; approx-MVUE 17.7 -> 9.8, 26.3 -> 19.1, 44 -> 39, 81.3 -> 80.6.  Hence the line at 16384 x 4096.
+constexpr int64_t HALF_MOST = (int64_t)16384 * 4096;        // elements
+template <int M, int EST, bool HI0>
+__global__ __launch_bounds__(256) void prune_compress_half_kernel(
+    const void *__restrict__ g, int64_t n_groups, int64_t O, int64_t ldg, uint32_t key0, uint32_t key1, uint32_t stream_id,
+    void *__restrict__ vals, uint16_t *__restrict__ meta)
+{
+    prune_compress_body<NM_DT_BF16, M, EST, false, 0, HI0, true, 4>(g, n_groups, O, ldg, key0, key1, stream_id, vals, meta, nullptr, 0);
 }
 template <int DT, int M, int EST, bool NT>
 __global__ __launch_bounds__(256) void prune_producer_kernel(
     const void *__restrict__ u, int64_t n_groups, int64_t O, int64_t ldu, uint32_t key0, uint32_t key1, uint32_t stream_id,
     void *__restrict__ vals, uint16_t *__restrict__ meta, ProdArg pa)
 {
-    prune_compress_body<DT, M, EST, false, true, false, NT>(u, n_groups, O, ldu, key0, key1, stream_id, vals, meta, nullptr, 0, pa);
+    prune_compress_body<DT, M, EST, false, 1, false, NT>(u, n_groups, O, ldu, key0, key1, stream_id, vals, meta, nullptr, 0, pa);
 }
 // The bf16 optimal-2:4 kernel without the dense output needs 98 registers as the compiler would have it, two more
 // than let a fifth wave onto each SIMD; asked for five waves it fits 96 without spilling.
@@ -280,13 +349,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 5))) voi
     const void *__restrict__ g, int64_t n_groups, int64_t O, int64_t ldg, uint32_t key0, uint32_t key1, uint32_t stream_id,
     void *__restrict__ vals, uint16_t *__restrict__ meta)
 {
-    prune_compress_body<NM_DT_BF16, 4, 0, false, false, true>(g, n_groups, O, ldg, key0, key1, stream_id, vals, meta, nullptr, 0);
+    prune_compress_body<NM_DT_BF16, 4, 0, false, 0, true>(g, n_groups, O, ldg, key0, key1, stream_id, vals, meta, nullptr, 0);
 }
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 5))) void prune_compress_bf16_2of4_stream_kernel(
     const void *__restrict__ g, int64_t n_groups, int64_t O, int64_t ldg, uint32_t key0, uint32_t key1, uint32_t stream_id,
     void *__restrict__ vals, uint16_t *__restrict__ meta)
 {
-    prune_compress_body<NM_DT_BF16, 4, 0, false, false, true, true>(g, n_groups, O, ldg, key0, key1, stream_id, vals, meta, nullptr, 0);
+    prune_compress_body<NM_DT_BF16, 4, 0, false, 0, true, true>(g, n_groups, O, ldg, key0, key1, stream_id, vals, meta, nullptr, 0);
 }
 
 // ------------------------------------------------------------------------------------
@@ -850,16 +919,28 @@ static hipError_t launch_prune_t(const void *g, int64_t T, int64_t O, int64_t ld
     // hi0: every call index (block / 4, or block / 2 for approx-MVUE's two words per block) lies below 2^32
     const bool hi0 = EST != 4 && (uint64_t)(T / M) * (uint64_t)O <= ((uint64_t)1 << (EST == 1 ? 33 : 34));
     const dim3 grid((unsigned)blocks);
+    const bool half = DT == NM_DT_BF16 && (EST == 0 || EST == 1) && threads % 32 == 0 && 2 * blocks <= 0x7fffffffll &&
+                      (M == 2 || T * O <= HALF_MOST);             // (M = 4: hi0 holds at these sizes)
 #define NM_ARGS g, groups, O, ldg, (uint32_t)seed, (uint32_t)(seed >> 32), stream_id, vals, meta
     if (dense)
         hipLaunchKernelGGL((prune_compress_kernel<DT, M, EST, true>), grid, dim3(256), 0, st, NM_ARGS, dense, ldd);
+    else if (half) {
+        if constexpr (DT == NM_DT_BF16 && (EST == 0 || EST == 1)) {
+            const dim3 half_grid((unsigned)((2 * threads + 255) / 256));
+            if (hi0) hipLaunchKernelGGL((prune_compress_half_kernel<M, EST, true>), half_grid, dim3(256), 0, st, NM_ARGS);
+            else if constexpr (M == 2) hipLaunchKernelGGL((prune_compress_half_kernel<M, EST, false>), half_grid, dim3(256), 0, st, NM_ARGS);
+        }
+    }
     else if (DT == NM_DT_BF16 && M == 4 && EST == 0 && hi0 && threads % 64 == 0)
         hipLaunchKernelGGL(prune_compress_bf16_2of4_stream_kernel, grid, dim3(256), 0, st, NM_ARGS);
     else if (DT == NM_DT_BF16 && M == 4 && EST == 0 && hi0)
         hipLaunchKernelGGL(prune_compress_bf16_2of4_kernel, grid, dim3(256), 0, st, NM_ARGS);
     else if (threads % 64 == 0) {
-        if (hi0) hipLaunchKernelGGL((prune_compress_stream_kernel<DT, M, EST, true>), grid, dim3(256), 0, st, NM_ARGS);
-        else hipLaunchKernelGGL((prune_compress_stream_kernel<DT, M, EST, false>), grid, dim3(256), 0, st, NM_ARGS);
+        if constexpr (!(DT == NM_DT_BF16 && M == 2 && EST == 0)) {             // (that one runs with half the columns)
+            if (hi0) hipLaunchKernelGGL((prune_compress_stream_kernel<DT, M, EST, true>), grid, dim3(256), 0, st, NM_ARGS);
+            else hipLaunchKernelGGL((prune_compress_stream_kernel<DT, M, EST, false>), grid, dim3(256), 0, st, NM_ARGS);
+        } else
+            hipLaunchKernelGGL((prune_compress_kernel<DT, M, EST, false>), grid, dim3(256), 0, st, NM_ARGS, dense, ldd);
     } else
         hipLaunchKernelGGL((prune_compress_kernel<DT, M, EST, false>), grid, dim3(256), 0, st, NM_ARGS, dense, ldd);
 #undef NM_ARGS

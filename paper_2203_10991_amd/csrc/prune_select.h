@@ -250,6 +250,34 @@ __device__ __forceinline__ uint4 load_global(const void *p)
     const u32x4_t t = *(const NM_GLOBAL u32x4_t *)p;
     return make_uint4(t.x, t.y, t.z, t.w);
 }
+// 8-byte pieces (the other half of the vector is zero and never read)
+typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint4 load_stream8(const void *p)
+{
+    const u32x2_t t = __builtin_nontemporal_load((const NM_GLOBAL u32x2_t *)p);
+    return make_uint4(t.x, t.y, 0u, 0u);
+}
+__device__ __forceinline__ uint4 load_global8(const void *p)
+{
+    const u32x2_t t = *(const NM_GLOBAL u32x2_t *)p;
+    return make_uint4(t.x, t.y, 0u, 0u);
+}
+// the same pieces through a buffer descriptor: zeros past its bound, nothing stored past it
+template <int BYTES> __device__ __forceinline__ uint4 buffer_piece(__amdgpu_buffer_rsrc_t r, uint32_t offset)
+{
+    if constexpr (BYTES == 16) {
+        const u32x4_t t = __builtin_amdgcn_raw_buffer_load_b128(r, (int)offset, 0, 0);
+        return make_uint4(t.x, t.y, t.z, t.w);
+    } else {
+        const u32x2_t t = __builtin_amdgcn_raw_buffer_load_b64(r, (int)offset, 0, 0);
+        return make_uint4(t.x, t.y, 0u, 0u);
+    }
+}
+template <int BYTES> __device__ __forceinline__ void buffer_put_piece(__amdgpu_buffer_rsrc_t r, uint32_t offset, const uint4 &v)
+{
+    if constexpr (BYTES == 16) { const u32x4_t t = {v.x, v.y, v.z, v.w}; __builtin_amdgcn_raw_buffer_store_b128(t, r, (int)offset, 0, 0); }
+    else { const u32x2_t t = {v.x, v.y}; __builtin_amdgcn_raw_buffer_store_b64(t, r, (int)offset, 0, 0); }
+}
 __device__ __forceinline__ void store_stream(void *p, const uint4 &v)
 {
     const u32x4_t t = {v.x, v.y, v.z, v.w};

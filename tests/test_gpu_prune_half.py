@@ -1,0 +1,52 @@
+"""The prune kernels with four bf16 columns per thread: sizes at which their launch changes form (one wave, a partly filled
+workgroup, a thread count that is no multiple of a wave), the largest size that takes them and the first beyond it, padded
+strides; vals and meta bit for bit against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2203_10991_amd import synth
+from gpu_util import DEV, to_dev, to_host
+
+pytestmark = pytest.mark.gpu
+
+
+def _g(T, O, seed):
+    w = synth.Workload("t", T, O, 8, "bf16", "2:4", 0.0, 2.5, 0.2)
+    return synth.make_g(w, seed)
+
+
+@pytest.mark.parametrize("T,O,ld", [(16, 256, 256), (16, 8, 8), (32, 128, 136), (48, 72, 72), (16, 264, 264), (1584, 96, 104), (64, 1024, 1024), (528, 40, 40)])
+@pytest.mark.parametrize("which", ["1of2", "2of4", "approx"])
+def test_small_sizes_match_the_oracle(oracle, T, O, ld, which):
+    import paper_2203_10991_amd as nm
+    g = _g(T, O, T + O)
+    d = torch.zeros((T, ld), dtype=torch.bfloat16, device=DEV)
+    d[:, :O] = to_dev(g)
+    if which == "1of2":
+        v, m, _ = nm.mvue_prune_1of2(d[:, :O], seed=7, stream_id=3)
+        ov, om, _ = oracle.prune_1of2(g, 7, 3)
+    elif which == "2of4":
+        v, m, _ = nm.mvue_prune_2of4(d[:, :O], seed=7, stream_id=3)
+        ov, om, _ = oracle.prune_2of4(g, 7, 3)
+    else:
+        v, m, _ = nm.mvue_prune_2of4(d[:, :O], seed=7, stream_id=3, mode=1)
+        ov, om, _ = oracle.prune_2of4_approx(g, 7, 3)
+    assert np.array_equal(to_host(m), om) and np.array_equal(to_host(v), ov)
+
+
+@pytest.mark.parametrize("T", [16384, 16400])
+@pytest.mark.parametrize("which", ["1of2", "2of4", "approx"])
+def test_either_side_of_the_line_matches_the_oracle(oracle, T, which):
+    import paper_2203_10991_amd as nm
+    O = 4096
+    g = _g(T, O, 5)
+    gd = to_dev(g)
+    if which == "1of2":
+        v, m, _ = nm.mvue_prune_1of2(gd, seed=9, stream_id=1)
+        ov, om, _ = oracle.prune_1of2(g, 9, 1)
+    else:
+        mode = 1 if which == "approx" else 0
+        v, m, _ = nm.mvue_prune_2of4(gd, seed=9, stream_id=1, mode=mode)
+        ov, om, _ = (oracle.prune_2of4_approx if mode else oracle.prune_2of4)(g, 9, 1)
+    assert np.array_equal(to_host(m), om) and np.array_equal(to_host(v), ov)
