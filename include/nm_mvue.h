@@ -382,6 +382,22 @@ int nm_conv_update(const void *gy, int gy_channels_last, const void *x, int x_ch
                    void *workspace, size_t workspace_bytes, void *hip_stream);
 size_t nm_conv_update_workspace(int64_t N, int64_t C, int64_t O, int64_t H, int64_t W, int k, int q8);
 
+/*
+ * Weight and bias gradient of a linear layer in one call (bf16 tensors): prune, update GEMM, conversion.
+ *   g [T x O], h [T x I]   bf16, row strides ldg, ldh; T is any positive number (rows up to a whole token group count as zeros)
+ *   act [T x O], lda       NULL, or the output of the ReLU behind the layer (bf16; not with q8): the gradient is then
+ *                          g * [act > 0] and is also written to g_out (row stride ldgo)
+ *   m, mode                2 = MVUE 1:2; 4 = MVUE 2:4, mode as in mvue_prune_2of4
+ *   q8                     != 0: scales, e4m3 cast, e5m2 kept values and the 8-bit product (I % 16 == 0)
+ *   dW [O x I], db [O]     bf16, contiguous; db = column sums of the gradient (NULL = skip)
+ * Masks and kept values are those of mvue_prune_* on the gradient padded with zero rows to a multiple of 16 (q8: 32);
+ * O % 8 == 0, I % 8 == 0.  workspace: nm_linear_update_workspace(...) bytes (0 for sizes the call does not take).
+ */
+int nm_linear_update(const void *g, int64_t ldg, const void *act, int64_t lda, const void *h, int64_t ldh, int64_t T, int64_t O,
+                     int64_t I, int m, int mode, int q8, uint64_t seed, uint32_t stream_id, void *g_out, int64_t ldgo,
+                     void *dW, void *db, void *workspace, size_t workspace_bytes, void *hip_stream);
+size_t nm_linear_update_workspace(int64_t T, int64_t O, int64_t I, int q8, int bias);
+
 /* Message of the last error on this thread ("" if none).  Static storage; do not free. */
 const char *nm_last_error(void);
 

@@ -92,6 +92,10 @@ def load():
     lib.nm_conv_update.restype = i32
     lib.nm_conv_update_workspace.argtypes = [i64, i64, i64, i64, i64, i32, i32]
     lib.nm_conv_update_workspace.restype = sz
+    lib.nm_linear_update.argtypes = [vp, i64, vp, i64, vp, i64, i64, i64, i64, i32, i32, i32, u64, u32, vp, i64, vp, vp, vp, sz, vp]
+    lib.nm_linear_update.restype = i32
+    lib.nm_linear_update_workspace.argtypes = [i64, i64, i64, i32, i32]
+    lib.nm_linear_update_workspace.restype = sz
     for f in (lib.mvue_prune_1of2, lib.mvue_prune_2of4, lib.nm_compress, lib.nm_update_gemm, lib.mvue_prune_2of4_q8,
               lib.nm_update_gemm_q8):
         f.restype = i32
@@ -565,3 +569,37 @@ def nm_conv_update(gy: torch.Tensor, x: torch.Tensor, k: int, q8: bool = False, 
     _check(lib.nm_conv_update(_ptr(gy), g_cl, _ptr(x), x_cl, N, C, O, H, W, k, int(q8), mode, seed, stream_id, _ptr(dW), _ptr(workspace),
                               workspace.numel() * workspace.element_size(), _stream(gy)))
     return dW
+
+
+def _rows_of(t: torch.Tensor):
+    """(tensor, row stride) of a 2-D bf16 tensor whose rows start on 16-byte boundaries; a copy where they do not."""
+    if t.stride(1) != 1 or t.stride(0) < t.shape[1] or t.stride(0) % 8 or t.stride(0) > 1 << 21:
+        t = t.contiguous()
+    return t, t.stride(0) if t.shape[0] > 1 else t.shape[1]
+
+
+def nm_linear_update_workspace(T: int, O: int, I: int, q8: bool = False, bias: bool = False) -> int:
+    """Bytes of workspace of nm_linear_update; 0 where it does not take the sizes."""
+    return int(load().nm_linear_update_workspace(T, O, I, int(q8), int(bias)))
+
+
+def nm_linear_update(g: torch.Tensor, h: torch.Tensor, nm: str = "2:4", mode: int = 0, q8: bool = False, seed: int = 0, stream_id: int = 0,
+                     act: Optional[torch.Tensor] = None, bias: bool = False):
+    """(dW [O x I], db [O] or None, g_out or None) of a linear layer, bf16, from its gradient g [T x O] and input h [T x I], in one
+    library call.  act: the output of a ReLU behind the layer; the gradient is then g * [act > 0], returned as g_out."""
+    lib = load()
+    if any(t.dtype != torch.bfloat16 or not t.is_cuda or t.dim() != 2 for t in ((g, h) if act is None else (g, h, act))):
+        raise TypeError("nm_linear_update takes 2-D bfloat16 tensors on the GPU")
+    (T, O), I = g.shape, h.shape[1]
+    if h.shape[0] != T or (act is not None and act.shape != g.shape):
+        raise ValueError(f"g {tuple(g.shape)}, h {tuple(h.shape)} and act do not fit")
+    need = lib.nm_linear_update_workspace(T, O, I, q8, bias)
+    g, ldg = _rows_of(g)
+    h, ldh = _rows_of(h)
+    act, lda = _rows_of(act) if act is not None else (None, 0)
+    new = lambda *shape: torch.empty(shape, dtype=torch.bfloat16, device=g.device)          # noqa: E731
+    dW, db, g_out = new(O, I), new(O) if bias else None, new(T, O) if act is not None else None
+    workspace = torch.empty(max(need, 1), dtype=torch.uint8, device=g.device)
+    _check(lib.nm_linear_update(_ptr(g), ldg, _ptr(act), lda, _ptr(h), ldh, T, O, I, 2 if nm == "1:2" else 4, 0 if nm == "1:2" else mode, q8,
+                                seed, stream_id, _ptr(g_out), O, _ptr(dW), _ptr(db), _ptr(workspace), need, _stream(g)))
+    return dW, db, g_out

@@ -150,6 +150,13 @@ def _update_gemm_q8(g2: torch.Tensor, h2: torch.Tensor, cfg: NMConfig) -> torch.
     return api.nm_update_gemm_q8(v8, m32, h8, alpha=(sg, sh))
 
 
+def _one_call(g2: torch.Tensor, h2: torch.Tensor, weight: torch.Tensor, cfg: NMConfig, bias: bool) -> bool:
+    """Whether the layer's update is one library call (api.nm_linear_update): bf16 tensors at sizes it takes."""
+    return (cfg.precision in ("native", "q8") and cfg.nm in ("1:2", "2:4") and g2.is_cuda and h2.is_cuda
+            and g2.dtype == h2.dtype == weight.dtype == torch.bfloat16
+            and api.nm_linear_update_workspace(g2.shape[0], g2.shape[1], h2.shape[1], cfg.precision == "q8", bias) > 0)
+
+
 class _NMLinearFn(torch.autograd.Function):
     @staticmethod
     def forward(ctx, x, weight, bias, cfg):
@@ -161,10 +168,17 @@ class _NMLinearFn(torch.autograd.Function):
     def backward(ctx, gy):
         x, weight = ctx.saved_tensors
         dx = gy @ weight if ctx.needs_input_grad[0] else None                     # backward phase: dense (eq. (2))
-        dW = None
-        if ctx.needs_input_grad[1]:
-            dW = _update_gemm(gy.reshape(-1, gy.shape[-1]), x.reshape(-1, x.shape[-1]), ctx.cfg).to(weight.dtype)
-        db = gy.reshape(-1, gy.shape[-1]).sum(0) if ctx.has_bias and ctx.needs_input_grad[2] else None
+        dW = db = None
+        g2, h2, cfg = gy.reshape(-1, gy.shape[-1]), x.reshape(-1, x.shape[-1]), ctx.cfg
+        bias = ctx.has_bias and ctx.needs_input_grad[2]
+        if ctx.needs_input_grad[1] and _one_call(g2, h2, weight, cfg, bias):
+            dW, db, _ = api.nm_linear_update(g2, h2, nm=cfg.nm, mode=cfg.mode, q8=cfg.precision == "q8", seed=cfg.current_seed(),
+                                             stream_id=cfg.stream_id, bias=bias)
+        else:
+            if ctx.needs_input_grad[1]:
+                dW = _update_gemm(g2, h2, cfg).to(weight.dtype)
+            if bias:
+                db = g2.sum(0)
         if ctx.cfg.auto_advance:
             ctx.cfg.advance()
         return dx, dW, db, None
@@ -198,13 +212,17 @@ class _NMLinearReLUFn(torch.autograd.Function):
         x, weight, y = ctx.saved_tensors
         cfg = ctx.cfg
         O = weight.shape[0]
-        u2 = gy.reshape(-1, O)
-        d2 = (y.reshape(-1, O) > 0).to(gy.dtype)
-        h2 = x.reshape(-1, x.shape[-1])
+        u2, y2, h2 = gy.reshape(-1, O), y.reshape(-1, O), x.reshape(-1, x.shape[-1])
+        bias = ctx.has_bias and ctx.needs_input_grad[2]
         T = u2.shape[0]
+        dW = db = None
         fused = (cfg.precision == "native" and cfg.nm in ("1:2", "2:4") and u2.is_cuda and O % 8 == 0 and h2.shape[1] % 8 == 0
                  and u2.dtype == h2.dtype and u2.dtype in (torch.float32, torch.bfloat16) and ctx.needs_input_grad[1])
-        if fused:
+        if fused and y2.dtype == u2.dtype and _one_call(u2, h2, weight, cfg, bias):
+            dW, db, g2 = api.nm_linear_update(u2, h2, nm=cfg.nm, mode=cfg.mode, seed=cfg.current_seed(), stream_id=cfg.stream_id, act=y2,
+                                              bias=bias)
+        elif fused:                                       # binary32: the producer form of the prune, then the usual GEMM
+            d2 = (y2 > 0).to(gy.dtype)
             pad = (-T) % 16
             if pad:                                       # zero rows prune to zeros and add nothing to dW
                 u2, d2, h2 = F.pad(u2, (0, 0, 0, pad)), F.pad(d2, (0, 0, 0, pad)), F.pad(h2, (0, 0, 0, pad))
@@ -213,10 +231,15 @@ class _NMLinearReLUFn(torch.autograd.Function):
             dW = api.nm_update_gemm(vals, meta, h2.contiguous()).to(weight.dtype)
             g2 = g2[:T]
         else:                                             # 8-bit and three-term modes: separate product, then the usual path
-            g2 = u2 * d2
-            dW = _update_gemm(g2, h2, cfg).to(weight.dtype) if ctx.needs_input_grad[1] else None
+            g2 = u2 * (y2 > 0).to(gy.dtype)
+            if ctx.needs_input_grad[1] and _one_call(g2, h2, weight, cfg, bias):
+                dW, db, _ = api.nm_linear_update(g2, h2, nm=cfg.nm, mode=cfg.mode, q8=cfg.precision == "q8", seed=cfg.current_seed(),
+                                                 stream_id=cfg.stream_id, bias=bias)
+            elif ctx.needs_input_grad[1]:
+                dW = _update_gemm(g2, h2, cfg).to(weight.dtype)
         dx = (g2 @ weight).reshape(x.shape) if ctx.needs_input_grad[0] else None
-        db = g2.sum(0) if ctx.has_bias and ctx.needs_input_grad[2] else None
+        if bias and db is None:
+            db = g2.sum(0)
         if cfg.auto_advance:
             cfg.advance()
         return dx, dW, db, None

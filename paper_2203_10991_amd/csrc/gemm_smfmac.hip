@@ -54,6 +54,7 @@ __global__ __launch_bounds__(WM * WN * 64) void update_gemm_smfmac_kernel(
     float *__restrict__ out, int64_t ldo, int64_t slab_stride,       // out + z*slab_stride
     int64_t n_groups, int64_t groups_per_slab, int64_t O, int64_t I, int tiles_m, int tiles_n, int accumulate,
     int64_t o_first, int64_t o_end,          // the launch computes rows [o_first, o_end) of dW; tiles_m counts its M-tiles
+    int64_t h_rows,                          // rows h has: n_groups * 16, or up to 15 fewer (the rest count as zeros; not with SHIFTED)
     ShiftArg sh)                             // (SHIFTED only)
 {
     constexpr int TM = WM * AB * 32, TN = WN * BB * 32;
@@ -168,7 +169,7 @@ __global__ __launch_bounds__(WM * WN * 64) void update_gemm_smfmac_kernel(
         if constexpr (SHIFTED)       // rows -margin .. T+margin-1 of x are readable; offsets are relative to row t0 - margin
             rh = rsrc((const char *)h + (t0 - sh.margin) * ldh * 2, ((T - t0 - 1 + 2 * (int64_t)sh.margin) * ldh + sh.cb) * 2);
         else
-        rh = rsrc((const char *)h + t0 * ldh * 2, ((T - t0 - 1) * ldh + I) * 2);
+        rh = rsrc((const char *)h + t0 * ldh * 2, ((h_rows - t0 - 1) * ldh + I) * 2);
         rv = rsrc((const char *)vals + Gs * O * 16, (n_groups - Gs) * O * 16);
         rm = rsrc((const char *)meta + Gs * O * 2, (n_groups - Gs) * O * 2);
     };
@@ -192,6 +193,9 @@ __global__ __launch_bounds__(WM * WN * 64) void update_gemm_smfmac_kernel(
     };
     // first stage (relative to the slab) in which this wave's token group lies past the end of the tensor
     const int first_missing = (int)min((int64_t)0x7fffffff, (n_groups - g_begin - wgrp + 1) / 2);
+    // stage in which this wave's token group has fewer than 16 rows of h (-1: none)
+    const int64_t last_group = h_rows / 16;
+    const int partial = !SHIFTED && h_rows < T && last_group >= g_begin && (last_group - g_begin) % 2 == wgrp ? (int)min((int64_t)0x7fffffff, (last_group - g_begin) / 2) : -1;
     // "stage `it` has landed" while the loads of the IN_FLIGHT stages fetched after it may still be on
     // their way ...
     auto stage_ready = [&](auto in_flight_c, int it, char *stage) {
@@ -204,6 +208,13 @@ __global__ __launch_bounds__(WM * WN * 64) void update_gemm_smfmac_kernel(
             for (int c = lane; c < B_ROWS * CPR; c += 64) *(uint4 *)(stage + wave * B_ROWS * (TN * 2) + c * 16) = z;
             for (int c = lane; c < A_SLOTS; c += 64) *(uint4 *)(stage + A_OFF + (wave * A_SLOTS + c) * 16) = z;
             for (int c = lane; c < M_SLOTS / 8; c += 64) *(uint4 *)(stage + M_OFF + wave * M_SLOTS * 2 + c * 16) = z;
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        }
+        if (!SHIFTED && it == partial) {             // the h rows past the last token of this wave's share
+            const int rows_left = (int)(h_rows % 16) - (wave * B_ROWS - 16 * wgrp);
+            const uint4 z = make_uint4(0, 0, 0, 0);
+            for (int c = lane; c < B_ROWS * CPR; c += 64)
+                if (c / CPR >= rows_left) *(uint4 *)(stage + wave * B_ROWS * (TN * 2) + c * 16) = z;
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         }
         // ... and every other wave's part of it too.  A bare barrier: __syncthreads() would add a
@@ -751,20 +762,14 @@ size_t update_gemm_smfmac_shifted_workspace(int64_t T, int64_t O, int64_t I)
     return splitk_workspace_bytes(make_plan(T, O, I, true).slabs, O, I);
 }
 
-hipError_t launch_update_gemm_smfmac(const void *vals, const uint16_t *meta, const void *h, int64_t ldh, float *dW,
-                                     int64_t lddw, int64_t T, int64_t O, int64_t I, float beta, void *workspace,
-                                     hipStream_t st)
+// The kernels of a plan, into `tg`.  h_rows < T: only for plans without 384-row tiles
+static hipError_t run_plan(const Plan &p, const OutTarget &tg, const void *vals, const uint16_t *meta, const void *h, int64_t ldh, int64_t h_rows,
+                           int64_t T, int64_t O, int64_t I, hipStream_t st)
 {
-    const Plan p = make_plan(T, O, I);
-    const int accumulate = beta != 0.f;
-    const OutTarget tg = splitk_target(p.slabs, dW, lddw, workspace, O, I, accumulate);
-    float *out = tg.out;
-    const int64_t ldo = tg.ldo, slab_stride = tg.slab_stride;
-    const int acc_flag = tg.accumulate;
     if (p.tall_rows > 0) {
         dim3 tall_grid((unsigned)(p.tall_tiles_m * p.tiles_n), 1, 1);
         hipLaunchKernelGGL(update_gemm_smfmac_tall_kernel, tall_grid, dim3(512), 0, st, (const uint16_t *)vals, meta, (const uint16_t *)h,
-                           ldh, out, ldo, slab_stride, T / 16, p.groups_per_slab, O, I, p.tall_tiles_m, p.tiles_n, acc_flag,
+                           ldh, tg.out, tg.ldo, tg.slab_stride, T / 16, p.groups_per_slab, O, I, p.tall_tiles_m, p.tiles_n, tg.accumulate,
                            (int64_t)0, p.tall_rows);
         hipError_t e0 = hipGetLastError();
         if (e0 != hipSuccess) return e0;
@@ -773,17 +778,43 @@ hipError_t launch_update_gemm_smfmac(const void *vals, const uint16_t *meta, con
         dim3 grid((unsigned)(p.tiles_m * p.tiles_n), 1, (unsigned)p.slabs);
 #define NM_LAUNCH(WM, WN, AB, BB)                                                                                     \
     hipLaunchKernelGGL((update_gemm_smfmac_kernel<WM, WN, AB, BB>), grid, dim3(WM * WN * 64), 0, st, (const uint16_t *)vals,   \
-                       meta, (const uint16_t *)h, ldh, out, ldo, slab_stride, T / 16, p.groups_per_slab, O, I,         \
-                       p.tiles_m, p.tiles_n, acc_flag, p.tall_rows, O, ShiftArg{})
+                       meta, (const uint16_t *)h, ldh, tg.out, tg.ldo, tg.slab_stride, T / 16, p.groups_per_slab, O, I,         \
+                       p.tiles_m, p.tiles_n, tg.accumulate, p.tall_rows, O, h_rows, ShiftArg{})
         if (p.shape == 0) NM_LAUNCH(2, 4, 4, 2);
         else if (p.shape == 3) NM_LAUNCH(4, 2, 2, 2);
         else NM_LAUNCH(2, 2, 2, 2);
 #undef NM_LAUNCH
     }
-    hipError_t e = hipGetLastError();
+    return hipGetLastError();
+}
+
+hipError_t launch_update_gemm_smfmac(const void *vals, const uint16_t *meta, const void *h, int64_t ldh, float *dW,
+                                     int64_t lddw, int64_t T, int64_t O, int64_t I, float beta, void *workspace,
+                                     hipStream_t st)
+{
+    const Plan p = make_plan(T, O, I);
+    const int accumulate = beta != 0.f;
+    const OutTarget tg = splitk_target(p.slabs, dW, lddw, workspace, O, I, accumulate);
+    hipError_t e = run_plan(p, tg, vals, meta, h, ldh, T, T, O, I, st);
     if (e != hipSuccess) return e;
     if (p.slabs > 1) e = launch_splitk_reduce((const float *)workspace, p.slabs, dW, lddw, O, I, accumulate, 1.0f, st);
     return e;
+}
+
+// (needs_whole_rows: the plan has 384-row tiles, whose kernel wants every row of the last token group)
+size_t update_gemm_smfmac_parts_bytes(int64_t T, int64_t O, int64_t I, bool *needs_whole_rows)
+{
+    const Plan p = make_plan(T, O, I);
+    *needs_whole_rows = p.tall_rows > 0;
+    return (size_t)p.slabs * (size_t)O * (size_t)I * sizeof(float);
+}
+
+hipError_t launch_update_gemm_smfmac_parts(const void *vals, const uint16_t *meta, const void *h, int64_t ldh, int64_t h_rows, int64_t T,
+                                           int64_t O, int64_t I, float *part, int *slabs, hipStream_t st)
+{
+    const Plan p = make_plan(T, O, I);
+    *slabs = p.slabs;
+    return run_plan(p, OutTarget{part, I, O * I, 0}, vals, meta, h, ldh, h_rows, T, O, I, st);
 }
 
 // The kernels of a plan on the shift table (no 384-row tiles there), into `tg`
@@ -796,7 +827,7 @@ static hipError_t run_shifted(const Plan &p, const OutTarget &tg, const void *va
 #define NM_LAUNCH(WM, WN, AB, BB)                                                                                     \
     hipLaunchKernelGGL((update_gemm_smfmac_kernel<WM, WN, AB, BB, true>), grid, dim3(WM * WN * 64), 0, st,              \
                        (const uint16_t *)vals, meta, (const uint16_t *)x, ldx, tg.out, tg.ldo, tg.slab_stride, T / 16,   \
-                       p.groups_per_slab, O, I, p.tiles_m, p.tiles_n, tg.accumulate, (int64_t)0, O, sh)
+                       p.groups_per_slab, O, I, p.tiles_m, p.tiles_n, tg.accumulate, (int64_t)0, O, T, sh)
     if (p.shape == 0) NM_LAUNCH(2, 4, 4, 2);
     else if (p.shape == 1) NM_LAUNCH(2, 2, 2, 2);
     else if (p.shape == 3) NM_LAUNCH(4, 2, 2, 2);

@@ -663,6 +663,29 @@ size_t update_gemm_q8_workspace(int64_t T, int64_t O, int64_t I)
     return splitk_workspace_bytes(make_plan_q8(T, O, I).slabs, O, I);
 }
 
+// The kernels of a plan, into `tg`, scaled by `ap`
+static hipError_t run_q8_plan(const PlanQ8 &p, const OutTarget &tg, const AlphaPair &ap, const uint8_t *vals8, const uint32_t *meta32,
+                              const uint8_t *h8, int64_t ldh, int64_t T, int64_t O, int64_t I, hipStream_t st)
+{
+    if (p.tall_rows > 0) {
+        hipLaunchKernelGGL(update_gemm_smfmac_q8_tall_kernel, dim3((unsigned)(p.tall_tiles_m * p.tiles_n)), dim3(512), 0, st,
+                           vals8, meta32, h8, ldh, tg.out, tg.ldo, T / 32, O, I, p.tall_tiles_m, p.tiles_n, ap.acc, ap.alpha, p.tall_rows);
+        hipError_t e0 = hipGetLastError();
+        if (e0 != hipSuccess) return e0;
+        if (p.tiles_m == 0) return hipSuccess;
+    }
+    dim3 grid((unsigned)(p.tiles_m * p.tiles_n), 1, (unsigned)p.slabs);
+#define NM_LAUNCH(WM, WN, AB, BB)                                                                                     \
+    hipLaunchKernelGGL((update_gemm_smfmac_q8_kernel<WM, WN, AB, BB>), grid, dim3(WM * WN * 64), 0, st, vals8, meta32, h8,    \
+                       ldh, tg.out, tg.ldo, tg.slab_stride, T / 32, p.groups_per_slab, O, I, p.tiles_m, p.tiles_n, ap.acc, ap.alpha,  \
+                       p.tall_rows, ShiftArg{})
+    if (p.shape == 0) NM_LAUNCH(2, 4, 4, 2);
+    else if (p.shape == 1) NM_LAUNCH(2, 4, 2, 2);
+    else NM_LAUNCH(1, 4, 2, 2);
+#undef NM_LAUNCH
+    return hipGetLastError();
+}
+
 hipError_t launch_update_gemm_q8(const uint8_t *vals8, const uint32_t *meta32, const uint8_t *h8, int64_t ldh, float *dW,
                                  int64_t lddw, int64_t T, int64_t O, int64_t I, AlphaArg alpha, float beta, void *workspace,
                                  hipStream_t st)
@@ -671,32 +694,25 @@ hipError_t launch_update_gemm_q8(const uint8_t *vals8, const uint32_t *meta32, c
     const PlanQ8 p = make_plan_q8(T, O, I);
     const int accumulate = beta != 0.f;
     const OutTarget tg = splitk_target(p.slabs, dW, lddw, workspace, O, I, accumulate);
-    float *out = tg.out;
-    const int64_t ldo = tg.ldo, slab_stride = tg.slab_stride;
     // partial sums are scaled once, in the second pass; otherwise the kernels scale, by a host or a device value
     const AlphaPair ap = p.slabs > 1 ? AlphaPair{tg.accumulate, 1.0f} : encode_alpha(tg.accumulate, alpha, st);
-    const int acc_flag = ap.acc;
-    const float k_alpha = ap.alpha;
-    if (p.tall_rows > 0) {
-        hipLaunchKernelGGL(update_gemm_smfmac_q8_tall_kernel, dim3((unsigned)(p.tall_tiles_m * p.tiles_n)), dim3(512), 0, st,
-                           vals8, meta32, h8, ldh, out, ldo, T / 32, O, I, p.tall_tiles_m, p.tiles_n, acc_flag, k_alpha, p.tall_rows);
-        hipError_t e0 = hipGetLastError();
-        if (e0 != hipSuccess) return e0;
-        if (p.tiles_m == 0) return hipSuccess;
-    }
-    dim3 grid((unsigned)(p.tiles_m * p.tiles_n), 1, (unsigned)p.slabs);
-#define NM_LAUNCH(WM, WN, AB, BB)                                                                                     \
-    hipLaunchKernelGGL((update_gemm_smfmac_q8_kernel<WM, WN, AB, BB>), grid, dim3(WM * WN * 64), 0, st, vals8, meta32, h8,    \
-                       ldh, out, ldo, slab_stride, T / 32, p.groups_per_slab, O, I, p.tiles_m, p.tiles_n, acc_flag, k_alpha,  \
-                       p.tall_rows, ShiftArg{})
-    if (p.shape == 0) NM_LAUNCH(2, 4, 4, 2);
-    else if (p.shape == 1) NM_LAUNCH(2, 4, 2, 2);
-    else NM_LAUNCH(1, 4, 2, 2);
-#undef NM_LAUNCH
-    hipError_t e = hipGetLastError();
+    hipError_t e = run_q8_plan(p, tg, ap, vals8, meta32, h8, ldh, T, O, I, st);
     if (e != hipSuccess) return e;
     if (p.slabs > 1) e = launch_splitk_reduce((const float *)workspace, p.slabs, dW, lddw, O, I, accumulate, alpha, st);
     return e;
+}
+
+size_t update_gemm_q8_parts_bytes(int64_t T, int64_t O, int64_t I)
+{
+    return (size_t)make_plan_q8(T, O, I).slabs * (size_t)O * (size_t)I * sizeof(float);
+}
+
+hipError_t launch_update_gemm_q8_parts(const uint8_t *vals8, const uint32_t *meta32, const uint8_t *h8, int64_t ldh, int64_t T, int64_t O,
+                                       int64_t I, float *part, int *slabs, hipStream_t st)
+{
+    const PlanQ8 p = make_plan_q8(T, O, I);
+    *slabs = p.slabs;
+    return run_q8_plan(p, OutTarget{part, I, O * I, 0}, AlphaPair{0, 1.0f}, vals8, meta32, h8, ldh, T, O, I, st);
 }
 
 size_t update_gemm_q8_shifted_workspace(int64_t T, int64_t O, int64_t I)

@@ -61,4 +61,87 @@ hipError_t launch_finish_conv(const float *part, int slabs, void *dW, int64_t O,
     return hipGetLastError();
 }
 
+// Linear: dW[o][i] (bf16) = alpha * sum_z part[z][o][i], and beside it -- workgroups past the first dw_blocks -- the bias gradient
+// db[o] (bf16) = the sum of the token groups' column sums csum[G][o].  The sums of dW run as in splitk_reduce_kernel (R threads
+// per float4); a column's groups are summed by 64 threads, each a strided share in order, and a fixed tree over LDS.
+// Bound: launch latency and one read of the partial sums.  Sum, conversion and bias were three to five launches.
+constexpr int DB_COLS = 16;                                              // columns of a bias workgroup: 4 float4 x 64 groups in flight
+template <int R>
+__global__ __launch_bounds__(256) void finish_linear_kernel(const float *__restrict__ part, int slabs, int64_t O, int64_t I, uint16_t *__restrict__ dW,
+                                                            AlphaArg al, int dw_blocks, const float *__restrict__ csum, int64_t groups,
+                                                            uint16_t *__restrict__ db)
+{
+    __shared__ float4 sums[256];
+    if ((int)blockIdx.x < dw_blocks) {
+        const float alpha = alpha_of(al);
+        const int64_t n4 = O * I / 4, idx = (int64_t)blockIdx.x * (256 / R) + threadIdx.x / R;       // (I % 8 == 0: rows are whole float4s)
+        const int r = threadIdx.x % R;
+        const bool valid = idx < n4;
+        float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (valid)
+            for (int z = r; z < slabs; z += R) {
+                const float4 v = *(const float4 *)(part + (int64_t)z * O * I + idx * 4);
+                s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+            }
+#pragma unroll
+        for (int d = 1; d < R; d <<= 1) {
+            s.x += __shfl_xor(s.x, d); s.y += __shfl_xor(s.y, d); s.z += __shfl_xor(s.z, d); s.w += __shfl_xor(s.w, d);
+        }
+        if (valid && r == 0) *(uint2 *)(dW + idx * 4) = make_uint2(pack_bf16_rne(s.x * alpha, s.y * alpha), pack_bf16_rne(s.z * alpha, s.w * alpha));
+        return;
+    }
+    const int64_t c0 = (int64_t)(blockIdx.x - dw_blocks) * DB_COLS + (threadIdx.x & 3) * 4;
+    const int g = threadIdx.x >> 2;
+    float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (c0 < O)
+        for (int64_t G = g; G < groups; G += 64) {
+            const float4 v = *(const float4 *)(csum + G * O + c0);
+            s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+        }
+    sums[threadIdx.x] = s;
+    for (int d = 32; d >= 1; d >>= 1) {
+        __syncthreads();
+        if (g < d) {
+            const float4 v = sums[threadIdx.x + 4 * d];
+            float4 &m = sums[threadIdx.x];
+            m.x += v.x; m.y += v.y; m.z += v.z; m.w += v.w;
+        }
+    }
+    if (g == 0 && c0 < O) {
+        const float4 m = sums[threadIdx.x];
+        *(uint2 *)(db + c0) = make_uint2(pack_bf16_rne(m.x, m.y), pack_bf16_rne(m.z, m.w));
+    }
+}
+
+hipError_t launch_finish_linear(const float *part, int slabs, int64_t O, int64_t I, void *dW, AlphaArg alpha, const float *csum, int64_t groups,
+                                void *db, hipStream_t st)
+{
+    const int R = slabs >= 12 ? 8 : 1;
+    const int64_t dw_blocks = (O * I / 4 + 256 / R - 1) / (256 / R), db_blocks = db ? (O + DB_COLS - 1) / DB_COLS : 0;
+    if (dw_blocks + db_blocks > 0x7fffffffll) return hipErrorInvalidConfiguration;
+    const dim3 grid((unsigned)(dw_blocks + db_blocks));
+    if (R == 8)
+        hipLaunchKernelGGL(finish_linear_kernel<8>, grid, dim3(256), 0, st, part, slabs, O, I, (uint16_t *)dW, alpha, (int)dw_blocks, csum, groups, (uint16_t *)db);
+    else
+        hipLaunchKernelGGL(finish_linear_kernel<1>, grid, dim3(256), 0, st, part, slabs, O, I, (uint16_t *)dW, alpha, (int)dw_blocks, csum, groups, (uint16_t *)db);
+    return hipGetLastError();
+}
+
+// rows [0, rows) of h (C columns, row stride ld, bf16) and zeros up to out_rows, contiguous
+__global__ __launch_bounds__(256) void pad_rows_kernel(const uint16_t *__restrict__ h, int64_t rows, int64_t C, int64_t ld, uint16_t *__restrict__ out, int64_t out_rows)
+{
+    const int64_t cpr = C / 8, i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= out_rows * cpr) return;
+    const int64_t r = i / cpr, c = (i - r * cpr) * 8;
+    *(uint4 *)(out + r * C + c) = r < rows ? *(const uint4 *)(h + r * ld + c) : make_uint4(0u, 0u, 0u, 0u);
+}
+
+hipError_t launch_pad_rows(const void *h, int64_t rows, int64_t C, int64_t ld, void *out, int64_t out_rows, hipStream_t st)
+{
+    const int64_t blocks = (out_rows * (C / 8) + 255) / 256;
+    if (blocks > 0x7fffffffll) return hipErrorInvalidConfiguration;
+    hipLaunchKernelGGL(pad_rows_kernel, dim3((unsigned)blocks), dim3(256), 0, st, (const uint16_t *)h, rows, C, ld, (uint16_t *)out, out_rows);
+    return hipGetLastError();
+}
+
 }  // namespace nm

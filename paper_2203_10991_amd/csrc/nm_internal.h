@@ -119,6 +119,24 @@ hipError_t launch_update_gemm_q8_shifted_parts(const uint8_t *vals8, const uint3
 // conv weight gradient, bf16 [O][C][taps] = alpha * sum over the slabs of part[slabs][O][taps][C]
 hipError_t launch_finish_conv(const float *part, int slabs, void *dW, int64_t O, int C, int taps, AlphaArg alpha, hipStream_t st);
 
+// ... of a linear layer (bf16 tensors, T tokens, not necessarily whole token groups)
+hipError_t launch_prune_layer(int m, int est, const void *g, int64_t ldg, const void *act, int64_t lda, int64_t T, int64_t O, uint64_t seed,
+                              uint32_t stream_id, void *gout, int64_t ldgo, void *vals, uint16_t *meta, float *csum, hipStream_t st);
+hipError_t launch_prune_q8_layer(int est, const void *g, int64_t ldg, int64_t T, int64_t O, uint64_t seed, uint32_t stream_id,
+                                 const float *rec, uint8_t *vals8, uint32_t *meta32, float *csum, hipStream_t st);
+hipError_t launch_cast_e4m3_rows(int dt, const void *h, int64_t R, int64_t C, int64_t ld, const float *rec, uint8_t *h8, int64_t ld8,
+                                 int64_t out_rows, hipStream_t st);
+hipError_t launch_pad_rows(const void *h, int64_t rows, int64_t C, int64_t ld, void *out, int64_t out_rows, hipStream_t st);
+size_t update_gemm_smfmac_parts_bytes(int64_t T, int64_t O, int64_t I, bool *needs_whole_rows);
+hipError_t launch_update_gemm_smfmac_parts(const void *vals, const uint16_t *meta, const void *h, int64_t ldh, int64_t h_rows, int64_t T,
+                                           int64_t O, int64_t I, float *part, int *slabs, hipStream_t st);
+size_t update_gemm_q8_parts_bytes(int64_t T, int64_t O, int64_t I);
+hipError_t launch_update_gemm_q8_parts(const uint8_t *vals8, const uint32_t *meta32, const uint8_t *h8, int64_t ldh, int64_t T, int64_t O,
+                                       int64_t I, float *part, int *slabs, hipStream_t st);
+// dW (bf16, contiguous [O][I]) = alpha * sum of the slabs; db (bf16 [O], may be null) = sum of the groups' column sums
+hipError_t launch_finish_linear(const float *part, int slabs, int64_t O, int64_t I, void *dW, AlphaArg alpha, const float *csum, int64_t groups,
+                                void *db, hipStream_t st);
+
 // The library's static device scratch array (nm_static.hip): its size, and its address on the current device
 // (looked up once per device; no allocation).
 size_t static_scratch_bytes();

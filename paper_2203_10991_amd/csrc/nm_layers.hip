@@ -74,9 +74,104 @@ const char *bad_conv_shape(int64_t N, int64_t C, int64_t O, int64_t H, int64_t W
     return nullptr;
 }
 
+struct LinearPlan {
+    int64_t Tp, groups;                   // tokens rounded up to whole groups of 16 (8-bit: 32)
+    bool copy_h;                          // h is copied with zero rows up to Tp
+    size_t recs, h, vals, meta, csum, part, bytes;
+};
+LinearPlan plan_linear(int64_t T, int64_t O, int64_t I, bool q8, bool bias)
+{
+    LinearPlan p;
+    const int64_t gt = q8 ? 32 : 16;
+    p.Tp = (T + gt - 1) / gt * gt;
+    p.groups = p.Tp / gt;
+    bool whole = false;
+    const size_t part = q8 ? nm::update_gemm_q8_parts_bytes(p.Tp, O, I) : nm::update_gemm_smfmac_parts_bytes(p.Tp, O, I, &whole);
+    p.copy_h = !q8 && whole && p.Tp != T;
+    Carver c;
+    p.recs = c.take(q8 ? 32 : 0);
+    p.h = c.take(q8 ? (size_t)p.Tp * I : p.copy_h ? (size_t)p.Tp * I * 2 : 0);
+    p.vals = c.take((size_t)(p.Tp / 2) * O * (q8 ? 1 : 2));
+    p.meta = c.take((size_t)p.groups * O * (q8 ? 4 : 2));
+    p.csum = c.take(bias ? (size_t)p.groups * O * 4 : 0);
+    p.part = c.take(part);
+    p.bytes = c.used;
+    return p;
+}
+const char *bad_linear_shape(int64_t T, int64_t O, int64_t I, int q8)
+{
+    const int64_t lim = (int64_t)1 << 21;
+    if (T < 1 || O < 1 || I < 1 || O > lim || I > lim || T > ((int64_t)1 << 34) / O || T > ((int64_t)1 << 36) / I)
+        return "sizes must be positive, O and I at most 2^21, T * O at most 2^34 and T * I at most 2^36";
+    if (O % 8 || I % (q8 ? 16 : 8)) return "O must be a multiple of 8 and I of 8 (16 with 8-bit operands)";
+    return nullptr;
+}
+
 }  // namespace
 
 extern "C" {
+
+size_t nm_linear_update_workspace(int64_t T, int64_t O, int64_t I, int q8, int bias)
+{
+    if (bad_linear_shape(T, O, I, q8)) return 0;
+    return plan_linear(T, O, I, q8 != 0, bias != 0).bytes;
+}
+
+int nm_linear_update(const void *g, int64_t ldg, const void *act, int64_t lda, const void *h, int64_t ldh, int64_t T, int64_t O, int64_t I,
+                     int m, int mode, int q8, uint64_t seed, uint32_t stream_id, void *g_out, int64_t ldgo, void *dW, void *db,
+                     void *workspace, size_t workspace_bytes, void *hip_stream)
+{
+    const char *fn = "nm_linear_update";
+    if (m != 2 && m != 4) return fail(NM_ERR_UNSUPPORTED, "%s: blocks of %d (2 = MVUE 1:2, 4 = MVUE 2:4)", fn, m);
+    if (mode != 0 && !(mode == 1 && m == 4)) return fail(NM_ERR_UNSUPPORTED, "%s: unknown mode %d (0 = optimal MVUE, 1 = approx-MVUE 2:4)", fn, mode);
+    if (act && q8) return fail(NM_ERR_UNSUPPORTED, "%s: the 8-bit form takes the gradient itself, not a ReLU's output beside it", fn);
+    if (const char *why = bad_linear_shape(T, O, I, q8)) return fail(NM_ERR_SHAPE, "%s: %s", fn, why);
+    if (!g || !h || !dW || (act && !g_out)) return fail(NM_ERR_NULL, "%s: g, h, dW (and g_out with act) must not be NULL", fn);
+    const int64_t lim = (int64_t)1 << 21;
+    if (ldg < O || ldh < I || ldg > lim || ldh > lim || (act && (lda < O || ldgo < O || lda > lim || ldgo > lim)))
+        return fail(NM_ERR_SHAPE, "%s: a row stride is smaller than its row or beyond 2^21", fn);
+    if (!aligned16(g) || !aligned16(h) || !aligned16(dW) || !aligned16(db) || !aligned16(workspace) || ldg % 8 || ldh % 8 ||
+        (act && (!aligned16(act) || !aligned16(g_out) || lda % 8 || ldgo % 8)))
+        return fail(NM_ERR_ALIGN, "%s: bases and row strides need 16-byte alignment", fn);
+    const LinearPlan p = plan_linear(T, O, I, q8 != 0, db != nullptr);
+    if (!workspace || workspace_bytes < p.bytes)
+        return fail(NM_ERR_WORKSPACE, "%s: workspace of %zu bytes required, %zu given", fn, p.bytes, workspace ? workspace_bytes : (size_t)0);
+    struct { const void *p; size_t n; } in[3] = {{g, (size_t)((T - 1) * ldg + O) * 2}, {h, (size_t)((T - 1) * ldh + I) * 2},
+                                                 {act, act ? (size_t)((T - 1) * lda + O) * 2 : 0}},
+                                        out[4] = {{dW, (size_t)O * I * 2}, {db, db ? (size_t)O * 2 : 0},
+                                                  {g_out, act ? (size_t)((T - 1) * ldgo + O) * 2 : 0}, {workspace, p.bytes}};
+    for (int i = 0; i < 4; ++i) {
+        for (int j = 0; j < 3; ++j) if (overlap(out[i].p, out[i].n, in[j].p, in[j].n)) return fail(NM_ERR_ALIAS, "%s: an output overlaps an input", fn);
+        for (int j = 0; j < i; ++j) if (overlap(out[i].p, out[i].n, out[j].p, out[j].n)) return fail(NM_ERR_ALIAS, "%s: two outputs overlap", fn);
+    }
+
+    hipStream_t st = (hipStream_t)hip_stream;
+    char *w = (char *)workspace;
+    float *part = (float *)(w + p.part), *csum = db ? (float *)(w + p.csum) : nullptr;
+    hipError_t e = hipSuccess;
+    int slabs = 1;
+    nm::AlphaArg alpha(1.0f);
+    if (q8) {
+        float *rec_g = (float *)(w + p.recs), *rec_h = rec_g + 4;
+        e = nm::launch_q8_scale_pair(g, T, O, ldg, 57344.0f / (float)m, rec_g, h, T, I, ldh, 448.0f, rec_h, st);
+        if (e == hipSuccess) e = nm::launch_cast_e4m3_rows(NM_DT_BF16, h, T, I, ldh, rec_h, (uint8_t *)(w + p.h), I, p.Tp, st);
+        if (e == hipSuccess)
+            e = nm::launch_prune_q8_layer(m == 2 ? 3 : mode, g, ldg, T, O, seed, stream_id, rec_g, (uint8_t *)(w + p.vals), (uint32_t *)(w + p.meta), csum, st);
+        if (e == hipSuccess)
+            e = nm::launch_update_gemm_q8_parts((const uint8_t *)(w + p.vals), (const uint32_t *)(w + p.meta), (const uint8_t *)(w + p.h), I, p.Tp, O, I,
+                                                part, &slabs, st);
+        alpha = nm::AlphaArg(1.0f, rec_g, rec_h);
+    } else {
+        if (p.copy_h) e = nm::launch_pad_rows(h, T, I, ldh, w + p.h, p.Tp, st);
+        if (e == hipSuccess)
+            e = nm::launch_prune_layer(m, mode, g, ldg, act, lda, T, O, seed, stream_id, g_out, ldgo, w + p.vals, (uint16_t *)(w + p.meta), csum, st);
+        if (e == hipSuccess)
+            e = nm::launch_update_gemm_smfmac_parts(w + p.vals, (const uint16_t *)(w + p.meta), p.copy_h ? w + p.h : h, p.copy_h ? I : ldh,
+                                                    p.copy_h ? p.Tp : T, p.Tp, O, I, part, &slabs, st);
+    }
+    if (e == hipSuccess) e = nm::launch_finish_linear(part, slabs, O, I, dW, alpha, csum, p.groups, db, st);
+    return launched(fn, e);
+}
 
 size_t nm_conv_update_workspace(int64_t N, int64_t C, int64_t O, int64_t H, int64_t W, int k, int q8)
 {

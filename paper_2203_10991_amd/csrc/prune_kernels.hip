@@ -39,6 +39,16 @@ struct ProdArg { const void *d; int64_t ldd; void *gout; int64_t ldgo; };
 // of its own otherwise.
 struct LayerArg { int64_t T; float *csum; };
 
+// The four column sums of a thread.  No branch on csum: with one, the compiler moves every kept value's arithmetic behind it, and
+// all rows stay in registers until there (218 instead of 81); without csum the descriptor is empty and the store is dropped.
+// G0: the workgroup's first token group.
+__device__ __forceinline__ void put_csum(const LayerArg &la, int64_t G0, int64_t G, int64_t O, int64_t col0, const float *cs)
+{
+    const auto r = __builtin_amdgcn_make_buffer_rsrc((char *)(la.csum + G0 * O), 0, la.csum ? 0x7fffffff : 0, 0x00020000);
+    const uint4 v = make_uint4(__float_as_uint(cs[0]), __float_as_uint(cs[1]), __float_as_uint(cs[2]), __float_as_uint(cs[3]));
+    buffer_put_piece<16>(r, (uint32_t)((G - G0) * O + col0) * 4u, v);
+}
+
 template <int DT, int PROD>
 __device__ __forceinline__ uint4 producer_row(const uint4 &u, const uint4 &d)
 {
@@ -91,9 +101,12 @@ __device__ __forceinline__ void prune_compress_body(
         else return NT ? load_stream8(p) : load_global8(p);
     };
     [[maybe_unused]] float cs[VEC];
-    auto add_columns = [&](const uint4 &v, bool first) {
-#pragma unroll
-        for (int c = 0; c < VEC; ++c) cs[c] = first ? Row<DT>::get(v, c) : cs[c] + Row<DT>::get(v, c);
+    auto add_rows = [&](int r, int n, int c) {            // n rows from r on into the sum of column c
+        if constexpr (LAYER) {
+            float q = Row<DT>::get(rows[r], c) + Row<DT>::get(rows[r + 1], c);
+            if (n == 4) q += Row<DT>::get(rows[r + 2], c) + Row<DT>::get(rows[r + 3], c);
+            cs[c] = r == 0 ? q : cs[c] + q;
+        }
     };
     auto fetch_rows = [&](const char *base, const char *dbase, int first) {
 #pragma unroll
@@ -128,15 +141,6 @@ __device__ __forceinline__ void prune_compress_body(
             for (int r = 0; r < 8; ++r) {
                 rows[first + r] = producer_row<DT, PROD>(rows[first + r], f[r]);
                 buffer_put_piece<RB>(ro, oo + (uint32_t)(first + r) * (uint32_t)pa.ldgo * ESZ, rows[first + r]);
-            }
-        }
-        if (la.csum) {
-#pragma unroll
-            for (int r = first; r < first + 8; ++r) add_columns(rows[r], r == 0);
-            if (first == 8) {
-                float *cp = la.csum + G * O + col0;
-#pragma unroll
-                for (int c = 0; c < VEC; c += 4) *(float4 *)(cp + c) = make_float4(cs[c], cs[c + 1], cs[c + 2], cs[c + 3]);
             }
         }
     };
@@ -200,6 +204,7 @@ __device__ __forceinline__ void prune_compress_body(
                 select_1of2(Row<DT>::get(rows[2 * b], c), Row<DT>::get(rows[2 * b + 1], c), words[c], k, v);
                 if (b & 1) put2(c, b >> 1, held[c], v); else held[c] = v;
                 md[c] |= ((uint32_t)((b & 1) << 1) | k) << (2 * b);
+                add_rows(2 * b, 2, c);
             } else {
                 float v0, v1; uint32_t nib;
                 if constexpr (EST == 1)
@@ -218,11 +223,16 @@ __device__ __forceinline__ void prune_compress_body(
                                     words[c], v0, v1, nib);
                 put2(c, b, v0, v1);
                 md[c] |= nib << (4 * b);
+                add_rows(4 * b, 4, c);
                 __builtin_amdgcn_sched_barrier(0);       // one block at a time: interleaving blocks only lengthens live ranges
             }
         }
     }
 
+    if constexpr (LAYER) {
+        static_assert(VEC == 4, "the sums leave as one float4");
+        put_csum(la, t0 / 16, G, O, col0, cs);
+    }
     // ---- kept values: 8 per column, VEC columns contiguous
     [[maybe_unused]] char *vp = (char *)vals_ + ((G * O + col0) * 8) * ESZ;            // = vals_ + 16 PC n (below): a wave's 64 threads own one run of it
     [[maybe_unused]] uint16_t *mp_late = nullptr;
@@ -336,6 +346,14 @@ __global__ __launch_bounds__(256) void prune_compress_half_kernel(
 {
     prune_compress_body<NM_DT_BF16, M, EST, false, 0, HI0, true, 4>(g, n_groups, O, ldg, key0, key1, stream_id, vals, meta, nullptr, 0);
 }
+// the form of a layer's backward pass (bf16; see LayerArg): PROD = 2 with the ReLU's derivative in front, else 0
+template <int M, int EST, int PROD, bool NT>
+__global__ __launch_bounds__(256) void prune_layer_kernel(
+    const void *__restrict__ g, int64_t n_groups, int64_t O, int64_t ldg, uint32_t key0, uint32_t key1, uint32_t stream_id,
+    void *__restrict__ vals, uint16_t *__restrict__ meta, ProdArg pa, LayerArg la)
+{
+    prune_compress_body<NM_DT_BF16, M, EST, false, PROD, true, NT, 4, true>(g, n_groups, O, ldg, key0, key1, stream_id, vals, meta, nullptr, 0, pa, la);
+}
 template <int DT, int M, int EST, bool NT>
 __global__ __launch_bounds__(256) void prune_producer_kernel(
     const void *__restrict__ u, int64_t n_groups, int64_t O, int64_t ldu, uint32_t key0, uint32_t key1, uint32_t stream_id,
@@ -369,18 +387,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 5))) voi
 // Output: 32-token groups, vals8[(G*O + o)*16 + 2i + s], meta32[G*O + o] (nibble i = quad i).
 // ------------------------------------------------------------------------------------
 // HI0: every Philox call index of the launch is below 2^32 (checked by the launcher), see prune_compress_body
-template <int DT, int EST, bool HI0>
+// VEC, LAYER: as in prune_compress_body (LAYER: T tokens, rows past them zero; csum [groups][O] or null)
+template <int DT, int EST, bool HI0, int VEC = Row<DT>::VEC, bool LAYER = false>
 __global__ __launch_bounds__(256) void prune_compress_q8_kernel(
     const void *__restrict__ g_, int64_t n_groups, int64_t O, int64_t ldg, uint32_t key0, uint32_t key1, uint32_t stream_id,
-    float scale, const float *__restrict__ scale_dev, uint8_t *__restrict__ vals8, uint32_t *__restrict__ meta32)
+    float scale, const float *__restrict__ scale_dev, uint8_t *__restrict__ vals8, uint32_t *__restrict__ meta32, LayerArg la)
 {
     if (scale_dev) scale = scale_dev[0];            // the scale as a device value (element 0 of a scale record)
     auto philox = [&](uint64_t ctr, uint32_t domain, uint32_t (&w4)[4]) {
         if constexpr (HI0) philox4x32_10_uniform_c123((uint32_t)ctr, 0u, stream_id, domain, key0, key1, w4);
         else philox4x32_10((uint32_t)ctr, (uint32_t)(ctr >> 32), stream_id, domain, key0, key1, w4);
     };
-    constexpr int VEC = Row<DT>::VEC;
-    constexpr int ESZ = DT == NM_DT_F32 ? 4 : 2;
+    constexpr int ESZ = DT == NM_DT_F32 ? 4 : 2, RB = VEC * ESZ;
     const int64_t ncg = O / VEC;
     const int64_t n = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (n >= n_groups * ncg) return;
@@ -391,9 +409,36 @@ __global__ __launch_bounds__(256) void prune_compress_q8_kernel(
     // rows live in two halves of 8 (two quad rows each); a half is refilled with the rows 16 further down as soon
     // as its quads are decided, through an address the compiler cannot see through (keeps the loads where they are)
     uint4 rows[16];
+    [[maybe_unused]] float cs[VEC];
+    [[maybe_unused]] const int64_t t0 = ((int64_t)blockIdx.x * 256 / ncg) * 32;           // (LAYER: as in prune_compress_body)
+    auto fetch_rows = [&](int first) {                                                    // tensor rows first .. first + 7 of the group
+        if constexpr (LAYER) {
+            const int64_t bytes = (la.T - t0) * ldg * ESZ;
+            const auto rg = __builtin_amdgcn_make_buffer_rsrc((char *)g_ + t0 * ldg * ESZ, 0, (int)(uint32_t)(bytes > 0xffffffffll ? 0xffffffffll : bytes), 0x00020000);
+            uint32_t token = (uint32_t)(G * 32 - t0);
+            if (first) asm volatile("" : "+v"(token));
+            const uint32_t og = (token * (uint32_t)ldg + (uint32_t)col0) * ESZ;
 #pragma unroll
-    for (int r = 0; r < 8; ++r) rows[r] = load_global(gp + (int64_t)r * ldg * ESZ);
+            for (int r = 0; r < 8; ++r) rows[(first + r) % 16] = buffer_piece<RB>(rg, og + (uint32_t)(first + r) * (uint32_t)ldg * ESZ);
+        } else {
+            const char *gp2 = gp;
+            if (first) asm volatile("" : "+v"(gp2));
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {
+                const char *p = gp2 + (int64_t)(first + r) * ldg * ESZ;
+                rows[(first + r) % 16] = RB == 16 ? load_global(p) : load_global8(p);
+            }
+        }
+    };
+    fetch_rows(0);
 
+    auto add_column = [&](auto b_c, int c) {             // the four rows of quad row b into the column's sum
+        if constexpr (LAYER) {
+            constexpr int r = (4 * decltype(b_c)::value) % 16;
+            const float q = (Row<DT>::get(rows[r], c) + Row<DT>::get(rows[r + 1], c)) + (Row<DT>::get(rows[r + 2], c) + Row<DT>::get(rows[r + 3], c));
+            cs[c] = decltype(b_c)::value == 0 ? q : cs[c] + q;
+        }
+    };
     uint32_t kept[VEC][4];        // 16 e5m2 codes per column
     uint32_t md[VEC];
 #pragma unroll
@@ -401,13 +446,7 @@ __global__ __launch_bounds__(256) void prune_compress_q8_kernel(
 
     static_for<8>([&](auto b_c) {                       // quad row b: tensor rows 4b .. 4b+3, held in rows[(4b) % 16 ..]
         constexpr int b = decltype(b_c)::value;
-        if constexpr (b == 1 || b == 2 || b == 4) {
-            const int first = b == 1 ? 8 : b == 2 ? 16 : 24;
-            const char *gp2 = gp;
-            asm volatile("" : "+v"(gp2));
-#pragma unroll
-            for (int r = 0; r < 8; ++r) rows[(first + r) % 16] = load_global(gp2 + (int64_t)(first + r) * ldg * ESZ);
-        }
+        if constexpr (b == 1 || b == 2 || b == 4) fetch_rows(b == 1 ? 8 : b == 2 ? 16 : 24);
         constexpr int R0 = (4 * b) % 16;
         if constexpr (EST == 3) {
             // MVUE 1:2: the quad row holds two pair rows; the kept value of pair row 2b+pr is slot pr of quad b, rounded
@@ -433,6 +472,7 @@ __global__ __launch_bounds__(256) void prune_compress_q8_kernel(
                     select_1of2(Row<DT>::get(rows[R0 + 2 * pr], c), Row<DT>::get(rows[R0 + 2 * pr + 1], c), sel[c], k, v);
                     kept[c][b / 2] = sr_e5m2_into<2 * (b & 1) + pr>(kept[c][b / 2], v * scale, rnd1[c] << 16);
                     md[c] |= ((uint32_t)(pr << 1) | k) << (4 * b + 2 * pr);
+                    if constexpr (pr == 1) add_column(b_c, c);
                 }
                 __builtin_amdgcn_sched_barrier(0);
             });
@@ -471,9 +511,14 @@ __global__ __launch_bounds__(256) void prune_compress_q8_kernel(
             kept[c][b / 2] = sr_e5m2_into<2 * (b & 1)>(kept[c][b / 2], v0 * scale, rnd[c] << 16);
             kept[c][b / 2] = sr_e5m2_into<2 * (b & 1) + 1>(kept[c][b / 2], v1 * scale, rnd[c] & 0xffff0000u);
             md[c] |= nib << (4 * b);
+            add_column(b_c, c);
             __builtin_amdgcn_sched_barrier(0);
         }
     });
+    if constexpr (LAYER) {
+        static_assert(VEC == 4, "the sums leave as one float4");
+        put_csum(la, t0 / 32, G, O, col0, cs);
+    }
 
     // 16 bytes per column, VEC columns contiguous; one index word per column
     uint4 *vp = (uint4 *)(vals8 + (G * O + col0) * 16);
@@ -488,20 +533,38 @@ template <int DT, int EST>
 static hipError_t launch_prune_q8_t(const void *g, int64_t T, int64_t O, int64_t ldg, uint64_t seed, uint32_t stream_id,
                                     float scale, const float *scale_dev, uint8_t *vals8, uint32_t *meta32, hipStream_t st)
 {
-    const int64_t groups = T / 32, threads = groups * (O / Row<DT>::VEC);
+    const int64_t groups = T / 32;
+    // bf16: four columns per thread (half a 16-byte row load), 70-90 registers and five to seven waves per SIMD where eight columns
+    // need 128-149 and leave three or four: optimal 2:4 512 x 512 17.4 -> 9.6 us, 12608 x 768 19.2 -> 15.6, 16384 x 4096 51.5 ->
+    // 49.2, 32768 x 28672 622 -> 625; MVUE 1:2 587 -> 582 and approx-MVUE 1258 -> 1143 us on the last.
+    constexpr int VEC = 4;
+    const int64_t threads = groups * (O / VEC);
     if (threads == 0) return hipSuccess;
     if ((threads + 255) / 256 > 0x7fffffffll) return hipErrorInvalidConfiguration;
-    // The bf16 optimal-2:4 kernel has a form for launches whose call indices (at most T*O/16 + 1) all lie below 2^32 (2^35 elements is a safe bound);
-    // the other instances run the general code, which the larger tensors take too.
-    if constexpr (DT == NM_DT_BF16 && EST == 0) {
-        if ((uint64_t)T * (uint64_t)O <= ((uint64_t)1 << 35)) {
-            hipLaunchKernelGGL((prune_compress_q8_kernel<DT, EST, true>), dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st,
-                               g, groups, O, ldg, (uint32_t)seed, (uint32_t)(seed >> 32), stream_id, scale, scale_dev, vals8, meta32);
-            return hipGetLastError();
-        }
-    }
-    hipLaunchKernelGGL((prune_compress_q8_kernel<DT, EST, false>), dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st,
-                       g, groups, O, ldg, (uint32_t)seed, (uint32_t)(seed >> 32), stream_id, scale, scale_dev, vals8, meta32);
+#define NM_Q8(HI0)                                                                                                                   \
+    hipLaunchKernelGGL((prune_compress_q8_kernel<DT, EST, HI0, VEC>), dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st,     \
+                       g, groups, O, ldg, (uint32_t)seed, (uint32_t)(seed >> 32), stream_id, scale, scale_dev, vals8, meta32, LayerArg{})
+    // call indices are at most T*O/8 (approx-MVUE and MVUE 1:2 make more of them than the optimal estimator); the binary32
+    // instances run the general code at every size
+    if (DT == NM_DT_BF16 && (uint64_t)T * (uint64_t)O <= ((uint64_t)1 << 34)) NM_Q8(DT == NM_DT_BF16);
+    else NM_Q8(false);
+#undef NM_Q8
+    return hipGetLastError();
+}
+
+// a layer's 8-bit prune (bf16, T tokens, T not necessarily a multiple of 32; T * O <= 2^34): est 0 optimal 2:4, 1 approx-MVUE 2:4,
+// 3 MVUE 1:2; csum (may be null): [ceil(T/32)][O] column sums of g per token group
+hipError_t launch_prune_q8_layer(int est, const void *g, int64_t ldg, int64_t T, int64_t O, uint64_t seed, uint32_t stream_id,
+                                 const float *rec, uint8_t *vals8, uint32_t *meta32, float *csum, hipStream_t st)
+{
+    const int64_t groups = (T + 31) / 32, threads = groups * (O / 4), blocks = (threads + 255) / 256;
+    if (threads == 0) return hipSuccess;
+    if (blocks > 0x7fffffffll) return hipErrorInvalidConfiguration;
+#define NM_Q8L(EST)                                                                                                                     \
+    hipLaunchKernelGGL((prune_compress_q8_kernel<NM_DT_BF16, EST, true, 4, true>), dim3((unsigned)blocks), dim3(256), 0, st, g, groups, O, \
+                       ldg, (uint32_t)seed, (uint32_t)(seed >> 32), stream_id, 1.0f, rec, vals8, meta32, LayerArg{T, csum})
+    if (est == 3) NM_Q8L(3); else if (est == 1) NM_Q8L(1); else NM_Q8L(0);
+#undef NM_Q8L
     return hipGetLastError();
 }
 
@@ -969,6 +1032,32 @@ hipError_t launch_prune_producer(int dt, int m, int est, const void *u, int64_t 
     if (dt == NM_DT_F32) { if (m == 2) NM_PROD(NM_DT_F32, 2, 0); else if (est == 1) NM_PROD(NM_DT_F32, 4, 1); else NM_PROD(NM_DT_F32, 4, 0); }
     else { if (m == 2) NM_PROD(NM_DT_BF16, 2, 0); else if (est == 1) NM_PROD(NM_DT_BF16, 4, 1); else NM_PROD(NM_DT_BF16, 4, 0); }
 #undef NM_PROD
+    return hipGetLastError();
+}
+
+// A layer's prune (bf16, T tokens, T not necessarily a multiple of 16; T * O <= 2^34): m = 2: MVUE 1:2; m = 4: est 0 optimal / 1
+// approx-MVUE 2:4.  act (may be null): the ReLU's output; g = u * [act > 0] is then written to gout.  csum (may be null):
+// [ceil(T/16)][O] column sums of g per token group.
+hipError_t launch_prune_layer(int m, int est, const void *g, int64_t ldg, const void *act, int64_t lda, int64_t T, int64_t O, uint64_t seed,
+                              uint32_t stream_id, void *gout, int64_t ldgo, void *vals, uint16_t *meta, float *csum, hipStream_t st)
+{
+    const int64_t groups = (T + 15) / 16, threads = groups * (O / 4), blocks = (threads + 255) / 256;
+    if (threads == 0) return hipSuccess;
+    if (blocks > 0x7fffffffll) return hipErrorInvalidConfiguration;
+    const ProdArg pa{act, lda, gout, ldgo};
+    const LayerArg la{T, csum};
+#define NM_LAYER(M, EST, PROD)                                                                                                         \
+    do {                                                                                                                                \
+        if (threads % 64 == 0)                                                                                                          \
+            hipLaunchKernelGGL((prune_layer_kernel<M, EST, PROD, true>), dim3((unsigned)blocks), dim3(256), 0, st, g, groups, O, ldg,   \
+                               (uint32_t)seed, (uint32_t)(seed >> 32), stream_id, vals, meta, pa, la);                                  \
+        else                                                                                                                            \
+            hipLaunchKernelGGL((prune_layer_kernel<M, EST, PROD, false>), dim3((unsigned)blocks), dim3(256), 0, st, g, groups, O, ldg,  \
+                               (uint32_t)seed, (uint32_t)(seed >> 32), stream_id, vals, meta, pa, la);                                  \
+    } while (0)
+    if (act) { if (m == 2) NM_LAYER(2, 0, 2); else if (est == 1) NM_LAYER(4, 1, 2); else NM_LAYER(4, 0, 2); }
+    else { if (m == 2) NM_LAYER(2, 0, 0); else if (est == 1) NM_LAYER(4, 1, 0); else NM_LAYER(4, 0, 0); }
+#undef NM_LAYER
     return hipGetLastError();
 }
 

@@ -169,14 +169,18 @@ __device__ __forceinline__ uint32_t pack4_e4m3(float a, float b, float c, float 
     return (uint32_t)w;
 }
 
-// one thread = 16 consecutive elements of a row -> one 16-byte store
+// one thread = 16 consecutive elements of a row -> one 16-byte store; rows past the R of h are zero codes
 template <int DT>
 __global__ __launch_bounds__(256) void cast_e4m3_kernel(const void *__restrict__ h_, int64_t R, int64_t C, int64_t ld,
-                                                       const float *__restrict__ rec, uint8_t *__restrict__ h8, int64_t ld8)
+                                                       const float *__restrict__ rec, uint8_t *__restrict__ h8, int64_t ld8, int64_t out_rows)
 {
     const int64_t cpr = C / 16, i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= R * cpr) return;
+    if (i >= out_rows * cpr) return;
     const int64_t r = i / cpr, c = (i - r * cpr) * 16;
+    if (r >= R) {
+        *(u32x4_t *)(h8 + r * ld8 + c) = u32x4_t{0u, 0u, 0u, 0u};
+        return;
+    }
     const float s = rec[0];
     float x[16];
     if constexpr (DT == NM_DT_F32) {
@@ -198,16 +202,22 @@ __global__ __launch_bounds__(256) void cast_e4m3_kernel(const void *__restrict__
     *(u32x4_t *)(h8 + r * ld8 + c) = o;
 }
 
-hipError_t launch_cast_e4m3(int dt, const void *h, int64_t R, int64_t C, int64_t ld, const float *rec, uint8_t *h8, int64_t ld8,
-                            hipStream_t st)
+hipError_t launch_cast_e4m3_rows(int dt, const void *h, int64_t R, int64_t C, int64_t ld, const float *rec, uint8_t *h8, int64_t ld8,
+                                 int64_t out_rows, hipStream_t st)
 {
-    const int64_t threads = R * (C / 16);
+    const int64_t threads = out_rows * (C / 16);
     if (threads == 0) return hipSuccess;
     const int64_t blocks = (threads + 255) / 256;
     if (blocks > 0x7fffffffll) return hipErrorInvalidConfiguration;
-    if (dt == NM_DT_F32) hipLaunchKernelGGL(cast_e4m3_kernel<NM_DT_F32>, dim3((unsigned)blocks), dim3(256), 0, st, h, R, C, ld, rec, h8, ld8);
-    else hipLaunchKernelGGL(cast_e4m3_kernel<NM_DT_BF16>, dim3((unsigned)blocks), dim3(256), 0, st, h, R, C, ld, rec, h8, ld8);
+    if (dt == NM_DT_F32) hipLaunchKernelGGL(cast_e4m3_kernel<NM_DT_F32>, dim3((unsigned)blocks), dim3(256), 0, st, h, R, C, ld, rec, h8, ld8, out_rows);
+    else hipLaunchKernelGGL(cast_e4m3_kernel<NM_DT_BF16>, dim3((unsigned)blocks), dim3(256), 0, st, h, R, C, ld, rec, h8, ld8, out_rows);
     return hipGetLastError();
+}
+
+hipError_t launch_cast_e4m3(int dt, const void *h, int64_t R, int64_t C, int64_t ld, const float *rec, uint8_t *h8, int64_t ld8,
+                            hipStream_t st)
+{
+    return launch_cast_e4m3_rows(dt, h, R, C, ld, rec, h8, ld8, R, st);
 }
 
 }  // namespace nm

@@ -1,0 +1,104 @@
+"""nm_linear_update (one call: prune, update GEMM, conversion, bias gradient) against the oracle on operands padded with zero
+rows, at the edges of what it does itself: token counts inside a group (h and g end there; what lies behind them in memory is NaN),
+one group, slabs whose last one is short, tiles of every plan, row strides, the ReLU's derivative, 8-bit operands."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2203_10991_amd import synth
+from gpu_util import DEV
+
+pytestmark = pytest.mark.gpu
+
+
+def _bits(t):
+    return t.contiguous().view(torch.int16).cpu().numpy().view(np.uint16)
+
+
+def _behind_nan(t, ld):
+    """t as a view of row stride ld with NaN in the padding columns and in 40 rows behind it"""
+    wide = torch.full((t.shape[0] + 40, ld), float("nan"), dtype=t.dtype, device=DEV)
+    wide[:t.shape[0], :t.shape[1]] = t
+    return wide[:t.shape[0], :t.shape[1]]
+
+
+def _padded(t, m):
+    return torch.nn.functional.pad(t, (0, 0, 0, (-t.shape[0]) % m))
+
+
+# T (ragged and not), O, I: 128x128 tiles in one pass and in slabs; 256x128 and 256x256 tiles (8 waves); many slabs
+SHAPES = [(1, 8, 16), (15, 72, 48), (16, 64, 64), (17, 136, 80), (33, 256, 128), (1576, 256, 128), (3001, 128, 64), (2047, 2048, 1024), (3183, 3072, 1536)]
+
+
+# (the plans are the same for every estimator: the large shapes run once per operand width)
+@pytest.mark.parametrize("form,T,O,I", [(f, *s) for f in ("2:4", "1:2", "approx", "q8", "relu") for s in SHAPES
+                                        if s[1] * s[2] <= 1 << 20 or f in ("2:4", "q8")])
+def test_linear_update_matches_the_oracle(oracle, form, T, O, I):
+    from paper_2203_10991_amd import api
+    torch.manual_seed(T)
+    g = (torch.randn(T, O, device=DEV) * torch.exp(2 * torch.randn(T, O, device=DEV))).to(torch.bfloat16)
+    g[torch.rand(T, O, device=DEV) < 0.2] = 0
+    h = torch.randn(T, I, device=DEV).to(torch.bfloat16)
+    gn, hn = _behind_nan(g, O + 8), _behind_nan(h, I + 24)
+    q8, act = form == "q8", None
+    if form == "relu":
+        act = torch.relu(torch.randn(T, O, device=DEV)).to(torch.bfloat16)
+    nm_, mode = ("1:2" if form == "1:2" else "2:4"), int(form == "approx")
+    dW, db, g_out = api.nm_linear_update(gn, hn, nm=nm_, mode=mode, q8=q8, seed=13, stream_id=4, bias=True,
+                                         act=None if act is None else _behind_nan(act, O + 16))
+    torch.cuda.synchronize()
+    if act is not None:
+        g = g * (act > 0).to(torch.bfloat16)
+        assert torch.equal(g_out.view(torch.int16), g.view(torch.int16))
+    gp, hp = _bits(_padded(g, 32 if q8 else 16)), _bits(_padded(h, 32 if q8 else 16))
+    rows = None                                                            # large cases: a band of dW's rows is enough for the oracle
+    if O * I > 1 << 20:
+        rows = np.r_[0:8, 248:264, O - 8:O]
+    cut = (lambda a: a) if rows is None else (lambda a: np.ascontiguousarray(a[:, rows]))
+    if q8:
+        sg, sh = oracle.pow2_scale(gp, 57344.0 / 4.0), oracle.pow2_scale(hp, 448.0)
+        v, m = oracle.prune_2of4_q8(gp, 13, 4, 0, sg)
+        want, wabs = oracle.update_gemm_q8(cut(v), cut(m), oracle.cast_e4m3(hp, sh), alpha=1.0 / (sg * sh))
+    else:
+        prune = {"1:2": oracle.prune_1of2, "approx": oracle.prune_2of4_approx}.get(form, oracle.prune_2of4)
+        v, m, _ = prune(gp, 13, 4)
+        want, wabs = oracle.update_gemm(cut(v), cut(m), hp)
+    got = dW.double().cpu().numpy()
+    got = got if rows is None else got[rows]
+    tol = 1e-3 if q8 else 1e-5                                             # the 8-bit instruction's product window; binary32 sums
+    assert np.isfinite(got).all()
+    assert (np.abs(got - want) <= tol * wabs + 2.0 ** -8 * np.abs(want) + 1e-30).all()      # + the bf16 result's rounding
+    assert np.linalg.norm(got - want) <= 3e-3 * np.linalg.norm(want)
+    gd = g.double()
+    err = (db.double() - gd.sum(0)).abs()
+    assert bool((err <= 1e-5 * gd.abs().sum(0) + 2.0 ** -8 * gd.sum(0).abs()).all())
+
+
+def test_linear_update_large_plan_with_ragged_tokens():
+    """enough tiles for the 384-row kernel, whose operands are copied to whole groups: against the separate calls"""
+    import paper_2203_10991_amd as nm
+    from paper_2203_10991_amd import api
+    torch.manual_seed(1)
+    T, O, I = 77, 6144, 3072
+    g, h = torch.randn(T, O, device=DEV).to(torch.bfloat16), torch.randn(T, I, device=DEV).to(torch.bfloat16)
+    dW, db, _ = api.nm_linear_update(_behind_nan(g, O + 8), _behind_nan(h, I + 8), seed=3, stream_id=1, bias=True)
+    v, m, _ = nm.mvue_prune_2of4(_padded(g, 16), seed=3, stream_id=1)
+    want = nm.nm_update_gemm(v, m, _padded(h, 16)).to(torch.bfloat16)
+    assert torch.equal(dW, want)
+
+
+def test_argument_errors_come_before_any_launch():
+    from paper_2203_10991_amd import api, NmError
+    lib = api.load()
+    g = torch.zeros(64, 64, dtype=torch.bfloat16, device=DEV)
+    p = g.data_ptr()
+    ok = dict(g=p, ldg=64, act=None, lda=0, h=p + 4096, ldh=64, T=16, O=64, I=64, m=4, mode=0, q8=0, seed=0, stream=0, gout=None, ldgo=0,
+              dW=p, db=None, ws=p, wb=1 << 30, st=None)
+    def call(**kw):
+        return lib.nm_linear_update(*{**ok, **kw}.values())
+    assert call(m=3) == 7 and call(mode=2) == 7 and call(m=2, mode=1) == 7 and call(q8=1, act=p, gout=p) == 7
+    assert call(O=60) == 2 and call(T=0) == 2 and call(q8=1, I=24) == 2 and call(ldg=32) == 2
+    assert call(h=None) == 1 and call(act=p) == 1 and call(dW=None) == 1
+    assert call(dW=p + 2) == 4 and call(ldg=68) == 4
+    assert call(wb=16) == 6 and call(ws=None) == 6
+    assert call() == 5 and lib.nm_linear_update_workspace(16, 60, 64, 0, 0) == 0
