@@ -536,12 +536,12 @@ def nm_update_gemm_q8_shifted(vals8: torch.Tensor, meta32: torch.Tensor, x8_full
 # ---- layers: one call per weight gradient
 
 def _image_layout(t: torch.Tensor):
-    """(tensor, channels_last) of a 4-D tensor as nm_conv_update takes it: contiguous in one of the two layouts."""
-    if t.is_contiguous():
-        return t, 0
-    if t.is_contiguous(memory_format=torch.channels_last):
-        return t, 1
-    return t.contiguous(), 0
+    """(tensor, channels_last) of a 4-D tensor as nm_conv_update takes it: contiguous in one of the two layouts, on a 16-byte
+    boundary (a view into a larger buffer may start anywhere); a copy where it is not."""
+    cl = not t.is_contiguous() and t.is_contiguous(memory_format=torch.channels_last)
+    if t.data_ptr() % 16 or not (cl or t.is_contiguous()):
+        t = t.clone(memory_format=torch.channels_last if cl else torch.contiguous_format)
+    return t, int(cl)
 
 
 def nm_conv_update_workspace(N: int, C: int, O: int, H: int, W: int, k: int, q8: bool = False) -> int:
@@ -573,8 +573,8 @@ def nm_conv_update(gy: torch.Tensor, x: torch.Tensor, k: int, q8: bool = False, 
 
 def _rows_of(t: torch.Tensor):
     """(tensor, row stride) of a 2-D bf16 tensor whose rows start on 16-byte boundaries; a copy where they do not."""
-    if t.stride(1) != 1 or t.stride(0) < t.shape[1] or t.stride(0) % 8 or t.stride(0) > 1 << 21:
-        t = t.contiguous()
+    if t.stride(1) != 1 or t.stride(0) < t.shape[1] or t.stride(0) % 8 or t.stride(0) > 1 << 21 or t.data_ptr() % 16:
+        t = t.clone(memory_format=torch.contiguous_format)
     return t, t.stride(0) if t.shape[0] > 1 else t.shape[1]
 
 

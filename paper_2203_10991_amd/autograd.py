@@ -91,17 +91,17 @@ def padded_rows(t_nchw: torch.Tensor, pad: int):
     return g.reshape(-1, g.shape[-1]), g.shape[2]
 
 
-def _conv_update_shifted(gy: torch.Tensor, x: torch.Tensor, k: int, cfg: NMConfig) -> torch.Tensor:
-    """Weight gradient [O, C, k, k] (binary32) of a k x k, stride-1, 'same' convolution without an im2col matrix:
+def _conv_update_shifted(gy: torch.Tensor, x: torch.Tensor, k: int, cfg: NMConfig, dtype: torch.dtype) -> torch.Tensor:
+    """Weight gradient [O, C, k, k] (binary32, or bf16 where the weight's `dtype` is) of a k x k, stride-1, 'same' convolution without an im2col matrix:
     gradient and activation live on the zero-padded channels-last grid, kernel tap (ky, kx) is a row shift of the
     activation rows (nm_update_gemm_shifted).  The N:M blocks run along the rows of that padded grid."""
     if not (gy.is_cuda and x.is_cuda):
         raise RuntimeError("the N:M update phase runs on the GPU only (no CPU fallback)")
     q8 = cfg.precision == "q8"
     N, O, H, W = gy.shape
-    if gy.dtype == torch.bfloat16 and api.nm_conv_update_workspace(N, x.shape[1], O, H, W, k, q8):
+    if gy.dtype == dtype == torch.bfloat16 and api.nm_conv_update_workspace(N, x.shape[1], O, H, W, k, q8):
         return api.nm_conv_update(gy, x, k, q8=q8, mode=cfg.mode, seed=cfg.current_seed(), stream_id=cfg.stream_id)
-    # sizes beyond the one-call form (grids of 2^31 rows): the same steps as tensor operations and separate library calls
+    # a binary32 weight (autocast) gets its sums unrounded, and sizes beyond the one-call form (grids of 2^31 rows): the same steps as tensor operations and separate library calls
     pad = k // 2
     xr, wp = padded_rows(x, pad)
     gr, _ = padded_rows(gy, pad)
@@ -279,7 +279,7 @@ class _NMConv2dFn(torch.autograd.Function):
                     and tuple(padding) == (kh // 2, kw // 2))
             cmul = 16 if ctx.cfg.precision == "q8" else 8
             if same and x.dtype == torch.bfloat16 and ctx.cfg.nm == "2:4" and C % cmul == 0 and O % 8 == 0 and kh * kw <= 32:
-                dW = _conv_update_shifted(gy, x, kh, ctx.cfg).to(weight.dtype)
+                dW = _conv_update_shifted(gy, x, kh, ctx.cfg, weight.dtype).to(weight.dtype)
             else:
                 # im2col (App. B: the convolution's update GEMM reduces over batch x output positions):
                 # h [N*L, C*kh*kw], g [N*L, O]

@@ -75,3 +75,31 @@ def test_conv_update_equals_the_separate_calls_at_a_layer_size():
         want = want.reshape(O, 3, 3, C).permute(0, 3, 1, 2).contiguous().to(torch.bfloat16)
         got = api.nm_conv_update(gy, x, 3, mode=mode, seed=5, stream_id=1)
         assert torch.equal(got, want)                                  # same operands, same kernels, same order of sums
+
+
+def test_views_off_a_16_byte_boundary_are_copied():
+    from paper_2203_10991_amd import api
+    torch.manual_seed(6)
+    gy, x = (torch.randn(2, c, 6, 6, device=DEV).to(torch.bfloat16) for c in (16, 32))
+
+    def shifted(t, fmt):
+        flat = torch.empty(t.numel() + 8, dtype=t.dtype, device=DEV)[1:1 + t.numel()]
+        n, c, h, w = t.shape
+        v = flat.view(n, h, w, c).permute(0, 3, 1, 2) if fmt is torch.channels_last else flat.view(n, c, h, w)
+        v.copy_(t)
+        assert v.data_ptr() % 16 and v.is_contiguous(memory_format=fmt)
+        return v
+    want = api.nm_conv_update(gy, x, 3, seed=4)
+    for fmt in (torch.contiguous_format, torch.channels_last):
+        assert torch.equal(api.nm_conv_update(shifted(gy, fmt), shifted(x, fmt), 3, seed=4), want)
+
+
+def test_a_binary32_weight_gets_unrounded_sums():
+    """autocast: bf16 tensors, binary32 weight -- its gradient keeps the binary32 sums"""
+    from paper_2203_10991_amd.autograd import NMConfig, _conv_update_shifted
+    torch.manual_seed(7)
+    gy, x = (torch.randn(2, c, 6, 6, device=DEV).to(torch.bfloat16) for c in (16, 32))
+    a = _conv_update_shifted(gy, x, 3, NMConfig(seed=4), torch.float32)
+    b = _conv_update_shifted(gy, x, 3, NMConfig(seed=4), torch.bfloat16)
+    assert a.dtype == torch.float32 and b.dtype == torch.bfloat16
+    assert torch.equal(a.to(torch.bfloat16), b) and not torch.equal(a.to(torch.bfloat16).float(), a)

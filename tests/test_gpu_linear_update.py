@@ -102,3 +102,22 @@ def test_argument_errors_come_before_any_launch():
     assert call(dW=p + 2) == 4 and call(ldg=68) == 4
     assert call(wb=16) == 6 and call(ws=None) == 6
     assert call() == 5 and lib.nm_linear_update_workspace(16, 60, 64, 0, 0) == 0
+
+
+def test_views_off_a_16_byte_boundary_are_copied():
+    """g, h and act as views that start 2 bytes past a boundary, at row strides the kernels take"""
+    from paper_2203_10991_amd import api
+    torch.manual_seed(5)
+    T, O, I = 40, 64, 48
+    make = lambda n: torch.randn(T, n, device=DEV).to(torch.bfloat16)      # noqa: E731
+    g, h, act = make(O), make(I), torch.relu(make(O))
+
+    def shifted(t):
+        wide = torch.full((T * 80 + 8,), float("nan"), dtype=t.dtype, device=DEV)
+        v = wide[1:1 + T * 80].view(T, 80)[:, :t.shape[1]]
+        v.copy_(t)
+        assert v.data_ptr() % 16
+        return v
+    want = api.nm_linear_update(g, h, seed=2, act=act, bias=True)
+    got = api.nm_linear_update(shifted(g), shifted(h), seed=2, act=shifted(act), bias=True)
+    assert all(torch.equal(a, b) for a, b in zip(got, want))
