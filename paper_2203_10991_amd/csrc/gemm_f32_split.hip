@@ -85,13 +85,17 @@ inline size_t round256(size_t b) { return (b + 255) / 256 * 256; }
 
 }  // namespace
 
+inline size_t segment_bytes(int64_t T, int64_t O, int64_t I)
+{
+    return round256(6 * (size_t)(T / 2) * O * 2) + round256(6 * (size_t)T * I * 2) + round256(6 * (size_t)(T / 16) * O * 2);
+}
+
 // workspace layout: [6 segments of vals][6 segments of h][6 copies of meta][workspace of the 16-bit GEMM over 6T tokens],
 // each part on a 256-byte boundary
 size_t update_gemm_f32_split_workspace(int64_t T, int64_t O, int64_t I)
 {
     if (T <= 0 || O <= 0 || I <= 0) return 0;
-    return round256(6 * (size_t)(T / 2) * O * 2) + round256(6 * (size_t)T * I * 2) + round256(6 * (size_t)(T / 16) * O * 2) +
-           round256(update_gemm_smfmac_workspace(6 * T, O, I));
+    return segment_bytes(T, O, I) + round256(update_gemm_smfmac_workspace(6 * T, O, I, segment_bytes(T, O, I)));
 }
 
 hipError_t launch_update_gemm_f32_split(const void *vals, const uint16_t *meta, const void *h, int64_t ldh, float *dW,
@@ -121,7 +125,7 @@ hipError_t launch_update_gemm_f32_split(const void *vals, const uint16_t *meta, 
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     // one run over the stacked operands: the reduction over 6T tokens sums the six products, in the order of the segments
-    return launch_update_gemm_smfmac(a, m, b, I, dW, lddw, 6 * T, O, I, beta, gemm_ws, st);
+    return launch_update_gemm_smfmac(a, m, b, I, dW, lddw, 6 * T, O, I, beta, gemm_ws, st, segment_bytes(T, O, I));
 }
 
 }  // namespace nm

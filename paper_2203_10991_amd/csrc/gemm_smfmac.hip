@@ -36,6 +36,7 @@ namespace nm {
 
 constexpr int KT = 32;            // tokens per LDS stage (one 32-token MFMA step, two 16-token groups)
 constexpr int NS = 6;             // LDS stages: one being consumed, one landed, four in flight
+constexpr int TALL_STAGES = 5;    // the same of the 384-row kernel
 
 // LDS image of one stage (all filled by direct loads, 64 consecutive lanes -> consecutive LDS bytes):
 //   [0, 64*TN)                h tile, [32 tokens][TN columns] bf16, rows unpadded.  Bank conflicts of the
@@ -365,21 +366,21 @@ __global__ __launch_bounds__(512) void update_gemm_smfmac_tall_kernel(
     float *__restrict__ out, int64_t ldo, int64_t slab_stride, int64_t n_groups, int64_t groups_per_slab,
     int64_t O, int64_t I, int tiles_m, int tiles_n, int accumulate, int64_t o_first, int64_t o_end)
 {
-    constexpr int WN = 4, AB = 6, BB = 2, TM = 384, TN = 256, TNS = 5;
+    constexpr int WN = 4, AB = 6, BB = 2, TM = 384, TN = 256, TNS = TALL_STAGES;
     constexpr int A_OFF = 64 * TN, M_OFF = A_OFF + 2 * TM * 16, STAGE = (M_OFF + 2 * TM * 2 + 1023) / 1024 * 1024;
     constexpr int LPS = 5;                                   // direct loads per wave and stage: 2 h, 2 vals, 1 meta
     static_assert(TNS * STAGE <= 160 * 1024, "LDS");
     __shared__ __attribute__((aligned(1024))) char S[TNS * STAGE];
 
-    int tm, tn;
-    tile_of_workgroup((int)blockIdx.x, tiles_m, tiles_n, tm, tn);
+    int tm, tn, slab;
+    tile_and_slab_of_workgroup(tiles_m, tiles_n, tm, tn, slab);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WN, wn = wave % WN;
     const int64_t m0 = o_first + (int64_t)tm * TM, n0 = (int64_t)tn * TN;
-    const int64_t g_begin = (int64_t)blockIdx.z * groups_per_slab;
+    const int64_t g_begin = (int64_t)slab * groups_per_slab;
     const int64_t g_end = min(n_groups, g_begin + groups_per_slab);
-    out += (int64_t)blockIdx.z * slab_stride;
+    out += (int64_t)slab * slab_stride;
 
     // accumulator blocks of rows a < 4 in accumulation registers (128), a = 4, 5 in ordinary ones (64)
     f32x16 acc[AB][BB];
@@ -662,7 +663,9 @@ struct Plan { int shape; int tm, tn; int tiles_m, tiles_n; int slabs; int64_t gr
 // shifted: the dense operand is row-shifted views of one matrix (it stays in the caches: few-row problems are then
 // bound by the tile's own work, and the 64 x 256 tile wastes none of it; streamed from HBM, as a materialised
 // operand is, the 128 x 128 tile measures faster)
-static Plan make_plan(int64_t T, int64_t O, int64_t I, bool shifted = false)
+// whole_rows: h has every row of the last token group (the 384-row kernel wants that); beside: bytes of the call's workspace that
+// are not partial sums
+static Plan make_plan(int64_t T, int64_t O, int64_t I, bool shifted = false, bool whole_rows = true, size_t beside = 0)
 {
     Plan p;
     const int64_t groups = T / 16;
@@ -741,19 +744,37 @@ static Plan make_plan(int64_t T, int64_t O, int64_t I, bool shifted = false)
                 p.shape = 3; p.tm = 256; p.tn = 128;
                 slabs = (int)s3;
             }
+            // A long reduction (binary32 as three bf16 terms runs over six times the tokens) over a width that 384-row tiles divide
+            // into a GPU-wide round better than 256-row tiles: the 384-row kernel in slabs, 1.36 times as long per stage.  Its
+            // predictions for the others run 10 % high here, so it has to win by 17 %.  55968 x 2960 x 1976: 4 slabs of 64 tiles on
+            // all CUs instead of 2 slabs of 96 on three quarters, 435 -> 356 us; 25904 x 272 x 16968
+            // 540 -> 232 us, 32224 x 5536 x 1432 452 -> 329, at the line 15360 x 23920 x 272 216 -> 191, beyond it 10832 x 272 x 14176
+            // 100 -> 102.  Not where it would take a workspace past the static
+            // scratch that holds the other plan's: such a call has to go on working without a workspace of the caller's.
+            int64_t s4 = 1;
+            const int64_t tiles4 = (O + 383) / 384 * ((I + 255) / 256);
+            const double cost4 = one_per_cu(tiles4, 0.60, 0.76, 0.0, s4), best = take0 ? std::min(cost0, take3 ? cost3 : cost0) : take3 ? cost3 : cost1;
+            auto fits = [&](int64_t sl) { return beside + splitk_workspace_bytes((int)sl, O, I) <= static_scratch_bytes(); };
+            if (!shifted && whole_rows && s4 > 1 && cost4 < 0.83 * best && (fits(s4) || !fits(slabs))) {
+                p.shape = 0; p.tm = 256; p.tn = 256;
+                p.tall_rows = O; p.tall_tiles_m = (int)((O + 383) / 384);
+                slabs = (int)s4;
+                p.tiles_m = 0;
+            } else
             p.tiles_m = (int)((O + p.tm - 1) / p.tm);
             p.tiles_n = (int)((I + p.tn - 1) / p.tn);
         }
     }
     p.slabs = slabs;
-    p.groups_per_slab = slab_groups(groups, p.slabs, 12);                    // whole trips of six LDS stages (2 groups each)
+    // whole trips of the kernel's LDS stages (2 groups each; one slab has no next one to run into)
+    p.groups_per_slab = slab_groups(groups, p.slabs, p.tall_rows == O ? 2 * TALL_STAGES : 2 * NS);
     return p;
 }
 
-size_t update_gemm_smfmac_workspace(int64_t T, int64_t O, int64_t I)
+size_t update_gemm_smfmac_workspace(int64_t T, int64_t O, int64_t I, size_t beside)
 {
     if (T <= 0 || O <= 0 || I <= 0) return 0;
-    return splitk_workspace_bytes(make_plan(T, O, I).slabs, O, I);
+    return splitk_workspace_bytes(make_plan(T, O, I, false, true, beside).slabs, O, I);
 }
 
 size_t update_gemm_smfmac_shifted_workspace(int64_t T, int64_t O, int64_t I)
@@ -767,7 +788,7 @@ static hipError_t run_plan(const Plan &p, const OutTarget &tg, const void *vals,
                            int64_t T, int64_t O, int64_t I, hipStream_t st)
 {
     if (p.tall_rows > 0) {
-        dim3 tall_grid((unsigned)(p.tall_tiles_m * p.tiles_n), 1, 1);
+        dim3 tall_grid((unsigned)(p.tall_tiles_m * p.tiles_n), 1, (unsigned)p.slabs);
         hipLaunchKernelGGL(update_gemm_smfmac_tall_kernel, tall_grid, dim3(512), 0, st, (const uint16_t *)vals, meta, (const uint16_t *)h,
                            ldh, tg.out, tg.ldo, tg.slab_stride, T / 16, p.groups_per_slab, O, I, p.tall_tiles_m, p.tiles_n, tg.accumulate,
                            (int64_t)0, p.tall_rows);
@@ -790,9 +811,9 @@ static hipError_t run_plan(const Plan &p, const OutTarget &tg, const void *vals,
 
 hipError_t launch_update_gemm_smfmac(const void *vals, const uint16_t *meta, const void *h, int64_t ldh, float *dW,
                                      int64_t lddw, int64_t T, int64_t O, int64_t I, float beta, void *workspace,
-                                     hipStream_t st)
+                                     hipStream_t st, size_t beside)
 {
-    const Plan p = make_plan(T, O, I);
+    const Plan p = make_plan(T, O, I, false, true, beside);
     const int accumulate = beta != 0.f;
     const OutTarget tg = splitk_target(p.slabs, dW, lddw, workspace, O, I, accumulate);
     hipError_t e = run_plan(p, tg, vals, meta, h, ldh, T, T, O, I, st);
@@ -802,17 +823,17 @@ hipError_t launch_update_gemm_smfmac(const void *vals, const uint16_t *meta, con
 }
 
 // (needs_whole_rows: the plan has 384-row tiles, whose kernel wants every row of the last token group)
-size_t update_gemm_smfmac_parts_bytes(int64_t T, int64_t O, int64_t I, bool *needs_whole_rows)
+size_t update_gemm_smfmac_parts_bytes(int64_t h_rows, int64_t T, int64_t O, int64_t I, bool *needs_whole_rows)
 {
-    const Plan p = make_plan(T, O, I);
+    const Plan p = make_plan(T, O, I, false, h_rows == T);
     *needs_whole_rows = p.tall_rows > 0;
     return (size_t)p.slabs * (size_t)O * (size_t)I * sizeof(float);
 }
 
 hipError_t launch_update_gemm_smfmac_parts(const void *vals, const uint16_t *meta, const void *h, int64_t ldh, int64_t h_rows, int64_t T,
-                                           int64_t O, int64_t I, float *part, int *slabs, hipStream_t st)
+                                           int64_t O, int64_t I, bool whole_rows, float *part, int *slabs, hipStream_t st)
 {
-    const Plan p = make_plan(T, O, I);
+    const Plan p = make_plan(T, O, I, false, whole_rows);
     *slabs = p.slabs;
     return run_plan(p, OutTarget{part, I, O * I, 0}, vals, meta, h, ldh, h_rows, T, O, I, st);
 }

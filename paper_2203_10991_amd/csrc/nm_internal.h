@@ -47,8 +47,8 @@ size_t update_gemm_workspace(int dt, int64_t T, int64_t O, int64_t I);
 // axis into slabs for shapes with few output tiles and sum the partials with launch_splitk_reduce
 hipError_t launch_update_gemm_smfmac(const void *vals, const uint16_t *meta, const void *h, int64_t ldh, float *dW,
                                      int64_t lddw, int64_t T, int64_t O, int64_t I, float beta, void *workspace,
-                                     hipStream_t st);
-size_t update_gemm_smfmac_workspace(int64_t T, int64_t O, int64_t I);
+                                     hipStream_t st, size_t beside = 0);     // beside: workspace bytes of the call that are not this GEMM's
+size_t update_gemm_smfmac_workspace(int64_t T, int64_t O, int64_t I, size_t beside = 0);
 size_t update_gemm_smfmac_shifted_workspace(int64_t T, int64_t O, int64_t I);
 // the same product with h given as n row-shifted views of one [rows x cb] matrix x (bf16): h[t][j*cb + c] = x[(t + rows[j])*ldx + c]
 hipError_t launch_update_gemm_smfmac_shifted(const void *vals, const uint16_t *meta, const void *x, int64_t ldx, int64_t cb,
@@ -127,9 +127,9 @@ hipError_t launch_prune_q8_layer(int est, const void *g, int64_t ldg, int64_t T,
 hipError_t launch_cast_e4m3_rows(int dt, const void *h, int64_t R, int64_t C, int64_t ld, const float *rec, uint8_t *h8, int64_t ld8,
                                  int64_t out_rows, hipStream_t st);
 hipError_t launch_pad_rows(const void *h, int64_t rows, int64_t C, int64_t ld, void *out, int64_t out_rows, hipStream_t st);
-size_t update_gemm_smfmac_parts_bytes(int64_t T, int64_t O, int64_t I, bool *needs_whole_rows);
+size_t update_gemm_smfmac_parts_bytes(int64_t h_rows, int64_t T, int64_t O, int64_t I, bool *needs_whole_rows);
 hipError_t launch_update_gemm_smfmac_parts(const void *vals, const uint16_t *meta, const void *h, int64_t ldh, int64_t h_rows, int64_t T,
-                                           int64_t O, int64_t I, float *part, int *slabs, hipStream_t st);
+                                           int64_t O, int64_t I, bool whole_rows, float *part, int *slabs, hipStream_t st);
 size_t update_gemm_q8_parts_bytes(int64_t T, int64_t O, int64_t I);
 hipError_t launch_update_gemm_q8_parts(const uint8_t *vals8, const uint32_t *meta32, const uint8_t *h8, int64_t ldh, int64_t T, int64_t O,
                                        int64_t I, float *part, int *slabs, hipStream_t st);

@@ -86,7 +86,7 @@ LinearPlan plan_linear(int64_t T, int64_t O, int64_t I, bool q8, bool bias)
     p.Tp = (T + gt - 1) / gt * gt;
     p.groups = p.Tp / gt;
     bool whole = false;
-    const size_t part = q8 ? nm::update_gemm_q8_parts_bytes(p.Tp, O, I) : nm::update_gemm_smfmac_parts_bytes(p.Tp, O, I, &whole);
+    const size_t part = q8 ? nm::update_gemm_q8_parts_bytes(p.Tp, O, I) : nm::update_gemm_smfmac_parts_bytes(T, p.Tp, O, I, &whole);
     p.copy_h = !q8 && whole && p.Tp != T;
     Carver c;
     p.recs = c.take(q8 ? 32 : 0);
@@ -167,7 +167,7 @@ int nm_linear_update(const void *g, int64_t ldg, const void *act, int64_t lda, c
             e = nm::launch_prune_layer(m, mode, g, ldg, act, lda, T, O, seed, stream_id, g_out, ldgo, w + p.vals, (uint16_t *)(w + p.meta), csum, st);
         if (e == hipSuccess)
             e = nm::launch_update_gemm_smfmac_parts(w + p.vals, (const uint16_t *)(w + p.meta), p.copy_h ? w + p.h : h, p.copy_h ? I : ldh,
-                                                    p.copy_h ? p.Tp : T, p.Tp, O, I, part, &slabs, st);
+                                                    p.copy_h ? p.Tp : T, p.Tp, O, I, T == p.Tp, part, &slabs, st);
     }
     if (e == hipSuccess) e = nm::launch_finish_linear(part, slabs, O, I, dW, alpha, csum, p.groups, db, st);
     return launched(fn, e);

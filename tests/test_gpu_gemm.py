@@ -232,3 +232,9 @@ def test_update_gemm_f32_split_special_values(nm):
     assert not torch.isfinite(dW[3]).any()
     keep = [r for r in range(O) if r != 3]
     assert torch.allclose(dW[keep], ref[keep], rtol=1e-5, atol=1e-5)
+
+
+@pytest.mark.parametrize("T,O,I,beta", [(52784, 264, 2440, 0.0),          # an odd number of token groups; slabs of whole trips, a short last one
+                                        (13008, 272, 11896, 1.0)])
+def test_long_reductions_on_384_row_tiles_in_slabs(nm, oracle, T, O, I, beta):
+    run_case(nm, oracle, synth.Workload(f"tall{T}x{O}x{I}", T, O, I, "bf16", "2:4", 0.0, 2.0, 0.3), seed=3, beta=beta)
