@@ -30,30 +30,12 @@
 
 namespace nm {
 
-typedef int i32x4 __attribute__((ext_vector_type(4)));
-typedef int i32x8 __attribute__((ext_vector_type(8)));
-
 constexpr int KT8 = 64;           // tokens per LDS stage (one 64-token MFMA step, two 32-token groups)
 constexpr int NS8 = 6;            // LDS stages
 
 union FragB8 { i32x8 v; u32x2 q[4]; };
 union FragA8 { i32x4 v; u32x4 u4; };
 
-// IN_VGPR: the accumulator block lives in ordinary registers (see acc_zero)
-template <bool IN_VGPR = false>
-__device__ __forceinline__ void smfmac_32x32x64_bf8_fp8(f32x16 &acc, const i32x4 &a, const i32x8 &b, uint32_t idx)
-{
-    if constexpr (IN_VGPR) asm volatile("v_smfmac_f32_32x32x64_bf8_fp8 %0, %1, %2, %3" : "+v"(acc) : "v"(a), "v"(b), "v"(idx));
-    else                   asm volatile("v_smfmac_f32_32x32x64_bf8_fp8 %0, %1, %2, %3" : "+a"(acc) : "v"(a), "v"(b), "v"(idx));
-}
-template <int OFFSET> __device__ __forceinline__ void lds_refill_tr8(u32x2 &r, uint32_t addr)
-{
-    asm volatile("ds_read_b64_tr_b8 %0, %1 offset:%2" : "+v"(r) : "v"(addr), "n"(OFFSET) : "memory");
-}
-template <int OFFSET> __device__ __forceinline__ void lds_refill_b64(u32x2 &r, uint32_t addr)
-{
-    asm volatile("ds_read_b64 %0, %1 offset:%2" : "+v"(r) : "v"(addr), "n"(OFFSET) : "memory");
-}
 // alpha * (one accumulator element) to global memory: the element is copied out of its accumulation register, scaled
 // and stored inside one statement, so that the compiler never holds whole blocks in ordinary registers
 __device__ __forceinline__ void store_acc_scaled(float *p, float v, float alpha)

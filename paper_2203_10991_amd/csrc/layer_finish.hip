@@ -9,21 +9,19 @@
 
 namespace nm {
 
-// Convolution: dW[o][c][tap] (bf16) = alpha * sum_z part[z][o][tap][c].  A workgroup takes one output channel and 64 input
+// Convolution: dW[o][c][tap] (bf16) = alpha * sum_z part[z][o][tap][c].  A workgroup takes one output channel and CW input
 // channels: R threads share a float4 of the partial sums (as in splitk_reduce_kernel: thread r sums slabs r, r+R, ... in
-// order, a fixed tree combines them), the results turn through LDS, and the 64 x taps values leave contiguous.
-// Bound: launch latency and one read of the partial sums.  Summing, permuting and converting were three launches and
-// 15-20 us on ResNet-50's layers; this is one of 6-10 us.
-// With many slabs (R = 8) the workgroup has 1024 threads: 128 of the up to 16 x taps sums run at a time.
-template <int R>
-__global__ __launch_bounds__(R == 8 ? 1024 : 256) void finish_conv_kernel(const float *__restrict__ part, int slabs, int64_t slab_stride, uint16_t *__restrict__ dW,
-                                                          int C, int taps, AlphaArg al)
+// order, a fixed tree combines them), the results turn through LDS, and the CW x taps values leave contiguous.
+// Bound: launch latency and one read of the partial sums.  With many slabs a workgroup is 32 channels wide (128-byte reads) and
+// has a thread for every sum of nine taps at once.
+template <int R, int CW, int NT>
+__global__ __launch_bounds__(NT) void finish_conv_kernel(const float *__restrict__ part, int slabs, int64_t slab_stride, uint16_t *__restrict__ dW,
+                                                         int C, int taps, AlphaArg al)
 {
-    __shared__ uint16_t turned[64 * 32];                                 // [channel][tap]
-    constexpr int NT = R == 8 ? 1024 : 256;
+    __shared__ uint16_t turned[CW * 32];                                 // [channel][tap]
     const float alpha = alpha_of(al);
     const int64_t o = blockIdx.x;
-    const int c0 = (int)blockIdx.y * 64, cols = min(64, C - c0), q4 = cols / 4;
+    const int c0 = (int)blockIdx.y * CW, cols = min(CW, C - c0), q4 = cols / 4;
     const float *src = part + o * (int64_t)taps * C + c0;
     const int r = threadIdx.x % R, tasks = taps * q4;
     for (int t0 = 0; t0 < tasks; t0 += NT / R) {
@@ -31,11 +29,14 @@ __global__ __launch_bounds__(R == 8 ? 1024 : 256) void finish_conv_kernel(const 
         const bool valid = t < tasks;
         const int tap = valid ? t / q4 : 0, c = valid ? (t % q4) * 4 : 0;
         float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (valid)
+        if (valid) {
+            const float *at = src + (int64_t)tap * C + c;
+#pragma unroll 4
             for (int z = r; z < slabs; z += R) {
-                const float4 v = *(const float4 *)(src + (int64_t)z * slab_stride + (int64_t)tap * C + c);
+                const float4 v = *(const float4 *)(at + (int64_t)z * slab_stride);
                 s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
             }
+        }
 #pragma unroll
         for (int d = 1; d < R; d <<= 1) {
             s.x += __shfl_xor(s.x, d); s.y += __shfl_xor(s.y, d); s.z += __shfl_xor(s.z, d); s.w += __shfl_xor(s.w, d);
@@ -53,11 +54,12 @@ __global__ __launch_bounds__(R == 8 ? 1024 : 256) void finish_conv_kernel(const 
 
 hipError_t launch_finish_conv(const float *part, int slabs, void *dW, int64_t O, int C, int taps, AlphaArg alpha, hipStream_t st)
 {
-    const dim3 grid((unsigned)O, (unsigned)((C + 63) / 64));
-    if (slabs >= 12)
-        hipLaunchKernelGGL(finish_conv_kernel<8>, grid, dim3(1024), 0, st, part, slabs, O * (int64_t)taps * C, (uint16_t *)dW, C, taps, alpha);
-    else
-        hipLaunchKernelGGL(finish_conv_kernel<1>, grid, dim3(256), 0, st, part, slabs, O * (int64_t)taps * C, (uint16_t *)dW, C, taps, alpha);
+#define NM_FINISH(R, CW, NT)                                                                                                                      \
+    hipLaunchKernelGGL((finish_conv_kernel<R, CW, NT>), dim3((unsigned)O, (unsigned)((C + CW - 1) / CW)), dim3(NT), 0, st, part, slabs,            \
+                       O * (int64_t)taps * C, (uint16_t *)dW, C, taps, alpha)
+    if (slabs >= 12) NM_FINISH(8, 32, 576);
+    else NM_FINISH(1, 64, 256);
+#undef NM_FINISH
     return hipGetLastError();
 }
 

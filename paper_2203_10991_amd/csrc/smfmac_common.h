@@ -15,7 +15,10 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x16 __attribute__((ext_vector_type(16)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef int i32x8 __attribute__((ext_vector_type(8)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 
 union Frag16 { bf16x16 v; s16x4 q[4]; };
@@ -130,6 +133,22 @@ template <int OFFSET> __device__ __forceinline__ u32x2 lds_read_b64(uint32_t add
     u32x2 r;
     asm volatile("ds_read_b64 %0, %1 offset:%2" : "=v"(r) : "v"(addr), "n"(OFFSET) : "memory");
     return r;
+}
+
+// the 8-bit forms
+template <bool IN_VGPR = false>
+__device__ __forceinline__ void smfmac_32x32x64_bf8_fp8(f32x16 &acc, const i32x4 &a, const i32x8 &b, uint32_t idx)
+{
+    if constexpr (IN_VGPR) asm volatile("v_smfmac_f32_32x32x64_bf8_fp8 %0, %1, %2, %3" : "+v"(acc) : "v"(a), "v"(b), "v"(idx));
+    else                   asm volatile("v_smfmac_f32_32x32x64_bf8_fp8 %0, %1, %2, %3" : "+a"(acc) : "v"(a), "v"(b), "v"(idx));
+}
+template <int OFFSET> __device__ __forceinline__ void lds_refill_tr8(u32x2 &r, uint32_t addr)
+{
+    asm volatile("ds_read_b64_tr_b8 %0, %1 offset:%2" : "+v"(r) : "v"(addr), "n"(OFFSET) : "memory");
+}
+template <int OFFSET> __device__ __forceinline__ void lds_refill_b64(u32x2 &r, uint32_t addr)
+{
+    asm volatile("ds_read_b64 %0, %1 offset:%2" : "+v"(r) : "v"(addr), "n"(OFFSET) : "memory");
 }
 
 // s_waitcnt vmcnt(N) only (expcnt / lgkmcnt left at their maxima): at most N vector-memory loads still in flight
