@@ -18,8 +18,12 @@
 // eight, consecutive rows at any shift): rows of 32 channels need nothing (four resp. eight of them are 256 contiguous bytes);
 // with 64 channels the halves of a row are exchanged by bit 1 (bit 2) of the row number.
 //
-// Bound: matrix pipeline, LDS reads close behind (576 against ~430 cycles per super-stage and SIMD); on grids with few channels one pass
-// over x and the compressed gradient.  Measured (batch 256, before -> after): see launch_conv_gemm.
+// Bound: matrix pipeline at the clock the power limit leaves (59 % busy at 1.7 GHz on a long 14 x 14 layer, no bank conflicts, LDS
+// 40 % busy); what it waits for is the barrier per super-stage of 576 matrix cycles, so the loads' address arithmetic between the
+// barriers was cut to two multiplies (with descriptors rebuilt per load: 166 instead of 150 us there).  On grids with few
+// channels one pass over x and the compressed gradient.  Measured at batch 256, general kernel -> this one: 56 x 56 x 64
+// 87 -> 42 us (8-bit 47 -> 43), 14 x 14 x 256 60 -> 51 us (8-bit
+// 38 -> 31), 7 x 7 x 512 70 -> 58 us (8-bit 51 -> 34).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -42,7 +46,7 @@ template <bool Q8, int CB> struct ConvTile {
     static constexpr int STEP = Q8 ? 64 : 32;                         // tokens of an MFMA step
     static constexpr int SS = STEP * KG;                              // tokens of a super-stage
     static constexpr int RB = CB * ESZ;                               // bytes of a ring row
-    static constexpr int MB = CG_TM * (Q8 ? 4 : 2);                   // index words of a token group
+    static constexpr int MW = Q8 ? 4 : 2, MB = 256;                   // bytes of an index word; of a token group's in LDS (one load of 64 lanes)
     static constexpr int SLOT = 2 * KG * (CG_TM * 16 + MB);           // vals and index words of a super-stage
     static constexpr int LDS = CG_RING + CG_SLOTS * SLOT > CG_XCH ? CG_RING + CG_SLOTS * SLOT : CG_XCH;
     static_assert(SS * RB == CG_BLOCK && LDS <= 160 * 1024, "ring blocks");
@@ -52,19 +56,14 @@ union ConvB { bf16x16 v16; i32x8 v8; u32x2 q[4]; s16x4 h[4]; };
 union ConvI { u32x2 w2; uint32_t w[2]; };
 union ConvA { bf16x8 v16; i32x4 v8; u32x4 u4; };
 
-// one direct load to LDS: 16 (4) bytes per lane at the lane's offset from the descriptor's base, lanes side by side from `to` on
-__device__ __forceinline__ void load16_to_lds(__amdgpu_buffer_rsrc_t from, char *to, uint32_t offset)
+// one direct load to LDS: 16 (4) bytes per lane, lane offset + scalar offset from the descriptor's base, lanes side by side from `to` on
+__device__ __forceinline__ void load16_to_lds(__amdgpu_buffer_rsrc_t from, char *to, uint32_t offset, uint32_t scalar_offset)
 {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(from, (lptr_t)to, 16, (int)offset, 0, 0, 0);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(from, (lptr_t)to, 16, (int)offset, (int)scalar_offset, 0, 0);
 }
-__device__ __forceinline__ void load4_to_lds(__amdgpu_buffer_rsrc_t from, char *to, uint32_t offset)
+__device__ __forceinline__ void load4_to_lds(__amdgpu_buffer_rsrc_t from, char *to, uint32_t offset, uint32_t scalar_offset)
 {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(from, (lptr_t)to, 4, (int)offset, 0, 0, 0);
-}
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const char *base, int64_t bytes)
-{
-    const uint32_t b = bytes <= 0 ? 0u : (bytes > 0x7fffffffll ? 0x7fffffffu : (uint32_t)bytes);
-    return __builtin_amdgcn_make_buffer_rsrc((void *)base, 0, (int)b, 0x00020000);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(from, (lptr_t)to, 4, (int)offset, (int)scalar_offset, 0, 0);
 }
 __device__ __forceinline__ uint32_t add_u16(uint32_t s, uint32_t v)   // (s + v) mod 2^16
 {
@@ -75,7 +74,7 @@ __device__ __forceinline__ uint32_t add_u16(uint32_t s, uint32_t v)   // (s + v)
 
 template <bool Q8, int CB>
 __global__ __launch_bounds__(CG_WAVES * 64) void conv_gemm_kernel(
-    const char *__restrict__ vals, const char *__restrict__ meta, const char *__restrict__ x,      // x: row -margin of the grid
+    const char *__restrict__ vals, const char *__restrict__ meta, const char *__restrict__ x,      // x: row -margin of the grid; T + P*SS rows
     float *__restrict__ part, int64_t T, int ss_per_slab, int O, int C, int tiles_n, int margin, ShiftArg sh)
 {
     using Tile = ConvTile<Q8, CB>;
@@ -102,9 +101,15 @@ __global__ __launch_bounds__(CG_WAVES * 64) void conv_gemm_kernel(
         for (int b = 0; b < 3; ++b) acc_zero<true>(acc[a][b]);
 
     // ---- direct loads: waves 0-3 bring two kilobytes of an x block each, waves 4 .. 4+GPS-1 one token group's vals and index
-    // words.  Every wave with a part issues two loads per super-stage, which is what the waits count.
-    const int64_t xrow = (int64_t)C * ESZ, x_bytes = (T + 2 * (int64_t)margin) * xrow, n_groups = n_ss_all * GPS;
-    uint32_t src[2];
+    // words.  Every wave with a part issues two loads per super-stage, which is what the waits count.  A wave's addresses are
+    // two descriptors at the slab's start, a lane offset, and a scalar offset that advances by a super-stage and stops at the
+    // tensor's last one: what is loaded again there is not used.  (Every scalar instruction here delays the next barrier.)
+    const int64_t xrow = (int64_t)C * ESZ, G0 = ss0 * GPS + (wave - 4);
+    const char *base0 = wave < 4 ? x + ss0 * SS * xrow : vals + G0 * O * 16, *base1 = wave < 4 ? base0 : meta + G0 * O * Tile::MW;
+    const __amdgpu_buffer_rsrc_t r0 = __builtin_amdgcn_make_buffer_rsrc((void *)base0, 0, 0x7fffffff, 0x00020000);
+    const __amdgpu_buffer_rsrc_t r1 = __builtin_amdgcn_make_buffer_rsrc((void *)base1, 0, 0x7fffffff, 0x00020000);
+    const uint32_t step0 = wave < 4 ? (uint32_t)(SS * xrow) : (uint32_t)(GPS * O * 16), step1 = wave < 4 ? step0 : (uint32_t)(GPS * O * Tile::MW);
+    uint32_t src[2], lds[2], lds_step = wave < 4 ? CG_BLOCK : Tile::SLOT;
     if (wave < 4) {
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
@@ -112,28 +117,29 @@ __global__ __launch_bounds__(CG_WAVES * 64) void conv_gemm_kernel(
             int pos = (at % RB) / 16;
             if constexpr (CB == 64) pos ^= ((r >> (Q8 ? 2 : 1)) & 1) * (RB / 32);
             src[i] = (uint32_t)(r * xrow + c0 * ESZ + pos * 16);
+            lds[i] = (uint32_t)(2 * wave + i) * 1024;
         }
     } else {
         src[0] = (uint32_t)min(o0 + 2 * (lane & 31) + (lane >> 5), O - 1) * 16u;       // slot q holds row 2*(q%32) + q/32
         src[1] = Q8 ? (uint32_t)min(o0 + lane, O - 1) * 4u : (uint32_t)min(o0 + 2 * (lane & 31), O - 2) * 2u;
+        lds[0] = (uint32_t)(CG_RING + (wave - 4) * (CG_TM * 16));
+        lds[1] = (uint32_t)(CG_RING + GPS * (CG_TM * 16) + (wave - 4) * MB);
     }
-    auto load_x = [&](int blk) {                                      // block `blk` of the slab (waves 0-3)
-        const int64_t at = (ss0 + blk) * (int64_t)SS * xrow;
-        const __amdgpu_buffer_rsrc_t rx = buffer_of(x + at, x_bytes - at);
-#pragma unroll
-        for (int i = 0; i < 2; ++i) load16_to_lds(rx, S + (blk & 7) * CG_BLOCK + (2 * wave + i) * 1024, src[i]);
+    const int loader = wave < 4 ? 1 : wave < 4 + GPS ? 2 : 0;
+    const int last = (int)min((int64_t)0x7fffffff, n_ss_all - 1 - ss0) + (wave < 4 ? P : 0);      // last block (super-stage) there is
+    // block (waves 0-3) or super-stage `i` of the slab
+    auto load_at = [&](int i) {
+        const uint32_t from = (uint32_t)min(i, last), to = (uint32_t)(i & 7) * lds_step;
+        if (loader == 1) {
+            load16_to_lds(r0, S + lds[0] + to, src[0], from * step0);
+            load16_to_lds(r0, S + lds[1] + to, src[1], from * step0);
+        } else if (loader == 2) {
+            load16_to_lds(r0, S + lds[0] + to, src[0], from * step0);
+            load4_to_lds(r1, S + lds[1] + to, src[1], from * step1);
+        }
     };
-    auto load_vals = [&](int s) {                                     // super-stage s of the slab (waves 4 .. 4+GPS-1)
-        const int64_t G = (ss0 + s) * GPS + (wave - 4), left = (n_groups - G) * O;
-        char *slot = S + CG_RING + (s & 7) * Tile::SLOT;
-        load16_to_lds(buffer_of(vals + G * O * 16, left * 16), slot + (wave - 4) * (CG_TM * 16), src[0]);
-        if (Q8 || lane < 32)
-            load4_to_lds(buffer_of(meta + G * O * (MB / CG_TM), left * (MB / CG_TM)), slot + GPS * (CG_TM * 16) + (wave - 4) * MB, src[1]);
-    };
-    auto load_stage = [&](int s) {                                    // what super-stage s needs beyond its predecessors
-        if (wave < 4) load_x(s + P);
-        else if (wave < 4 + GPS) load_vals(s);
-    };
+    const int ahead = wave < 4 ? P : 0;
+    auto load_stage = [&](int s) { load_at(s + ahead); };             // what super-stage s needs beyond its predecessors
 
     // ---- LDS reads.  bf16: read j of a B fragment covers 4 tokens at +4*(j%2) + 16*(j/2), 8-bit: 8 tokens at +8*(j%2) + 32*(j/2)
     const int li = lane & 15, hi = lane >> 5, grp = (lane >> 4) & 1;
@@ -147,13 +153,17 @@ __global__ __launch_bounds__(CG_WAVES * 64) void conv_gemm_kernel(
         b_at[b] = (uint32_t)(row * RB + h * (RB / 2) + in_row);
     }
     const uint32_t a_at = (uint32_t)(CG_RING + (2 * kgrp + hi) * (CG_TM * 16) + (lane & 31) * 16);
-    const uint32_t m_at = (uint32_t)(CG_RING + GPS * (CG_TM * 16) + (2 * kgrp + hi) * MB + (lane & 31) * (MB / 32));
-    ConvA af[2];
+    const uint32_t m_at = (uint32_t)(CG_RING + GPS * (CG_TM * 16) + (2 * kgrp + hi) * MB + (lane & 31) * (2 * Tile::MW));
+    // the sparse operand's fragments and index words in two sets, the dense operand's in one that is refilled in place
+    ConvA af[2][2];
     ConvB bf[3];
-    ConvI ix;
-    ix.w2 = u32x2{0, 0};
+    ConvI ix[2];
 #pragma unroll
-    for (int a = 0; a < 2; ++a) af[a].u4 = u32x4{0, 0, 0, 0};
+    for (int set = 0; set < 2; ++set) {
+        ix[set].w2 = u32x2{0, 0};
+#pragma unroll
+        for (int a = 0; a < 2; ++a) af[set][a].u4 = u32x4{0, 0, 0, 0};
+    }
 #pragma unroll
     for (int b = 0; b < 3; ++b)
 #pragma unroll
@@ -172,45 +182,58 @@ __global__ __launch_bounds__(CG_WAVES * 64) void conv_gemm_kernel(
             lds_refill_tr16<0>(bf[b].h[2], p2); lds_refill_tr16<0>(bf[b].h[3], p3);
         }
     };
-    auto read_a = [&](auto a_c, int s) {
-        constexpr int a = decltype(a_c)::value;
-        lds_refill_b128<a * 512>(af[a].u4, a_at + (uint32_t)(s & 7) * Tile::SLOT);
+    auto read_a = [&](auto set_c, int s) {                            // three reads
+        constexpr int set = decltype(set_c)::value;
+        const uint32_t so = (uint32_t)(s & 7) * Tile::SLOT;
+        lds_refill_b128<0>(af[set][0].u4, a_at + so);
+        lds_refill_b128<512>(af[set][1].u4, a_at + so);
+        if constexpr (Q8) lds_refill_b64<0>(ix[set].w2, m_at + so);
+        else lds_refill_b32<0>(ix[set].w[0], m_at + so);
     };
-    auto read_ix = [&](int s) {
-        const uint32_t p = m_at + (uint32_t)(s & 7) * Tile::SLOT;
-        if constexpr (Q8) lds_refill_b64<0>(ix.w2, p);
-        else lds_refill_b32<0>(ix.w[0], p);
-    };
-    auto mfma = [&](auto a_c, auto b_c) {
-        constexpr int a = decltype(a_c)::value, b = decltype(b_c)::value;
-        if constexpr (Q8) smfmac_32x32x64_bf8_fp8<true>(acc[a][b], af[a].v8, bf[b].v8, ix.w[a]);
-        else smfmac_32x32x32<-1, a, true>(acc[a][b], af[a].v16, bf[b].v16, ix.w[0]);
+    auto mfma2 = [&](auto set_c, auto b_c) {                          // column block b against both row blocks
+        constexpr int set = decltype(set_c)::value, b = decltype(b_c)::value;
+        if constexpr (Q8) {
+            smfmac_32x32x64_bf8_fp8<true>(acc[0][b], af[set][0].v8, bf[b].v8, ix[set].w[0]);
+            smfmac_32x32x64_bf8_fp8<true>(acc[1][b], af[set][1].v8, bf[b].v8, ix[set].w[1]);
+        } else {
+            smfmac_32x32x32<-1, 0, true>(acc[0][b], af[set][0].v16, bf[b].v16, ix[set].w[0]);
+            smfmac_32x32x32<-1, 1, true>(acc[1][b], af[set][1].v16, bf[b].v16, ix[set].w[0]);
+        }
     };
     using I0 = std::integral_constant<int, 0>; using I1 = std::integral_constant<int, 1>; using I2 = std::integral_constant<int, 2>;
 
     // ---- prologue: the blocks before the first super-stage's own, then CG_AHEAD super-stages
     if (wave < 4)
-        for (int b = 0; b < P; ++b) load_x(b);
+        for (int b = 0; b < P; ++b) load_at(b);
     for (int s = 0; s < CG_AHEAD; ++s) load_stage(s);
     wait_vmcnt<2 * (CG_AHEAD - 1)>();
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
-    // (the order of the reads is what the waits below count on: B0 B1 A0 A1 ix B2)
-    read_b(I0{}, 0); read_b(I1{}, 0); read_a(I0{}, 0); read_a(I1{}, 0); read_ix(0); read_b(I2{}, 0);
-    for (int s = 0; s < n_ss; ++s) {
+    // Super-stage s.  Reads in flight when it starts, in order: its B0 B1 B2, four each; with the three of the next sparse
+    // fragments and the refills behind them, 11 are always younger than the four that the next MFMAs wait for.
+    auto super_stage = [&](auto set_c, int s) {
+        constexpr int set = decltype(set_c)::value;
         // super-stage s+1 has landed, everywhere; every wave is past the reads of s-1, whose ring block and slot the loads take
         wait_vmcnt<2 * (CG_AHEAD - 2)>();
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
-        asm volatile("s_waitcnt lgkmcnt(4)" ::: "memory");
-        mfma(I0{}, I0{}); mfma(I1{}, I0{});
+        read_a(std::integral_constant<int, 1 - set>{}, s + 1);
+        asm volatile("s_waitcnt lgkmcnt(11)" ::: "memory");
+        mfma2(set_c, I0{});
         read_b(I0{}, s + 1);
         load_stage(s + CG_AHEAD);
-        mfma(I0{}, I1{}); mfma(I1{}, I1{});
+        asm volatile("s_waitcnt lgkmcnt(11)" ::: "memory");
+        mfma2(set_c, I1{});
         read_b(I1{}, s + 1);
-        asm volatile("s_waitcnt lgkmcnt(8)" ::: "memory");
-        mfma(I0{}, I2{}); mfma(I1{}, I2{});
-        read_a(I0{}, s + 1); read_a(I1{}, s + 1); read_ix(s + 1); read_b(I2{}, s + 1);
+        asm volatile("s_waitcnt lgkmcnt(11)" ::: "memory");
+        mfma2(set_c, I2{});
+        read_b(I2{}, s + 1);
+    };
+    read_a(I0{}, 0);
+    read_b(I0{}, 0); read_b(I1{}, 0); read_b(I2{}, 0);
+    for (int s = 0; s < n_ss; s += 2) {
+        super_stage(I0{}, s);
+        if (s + 1 < n_ss) super_stage(I1{}, s + 1);
     }
     // the matrix pipeline may still write the last accumulators; loads and reads that ran ahead must not land in the exchange
     __builtin_amdgcn_sched_barrier(0);
@@ -265,42 +288,46 @@ __global__ __launch_bounds__(CG_WAVES * 64) void conv_gemm_kernel(
 
 static int conv_cb(const ConvShape &cs) { return cs.C % 64 == 0 ? 64 : 32; }
 
-// Tokens of a super-stage: what the kernel wants the grid's rows rounded up to.  0: not a case of this kernel (another tap
-// count, channels that are no multiple of 32, few of a tile's 64 output channels used, an image so wide that the rows between
-// the first and the last tap do not fit the ring beside the blocks in flight).
-int conv_gemm_tokens(const ConvShape &cs, bool q8)
-{
-    if (cs.k != 3 || cs.C % 32 || 4 * (int64_t)cs.O < 3 * ((cs.O + CG_TM - 1) / CG_TM * CG_TM)) return 0;
-    const int cb = conv_cb(cs), ss = CG_BLOCK / (cb * (q8 ? 1 : 2)), margin = cs.W + 3;
-    return (2 * margin + ss - 1) / ss + CG_AHEAD <= 7 ? ss : 0;
-}
-
 // Slabs: enough to give every CU a workgroup, fewer where the partial sums cost more than the shorter slabs save (0.35 us
 // per super-stage; partial sums written and read back at about 2.2 MB per us)
-int conv_gemm_slabs(const ConvShape &cs, int64_t T, bool q8)
+static int64_t conv_slabs(const ConvShape &cs, int64_t n_ss)
 {
-    const int64_t n_ss = T / conv_gemm_tokens(cs, q8), tiles = (int64_t)((cs.O + CG_TM - 1) / CG_TM) * (cs.C / conv_cb(cs));
+    const int64_t tiles = (int64_t)((cs.O + CG_TM - 1) / CG_TM) * (cs.C / conv_cb(cs));
     const double best = std::sqrt((double)n_ss * 0.35 / ((double)cs.O * cs.C * 36.0 / 2.2e6));
     const int64_t slabs = std::max<int64_t>(1, std::min<int64_t>({256 / tiles, n_ss, (int64_t)(best + 0.5)}));
     const int64_t per = (n_ss + slabs - 1) / slabs;
-    return (int)((n_ss + per - 1) / per);
+    return (n_ss + per - 1) / per;
 }
 
-// x0: row 0 of the grid (margin rows before it and behind row T-1 are readable); part: [slabs][O][9][C] binary32
-hipError_t launch_conv_gemm(const ConvShape &cs, bool q8, const void *vals, const void *meta, const void *x0, int64_t T, float *part, hipStream_t st)
+// False: not a case of this kernel (another tap count, channels that are no multiple of 32, few of a tile's 64 output channels
+// used, an image so wide that the rows between the first and the last tap do not fit the ring beside the blocks in flight, a
+// slab beyond what a 31-bit byte offset reaches).
+bool conv_gemm_plan(const ConvShape &cs, bool q8, ConvGemmPlan &p)
 {
-    const int cb = conv_cb(cs), slabs = conv_gemm_slabs(cs, T, q8), tiles_n = cs.C / cb, Wp = cs.W + 2, margin = Wp + 1;
-    const int64_t n_ss = T / conv_gemm_tokens(cs, q8);
-    int64_t rows[9];
-    for (int t = 0; t < 9; ++t) rows[t] = (int64_t)(t / 3 - 1) * Wp + (t % 3 - 1);
+    if (cs.k != 3 || cs.C % 32 || 4 * (int64_t)cs.O < 3 * ((cs.O + CG_TM - 1) / CG_TM * CG_TM)) return false;
+    const int64_t ss = CG_BLOCK / (conv_cb(cs) * (q8 ? 1 : 2)), before = (2 * (cs.W + 3) + ss - 1) / ss;
+    if (before + CG_AHEAD > 7) return false;
+    const int64_t n_ss = ((int64_t)cs.N * (cs.H + 2) * (cs.W + 2) + ss - 1) / ss;
+    p.T = n_ss * ss;
+    p.x_rows = (n_ss + before) * ss;
+    p.slabs = (int)conv_slabs(cs, n_ss);
+    const int64_t per = (n_ss + p.slabs - 1) / p.slabs;
+    return (per + before + CG_AHEAD) * ss * std::max(cs.C * (q8 ? 1 : 2), cs.O * (q8 ? 1 : 2)) < ((int64_t)1 << 31) - 65536;
+}
+
+// x_full: p.x_rows rows of the grid from row -(W+3) on; part: [p.slabs][O][9][C] binary32
+hipError_t launch_conv_gemm(const ConvShape &cs, bool q8, const ConvGemmPlan &p, const void *vals, const void *meta, const void *x_full,
+                            float *part, hipStream_t st)
+{
+    const int cb = conv_cb(cs), slabs = p.slabs, tiles_n = cs.C / cb, Wp = cs.W + 2, margin = Wp + 1;
+    const int64_t n_ss = p.T / (CG_BLOCK / (cb * (q8 ? 1 : 2)));
     ShiftArg sh{};
-    for (int t = 0; t < 9; ++t) sh.rows[t] = (int)rows[t];
-    const char *x = (const char *)x0 - (int64_t)margin * cs.C * (q8 ? 1 : 2);
+    for (int t = 0; t < 9; ++t) sh.rows[t] = (t / 3 - 1) * Wp + (t % 3 - 1);
     const int64_t wgs = (int64_t)((cs.O + CG_TM - 1) / CG_TM) * tiles_n * slabs;
     if (wgs > 0x7fffffffll) return hipErrorInvalidConfiguration;
 #define NM_CONV(Q8, CB)                                                                                                                       \
-    hipLaunchKernelGGL((conv_gemm_kernel<Q8, CB>), dim3((unsigned)wgs), dim3(CG_WAVES * 64), 0, st, (const char *)vals, (const char *)meta, x, \
-                       part, T, (int)((n_ss + slabs - 1) / slabs), cs.O, cs.C, tiles_n, margin, sh)
+    hipLaunchKernelGGL((conv_gemm_kernel<Q8, CB>), dim3((unsigned)wgs), dim3(CG_WAVES * 64), 0, st, (const char *)vals, (const char *)meta, \
+                       (const char *)x_full, part, p.T, (int)((n_ss + slabs - 1) / slabs), cs.O, cs.C, tiles_n, margin, sh)
     if (q8) { if (cb == 64) NM_CONV(true, 64); else NM_CONV(true, 32); }
     else { if (cb == 64) NM_CONV(false, 64); else NM_CONV(false, 32); }
 #undef NM_CONV

@@ -116,11 +116,14 @@ hipError_t launch_update_gemm_smfmac_shifted_parts(const void *vals, const uint1
 size_t update_gemm_q8_shifted_parts_bytes(int64_t T, int64_t O, int64_t I);
 hipError_t launch_update_gemm_q8_shifted_parts(const uint8_t *vals8, const uint32_t *meta32, const uint8_t *x8, int64_t ldx, int64_t cb,
                                                const int64_t *rows, int n, int64_t T, int64_t O, float *part, int *slabs, hipStream_t st);
-// 3 x 3 convolutions with all taps of a channel block in one workgroup (gemm_conv.hip): the token count has to be a multiple of
-// conv_gemm_tokens (0: not a case of it); part: [conv_gemm_slabs][O][9][C]
-int conv_gemm_tokens(const ConvShape &cs, bool q8);
-int conv_gemm_slabs(const ConvShape &cs, int64_t T, bool q8);
-hipError_t launch_conv_gemm(const ConvShape &cs, bool q8, const void *vals, const void *meta, const void *x0, int64_t T, float *part, hipStream_t st);
+// 3 x 3 convolutions with all taps of a channel block in one workgroup (gemm_conv.hip)
+struct ConvGemmPlan {
+    int64_t T, x_rows;                    // tokens (the grid's rows rounded up) and rows of the activations' buffer, whatever its last ones hold
+    int slabs;                            // partial sums: [slabs][O][9][C]
+};
+bool conv_gemm_plan(const ConvShape &cs, bool q8, ConvGemmPlan &p);       // false: not a case of it
+hipError_t launch_conv_gemm(const ConvShape &cs, bool q8, const ConvGemmPlan &p, const void *vals, const void *meta, const void *x_full,
+                            float *part, hipStream_t st);
 // conv weight gradient, bf16 [O][C][taps] = alpha * sum over the slabs of part[slabs][O][taps][C]
 hipError_t launch_finish_conv(const float *part, int slabs, void *dW, int64_t O, int C, int taps, AlphaArg alpha, hipStream_t st);
 

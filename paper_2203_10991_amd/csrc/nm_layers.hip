@@ -41,7 +41,8 @@ struct Carver {
 struct ConvPlan {
     nm::ConvShape cs;
     int64_t T, margin, I;
-    int conv_slabs;                       // 0: the general update GEMM on shifted views
+    bool taps;                            // the nine-tap kernel; otherwise the general update GEMM on shifted views
+    nm::ConvGemmPlan gemm;
     size_t x_full, vals, meta, recs, part, bytes;
 };
 ConvPlan plan_conv(const nm::ConvShape &cs, bool q8)
@@ -50,17 +51,16 @@ ConvPlan plan_conv(const nm::ConvShape &cs, bool q8)
     p.cs = cs;
     const int pad = cs.k / 2;
     const int64_t Wp = cs.W + 2 * pad, rows = (int64_t)cs.N * (cs.H + 2 * pad) * Wp, gt = q8 ? 32 : 16;
-    const int64_t super = nm::conv_gemm_tokens(cs, q8), mult = super ? super : gt;
-    p.T = (rows + mult - 1) / mult * mult;
-    p.conv_slabs = super ? nm::conv_gemm_slabs(cs, p.T, q8) : 0;
+    p.taps = nm::conv_gemm_plan(cs, q8, p.gemm);
+    p.T = p.taps ? p.gemm.T : (rows + gt - 1) / gt * gt;
     p.margin = pad * Wp + pad;
     p.I = (int64_t)cs.C * cs.k * cs.k;
     Carver c;
     p.recs = c.take(32);
-    p.x_full = c.take((size_t)(p.T + 2 * p.margin) * cs.C * (q8 ? 1 : 2));
+    p.x_full = c.take((size_t)(p.taps ? p.gemm.x_rows : p.T + 2 * p.margin) * cs.C * (q8 ? 1 : 2));
     p.vals = c.take((size_t)(p.T / 2) * cs.O * (q8 ? 1 : 2));
     p.meta = c.take((size_t)(p.T / gt) * cs.O * (q8 ? 4 : 2));
-    p.part = c.take(super ? (size_t)p.conv_slabs * cs.O * p.I * sizeof(float)
+    p.part = c.take(p.taps ? (size_t)p.gemm.slabs * cs.O * p.I * sizeof(float)
                     : q8 ? nm::update_gemm_q8_shifted_parts_bytes(p.T, cs.O, p.I) : nm::update_gemm_smfmac_shifted_parts_bytes(p.T, cs.O, p.I));
     p.bytes = c.used;
     return p;
@@ -221,9 +221,9 @@ int nm_conv_update(const void *gy, int gy_channels_last, const void *x, int x_ch
     if (e == hipSuccess) e = nm::launch_grid_pack(cs, x, p.margin, p.T + 2 * p.margin, q8 ? rec_x : nullptr, w + p.x_full, st);
     if (e == hipSuccess) e = nm::launch_prune_grid(cs, mode, gy, p.T, seed, stream_id, q8 ? rec_g : nullptr, w + p.vals, w + p.meta, st);
     const char *x0 = w + p.x_full + p.margin * C * (q8 ? 1 : 2);
-    if (e == hipSuccess && p.conv_slabs) {
-        slabs = p.conv_slabs;
-        e = nm::launch_conv_gemm(cs, q8 != 0, w + p.vals, w + p.meta, x0, p.T, part, st);
+    if (e == hipSuccess && p.taps) {
+        slabs = p.gemm.slabs;
+        e = nm::launch_conv_gemm(cs, q8 != 0, p.gemm, w + p.vals, w + p.meta, w + p.x_full, part, st);
     } else if (e == hipSuccess)
         e = q8 ? nm::launch_update_gemm_q8_shifted_parts((const uint8_t *)(w + p.vals), (const uint32_t *)(w + p.meta), (const uint8_t *)x0, C, C,
                                                          shifts, k * k, p.T, O, part, &slabs, st)
