@@ -20,6 +20,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "nm_internal.h"
@@ -27,6 +28,7 @@
 namespace nm {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int F32_TM = 128, F32_TN = 256;
 // LDS row strides in floats: the two half-waves of a fragment read (rows 2kk and 2kk+1) hit disjoint banks
@@ -182,31 +184,173 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         }
 }
 
-// split-K plan: a pure function of the problem size
-struct PlanF32 { int tiles_m, tiles_n, slabs; int64_t groups_per_slab; };
+// ------------------------------------------------------------------------------------
+// Small and mid-sized outputs: 64 x 64 tile, operands straight from global memory to registers.  16 waves: two of 32 x 64 (two
+// accumulator blocks each) times eight groups of waves that each take an eighth of the slab's token groups; their sums meet
+// in LDS at the end, in a fixed order.  The order of a group's 16 tokens inside the reduction is free as long as both operands
+// agree on it: half-wave `hi` takes tokens 8*hi .. 8*hi+7, one per step, so that a lane needs two quads of its row of the sparse
+// operand -- one 16-byte load, expanded in registers for two MFMAs each -- and h comes as whole 128-byte lines, one per
+// half-wave and step; the waves that share columns find them in the CU's cache.  No LDS and no barrier in the loop: four waves
+// per SIMD and the loads of the next token group in flight cover the latency.  Every load is a descriptor that the scalar unit
+// advances, a constant lane offset and a constant scalar offset: vector instructions delay the matrix pipeline.
+// Every 128 tokens the blocks' sums are added to a second set of registers: rounding errors grow with the length of a chain.
+// ------------------------------------------------------------------------------------
+constexpr int F32S_T = 64, F32S_KG = 8, F32S_FOLD = 8;
+
+__global__ __launch_bounds__(1024) void update_gemm_f32_small_kernel(
+    const float *__restrict__ vals, const uint16_t *__restrict__ meta, const float *__restrict__ h, int64_t ldh,
+    float *__restrict__ out, int64_t ldo, int64_t slab_stride, int64_t n_groups, int64_t groups_per_slab,
+    int64_t O, int64_t I, int accumulate, int tiles_n)
+{
+    __shared__ float4 xch[F32S_KG / 2 * 2 * 8 * 64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave & 1, kq = wave >> 1;
+    const int hi = lane >> 5, m = lane & 31;
+    // consecutive workgroups of an XCD are neighbouring tiles of one slab: bands of 8 tile rows
+    const unsigned n = gridDim.x, xcd = blockIdx.x % 8, w_id = xcd * (n / 8) + min(xcd, n % 8) + blockIdx.x / 8;
+    const int tiles_m = (int)((O + F32S_T - 1) / F32S_T), tiles = tiles_m * tiles_n;
+    const int slab = (int)(w_id / tiles), t = (int)(w_id % tiles);
+    const int band = t / (8 * tiles_n), rows_b = min(8, tiles_m - 8 * band), in_band = t - band * 8 * tiles_n;
+    const int64_t o0 = (int64_t)(8 * band + in_band % rows_b) * F32S_T + 32 * wm, i0 = (int64_t)(in_band / rows_b) * F32S_T;
+    const int64_t s_begin = (int64_t)slab * groups_per_slab, s_end = min(n_groups, s_begin + groups_per_slab);
+    const int64_t per = (s_end - s_begin + F32S_KG - 1) / F32S_KG;
+    const int64_t g_begin = min(s_end, s_begin + kq * per);
+    const int n_g = (int)(min(s_end, g_begin + per) - g_begin);
+
+    // rows >= O and columns >= I are clamped to the last valid ones: their products are never stored
+    const uint32_t a_at = (uint32_t)(min(o0 + m, O - 1) * 32 + 16 * hi), m_at = (uint32_t)(min(o0 + m, O - 1) * 2);
+    const uint32_t b_at0 = (uint32_t)((8 * hi * ldh + min(i0 + m, I - 1)) * 4), b_at1 = (uint32_t)((8 * hi * ldh + min(i0 + 32 + m, I - 1)) * 4);
+    auto buffer_of = [](const void *p) { return __builtin_amdgcn_make_buffer_rsrc((void *)p, 0, 0x7fffffff, 0x00020000); };
+    struct Group { f32x4 a; uint32_t meta; float b0[8], b1[8]; };
+    auto load = [&](int i, Group &g) {                                // token group i of this wave (the last one again past the end)
+        const int64_t G = g_begin + min(i, n_g - 1);
+        const auto ra = buffer_of(vals + G * O * 8), rm = buffer_of(meta + G * O), rb = buffer_of(h + G * 16 * ldh);
+        g.a = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(ra, (int)a_at, 0, 0));
+        g.meta = (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(rm, (int)m_at, 0, 0);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            g.b0[k] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rb, (int)b_at0, (int)(k * ldh * 4), 0));
+            g.b1[k] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rb, (int)b_at1, (int)(k * ldh * 4), 0));
+        }
+    };
+    f32x16 acc[2], sum[2];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[0][r] = acc[1][r] = sum[0][r] = sum[1][r] = 0.f;
+    auto multiply = [&](const Group &g) {
+        const uint32_t w = g.meta >> (8 * hi);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const float v0 = q ? g.a[2] : g.a[0], v1 = q ? g.a[3] : g.a[1];
+            const uint32_t p0 = (w >> (4 * q)) & 3u, p1 = (w >> (4 * q + 2)) & 3u;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const float a = p0 == k ? v0 : p1 == k ? v1 : 0.f;
+                acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a, g.b0[4 * q + k], acc[0], 0, 0, 0);
+                acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a, g.b1[4 * q + k], acc[1], 0, 0, 0);
+            }
+        }
+    };
+    if (n_g > 0) {
+        Group ga, gb;
+        load(0, ga);
+        int since = 0;
+        for (int i = 0; i < n_g; i += 2) {
+            load(i + 1, gb);
+            multiply(ga);
+            load(i + 2, ga);
+            if (i + 1 < n_g) multiply(gb);
+            since += 2;
+            if (since == F32S_FOLD) {
+                since = 0;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) { sum[0][r] += acc[0][r]; sum[1][r] += acc[1][r]; acc[0][r] = acc[1][r] = 0.f; }
+            }
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) { sum[0][r] += acc[0][r]; sum[1][r] += acc[1][r]; }
+    // group k += group k + half
+#pragma unroll
+    for (int half = F32S_KG / 2; half >= 1; half /= 2) {
+        if (kq >= half && kq < 2 * half) {
+            float4 *dst = xch + ((kq - half) * 2 + wm) * 8 * 64 + lane;
+#pragma unroll
+            for (int r = 0; r < 8; ++r) dst[64 * r] = make_float4(sum[r / 4][4 * (r % 4)], sum[r / 4][4 * (r % 4) + 1], sum[r / 4][4 * (r % 4) + 2], sum[r / 4][4 * (r % 4) + 3]);
+        }
+        __syncthreads();
+        if (kq < half) {
+            const float4 *from = xch + (kq * 2 + wm) * 8 * 64 + lane;
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {
+                const float4 v = from[64 * r];
+                sum[r / 4][4 * (r % 4)] += v.x; sum[r / 4][4 * (r % 4) + 1] += v.y; sum[r / 4][4 * (r % 4) + 2] += v.z; sum[r / 4][4 * (r % 4) + 3] += v.w;
+            }
+        }
+        __syncthreads();
+    }
+    if (kq > 0) return;
+    out += (int64_t)slab * slab_stride;
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+        const int64_t col = i0 + 32 * b + m;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int64_t row = o0 + 8 * (r >> 2) + 4 * hi + (r & 3);
+            if (row < O && col < I) {
+                float *p = out + row * ldo + col;
+                *p = accumulate ? *p + sum[b][r] : sum[b][r];
+            }
+        }
+    }
+}
+
+// Plan: a pure function of the problem size.  Two workgroups of the 128 x 256 kernel share a CU, one of the 64 x 64 kernel fills it.
+// Microseconds, fitted to both kernels on 13 sizes (within 10 %): a token of a 128 x 256 tile 0.14 alone on its CU, 0.2425 for two,
+// 10 us of fill; a token of a 64 x 64 tile 0.0169, 4.5 us per round and 5 per launch; the second pass as in the 16-bit
+// plan.  The smaller tile has the finer grain -- it fills the GPU without (or with a quarter of) the slabs -- and the
+// larger one needs a quarter of the operand bytes and pays no fill per tile: it keeps outputs of many tiles over few tokens.
+// Measured, 128 x 256 -> 64 x 64, second pass included: 1024 x 1024 x 1024 38.7 -> 27.0 us, 512 x 512 x 256 28 -> 14, 16384 x 256 x 256
+// 37.6 -> 29.3, 8192 x 1536 x 2048 677 (576 workgroups, a second round of 64) -> 436; the other way 512 x 4096 x 4096 138 against
+// 219, 4096 x 2048 x 2048 278 against 300.
+struct PlanF32 { bool small; int tiles_m, tiles_n, slabs; int64_t groups_per_slab; };
 static PlanF32 make_plan_f32(int64_t T, int64_t O, int64_t I)
 {
-    PlanF32 p;
+    PlanF32 p{};
     const int64_t groups = T / 16;
-    p.tiles_m = (int)((O + F32_TM - 1) / F32_TM);
-    p.tiles_n = (int)((I + F32_TN - 1) / F32_TN);
-    const int64_t tiles = (int64_t)p.tiles_m * p.tiles_n;
+    auto tiles_of = [&](int64_t tm, int64_t tn) { return ((O + tm - 1) / tm) * ((I + tn - 1) / tn); };
+    const int64_t big = tiles_of(F32_TM, F32_TN), fine = tiles_of(F32S_T, F32S_T);
+    double best = 1e300;
     int64_t slabs = 1;
-    if (tiles < 256 && groups >= 16) {
-        slabs = (2 * 256 + tiles - 1) / tiles;            // about two workgroups per CU
-        if (slabs > groups / 8) slabs = groups / 8;       // at least 128 tokens per slab
-        if (slabs < 1) slabs = 1;
+    auto consider = [&](bool small, int64_t z) {
+        z = std::max<int64_t>(1, std::min<int64_t>(z, groups / (small ? 16 : 8)));       // at least 256 (128) tokens per slab
+        const int64_t wgs = z * (small ? fine : big), tokens = (groups + z - 1) / z * 16, per_round = small ? 256 : 512;
+        const double rounds = (double)((wgs + per_round - 1) / per_round);
+        double cost = small ? rounds * ((double)tokens * 0.0169 + 4.5) + 5.0 : rounds * (double)tokens * (wgs <= 256 ? 0.14 : 0.2425) + 10.0;
+        if (z > 1) cost += 4.0 + (double)(z + 1) * (double)O * (double)I * 4.0 / 3.5e6;
+        if (cost < best) { best = cost; p.small = small; slabs = z; }
+    };
+    consider(false, big < 256 ? 512 / big : 1);
+    consider(false, 256 / big);
+    if (O <= (int64_t)1 << 24) {                                      // (its lane offsets are 32 bits wide)
+        consider(true, 256 / fine);
+        consider(true, 1);
     }
+    p.tiles_m = (int)((O + (p.small ? F32S_T : F32_TM) - 1) / (p.small ? F32S_T : F32_TM));
+    p.tiles_n = (int)((I + (p.small ? F32S_T : F32_TN) - 1) / (p.small ? F32S_T : F32_TN));
     p.groups_per_slab = groups > 0 ? (groups + slabs - 1) / slabs : 1;
     p.slabs = groups > 0 ? (int)((groups + p.groups_per_slab - 1) / p.groups_per_slab) : 1;
     return p;
 }
 
+// What a call asks for is an upper bound of both kernels' plans, the slabs that give every CU two workgroups of the larger tile:
+// which calls fit a scratch of a given size does not depend on the kernel that runs.  (make_plan_f32 takes no more than this: at
+// most 512 / big slabs of the larger tile, and 256 / fine <= 256 / big of the smaller.)
 size_t update_gemm_f32_workspace(int64_t T, int64_t O, int64_t I)
 {
     if (T <= 0 || O <= 0 || I <= 0) return 0;
-    const PlanF32 p = make_plan_f32(T, O, I);
-    return p.slabs > 1 ? (size_t)p.slabs * (size_t)O * (size_t)I * sizeof(float) : 0;
+    const int64_t groups = T / 16, big = ((O + F32_TM - 1) / F32_TM) * ((I + F32_TN - 1) / F32_TN);
+    if (big >= 256 || groups < 16) return 0;
+    const int64_t slabs = std::max<int64_t>(1, std::min<int64_t>((512 + big - 1) / big, groups / 8)), per = (groups + slabs - 1) / slabs;
+    return (groups + per - 1) / per > 1 ? (size_t)((groups + per - 1) / per) * (size_t)O * (size_t)I * sizeof(float) : 0;
 }
 
 hipError_t launch_update_gemm_f32(const void *vals, const uint16_t *meta, const void *h, int64_t ldh, float *dW,
@@ -214,14 +358,24 @@ hipError_t launch_update_gemm_f32(const void *vals, const uint16_t *meta, const 
                                   hipStream_t st)
 {
     if (O == 0 || I == 0) return hipSuccess;
-    const PlanF32 p = make_plan_f32(T, O, I);
+    PlanF32 p = make_plan_f32(T, O, I);
+    if (p.small && ldh > (int64_t)1 << 24) {                          // rows further apart than 32-bit offsets reach: the other kernel, same slabs
+        p.small = false;
+        p.tiles_m = (int)((O + F32_TM - 1) / F32_TM);
+        p.tiles_n = (int)((I + F32_TN - 1) / F32_TN);
+    }
     const int accumulate = beta != 0.f;
     float *out = dW;
     int64_t ldo = lddw, slab_stride = 0;
     int acc_flag = accumulate;
     if (p.slabs > 1) { out = (float *)workspace; ldo = I; slab_stride = O * I; acc_flag = 0; }
-    dim3 grid((unsigned)p.tiles_n, (unsigned)p.tiles_m, (unsigned)p.slabs);
-    hipLaunchKernelGGL(update_gemm_f32_mfma_kernel, grid, dim3(256), 0, st, (const float *)vals, meta, (const float *)h,
+    if (p.small) {
+        const int64_t wgs = (int64_t)p.tiles_m * p.tiles_n * p.slabs;
+        if (wgs > 0x7fffffffll) return hipErrorInvalidConfiguration;
+        hipLaunchKernelGGL(update_gemm_f32_small_kernel, dim3((unsigned)wgs), dim3(1024), 0, st, (const float *)vals, meta, (const float *)h,
+                           ldh, out, ldo, slab_stride, T / 16, p.groups_per_slab, O, I, acc_flag, p.tiles_n);
+    } else
+        hipLaunchKernelGGL(update_gemm_f32_mfma_kernel, dim3((unsigned)p.tiles_n, (unsigned)p.tiles_m, (unsigned)p.slabs), dim3(256), 0, st, (const float *)vals, meta, (const float *)h,
                        ldh, out, ldo, slab_stride, T / 16, p.groups_per_slab, O, I, acc_flag);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

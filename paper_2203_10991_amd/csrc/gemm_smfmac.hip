@@ -749,13 +749,13 @@ static Plan make_plan(int64_t T, int64_t O, int64_t I, bool shifted = false, boo
             // predictions for the others run 10 % high here, so it has to win by 17 %.  55968 x 2960 x 1976: 4 slabs of 64 tiles on
             // all CUs instead of 2 slabs of 96 on three quarters, 435 -> 356 us; 25904 x 272 x 16968
             // 540 -> 232 us, 32224 x 5536 x 1432 452 -> 329, at the line 15360 x 23920 x 272 216 -> 191, beyond it 10832 x 272 x 14176
-            // 100 -> 102.  Not where it would take a workspace past the static
-            // scratch that holds the other plan's: such a call has to go on working without a workspace of the caller's.
+            // 100 -> 102.  Not where its workspace fits the static scratch and the other plan's does not, or the other way round: which
+            // calls work without a workspace of the caller's does not depend on the kernel that runs.
             int64_t s4 = 1;
             const int64_t tiles4 = (O + 383) / 384 * ((I + 255) / 256);
             const double cost4 = one_per_cu(tiles4, 0.60, 0.76, 0.0, s4), best = take0 ? std::min(cost0, take3 ? cost3 : cost0) : take3 ? cost3 : cost1;
             auto fits = [&](int64_t sl) { return beside + splitk_workspace_bytes((int)sl, O, I) <= static_scratch_bytes(); };
-            if (!shifted && whole_rows && s4 > 1 && cost4 < 0.83 * best && (fits(s4) || !fits(slabs))) {
+            if (!shifted && whole_rows && s4 > 1 && cost4 < 0.83 * best && fits(s4) == fits(slabs)) {
                 p.shape = 0; p.tm = 256; p.tn = 256;
                 p.tall_rows = O; p.tall_tiles_m = (int)((O + 383) / 384);
                 slabs = (int)s4;

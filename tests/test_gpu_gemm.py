@@ -238,3 +238,12 @@ def test_update_gemm_f32_split_special_values(nm):
                                         (13008, 272, 11896, 1.0)])
 def test_long_reductions_on_384_row_tiles_in_slabs(nm, oracle, T, O, I, beta):
     run_case(nm, oracle, synth.Workload(f"tall{T}x{O}x{I}", T, O, I, "bf16", "2:4", 0.0, 2.0, 0.3), seed=3, beta=beta)
+
+
+# binary32, around the line between the two kernels
+@pytest.mark.parametrize("T,O,I,beta", [(1024, 1000, 1016, 0.0),       # 64 x 64 tiles in one pass, ragged edges
+                                        (16 * 7, 72, 40, 1.0),         # fewer token groups than groups of waves
+                                        (16 * 257, 136, 264, 1.0),     # slabs of 64 x 64 tiles, a short last slab and last share
+                                        (256, 2040, 4096, 0.0)])       # 128 x 256 tiles
+def test_binary32_kernels_on_both_sides_of_the_line(nm, oracle, T, O, I, beta):
+    run_case(nm, oracle, synth.Workload(f"f32_{T}x{O}x{I}", T, O, I, "f32", "2:4", 0.0, 2.0, 0.3), seed=T, beta=beta)
