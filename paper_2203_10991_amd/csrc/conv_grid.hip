@@ -1,14 +1,16 @@
 // The padded channels-last grid of a convolution's update GEMM, straight from the tensors a layer holds.
 //
 // The update GEMM on shifted views (nm_update_gemm_shifted) wants activations and gradient on one zero-padded grid
-// [N][H+2p][W+2p][C] flattened to rows.  Two kernels make what it consumes in one pass each:
-//   grid_pack_kernel    activations [N, C, H, W] (channel planes, or channels last) -> the grid's rows with the zero
+// [N][H+2p][W+2p][C] flattened to rows.  One launch makes what it consumes, one pass over each tensor; its workgroups are
+// dealt to two tasks:
+//   grid_pack    activations [N, C, H, W] (channel planes, or channels last) -> the grid's rows with the zero
 //                       border and the zero margin rows, as bf16 or scaled and rounded to e4m3
-//   prune_grid_kernel   the same grid of the gradient, never written: a tile of it is put together in LDS, pruned 2:4 along the
+//   prune_grid   the same grid of the gradient, never written: a tile of it is put together in LDS, pruned 2:4 along the
 //                       grid's rows and compressed (16-token groups, bf16) or also rounded to e5m2 (32-token groups)
 // Masks and values are those of the ordinary prune on the materialised grid (same block index, same random words).
 //
-// Bound: HBM (one read of the tensor, one write of the result; the prune's arithmetic comes close).  Before, the layer
+// Bound: HBM (one read of each tensor, one write of each result); alone, the pack is bound by it and the prune by its vector
+// arithmetic, so the two tasks alternate workgroup by workgroup: FIGURES.  Before, the layer
 // made the grid with tensor operations: a fill and a strided permuting copy per padding, a fill and a copy per margin --
 // 375 us for the two tensors of a 256 x 64 x 56 x 56 layer, whose bytes take 60 us, then the prune read the grid again.
 #include <hip/hip_runtime.h>
@@ -38,7 +40,7 @@ inline GridGeom grid_geom(const ConvShape &s, int C)
 }
 
 // element offset of channel 0 of grid row r in the tensor, or -1 where the grid holds zeros
-template <bool CL> __device__ __forceinline__ int64_t grid_source(const GridGeom &gg, int64_t r)
+__device__ __forceinline__ int64_t grid_source(const GridGeom &gg, bool cl, int64_t r)
 {
     if (r < 0 || r >= gg.rows) return -1;
     const uint32_t q = (uint32_t)r / (uint32_t)gg.Wp, x = (uint32_t)r - q * (uint32_t)gg.Wp;      // (rows < 2^31: checked by the caller)
@@ -46,7 +48,7 @@ template <bool CL> __device__ __forceinline__ int64_t grid_source(const GridGeom
     const int xi = (int)x - gg.pad, yi = (int)y - gg.pad;
     if (xi < 0 || xi >= gg.W || yi < 0 || yi >= gg.H) return -1;
     const int64_t plane = (int64_t)gg.H * gg.W, s = (int64_t)yi * gg.W + xi;
-    return CL ? ((int64_t)n * plane + s) * gg.C : (int64_t)n * plane * gg.C + s;
+    return cl ? ((int64_t)n * plane + s) * gg.C : (int64_t)n * plane * gg.C + s;
 }
 
 // A tile of the grid in LDS: TILE_ROWS rows x TILE_COLS channels, 34 words per row (64 channels and two words of padding: a
@@ -55,14 +57,13 @@ constexpr int TILE_ROWS = 256, TILE_COLS = 64, TILE_LD = TILE_COLS / 2 + 2;
 
 // Channel planes: thread t owns grid row r0 + t, so the 64 lanes of a wave read runs of consecutive x of one channel; pairs of
 // channels share a word.  Channels last: eight threads share a row, 16 bytes each.
-template <bool CL>
-__device__ __forceinline__ void load_tile(uint32_t *tile, int64_t *offs, const uint16_t *__restrict__ src, const GridGeom &gg,
+__device__ __forceinline__ void load_tile(uint32_t *tile, int64_t *offs, const uint16_t *__restrict__ src, const GridGeom &gg, bool cl,
                                           int64_t r0, int c0)
 {
     const int tid = threadIdx.x;
     const int cols = min(TILE_COLS, gg.C - c0);                      // a multiple of 8
-    const int64_t o = grid_source<CL>(gg, r0 + tid);
-    if constexpr (!CL) {
+    const int64_t o = grid_source(gg, cl, r0 + tid);
+    if (!cl) {
         const int64_t plane = (int64_t)gg.H * gg.W;
         const uint16_t *p = src + (o < 0 ? 0 : o) + (int64_t)c0 * plane;      // (a border row reads image 0 and drops it)
         const uint32_t keep = o < 0 ? 0u : 0xffffffffu;
@@ -109,15 +110,13 @@ __device__ __forceinline__ uint32_t e4m3_of_words(uint32_t a, uint32_t b, float 
     return (uint32_t)w;
 }
 
-template <bool CL, bool Q8>
-__global__ __launch_bounds__(256) void grid_pack_kernel(const uint16_t *__restrict__ x, GridGeom gg, int64_t margin, int64_t out_rows,
-                                                        const float *__restrict__ rec, void *__restrict__ out_)
+template <bool Q8>
+__device__ __forceinline__ void grid_pack(uint32_t *tile, int64_t *offs, const uint16_t *__restrict__ x, const GridGeom &gg, bool cl, int64_t margin,
+                                          int64_t out_rows, const float *__restrict__ rec, void *__restrict__ out_, int64_t bx, int by)
 {
-    __shared__ uint32_t tile[TILE_ROWS * TILE_LD];
-    __shared__ int64_t offs[CL ? TILE_ROWS : 1];
-    const int64_t r0 = (int64_t)blockIdx.x * TILE_ROWS;                 // out row
-    const int c0 = (int)blockIdx.y * TILE_COLS;
-    load_tile<CL>(tile, offs, x, gg, r0 - margin, c0);
+    const int64_t r0 = bx * TILE_ROWS;                                  // out row
+    const int c0 = by * TILE_COLS;
+    load_tile(tile, offs, x, gg, cl, r0 - margin, c0);
     constexpr int PER = Q8 ? 16 : 8;                                    // channels of a 16-byte piece
     constexpr int PR = TILE_COLS / PER;                                 // pieces per row
     const float s = Q8 ? rec[0] : 1.0f;
@@ -138,17 +137,6 @@ __global__ __launch_bounds__(256) void grid_pack_kernel(const uint16_t *__restri
             *(uint4 *)((uint16_t *)out_ + (r0 + row) * gg.C + c) = o;
         }
     }
-}
-
-hipError_t launch_grid_pack(const ConvShape &cs, const void *x, int64_t margin, int64_t out_rows, const float *rec, void *out, hipStream_t st)
-{
-    const GridGeom gg = grid_geom(cs, cs.C);
-    const dim3 grid((unsigned)((out_rows + TILE_ROWS - 1) / TILE_ROWS), (unsigned)((cs.C + TILE_COLS - 1) / TILE_COLS));
-#define NM_PACK(CL, Q8) hipLaunchKernelGGL((grid_pack_kernel<CL, Q8>), grid, dim3(256), 0, st, (const uint16_t *)x, gg, margin, out_rows, rec, out)
-    if (cs.x_channels_last) { if (rec) NM_PACK(true, true); else NM_PACK(true, false); }
-    else { if (rec) NM_PACK(false, true); else NM_PACK(false, false); }
-#undef NM_PACK
-    return hipGetLastError();
 }
 
 // ------------------------------------------------------------------------------------
@@ -188,16 +176,14 @@ __device__ __forceinline__ void philox_call(uint64_t ctr, uint32_t stream_id, ui
     else philox4x32_10((uint32_t)ctr, (uint32_t)(ctr >> 32), stream_id, domain, key0, key1, w4);
 }
 
-template <bool CL, int EST, bool HI0>
-__global__ __launch_bounds__(256) void prune_grid_kernel(const uint16_t *__restrict__ g, GridGeom gg, int64_t n_groups, uint32_t key0,
-                                                         uint32_t key1, uint32_t stream_id, uint16_t *__restrict__ vals,
-                                                         uint16_t *__restrict__ meta)
+template <int EST, bool HI0>
+__device__ __forceinline__ void prune_grid(uint32_t *tile, int64_t *offs, const uint16_t *__restrict__ g, const GridGeom &gg, bool cl, int64_t n_groups,
+                                           uint32_t key0, uint32_t key1, uint32_t stream_id, uint16_t *__restrict__ vals,
+                                           uint16_t *__restrict__ meta, int64_t bx, int by)
 {
-    __shared__ __attribute__((aligned(16))) uint32_t tile[TILE_ROWS * TILE_LD];
-    __shared__ int64_t offs[CL ? TILE_ROWS : 1];
-    const int64_t r0 = (int64_t)blockIdx.x * TILE_ROWS;
-    const int c0 = (int)blockIdx.y * TILE_COLS, O = gg.C;
-    load_tile<CL>(tile, offs, g, gg, r0, c0);
+    const int64_t r0 = bx * TILE_ROWS;
+    const int c0 = by * TILE_COLS, O = gg.C;
+    load_tile(tile, offs, g, gg, cl, r0, c0);
 
     const int tid = threadIdx.x, cq = tid & 15, gi = tid >> 4;          // four columns 4cq .. 4cq+3 of token group gi of the tile
     const int64_t G = r0 / 16 + gi;
@@ -246,17 +232,15 @@ __global__ __launch_bounds__(256) void prune_grid_kernel(const uint16_t *__restr
     if (col < O && G < n_groups) *(uint2 *)(meta + G * O + col) = make_uint2(md[0] | (md[1] << 16), md[2] | (md[3] << 16));
 }
 
-template <bool CL, int EST, bool HI0>
-__global__ __launch_bounds__(256) void prune_grid_q8_kernel(const uint16_t *__restrict__ g, GridGeom gg, int64_t n_groups, uint32_t key0,
-                                                            uint32_t key1, uint32_t stream_id, const float *__restrict__ rec,
-                                                            uint8_t *__restrict__ vals8, uint32_t *__restrict__ meta32)
+template <int EST, bool HI0>
+__device__ __forceinline__ void prune_grid_q8(uint32_t *tile, int64_t *offs, const uint16_t *__restrict__ g, const GridGeom &gg, bool cl, int64_t n_groups,
+                                              uint32_t key0, uint32_t key1, uint32_t stream_id, const float *__restrict__ rec,
+                                              uint8_t *__restrict__ vals8, uint32_t *__restrict__ meta32, int64_t bx, int by)
 {
-    __shared__ __attribute__((aligned(16))) uint32_t tile[TILE_ROWS * TILE_LD];
-    __shared__ int64_t offs[CL ? TILE_ROWS : 1];
-    const int64_t r0 = (int64_t)blockIdx.x * TILE_ROWS;
-    const int c0 = (int)blockIdx.y * TILE_COLS, O = gg.C;
+    const int64_t r0 = bx * TILE_ROWS;
+    const int c0 = by * TILE_COLS, O = gg.C;
     const float scale = rec[0];
-    load_tile<CL>(tile, offs, g, gg, r0, c0);
+    load_tile(tile, offs, g, gg, cl, r0, c0);
 
     const int tid = threadIdx.x, cp = tid & 31, gi = tid >> 5;          // columns 2cp, 2cp+1 of token group gi (8 groups in the tile)
     const bool odd = cp & 1;
@@ -311,28 +295,50 @@ __global__ __launch_bounds__(256) void prune_grid_q8_kernel(const uint16_t *__re
     if (col < O && G < n_groups) *(uint2 *)(meta32 + G * O + col) = make_uint2(md[0], md[1]);
 }
 
-// est: 0 optimal MVUE 2:4, 1 approx-MVUE 2:4; T: grid rows rounded up to whole groups (16 tokens, or 32 with rec: 8-bit output)
-hipError_t launch_prune_grid(const ConvShape &cs, int est, const void *gy, int64_t T, uint64_t seed, uint32_t stream_id, const float *rec,
-                             void *vals, void *meta, hipStream_t st)
+struct PackTask { const uint16_t *x; GridGeom gg; bool cl; int64_t margin, out_rows; const float *rec; void *out; int64_t rows, blocks; };
+struct PruneTask { const uint16_t *g; GridGeom gg; bool cl; int64_t n_groups; const float *rec; void *vals, *meta; int64_t rows, blocks; };
+
+// `rows` workgroups along the grid's rows (fastest) and the rest along the channels, for either task
+template <bool Q8, int EST, bool HI0>
+__global__ __launch_bounds__(256) void grid_kernel(PackTask a, PruneTask b, uint32_t key0, uint32_t key1, uint32_t stream_id)
 {
-    const GridGeom gg = grid_geom(cs, cs.O);
-    const dim3 grid((unsigned)((T + TILE_ROWS - 1) / TILE_ROWS), (unsigned)((cs.O + TILE_COLS - 1) / TILE_COLS));
+    __shared__ __attribute__((aligned(16))) uint32_t tile[TILE_ROWS * TILE_LD];
+    __shared__ int64_t offs[TILE_ROWS];
+    // workgroup n is a pack where the running share of packs, n * blocks / total, steps at n+1
+    const int64_t total = a.blocks + b.blocks, n = blockIdx.x, packs = n * a.blocks / total;
+    if ((n + 1) * a.blocks / total != packs) {
+        grid_pack<Q8>(tile, offs, a.x, a.gg, a.cl, a.margin, a.out_rows, a.rec, a.out, packs % a.rows, (int)(packs / a.rows));
+    } else {
+        const int64_t p = n - packs;
+        if constexpr (Q8)
+            prune_grid_q8<EST, HI0>(tile, offs, b.g, b.gg, b.cl, b.n_groups, key0, key1, stream_id, b.rec, (uint8_t *)b.vals, (uint32_t *)b.meta,
+                                    p % b.rows, (int)(p / b.rows));
+        else
+            prune_grid<EST, HI0>(tile, offs, b.g, b.gg, b.cl, b.n_groups, key0, key1, stream_id, (uint16_t *)b.vals, (uint16_t *)b.meta,
+                                 p % b.rows, (int)(p / b.rows));
+    }
+}
+
+// x, margin, out_rows, rec_x, x_out: the activations' rows [-margin, out_rows - margin), as bf16 (rec_x == nullptr) or e4m3.
+// est: 0 optimal MVUE 2:4, 1 approx-MVUE 2:4; T: the gradient's grid rows rounded up to whole groups (16 tokens, or 32 with rec_g: 8-bit)
+hipError_t launch_grid(const ConvShape &cs, const void *x, int64_t margin, int64_t out_rows, const float *rec_x, void *x_out, int est,
+                       const void *gy, int64_t T, uint64_t seed, uint32_t stream_id, const float *rec_g, void *vals, void *meta, hipStream_t st)
+{
+    const bool q8 = rec_g != nullptr;
+    PackTask a{(const uint16_t *)x, grid_geom(cs, cs.C), cs.x_channels_last, margin, out_rows, rec_x, x_out, (out_rows + TILE_ROWS - 1) / TILE_ROWS, 0};
+    PruneTask b{(const uint16_t *)gy, grid_geom(cs, cs.O), cs.g_channels_last, T / (q8 ? 32 : 16), rec_g, vals, meta, (T + TILE_ROWS - 1) / TILE_ROWS, 0};
+    a.blocks = a.rows * ((cs.C + TILE_COLS - 1) / TILE_COLS);
+    b.blocks = b.rows * ((cs.O + TILE_COLS - 1) / TILE_COLS);
+    if (a.blocks + b.blocks > 0x7fffffffll) return hipErrorInvalidConfiguration;
     // call indices are at most T*O/8 + 1 (approx-MVUE; a quarter block row less otherwise)
     const bool hi0 = (uint64_t)T * (uint64_t)cs.O <= ((uint64_t)1 << 34);
-#define NM_PG(CL, EST, HI0)                                                                                                              \
-    do {                                                                                                                                 \
-        if (rec)                                                                                                                         \
-            hipLaunchKernelGGL((prune_grid_q8_kernel<CL, EST, HI0>), grid, dim3(256), 0, st, (const uint16_t *)gy, gg, T / 32,            \
-                               (uint32_t)seed, (uint32_t)(seed >> 32), stream_id, rec, (uint8_t *)vals, (uint32_t *)meta);               \
-        else                                                                                                                             \
-            hipLaunchKernelGGL((prune_grid_kernel<CL, EST, HI0>), grid, dim3(256), 0, st, (const uint16_t *)gy, gg, T / 16,               \
-                               (uint32_t)seed, (uint32_t)(seed >> 32), stream_id, (uint16_t *)vals, (uint16_t *)meta);                   \
-    } while (0)
-#define NM_PG2(CL, EST) do { if (hi0) NM_PG(CL, EST, true); else NM_PG(CL, EST, false); } while (0)
-    if (cs.g_channels_last) { if (est == 1) NM_PG2(true, 1); else NM_PG2(true, 0); }
-    else { if (est == 1) NM_PG2(false, 1); else NM_PG2(false, 0); }
-#undef NM_PG2
-#undef NM_PG
+    const dim3 grid((unsigned)(a.blocks + b.blocks));
+#define NM_GRID(Q8, EST, HI0) hipLaunchKernelGGL((grid_kernel<Q8, EST, HI0>), grid, dim3(256), 0, st, a, b, (uint32_t)seed, (uint32_t)(seed >> 32), stream_id)
+#define NM_GRID2(Q8, EST) do { if (hi0) NM_GRID(Q8, EST, true); else NM_GRID(Q8, EST, false); } while (0)
+    if (q8) { if (est == 1) NM_GRID2(true, 1); else NM_GRID2(true, 0); }
+    else { if (est == 1) NM_GRID2(false, 1); else NM_GRID2(false, 0); }
+#undef NM_GRID2
+#undef NM_GRID
     return hipGetLastError();
 }
 

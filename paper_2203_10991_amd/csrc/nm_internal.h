@@ -101,12 +101,11 @@ hipError_t launch_rw_mix_probe(const void *src, void *dst, int64_t n_blocks, hip
 // ---- layers (nm_layers.hip): a k x k, stride-1, "same" convolution on bf16 tensors [N, C, H, W] / [N, O, H, W], each stored
 // as channel planes or channels last
 struct ConvShape { int N, C, O, H, W, k; bool x_channels_last, g_channels_last; };
-// rows [-margin, out_rows - margin) of the zero-padded channels-last grid of the activations, as bf16 (rec == nullptr) or
-// e4m3(x * rec[0])
-hipError_t launch_grid_pack(const ConvShape &cs, const void *x, int64_t margin, int64_t out_rows, const float *rec, void *out, hipStream_t st);
-// 2:4 prune (est 0 optimal, 1 approx-MVUE) of the gradient on that grid, T rows; rec: 8-bit output in 32-token groups
-hipError_t launch_prune_grid(const ConvShape &cs, int est, const void *gy, int64_t T, uint64_t seed, uint32_t stream_id, const float *rec,
-                             void *vals, void *meta, hipStream_t st);
+// one launch: rows [-margin, out_rows - margin) of the zero-padded channels-last grid of the activations, as bf16 (rec_x == nullptr) or
+// e4m3(x * rec_x[0]), and the 2:4 prune (est 0 optimal, 1 approx-MVUE) of the gradient on that grid, T rows; rec_g: 8-bit
+// output in 32-token groups
+hipError_t launch_grid(const ConvShape &cs, const void *x, int64_t margin, int64_t out_rows, const float *rec_x, void *x_out, int est,
+                       const void *gy, int64_t T, uint64_t seed, uint32_t stream_id, const float *rec_g, void *vals, void *meta, hipStream_t st);
 
 // The update GEMMs without their second pass: binary32 partial sums part[slabs][O][I], at most parts_bytes of them (one
 // slab where the plan has no split); the caller sums them with launch_finish.

@@ -218,8 +218,9 @@ int nm_conv_update(const void *gy, int gy_channels_last, const void *x, int x_ch
         e = nm::launch_q8_scale_pair(gy, 1, gn, gn, 57344.0f / 4.0f, rec_g, x, 1, xn, xn, 448.0f, rec_x, st);
         alpha = nm::AlphaArg(1.0f, rec_g, rec_x);
     }
-    if (e == hipSuccess) e = nm::launch_grid_pack(cs, x, p.margin, p.T + 2 * p.margin, q8 ? rec_x : nullptr, w + p.x_full, st);
-    if (e == hipSuccess) e = nm::launch_prune_grid(cs, mode, gy, p.T, seed, stream_id, q8 ? rec_g : nullptr, w + p.vals, w + p.meta, st);
+    if (e == hipSuccess)
+        e = nm::launch_grid(cs, x, p.margin, p.T + 2 * p.margin, q8 ? rec_x : nullptr, w + p.x_full, mode, gy, p.T, seed, stream_id,
+                            q8 ? rec_g : nullptr, w + p.vals, w + p.meta, st);
     const char *x0 = w + p.x_full + p.margin * C * (q8 ? 1 : 2);
     if (e == hipSuccess && p.taps) {
         slabs = p.gemm.slabs;
