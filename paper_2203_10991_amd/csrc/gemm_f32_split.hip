@@ -11,6 +11,11 @@
 // segment k holding the planes of term k (the compressed operand's planes share its index words, which are copied once
 // per segment), smallest terms first, all accumulated in binary32 in the same accumulation registers.  Six times the
 // 16-bit sparse work costs less than half of one dense fp32 GEMM.
+// Where the plan cuts the reduction into an even number of slabs, nine planes are enough instead of twelve: with the stacks
+//     a0 a1 a0 a1 a2   and   b2 b1 b0 b0
+// the windows (a0 a1 a2, b2 b1 b0) and (a0 a1 a0, b1 b0 b0) hold the six products, and half of the slabs take either window.
+// The product of the leading terms still comes last: with four planes each (a0 a0 a1 a2 against b2 b1 b0 b0) small terms were
+// added to large sums, and the results were six times as far apart.  9328 x 2960 x 1976: the call 472 -> 441 us, distance from the first form's results 9e-8 of their norm (four and four planes: 6e-7).
 //
 // Non-finite inputs: the first plane carries the infinity or NaN, the other two are zero; the results they touch are
 // non-finite, though an infinity may come out as a NaN (infinity times a zero low-order term).
@@ -45,9 +50,11 @@ __device__ __forceinline__ void split3(float x, uint32_t &p0, uint32_t &p1, uint
 // plane TERM_A[k], segment k of the activations plane TERM_B[k]; smallest products first.
 struct SplitDst { uint16_t *seg[6]; int plane[6]; };
 constexpr int TERM_A[6] = {2, 1, 0, 1, 0, 0}, TERM_B[6] = {0, 1, 2, 0, 1, 0};
+constexpr int WINDOW_A[5] = {0, 1, 0, 1, 2}, WINDOW_B[4] = {2, 1, 0, 0};
 
-// x: rows x cols binary32 (row stride ld, cols % 4 == 0) -> six contiguous rows x cols bf16 segments, segment k
+// x: rows x cols binary32 (row stride ld, cols % 4 == 0) -> SEGS contiguous rows x cols bf16 segments, segment k
 // holding plane dst.plane[k] of x
+template <int SEGS>
 __global__ __launch_bounds__(256) void split3_bf16_kernel(const float *__restrict__ x, int64_t rows, int64_t cols, int64_t ld,
                                                           SplitDst dst)
 {
@@ -66,7 +73,7 @@ __global__ __launch_bounds__(256) void split3_bf16_kernel(const float *__restric
     for (int i = 0; i < 3; ++i) w[i] = make_uint2(p[i][0] | (p[i][1] << 16), p[i][2] | (p[i][3] << 16));
     const int64_t o = r * cols + c;
 #pragma unroll
-    for (int k = 0; k < 6; ++k) {
+    for (int k = 0; k < SEGS; ++k) {
         const int i = dst.plane[k];
         *(uint2 *)(dst.seg[k] + o) = i == 0 ? w[0] : (i == 1 ? w[1] : w[2]);
     }
@@ -111,19 +118,24 @@ hipError_t launch_update_gemm_f32_split(const void *vals, const uint16_t *meta, 
     uint16_t *m = (uint16_t *)((char *)b + round256(6 * (size_t)b_elems * 2));
     void *gemm_ws = (char *)m + round256(6 * (size_t)m_bytes);
     SplitDst da, db;
-    for (int k = 0; k < 6; ++k) {
-        da.seg[k] = a + k * a_elems; da.plane[k] = TERM_A[k];
-        db.seg[k] = b + k * b_elems; db.plane[k] = TERM_B[k];
-    }
+    const bool windows = update_gemm_smfmac_window_slabs(T, O, I, segment_bytes(T, O, I)) != 0;
+    for (int k = 0; k < (windows ? 5 : 6); ++k) { da.seg[k] = a + k * a_elems; da.plane[k] = windows ? WINDOW_A[k] : TERM_A[k]; }
+    for (int k = 0; k < (windows ? 4 : 6); ++k) { db.seg[k] = b + k * b_elems; db.plane[k] = windows ? WINDOW_B[k] : TERM_B[k]; }
     const int64_t na = a_elems / 4, nb = T * (I / 4), nm16 = m_bytes / 16;
     if ((na + 255) / 256 > 0x7fffffffll || (nb + 255) / 256 > 0x7fffffffll) return hipErrorInvalidConfiguration;   // one thread per 4 values
-    hipLaunchKernelGGL(split3_bf16_kernel, dim3((unsigned)((na + 255) / 256)), dim3(256), 0, st, (const float *)vals,
-                       (int64_t)1, a_elems, a_elems, da);
-    hipLaunchKernelGGL(split3_bf16_kernel, dim3((unsigned)((nb + 255) / 256)), dim3(256), 0, st, (const float *)h, T, I, ldh, db);
+#define NM_SPLIT(SEGS_A, SEGS_B)                                                                                                            \
+    do {                                                                                                                               \
+        hipLaunchKernelGGL(split3_bf16_kernel<SEGS_A>, dim3((unsigned)((na + 255) / 256)), dim3(256), 0, st, (const float *)vals,         \
+                           (int64_t)1, a_elems, a_elems, da);                                                                          \
+        hipLaunchKernelGGL(split3_bf16_kernel<SEGS_B>, dim3((unsigned)((nb + 255) / 256)), dim3(256), 0, st, (const float *)h, T, I, ldh, db); \
+    } while (0)
+    if (windows) NM_SPLIT(5, 4); else NM_SPLIT(6, 6);
+#undef NM_SPLIT
     hipLaunchKernelGGL(replicate_kernel, dim3((unsigned)((nm16 + 255) / 256)), dim3(256), 0, st, (const uint4 *)meta, (uint4 *)m,
-                       nm16, 6);
+                       nm16, windows ? 3 : 6);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
+    if (windows) return launch_update_gemm_smfmac_windows(a, m, b, dW, lddw, T, O, I, beta, gemm_ws, st, segment_bytes(T, O, I));
     // one run over the stacked operands: the reduction over 6T tokens sums the six products, in the order of the segments
     return launch_update_gemm_smfmac(a, m, b, I, dW, lddw, 6 * T, O, I, beta, gemm_ws, st, segment_bytes(T, O, I));
 }
