@@ -202,7 +202,7 @@ class _NMLinearReLUFn(torch.autograd.Function):
 
     @staticmethod
     def forward(ctx, x, weight, bias, cfg):
-        y = F.linear(x, weight, bias).relu_()             # in place: the product is this function's own (16384 x 4096: 39 -> 31 us)
+        y = F.linear(x, weight, bias).relu_()             # in place: the product is this function's own (back to back with it, 16384 x 1024 -> 4096: 157 -> 150 us)
         ctx.save_for_backward(x, weight, y)               # relu'(z) = [y > 0]
         ctx.cfg, ctx.has_bias = cfg, bias is not None
         return y

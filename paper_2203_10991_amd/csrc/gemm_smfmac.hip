@@ -115,7 +115,7 @@ __global__ __launch_bounds__(WM * WN * 64) void update_gemm_smfmac_kernel(
     };
 
     int tm, tn, slab;
-    tile_and_slab_of_workgroup(tiles_m, tiles_n, tm, tn, slab);
+    tile_and_slab_of_workgroup(tiles_m, tiles_n, n_groups * 16 * (O + 2 * (SHIFTED ? sh.cb : I)), tm, tn, slab);
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);       // wave-uniform: keeps LDS bases scalar
@@ -390,7 +390,7 @@ __global__ __launch_bounds__(512) void update_gemm_smfmac_tall_kernel(
     __shared__ __attribute__((aligned(1024))) char S[TNS * STAGE];
 
     int tm, tn, slab;
-    tile_and_slab_of_workgroup(tiles_m, tiles_n, tm, tn, slab);
+    tile_and_slab_of_workgroup(tiles_m, tiles_n, n_groups * 16 * (O + 2 * I), tm, tn, slab);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WN, wn = wave % WN;

@@ -102,7 +102,7 @@ __global__ __launch_bounds__(WM * WN * 64) void update_gemm_smfmac_q8_kernel(
     auto buf = [&](auto u_c) -> char * { return S + (decltype(u_c)::value % NS8) * STAGE_BYTES; };
 
     int tm, tn, slab;
-    tile_and_slab_of_workgroup(tiles_m, tiles_n, tm, tn, slab);
+    tile_and_slab_of_workgroup(tiles_m, tiles_n, n_groups * 16 * (O + 2 * (SHIFTED ? sh.cb : I)), tm, tn, slab);
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);

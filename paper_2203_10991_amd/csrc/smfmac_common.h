@@ -216,23 +216,25 @@ __device__ __forceinline__ float alpha_of(const AlphaArg &al)
 struct ShiftArg { int cb, n, margin; int rows[32]; };
 
 // Split-K launches (gridDim.z slabs of the reduction axis, gridDim.x tiles): workgroups are dealt round-robin to the
-// XCDs in launch order (x fastest, then z).  The (slab, tile) pairs are re-dealt: XCD x takes a contiguous run of the
-// slab-major list, so that its workgroups form a block of one slab's tiles (two slabs' at a boundary) and share that
-// slab's operand strips through its L2.  Keeping a tile on one XCD for every slab instead makes each XCD pull every
-// slab's rows.  Inside a slab the tiles go row by row where a run then holds four rows or more, else along bands of 8 rows:
-// either way a run is a compact block.  Measured against tiles kept on an XCD, operands in no cache, reduction pass included:
-// 16384 x 4096 x 1024 (64 tiles, 4 slabs) 100 -> 97 us, 12608 x 3072 x 768 (72 tiles, 3 slabs) 58.5 -> 55 (bands: 57.5),
-// 12608 x 768 x 3072 65 -> 62.5 (row by row: 64.6).
-__device__ __forceinline__ void tile_and_slab_of_workgroup(int tiles_m, int tiles_n, int &tm, int &tn, int &slab)
+// XCDs in launch order (x fastest, then z).  With a tile count that is a multiple of 8 a tile then stays on one XCD for every
+// slab, and each XCD pulls its tiles' strips of every slab.  With operands (`bytes`) beyond what the L2s hold (8 x 4 MB), and with
+// other tile counts, whose tiles would land on all XCDs, the (slab, tile) pairs are re-dealt: XCD x takes a contiguous run of
+// the slab-major list, a block of one slab's tiles (two slabs' at a boundary) that share that slab's strips through its L2.
+// Inside a slab the tiles go row by row where a run holds four rows or more (and with small operands), else along bands of 8
+// rows: either way a run is a compact block.  Tiles kept on an XCD -> re-dealt, operands in no cache, reduction pass
+// included: 21680 x 544 x 4192 148 -> 115 us, 49152 x 1024 x 1024 102 -> 85, 16384 x 4096 x 1024 100 -> 97, 12608 x 3072 x 768 60.3 -> 58.3;
+// the other way with 9 MB of operands, 4096 x 1024 x 512 18.0 against 21.1, 27 MB even (8192 x 2048 x 512 29.1 against 29.4).
+__device__ __forceinline__ void tile_and_slab_of_workgroup(int tiles_m, int tiles_n, int64_t bytes, int &tm, int &tn, int &slab)
 {
-    if (gridDim.z > 1) {
+    const bool large = bytes >= (int64_t)32 << 20;
+    if (gridDim.z > 1 && (large || gridDim.x % 8 != 0)) {
         const unsigned n = gridDim.x * gridDim.z;
         const unsigned L = blockIdx.z * gridDim.x + blockIdx.x, xcd = L % 8, idx = L / 8;
         const unsigned first = xcd * (n / 8) + min(xcd, n % 8);        // workgroups that XCDs 0 .. xcd-1 hold
         const unsigned g = first + idx;
         slab = (int)(g / gridDim.x);
         const int t = (int)(g % gridDim.x);
-        if ((unsigned)tiles_n * 4 <= n / 8) { tm = t / tiles_n; tn = t % tiles_n; }
+        if (!large || (unsigned)tiles_n * 4 <= n / 8) { tm = t / tiles_n; tn = t % tiles_n; }
         else {
             const int band = t / (8 * tiles_n), band_rows = min(8, tiles_m - 8 * band), in_band = t - band * 8 * tiles_n;
             tm = 8 * band + in_band % band_rows;
