@@ -247,3 +247,9 @@ def test_long_reductions_on_384_row_tiles_in_slabs(nm, oracle, T, O, I, beta):
                                         (256, 2040, 4096, 0.0)])       # 128 x 256 tiles
 def test_binary32_kernels_on_both_sides_of_the_line(nm, oracle, T, O, I, beta):
     run_case(nm, oracle, synth.Workload(f"f32_{T}x{O}x{I}", T, O, I, "f32", "2:4", 0.0, 2.0, 0.3), seed=T, beta=beta)
+
+
+# even slab counts (the operands are windows over nine stacked planes): 128- and 256-row tiles, 384-row tiles; beta; a token count that no trip divides
+@pytest.mark.parametrize("T,O,I,beta", [(4096, 640, 1024, 0.0), (528, 200, 152, 1.0), (8816, 264, 2440, 0.0)])
+def test_binary32_as_three_terms_in_slabs(nm, oracle, T, O, I, beta):
+    split_case(nm, oracle, T, O, I, seed=5, beta=beta, sample=None if beta else 4000)
