@@ -377,7 +377,8 @@ __global__ __launch_bounds__(WM * WN * 64) void update_gemm_smfmac_kernel(
 // LDS image of a stage: h tile [32][256] bf16 (swizzled as above) | vals [2 groups][384 slots] x 16 B
 // (slot 192*wm + 32*a + m) | meta [2 groups][384 rows] x 2 B; five stages rotate.
 // ------------------------------------------------------------------------------------
-template <bool WINDOWS>
+// SLABS: launched with gridDim.z slabs; without, one slab and the same code with fewer scalar registers alive (one spill less)
+template <bool SLABS, bool WINDOWS>
 __global__ __launch_bounds__(512) void update_gemm_smfmac_tall_kernel(
     const uint16_t *__restrict__ vals, const uint16_t *__restrict__ meta, const uint16_t *__restrict__ h, int64_t ldh,
     float *__restrict__ out, int64_t ldo, int64_t slab_stride, int64_t n_groups, int64_t groups_per_slab,
@@ -389,8 +390,9 @@ __global__ __launch_bounds__(512) void update_gemm_smfmac_tall_kernel(
     static_assert(TNS * STAGE <= 160 * 1024, "LDS");
     __shared__ __attribute__((aligned(1024))) char S[TNS * STAGE];
 
-    int tm, tn, slab;
-    tile_and_slab_of_workgroup(tiles_m, tiles_n, n_groups * 16 * (O + 2 * I), tm, tn, slab);
+    int tm, tn, slab = 0;
+    if constexpr (SLABS) tile_and_slab_of_workgroup(tiles_m, tiles_n, n_groups * 16 * (O + 2 * I), tm, tn, slab);
+    else tile_of_workgroup((int)blockIdx.x, tiles_m, tiles_n, tm, tn);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WN, wn = wave % WN;
@@ -808,9 +810,12 @@ static hipError_t run_plan(const Plan &p, const OutTarget &tg, const void *vals,
 {
     if (p.tall_rows > 0) {
         dim3 tall_grid((unsigned)(p.tall_tiles_m * p.tiles_n), 1, (unsigned)p.slabs);
-        hipLaunchKernelGGL(update_gemm_smfmac_tall_kernel<WINDOWS>, tall_grid, dim3(512), 0, st, (const uint16_t *)vals, meta, (const uint16_t *)h,
-                           ldh, tg.out, tg.ldo, tg.slab_stride, T / 16, p.groups_per_slab, O, I, p.tall_tiles_m, p.tiles_n, tg.accumulate,
-                           (int64_t)0, p.tall_rows);
+#define NM_TALL(SLABS)                                                                                                              \
+    hipLaunchKernelGGL((update_gemm_smfmac_tall_kernel<SLABS, WINDOWS>), tall_grid, dim3(512), 0, st, (const uint16_t *)vals, meta,   \
+                       (const uint16_t *)h, ldh, tg.out, tg.ldo, tg.slab_stride, T / 16, p.groups_per_slab, O, I, p.tall_tiles_m,      \
+                       p.tiles_n, tg.accumulate, (int64_t)0, p.tall_rows)
+        if (WINDOWS || p.slabs > 1) NM_TALL(true); else NM_TALL(WINDOWS);
+#undef NM_TALL
         hipError_t e0 = hipGetLastError();
         if (e0 != hipSuccess) return e0;
     }
