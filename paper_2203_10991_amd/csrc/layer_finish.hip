@@ -12,8 +12,9 @@ namespace nm {
 // Convolution: dW[o][c][tap] (bf16) = alpha * sum_z part[z][o][tap][c].  A workgroup takes one output channel and CW input
 // channels: R threads share a float4 of the partial sums (as in splitk_reduce_kernel: thread r sums slabs r, r+R, ... in
 // order, a fixed tree combines them), the results turn through LDS, and the CW x taps values leave contiguous.
-// Bound: launch latency and one read of the partial sums.  With many slabs a workgroup is 32 channels wide (128-byte reads) and
-// has a thread for every sum of nine taps at once.
+// Bound: launch latency and one read of the partial sums.  With many slabs a workgroup is 32 channels wide (128-byte reads), with 64 or
+// more -- few tiles, so few output channels to deal out -- 16, and has a thread for every sum of nine taps at once: 254 slabs of
+// 64 x 64 x 9 10.8 us at 32 channels and 8 threads a sum, 8.4 at 16 and 16.
 template <int R, int CW, int NT>
 __global__ __launch_bounds__(NT) void finish_conv_kernel(const float *__restrict__ part, int slabs, int64_t slab_stride, uint16_t *__restrict__ dW,
                                                          int C, int taps, AlphaArg al)
@@ -57,7 +58,8 @@ hipError_t launch_finish_conv(const float *part, int slabs, void *dW, int64_t O,
 #define NM_FINISH(R, CW, NT)                                                                                                                      \
     hipLaunchKernelGGL((finish_conv_kernel<R, CW, NT>), dim3((unsigned)O, (unsigned)((C + CW - 1) / CW)), dim3(NT), 0, st, part, slabs,            \
                        O * (int64_t)taps * C, (uint16_t *)dW, C, taps, alpha)
-    if (slabs >= 12) NM_FINISH(8, 32, 576);
+    if (slabs >= 64) NM_FINISH(16, 16, 576);
+    else if (slabs >= 12) NM_FINISH(8, 32, 576);
     else NM_FINISH(1, 64, 256);
 #undef NM_FINISH
     return hipGetLastError();
