@@ -132,6 +132,7 @@ hipError_t launch_conv_gemm(const ConvShape &cs, bool q8, const ConvGemmPlan &p,
 hipError_t launch_finish_conv(const float *part, int slabs, void *dW, int64_t O, int C, int taps, AlphaArg alpha, hipStream_t st);
 
 // ... of a linear layer (bf16 tensors, T tokens, not necessarily whole token groups)
+constexpr int64_t LAYER_LD_MOST = (int64_t)1 << 21;       // largest row stride, in elements: the prune's offsets inside a wave are 32 bits wide
 hipError_t launch_prune_layer(int m, int est, const void *g, int64_t ldg, const void *act, int64_t lda, int64_t T, int64_t O, uint64_t seed,
                               uint32_t stream_id, void *gout, int64_t ldgo, void *vals, uint16_t *meta, float *csum, hipStream_t st);
 hipError_t launch_prune_q8_layer(int est, const void *g, int64_t ldg, int64_t T, int64_t O, uint64_t seed, uint32_t stream_id,

@@ -131,7 +131,7 @@ int nm_linear_update(const void *g, int64_t ldg, const void *act, int64_t lda, c
     if (act && q8) return fail(NM_ERR_UNSUPPORTED, "%s: the 8-bit form takes the gradient itself, not a ReLU's output beside it", fn);
     if (const char *why = bad_linear_shape(T, O, I, q8)) return fail(NM_ERR_SHAPE, "%s: %s", fn, why);
     if (!g || !h || !dW || (act && !g_out)) return fail(NM_ERR_NULL, "%s: g, h, dW (and g_out with act) must not be NULL", fn);
-    const int64_t lim = (int64_t)1 << 21;
+    const int64_t lim = nm::LAYER_LD_MOST;
     if (ldg < O || ldh < I || ldg > lim || ldh > lim || (act && (lda < O || ldgo < O || lda > lim || ldgo > lim)))
         return fail(NM_ERR_SHAPE, "%s: a row stride is smaller than its row or beyond 2^21", fn);
     if (!aligned16(g) || !aligned16(h) || !aligned16(dW) || !aligned16(db) || !aligned16(workspace) || ldg % 8 || ldh % 8 ||

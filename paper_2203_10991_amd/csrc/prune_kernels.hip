@@ -37,11 +37,20 @@ struct ProdArg { const void *d; int64_t ldd; void *gout; int64_t ldgo; };
 // as zeros through the bounds of buffer descriptors (and are not written to gout), so nothing is copied to pad them.  csum (may
 // be null): the sum of every column over the thread's 16 rows, csum[G][o], the first half of the bias gradient -- a pass over g
 // of its own otherwise.
+// Offsets are 32 bits wide, from the first token group of the thread's WAVE: its 64 threads of four columns reach over 32 groups at
+// O = 8 and over fewer at any larger O, which at strides up to LAYER_LD_MOST is less than 2^32 bytes.  (From the WORKGROUP's first
+// group they would wrap at O = 8 beyond a stride of 2^20, with 32-token groups beyond 2^19.)
 struct LayerArg { int64_t T; float *csum; };
+static_assert(32 * 32 * LAYER_LD_MOST * 2 <= (int64_t)1 << 32, "32-bit offsets inside a wave: 32 groups of 32 tokens, bf16");
+// first token group of the wave's threads
+__device__ __forceinline__ int64_t wave_first_group(int64_t ncg)
+{
+    return ((int64_t)blockIdx.x * 256 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x & ~63u))) / ncg;
+}
 
 // The four column sums of a thread.  No branch on csum: with one, the compiler moves every kept value's arithmetic behind it, and
 // all rows stay in registers until there (218 instead of 81); without csum the descriptor is empty and the store is dropped.
-// G0: the workgroup's first token group.
+// G0: the wave's first token group.
 __device__ __forceinline__ void put_csum(const LayerArg &la, int64_t G0, int64_t G, int64_t O, int64_t col0, const float *cs)
 {
     const auto r = __builtin_amdgcn_make_buffer_rsrc((char *)(la.csum + G0 * O), 0, la.csum ? 0x7fffffff : 0, 0x00020000);
@@ -119,9 +128,9 @@ __device__ __forceinline__ void prune_compress_body(
             }
         }
     };
-    // LAYER: everything through descriptors based at the workgroup's first token group, with the bytes up to the last token as bound
-    // (rows and columns stay below 2^21 elements and T rows: a workgroup's offsets fit 32 bits; the caller checks)
-    [[maybe_unused]] const int64_t t0 = ((int64_t)blockIdx.x * 256 / ncg) * 16;
+    // LAYER: everything through descriptors based at the wave's first token group, with the bytes up to the last token as bound
+    // (offsets of 32 bits: see LayerArg)
+    [[maybe_unused]] const int64_t t0 = LAYER ? wave_first_group(ncg) * 16 : 0;
     auto rows_rsrc = [&](const void *p, int64_t ld) {
         const int64_t bytes = (la.T - t0) * ld * ESZ;
         return __builtin_amdgcn_make_buffer_rsrc((char *)p + t0 * ld * ESZ, 0, (int)(uint32_t)(bytes > 0xffffffffll ? 0xffffffffll : bytes), 0x00020000);
@@ -410,7 +419,7 @@ __global__ __launch_bounds__(256) void prune_compress_q8_kernel(
     // as its quads are decided, through an address the compiler cannot see through (keeps the loads where they are)
     uint4 rows[16];
     [[maybe_unused]] float cs[VEC];
-    [[maybe_unused]] const int64_t t0 = ((int64_t)blockIdx.x * 256 / ncg) * 32;           // (LAYER: as in prune_compress_body)
+    [[maybe_unused]] const int64_t t0 = LAYER ? wave_first_group(ncg) * 32 : 0;           // (as in prune_compress_body)
     auto fetch_rows = [&](int first) {                                                    // tensor rows first .. first + 7 of the group
         if constexpr (LAYER) {
             const int64_t bytes = (la.T - t0) * ldg * ESZ;

@@ -121,3 +121,40 @@ def test_views_off_a_16_byte_boundary_are_copied():
     want = api.nm_linear_update(g, h, seed=2, act=act, bias=True)
     got = api.nm_linear_update(shifted(g), shifted(h), seed=2, act=shifted(act), bias=True)
     assert all(torch.equal(a, b) for a, b in zip(got, want))
+
+
+@pytest.mark.parametrize("form,O,T,ld", [("2:4", 8, 2100, 1 << 21),        # 256 threads of four columns span 2048 tokens: 8 GiB at this stride
+                                         ("relu", 8, 2100, 1 << 21),
+                                         ("q8", 8, 4200, 1 << 20),         # ... 4096 tokens
+                                         ("q8", 16, 2100, 1 << 21),        # ... 2048
+                                         ("q8", 24, 1500, 1 << 21)])       # ... up to 1408, waves that start inside a row of groups
+def test_row_strides_that_put_a_workgroups_rows_beyond_4_gib(form, O, T, ld):
+    """g, h, act and g_out as columns of matrices with very long rows: the same bits as from contiguous operands"""
+    from paper_2203_10991_amd import api
+    torch.manual_seed(O)
+    I, q8 = 16, form == "q8"
+    wide = torch.empty(T * ld, dtype=torch.bfloat16, device=DEV).view(T, ld)
+
+    def column(t, at):
+        v = wide[:, at:at + t.shape[1]]
+        v.copy_(t)
+        return v
+    g = (torch.randn(T, O, device=DEV) * torch.exp(2 * torch.randn(T, O, device=DEV))).to(torch.bfloat16)
+    h = torch.randn(T, I, device=DEV).to(torch.bfloat16)
+    act = torch.relu(torch.randn(T, O, device=DEV)).to(torch.bfloat16) if form == "relu" else None
+    kw = dict(q8=q8, seed=3, stream_id=1, bias=True)
+    want = api.nm_linear_update(g, h, act=act, **kw)
+    gv, hv, av = column(g, 0), column(h, 64), None if act is None else column(act, 128)
+    got = api.nm_linear_update(gv, hv, act=av, **kw)
+    assert all(a is None and b is None or torch.equal(a, b) for a, b in zip(got, want))
+    if act is None:
+        return
+    out = torch.empty(T * ld, dtype=torch.bfloat16, device=DEV).view(T, ld)
+    for row in (0, 1023, 1024, 2047, T - 1):
+        out[row, O:O + 8] = 7.0                                            # (what lies beside the rows stays as it is)
+    lib, dW, db = api.load(), torch.empty_like(want[0]), torch.empty_like(want[1])
+    ws = torch.empty(lib.nm_linear_update_workspace(T, O, I, 0, 1), dtype=torch.uint8, device=DEV)
+    assert lib.nm_linear_update(gv.data_ptr(), ld, av.data_ptr(), ld, hv.data_ptr(), ld, T, O, I, 4, 0, 0, 3, 1, out.data_ptr(), ld, dW.data_ptr(),
+                                db.data_ptr(), ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream) == 0
+    assert torch.equal(dW, want[0]) and torch.equal(db, want[1]) and torch.equal(out[:, :O], want[2])
+    assert bool((out[[0, 1023, 1024, 2047, T - 1], O:O + 8] == 7.0).all())
