@@ -150,6 +150,12 @@ def _update_gemm_q8(g2: torch.Tensor, h2: torch.Tensor, cfg: NMConfig) -> torch.
     return api.nm_update_gemm_q8(v8, m32, h8, alpha=(sg, sh))
 
 
+def _bias_in_call(bias: bool) -> bool:
+    """Whether the library call makes the bias gradient: not under create_graph=True (gradients are then recorded), where it stays a
+    sum that can be differentiated with respect to the incoming gradient."""
+    return bias and not torch.is_grad_enabled()
+
+
 def _one_call(g2: torch.Tensor, h2: torch.Tensor, weight: torch.Tensor, cfg: NMConfig, bias: bool) -> bool:
     """Whether the layer's update is one library call (api.nm_linear_update): bf16 tensors at sizes it takes."""
     return (cfg.precision in ("native", "q8") and cfg.nm in ("1:2", "2:4") and g2.is_cuda and h2.is_cuda
@@ -171,14 +177,14 @@ class _NMLinearFn(torch.autograd.Function):
         dW = db = None
         g2, h2, cfg = gy.reshape(-1, gy.shape[-1]), x.reshape(-1, x.shape[-1]), ctx.cfg
         bias = ctx.has_bias and ctx.needs_input_grad[2]
-        if ctx.needs_input_grad[1] and _one_call(g2, h2, weight, cfg, bias):
+        bias_in_call = _bias_in_call(bias)
+        if ctx.needs_input_grad[1] and _one_call(g2, h2, weight, cfg, bias_in_call):
             dW, db, _ = api.nm_linear_update(g2, h2, nm=cfg.nm, mode=cfg.mode, q8=cfg.precision == "q8", seed=cfg.current_seed(),
-                                             stream_id=cfg.stream_id, bias=bias)
-        else:
-            if ctx.needs_input_grad[1]:
-                dW = _update_gemm(g2, h2, cfg).to(weight.dtype)
-            if bias:
-                db = g2.sum(0)
+                                             stream_id=cfg.stream_id, bias=bias_in_call)
+        elif ctx.needs_input_grad[1]:
+            dW = _update_gemm(g2, h2, cfg).to(weight.dtype)
+        if bias and db is None:
+            db = g2.sum(0)
         if ctx.cfg.auto_advance:
             ctx.cfg.advance()
         return dx, dW, db, None
@@ -232,9 +238,10 @@ class _NMLinearReLUFn(torch.autograd.Function):
             g2 = g2[:T]
         else:                                             # 8-bit and three-term modes: separate product, then the usual path
             g2 = u2 * (y2 > 0).to(gy.dtype)
-            if ctx.needs_input_grad[1] and _one_call(g2, h2, weight, cfg, bias):
+            bias_in_call = _bias_in_call(bias)
+            if ctx.needs_input_grad[1] and _one_call(g2, h2, weight, cfg, bias_in_call):
                 dW, db, _ = api.nm_linear_update(g2, h2, nm=cfg.nm, mode=cfg.mode, q8=cfg.precision == "q8", seed=cfg.current_seed(),
-                                                 stream_id=cfg.stream_id, bias=bias)
+                                                 stream_id=cfg.stream_id, bias=bias_in_call)
             elif ctx.needs_input_grad[1]:
                 dW = _update_gemm(g2, h2, cfg).to(weight.dtype)
         dx = (g2 @ weight).reshape(x.shape) if ctx.needs_input_grad[0] else None

@@ -158,3 +158,25 @@ def test_row_strides_that_put_a_workgroups_rows_beyond_4_gib(form, O, T, ld):
                                 db.data_ptr(), ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream) == 0
     assert torch.equal(dW, want[0]) and torch.equal(db, want[1]) and torch.equal(out[:, :O], want[2])
     assert bool((out[[0, 1023, 1024, 2047, T - 1], O:O + 8] == 7.0).all())
+
+
+@pytest.mark.parametrize("cls,precision", [("NMLinear", "native"), ("NMLinear", "q8"), ("NMLinearReLU", "q8")])
+def test_the_bias_gradient_stays_differentiable_under_create_graph(cls, precision):
+    """db = column sums of the incoming gradient (times the ReLU's derivative): its derivative with respect to that gradient"""
+    from paper_2203_10991_amd import autograd
+    torch.manual_seed(8)
+    layer = getattr(autograd, cls)(64, 32, cfg=autograd.NMConfig(precision=precision), device=DEV, dtype=torch.bfloat16)
+    x = torch.randn(40, 64, device=DEV).to(torch.bfloat16)
+    gy = torch.randn(40, 32, device=DEV).to(torch.bfloat16).requires_grad_()
+    v = torch.randn(32, device=DEV).to(torch.bfloat16)
+    y = layer(x)
+    dW, db = torch.autograd.grad(y, (layer.weight, layer.bias), gy, create_graph=True)
+    (ggy,) = torch.autograd.grad((db * v).sum(), gy)
+    want = v.expand(40, 32)
+    assert torch.equal(ggy, torch.where(y > 0, want, 0) if cls == "NMLinearReLU" else want)
+    plain = torch.autograd.grad(layer(x), (layer.weight, layer.bias), gy.detach())
+    assert torch.equal(dW, plain[0])
+    g = gy.detach().double() * ((y > 0) if cls == "NMLinearReLU" else 1.0)
+    # both sums are in binary32 and rounded once to bf16
+    for b in (db, plain[1]):
+        assert bool(((b.double() - g.sum(0)).abs() <= 2.0 ** -8 * g.sum(0).abs() + 1e-5 * g.abs().sum(0)).all())
