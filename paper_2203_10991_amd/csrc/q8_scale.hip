@@ -48,10 +48,12 @@ __device__ __forceinline__ void write_scale(float *rec, uint32_t mb, float top)
 // 1024 workgroups: 12608 x 3072 22 / 22 / 36 / 50 us, 32768 x 28672 350 / 311 / 322 / 343 us; and with 16 instead of 128 KB per
 // workgroup 4096 x 1024 takes 12-17 us instead of 10).
 // A contiguous tensor is one row of R * C elements: the 64-bit division of a piece's number by the row length, once per
-// 16 bytes, cost more instructions than everything else in the loop.
+// 16 bytes, cost more instructions than everything else in the loop.  Strided rows of at most 1024 pieces go several to a trip, each on
+// the smallest power of two of threads that holds it, four trips' loads in flight (with a row per trip 802816 x 64 bf16 at a
+// stride of 128 took 1077 us on eight threads of every workgroup; now 23; 50176 x 256 at 512 51 -> 11, 32768 x 8192 at 8200 110 -> 96).
 // Measured, launches included, before -> after: 12608 x 768 bf16 192 -> 11 us, 32768 x 28672 398 -> 312 us (6.0 TB/s).
 constexpr int AMAX_THREADS = 1024, AMAX_BLOCKS = 256, AMAX_UNROLL = 4;
-constexpr int AMAX_PIECES = 8 * AMAX_THREADS;         // 16-byte pieces a workgroup takes at least: 128 KB
+constexpr int AMAX_PIECES = 8 * AMAX_THREADS;         // 16-byte pieces a workgroup takes at least: 128 KB (of a strided row that is longer than a trip: one row)
 
 template <int DT> __device__ __forceinline__ uint32_t amax_piece(uint32_t m, const u32x4_t &v)
 {
@@ -63,8 +65,9 @@ template <int DT> __device__ __forceinline__ uint32_t amax_piece(uint32_t m, con
     return m;
 }
 
-// one tensor of a launch: R rows of C elements at a stride of ld, handled by `blocks` workgroups
-struct AmaxArg { const void *t; int64_t R, C, ld; float top; float *rec; int blocks; };
+// one tensor of a launch: R rows of C elements at a stride of ld, handled by `blocks` workgroups.  row_shift >= 0: rows of at most
+// 1024 pieces, 2^row_shift threads to a row; -1: workgroups share rows or take them one by one
+struct AmaxArg { const void *t; int64_t R, C, ld; float top; float *rec; int blocks, row_shift; };
 
 // (a launch takes one tensor, or the two of a layer: workgroups [0, a.blocks) the first, the others the second)
 template <int DT>
@@ -77,11 +80,28 @@ __global__ __launch_bounds__(AMAX_THREADS) void q8_amax_kernel(AmaxArg a, AmaxAr
     const float top = second ? b.top : a.top;
     float *rec = second ? b.rec : a.rec;
     constexpr int VEC = DT == NM_DT_F32 ? 4 : 8, ESZ = DT == NM_DT_F32 ? 4 : 2;
+    const int row_shift = second ? b.row_shift : a.row_shift;
     const int64_t cpr = C / VEC;
     uint32_t m = 0;
     // `split` workgroups share a row when there are fewer rows than workgroups
     const int64_t split = R >= n_blocks ? 1 : n_blocks / R;
     const int64_t part = bid % split;
+    if (row_shift >= 0) {
+        const int64_t step = n_blocks * (AMAX_THREADS >> row_shift), piece = threadIdx.x & ((1 << row_shift) - 1);
+        if (piece < cpr) {
+            int64_t r = bid * (AMAX_THREADS >> row_shift) + (threadIdx.x >> row_shift);
+            const char *at = (const char *)t_ + (r * ld + piece * VEC) * ESZ;
+            const int64_t step_bytes = step * ld * ESZ;
+            for (; r + (AMAX_UNROLL - 1) * step < R; r += AMAX_UNROLL * step, at += AMAX_UNROLL * step_bytes) {
+                u32x4_t v[AMAX_UNROLL];
+#pragma unroll
+                for (int k = 0; k < AMAX_UNROLL; ++k) v[k] = *(const u32x4_t *)(at + k * step_bytes);
+#pragma unroll
+                for (int k = 0; k < AMAX_UNROLL; ++k) m = amax_piece<DT>(m, v[k]);
+            }
+            for (; r < R; r += step, at += step_bytes) m = amax_piece<DT>(m, *(const u32x4_t *)at);
+        }
+    } else
     for (int64_t r = bid / split; r < R; r += n_blocks / split) {
         const u32x4_t *row = (const u32x4_t *)((const char *)t_ + r * ld * ESZ);
         int64_t i = part * AMAX_THREADS + threadIdx.x;
@@ -126,10 +146,16 @@ __global__ void q8_scale_empty_kernel(float *rec)
 static AmaxArg amax_arg(int dt, const void *t, int64_t R, int64_t C, int64_t ld, float top, float *rec, int most_blocks)
 {
     if (ld == C) { C *= R; ld = C; R = 1; }
-    const int vec = dt == NM_DT_F32 ? 4 : 8;
-    const int64_t per_row = (C / vec + AMAX_PIECES - 1) / AMAX_PIECES;        // workgroups that a row's pieces fill
+    const int64_t cpr = C / (dt == NM_DT_F32 ? 4 : 8);
+    if (R > 1 && cpr <= AMAX_THREADS) {
+        int shift = 0;
+        while (((int64_t)1 << shift) < cpr) ++shift;
+        const int64_t rows = AMAX_PIECES >> shift;                             // rows of a workgroup's least share
+        return AmaxArg{t, R, C, ld, top, rec, (int)std::min<int64_t>(most_blocks, (R + rows - 1) / rows), shift};
+    }
+    const int64_t per_row = (cpr + AMAX_PIECES - 1) / AMAX_PIECES;            // workgroups that a row's pieces fill
     const int64_t blocks = R >= most_blocks ? most_blocks : R * std::min<int64_t>(per_row, most_blocks / R);
-    return AmaxArg{t, R, C, ld, top, rec, (int)blocks};
+    return AmaxArg{t, R, C, ld, top, rec, (int)blocks, -1};
 }
 
 hipError_t launch_q8_scale(int dt, const void *t, int64_t R, int64_t C, int64_t ld, float top, float *rec, hipStream_t st)
