@@ -1,5 +1,5 @@
-// Sanitizer driver for the host side of the C ABI (test infrastructure): csrc/nm_abi.hip is compiled for the host
-// only under -fsanitize=address,undefined and linked with the stub launchers below instead of the kernels, so the
+// Sanitizer driver for the host side of the C ABI (test infrastructure): csrc/nm_abi.hip and csrc/nm_layers.hip are compiled for
+// the host only under -fsanitize=address,undefined and linked with the stub launchers below instead of the kernels, so the
 // argument validation -- everything that runs before a launch -- executes on a machine without a GPU.  The driver
 // walks the error paths (null, ragged, misaligned, overlapping, absurdly large arguments: the range arithmetic must
 // not overflow) and the accepting paths (on which the stubs read what the real launchers read on the host).
@@ -49,6 +49,42 @@ size_t update_gemm_workspace(int, int64_t T, int64_t O, int64_t I) { return O * 
 size_t update_gemm_q8_workspace(int64_t T, int64_t O, int64_t I) { return update_gemm_workspace(1, T, O, I); }
 size_t update_gemm_smfmac_shifted_workspace(int64_t T, int64_t O, int64_t I) { return update_gemm_workspace(1, T, O, I); }
 size_t update_gemm_q8_shifted_workspace(int64_t T, int64_t O, int64_t I) { return update_gemm_workspace(1, T, O, I); }
+// the layer entry points (nm_layers.hip); the nine-tap plan as the real one's for images it takes
+struct ConvShape { int N, C, O, H, W, k; bool x_channels_last, g_channels_last; };
+struct ConvGemmPlan { int64_t T, x_rows; int slabs; };
+hipError_t launch_q8_scale_pair(const void *, int64_t, int64_t, int64_t, float, float *, const void *, int64_t, int64_t, int64_t, float, float *,
+                                hipStream_t) { ++g_launches; return hipSuccess; }
+hipError_t launch_cast_e4m3_rows(int, const void *, int64_t, int64_t, int64_t, const float *, uint8_t *, int64_t, int64_t, hipStream_t) { ++g_launches; return hipSuccess; }
+hipError_t launch_pad_rows(const void *, int64_t, int64_t, int64_t, void *, int64_t, hipStream_t) { ++g_launches; return hipSuccess; }
+hipError_t launch_prune_layer(int, int, const void *, int64_t, const void *, int64_t, int64_t, int64_t, uint64_t, uint32_t, void *, int64_t, void *, uint16_t *,
+                              float *, hipStream_t) { ++g_launches; return hipSuccess; }
+hipError_t launch_prune_q8_layer(int, const void *, int64_t, int64_t, int64_t, uint64_t, uint32_t, const float *, uint8_t *, uint32_t *, float *,
+                                 hipStream_t) { ++g_launches; return hipSuccess; }
+size_t update_gemm_smfmac_parts_bytes(int64_t h_rows, int64_t T, int64_t O, int64_t I, bool *whole) { *whole = h_rows != T && O >= 1024; return (size_t)(2 * O * I * 4); }
+hipError_t launch_update_gemm_smfmac_parts(const void *, const uint16_t *, const void *, int64_t, int64_t, int64_t, int64_t, int64_t, bool, float *, int *slabs,
+                                           hipStream_t) { *slabs = 2; ++g_launches; return hipSuccess; }
+size_t update_gemm_q8_parts_bytes(int64_t, int64_t O, int64_t I) { return (size_t)(2 * O * I * 4); }
+hipError_t launch_update_gemm_q8_parts(const uint8_t *, const uint32_t *, const uint8_t *, int64_t, int64_t, int64_t, int64_t, float *, int *slabs,
+                                       hipStream_t) { *slabs = 2; ++g_launches; return hipSuccess; }
+hipError_t launch_finish_linear(const float *, int, int64_t, int64_t, void *, AlphaArg, const float *, int64_t, void *, hipStream_t) { ++g_launches; return hipSuccess; }
+hipError_t launch_grid(const ConvShape &, const void *, int64_t, int64_t, const float *, void *, int, const void *, int64_t, uint64_t, uint32_t, const float *, void *,
+                       void *, hipStream_t) { ++g_launches; return hipSuccess; }
+bool conv_gemm_plan(const ConvShape &cs, bool, ConvGemmPlan &p)
+{
+    if (cs.k != 3 || cs.C % 32 || cs.O < 48 || cs.W > 90) return false;
+    p.T = ((int64_t)cs.N * (cs.H + 2) * (cs.W + 2) + 127) / 128 * 128; p.x_rows = p.T + 512; p.slabs = 2;
+    return true;
+}
+hipError_t launch_conv_gemm(const ConvShape &, bool, const ConvGemmPlan &, const void *, const void *, const void *, float *, hipStream_t) { ++g_launches; return hipSuccess; }
+size_t update_gemm_smfmac_shifted_parts_bytes(int64_t, int64_t O, int64_t I) { return (size_t)(2 * O * I * 4); }
+size_t update_gemm_q8_shifted_parts_bytes(int64_t, int64_t O, int64_t I) { return (size_t)(2 * O * I * 4); }
+hipError_t launch_update_gemm_smfmac_shifted_parts(const void *, const uint16_t *, const void *, int64_t, int64_t, const int64_t *rows, int n, int64_t, int64_t, float *,
+                                                   int *slabs, hipStream_t)
+{ *slabs = 2; ++g_launches; return read_rows(rows, n) == INT64_MIN ? hipErrorUnknown : hipSuccess; }
+hipError_t launch_update_gemm_q8_shifted_parts(const uint8_t *, const uint32_t *, const uint8_t *, int64_t, int64_t, const int64_t *rows, int n, int64_t, int64_t, float *,
+                                               int *slabs, hipStream_t)
+{ *slabs = 2; ++g_launches; return read_rows(rows, n) == INT64_MIN ? hipErrorUnknown : hipSuccess; }
+hipError_t launch_finish_conv(const float *, int, void *, int64_t, int, int, AlphaArg, hipStream_t) { ++g_launches; return hipSuccess; }
 size_t static_scratch_bytes() { return (size_t)32 << 20; }
 static char fake_scratch[64];
 hipError_t static_scratch(void **p) { *p = fake_scratch; return hipSuccess; }
@@ -208,6 +244,80 @@ int main()
     EXPECT(nm_update_gemm_shifted(vals, m16, x0, cb, cb, shifts, 9, dW, 9 * cb, huge, O, NM_BF16, 0.f, ws, wsb, nullptr), NM_ERR_SHAPE);
     EXPECT(nm_update_gemm_q8_shifted((const uint8_t *)vals, m32, (const uint8_t *)x0, cb, cb, shifts, 9, dW, huge, T, O, 1.f, 0.f, ws, wsb, nullptr),
            NM_ERR_SHAPE);
+    // ---- layers.  Addresses only: nothing is dereferenced on the host
+    {
+        char *base = (char *)((uintptr_t)1 << 32);
+        void *a = base, *b = base + ((int64_t)1 << 40), *out = base + ((int64_t)2 << 40), *bias = base + ((int64_t)3 << 40), *gout = base + ((int64_t)4 << 40),
+             *lws = base + ((int64_t)5 << 40);
+        const int64_t ld_most = (int64_t)1 << 21, lim = (int64_t)1 << 21;
+        auto linear = [&](int64_t T_, int64_t O_, int64_t I_, int m, int mode, int q8, void *act, int64_t ldg, int64_t ldh, void *db, void *w_) {
+            return nm_linear_update(a, ldg, act, ldg, b, ldh, T_, O_, I_, m, mode, q8, 1, 2, act ? gout : nullptr, O_, out, db, w_,
+                                    nm_linear_update_workspace(T_, O_, I_, q8, db != nullptr), nullptr);
+        };
+        void *act = base + ((int64_t)6 << 40);
+        for (int64_t T_ : {(int64_t)1, (int64_t)77, (int64_t)1024})
+            for (int q8 = 0; q8 < 2; ++q8) {
+                EXPECT(linear(T_, 64, 128, 4, 0, q8, nullptr, 64, 128, bias, lws), NM_OK);
+                EXPECT(linear(T_, 2048, 128, 4, 1, q8, nullptr, 2048, 128, nullptr, lws), NM_OK);
+                EXPECT(linear(T_, 64, 128, 2, 0, q8, nullptr, 72, 136, bias, lws), NM_OK);
+                EXPECT(linear(T_, 8, 16, 4, 0, q8, nullptr, ld_most, ld_most, bias, lws), NM_OK);
+                EXPECT(linear(T_, 8, 16, 4, 0, q8, nullptr, ld_most + 8, 16, bias, lws), NM_ERR_SHAPE);
+                EXPECT(linear(T_, 8, 16, 4, 0, q8, nullptr, 8, ld_most + 8, bias, lws), NM_ERR_SHAPE);
+            }
+        EXPECT(linear(100, 64, 128, 4, 0, 0, act, 64, 128, bias, lws), NM_OK);
+        EXPECT(linear(100, 64, 128, 4, 0, 1, act, 64, 128, bias, lws), NM_ERR_UNSUPPORTED);
+        EXPECT(linear(100, 64, 128, 3, 0, 0, nullptr, 64, 128, bias, lws), NM_ERR_UNSUPPORTED);
+        EXPECT(linear(100, 64, 128, 2, 1, 0, nullptr, 64, 128, bias, lws), NM_ERR_UNSUPPORTED);
+        EXPECT(linear(100, 64, 128, 4, 0, 0, nullptr, 64, 128, bias, nullptr), NM_ERR_WORKSPACE);
+        EXPECT(linear(100, 64, 128, 4, 0, 0, nullptr, 64, 128, out, lws), NM_ERR_ALIAS);
+        EXPECT(linear(100, 64, 128, 4, 0, 0, nullptr, 64, 128, (char *)bias + 2, lws), NM_ERR_ALIGN);
+        for (int64_t bad : {(int64_t)0, (int64_t)-16, huge, INT64_MAX, INT64_MIN}) {
+            EXPECT(linear(bad, 64, 128, 4, 0, 0, nullptr, 64, 128, bias, lws), NM_ERR_SHAPE);
+            EXPECT(linear(100, bad, 128, 4, 0, 0, nullptr, bad, 128, bias, lws), NM_ERR_SHAPE);
+            EXPECT(linear(100, 64, bad, 4, 0, 1, nullptr, 64, bad, bias, lws), NM_ERR_SHAPE);
+            EXPECT(linear(100, 64, 128, 4, 0, 0, nullptr, bad == huge ? bad : -8, 128, bias, lws), NM_ERR_SHAPE);
+            if (nm_linear_update_workspace(bad, 64, 128, 0, 1) || nm_linear_update_workspace(64, bad, 128, 0, 1) || nm_linear_update_workspace(64, 64, bad, 1, 1)) ++failures;
+        }
+        EXPECT(linear((((int64_t)1 << 34) / lim) + 1, lim, 16, 4, 0, 0, nullptr, lim, 16, bias, lws), NM_ERR_SHAPE);
+        if (!nm_linear_update_workspace(((int64_t)1 << 34) / lim, lim, 16, 0, 1) || !nm_linear_update_workspace((int64_t)1 << 31, 8, 32, 1, 1)) ++failures;
+
+        auto conv = [&](int64_t N, int64_t C, int64_t O_, int64_t H, int64_t W, int k, int q8, int mode, const void *x_, void *dW_, void *w_) {
+            return nm_conv_update(a, 0, x_, 1, N, C, O_, H, W, k, q8, mode, 1, 2, dW_, w_, nm_conv_update_workspace(N, C, O_, H, W, k, q8), nullptr);
+        };
+        for (int q8 = 0; q8 < 2; ++q8)
+            for (int mode = 0; mode < 2; ++mode)
+                for (int k : {1, 3, 5}) {
+                    EXPECT(conv(2, 64, 64, 14, 14, k, q8, mode, b, out, lws), NM_OK);
+                    EXPECT(conv(1, 16, 8, 1, 300, k, q8, mode, b, out, lws), NM_OK);
+                }
+        // kernel sizes whose square does not fit an int among them
+        for (int k : {0, -1, -3, 2, 4, 7, 9, 46339, 46341, 65535, 65537, INT32_MAX, INT32_MIN, INT32_MIN + 1}) {
+            EXPECT(conv(2, 64, 64, 14, 14, k, 0, 0, b, out, lws), NM_ERR_SHAPE);
+            if (nm_conv_update_workspace(2, 64, 64, 14, 14, k, 1)) ++failures;
+        }
+        for (int64_t bad : {(int64_t)0, (int64_t)-8, ((int64_t)1 << 20) + 16, huge, INT64_MAX, INT64_MIN}) {
+            EXPECT(conv(bad, 64, 64, 14, 14, 3, 0, 0, b, out, lws), NM_ERR_SHAPE);
+            EXPECT(conv(2, bad, 64, 14, 14, 3, 0, 0, b, out, lws), NM_ERR_SHAPE);
+            EXPECT(conv(2, 64, bad, 14, 14, 3, 0, 0, b, out, lws), NM_ERR_SHAPE);
+            EXPECT(conv(2, 64, 64, bad, 14, 3, 0, 0, b, out, lws), NM_ERR_SHAPE);
+            EXPECT(conv(2, 64, 64, 14, bad, 3, 0, 0, b, out, lws), NM_ERR_SHAPE);
+        }
+        EXPECT(conv(1 << 20, 8, 8, 1 << 20, 1 << 10, 5, 0, 0, b, out, lws), NM_ERR_SHAPE);
+        EXPECT(conv(2, 1 << 20, 8, 14, 1 << 20, 5, 0, 0, b, out, lws), NM_ERR_SHAPE);
+        EXPECT(conv(2, 24, 64, 14, 14, 3, 1, 0, b, out, lws), NM_ERR_SHAPE);
+        EXPECT(conv(2, 64, 60, 14, 14, 3, 0, 0, b, out, lws), NM_ERR_SHAPE);
+        EXPECT(conv(2, 64, 64, 14, 14, 3, 0, 2, b, out, lws), NM_ERR_UNSUPPORTED);
+        EXPECT(conv(2, 64, 64, 14, 14, 3, 0, 0, nullptr, out, lws), NM_ERR_NULL);
+        EXPECT(conv(2, 64, 64, 14, 14, 3, 0, 0, b, nullptr, lws), NM_ERR_NULL);
+        EXPECT(conv(2, 64, 64, 14, 14, 3, 0, 0, (char *)b + 8, out, lws), NM_ERR_ALIGN);
+        EXPECT(conv(2, 64, 64, 14, 14, 3, 0, 0, b, (char *)out + 2, lws), NM_ERR_ALIGN);
+        EXPECT(conv(2, 64, 64, 14, 14, 3, 0, 0, b, out, nullptr), NM_ERR_WORKSPACE);
+        EXPECT(conv(2, 64, 64, 14, 14, 3, 0, 0, b, (char *)b + 64, lws), NM_ERR_ALIAS);
+        EXPECT(conv(2, 64, 64, 14, 14, 3, 0, 0, b, out, (char *)a - 256), NM_ERR_ALIAS);
+        EXPECT(conv(2, 64, 64, 14, 14, 3, 0, 0, b, out, (char *)out + 256), NM_ERR_ALIAS);
+        EXPECT(nm_conv_update(a, 0, b, 0, 2, 64, 64, 14, 14, 3, 0, 0, 1, 2, out, lws, nm_conv_update_workspace(2, 64, 64, 14, 14, 3, 0) - 1, nullptr),
+               NM_ERR_WORKSPACE);
+    }
     if (failures) { fprintf(stderr, "abi sanitizer driver: %d failures\n", failures); return 1; }
     printf("abi sanitizer driver ok (%d stub launches)\n", g_launches);
     return 0;

@@ -2,7 +2,7 @@
 
   * the C oracle, compiled together with tests/san_oracle_driver.c, on exactly-sized buffers with ragged shapes, padded
     strides and edge values -- an access past an end, a signed overflow or a misaligned access aborts the run;
-  * the host side of the C ABI: csrc/nm_abi.hip compiled for the host only and linked with stub launchers
+  * the host side of the C ABI: csrc/nm_abi.hip and csrc/nm_layers.hip compiled for the host only and linked with stub launchers
     (tests/san_abi_driver.cpp), walking every validation path, including absurdly large sizes whose byte ranges must
     not overflow.
 """
@@ -37,14 +37,15 @@ def test_abi_validation_under_asan_and_ubsan(tmp_path):
     if not os.path.exists(hipcc) or shutil.which("g++") is None:
         pytest.skip("needs hipcc (host-only compile of the ABI layer) and g++")
     rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
-    obj, exe = str(tmp_path / "nm_abi_san.o"), str(tmp_path / "san_abi")
+    objs, exe = [str(tmp_path / f"{n}_san.o") for n in ("nm_abi", "nm_layers")], str(tmp_path / "san_abi")
     # sanitizer flags go to the host compilation only
     host_san = []
     for f in ("-fsanitize=address", "-fsanitize=undefined", "-fno-sanitize-recover=all"):
         host_san += ["-Xarch_host", f]
-    _run([hipcc, "--offload-arch=gfx950", "--offload-host-only", "-O1", "-g", "-std=c++17", "-fPIC", *host_san, "-c",
-          os.path.join(ROOT, "paper_2203_10991_amd", "csrc", "nm_abi.hip"), "-o", obj], cwd=str(tmp_path))
+    for name, obj in zip(("nm_abi", "nm_layers"), objs):
+        _run([hipcc, "--offload-arch=gfx950", "--offload-host-only", "-O1", "-g", "-std=c++17", "-fPIC", *host_san, "-c",
+              os.path.join(ROOT, "paper_2203_10991_amd", "csrc", f"{name}.hip"), "-o", obj], cwd=str(tmp_path))
     _run(["g++", "-std=c++17", *SAN, "-D__HIP_PLATFORM_AMD__", f"-I{rocm}/include", f"-I{ROOT}/include",
-          os.path.join(ROOT, "tests", "san_abi_driver.cpp"), obj, "-o", exe, f"-L{rocm}/lib", "-lamdhip64", f"-Wl,-rpath,{rocm}/lib"])
+          os.path.join(ROOT, "tests", "san_abi_driver.cpp"), *objs, "-o", exe, f"-L{rocm}/lib", "-lamdhip64", f"-Wl,-rpath,{rocm}/lib"])
     r = _run([exe], env=ENV, timeout=300)
     assert "abi sanitizer driver ok" in r.stdout
