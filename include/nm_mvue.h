@@ -374,8 +374,10 @@ int nm_update_gemm_q8_shifted_ds(const uint8_t *vals8, const uint32_t *meta32, c
  *   dW [O, C, k, k]                   bf16, contiguous
  * Masks and kept values are those of mvue_prune_2of4 (q8 != 0: mvue_prune_2of4_q8_ds with nm_q8_scale's record) on the
  * gradient's zero-padded channels-last grid, rows rounded up to a multiple of 16 (32); same mode, seed, stream_id.
- * q8: scales, the e4m3 cast and the 8-bit product are part of the call.  k odd, k*k <= 32; O % 8 == 0, C % 8 == 0
- * (q8: C % 16 == 0).  workspace: nm_conv_update_workspace(...) bytes (0 for sizes the call does not take).
+ * q8: scales, the e4m3 cast and the 8-bit product are part of the call.  k = 1, 3 or 5; O % 8 == 0, C % 8 == 0
+ * (q8: C % 16 == 0).  Every size 1 .. 2^20, N*(H+k)*(W+k) at most 2^31 - 65536 and that times max(C, O) at most 2^58,
+ * ((W+k)*k + 1024)*C at most 2^30.  gy, x, dW and the workspace on 16-byte boundaries.
+ * workspace: nm_conv_update_workspace(...) bytes (0 for sizes the call does not take).
  */
 int nm_conv_update(const void *gy, int gy_channels_last, const void *x, int x_channels_last, int64_t N, int64_t C, int64_t O,
                    int64_t H, int64_t W, int k, int q8, int mode, uint64_t seed, uint32_t stream_id, void *dW,
@@ -384,14 +386,17 @@ size_t nm_conv_update_workspace(int64_t N, int64_t C, int64_t O, int64_t H, int6
 
 /*
  * Weight and bias gradient of a linear layer in one call (bf16 tensors): prune, update GEMM, conversion.
- *   g [T x O], h [T x I]   bf16, row strides ldg, ldh; T is any positive number (rows up to a whole token group count as zeros)
+ *   g [T x O], h [T x I]   bf16, row strides ldg, ldh; T need not be whole token groups (rows up to one count as zeros)
  *   act [T x O], lda       NULL, or the output of the ReLU behind the layer (bf16; not with q8): the gradient is then
  *                          g * [act > 0] and is also written to g_out (row stride ldgo)
  *   m, mode                2 = MVUE 1:2; 4 = MVUE 2:4, mode as in mvue_prune_2of4
  *   q8                     != 0: scales, e4m3 cast, e5m2 kept values and the 8-bit product (I % 16 == 0)
  *   dW [O x I], db [O]     bf16, contiguous; db = column sums of the gradient (NULL = skip)
  * Masks and kept values are those of mvue_prune_* on the gradient padded with zero rows to a multiple of 16 (q8: 32);
- * O % 8 == 0, I % 8 == 0.  workspace: nm_linear_update_workspace(...) bytes (0 for sizes the call does not take).
+ * O % 8 == 0, I % 8 == 0.  O and I at most 2^21, T*O at most 2^34, T*I at most 2^36; row strides at most 2^21 elements (a stride
+ * is not among the arguments of the workspace query: a size it answers may still be refused for its strides).  Every base on a
+ * 16-byte boundary, every stride a multiple of 8.
+ * workspace: nm_linear_update_workspace(...) bytes (0 for sizes the call does not take).
  */
 int nm_linear_update(const void *g, int64_t ldg, const void *act, int64_t lda, const void *h, int64_t ldh, int64_t T, int64_t O,
                      int64_t I, int m, int mode, int q8, uint64_t seed, uint32_t stream_id, void *g_out, int64_t ldgo,

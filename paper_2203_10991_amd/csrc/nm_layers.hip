@@ -70,7 +70,7 @@ const char *bad_conv_shape(int64_t N, int64_t C, int64_t O, int64_t H, int64_t W
 {
     const int64_t lim = (int64_t)1 << 20;
     if (N < 1 || C < 1 || O < 1 || H < 1 || W < 1 || N > lim || C > lim || O > lim || H > lim || W > lim) return "every size must be in 1..2^20";
-    if (k != 1 && k != 3 && k != 5) return "the kernel must be odd, with at most 32 taps";
+    if (k != 1 && k != 3 && k != 5) return "the kernel must be 1, 3 or 5 wide";
     if (O % 8 || C % (q8 ? 16 : 8)) return "O must be a multiple of 8 and C of 8 (16 with 8-bit operands)";
     const int64_t Hp = H + k, Wp = W + k, cmax = C > O ? C : O, rows_lim = ((int64_t)1 << 31) - 65536;
     if (N > rows_lim / Hp / Wp || (Wp * k + 1024) * C > (1ll << 30)) return "the padded grid exceeds what 32-bit row numbers and byte offsets reach";
