@@ -192,7 +192,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // operand -- one 16-byte load, expanded in registers for two MFMAs each -- and h comes as whole 128-byte lines, one per
 // half-wave and step; the waves that share columns find them in the CU's cache.  No LDS and no barrier in the loop: four waves
 // per SIMD and the loads of the next token group in flight cover the latency.  Every load is a descriptor that the scalar unit
-// advances, a constant lane offset and a constant scalar offset: vector instructions delay the matrix pipeline.
+// advances, a constant lane offset and a constant scalar offset: vector instructions delay the matrix pipeline.  (The offsets are 32
+// bits wide: 15 rows of h and a token group's O values; the entry point refuses O and ldh beyond 2^21, which leaves a factor of 16.)
 // Every 128 tokens the blocks' sums are added to a second set of registers: rounding errors grow with the length of a chain.
 // ------------------------------------------------------------------------------------
 constexpr int F32S_T = 64, F32S_KG = 8, F32S_FOLD = 8;
@@ -330,10 +331,8 @@ static PlanF32 make_plan_f32(int64_t T, int64_t O, int64_t I)
     };
     consider(false, big < 256 ? 512 / big : 1);
     consider(false, 256 / big);
-    if (O <= (int64_t)1 << 24) {                                      // (its lane offsets are 32 bits wide)
-        consider(true, 256 / fine);
-        consider(true, 1);
-    }
+    consider(true, 256 / fine);
+    consider(true, 1);
     p.tiles_m = (int)((O + (p.small ? F32S_T : F32_TM) - 1) / (p.small ? F32S_T : F32_TM));
     p.tiles_n = (int)((I + (p.small ? F32S_T : F32_TN) - 1) / (p.small ? F32S_T : F32_TN));
     p.groups_per_slab = groups > 0 ? (groups + slabs - 1) / slabs : 1;
@@ -358,12 +357,7 @@ hipError_t launch_update_gemm_f32(const void *vals, const uint16_t *meta, const 
                                   hipStream_t st)
 {
     if (O == 0 || I == 0) return hipSuccess;
-    PlanF32 p = make_plan_f32(T, O, I);
-    if (p.small && ldh > (int64_t)1 << 24) {                          // rows further apart than 32-bit offsets reach: the other kernel, same slabs
-        p.small = false;
-        p.tiles_m = (int)((O + F32_TM - 1) / F32_TM);
-        p.tiles_n = (int)((I + F32_TN - 1) / F32_TN);
-    }
+    const PlanF32 p = make_plan_f32(T, O, I);
     const int accumulate = beta != 0.f;
     float *out = dW;
     int64_t ldo = lddw, slab_stride = 0;
