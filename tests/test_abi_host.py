@@ -242,3 +242,32 @@ def test_workspace_queries_over_random_shapes(lib):
         # the three-term mode holds six bf16 planes besides the 16-bit kernel's own workspace
         need3 = lib.nm_update_gemm_workspace(T, O, I, 2)
         assert need3 >= 3 * (T // 2 * O * 2) + 3 * (T * I * 2) + lib.nm_update_gemm_workspace(T, O, I, 1)
+
+
+def test_layer_calls_argument_errors(lib):
+    """nm_conv_update and the strides of nm_linear_update (its other errors: tests/test_gpu_linear_update.py)"""
+    far = lambda i: P + (i << 40)                               # noqa: E731
+    ok = dict(gy=far(0), gcl=0, x=far(1), xcl=1, N=2, C=64, O=64, H=14, W=14, k=3, q8=0, mode=0, seed=0, stream=0, dW=far(2), ws=far(3), wb=1 << 40, st=None)
+
+    def conv(**kw):
+        return lib.nm_conv_update(*{**ok, **kw}.values())
+    assert conv(mode=2) == NM_ERR_UNSUPPORTED and b"mode" in lib.nm_last_error()
+    for kw in (dict(N=0), dict(H=-1), dict(W=1 << 21), dict(O=60), dict(C=12), dict(C=24, q8=1), dict(k=2), dict(k=7), dict(k=46341), dict(k=-3),
+               dict(N=1 << 20, H=1 << 10, W=1 << 10), dict(C=1 << 20, W=1 << 12)):
+        assert conv(**kw) == NM_ERR_SHAPE, kw
+        a = {**ok, **kw}
+        assert lib.nm_conv_update_workspace(a["N"], a["C"], a["O"], a["H"], a["W"], a["k"], a["q8"]) == 0, kw
+    assert conv(gy=None) == NM_ERR_NULL and conv(x=None) == NM_ERR_NULL and conv(dW=None) == NM_ERR_NULL
+    assert conv(gy=far(0) + 2) == NM_ERR_ALIGN and conv(x=far(1) + 8) == NM_ERR_ALIGN and conv(dW=far(2) + 4) == NM_ERR_ALIGN and conv(ws=far(3) + 8) == NM_ERR_ALIGN
+    need = lib.nm_conv_update_workspace(2, 64, 64, 14, 14, 3, 0)
+    assert need > 0 and conv(wb=need - 1) == NM_ERR_WORKSPACE and conv(ws=None) == NM_ERR_WORKSPACE
+    assert conv(dW=far(1) + 64) == NM_ERR_ALIAS and conv(ws=far(0) + 64) == NM_ERR_ALIAS and conv(ws=far(2) - 256) == NM_ERR_ALIAS
+    lin = dict(g=far(0), ldg=8, act=None, lda=0, h=far(1), ldh=16, T=64, O=8, I=16, m=4, mode=0, q8=0, seed=0, stream=0, gout=None, ldgo=0, dW=far(2),
+               db=None, ws=far(3), wb=1 << 30, st=None)
+
+    def linear(**kw):
+        return lib.nm_linear_update(*{**lin, **kw}.values())
+    most = 1 << 21
+    relu = dict(act=far(4), lda=8, gout=far(5), ldgo=8)
+    for kw in (dict(ldg=most + 8), dict(ldh=most + 8), dict(relu, lda=most + 8), dict(relu, ldgo=most + 8), dict(ldg=0), dict(ldh=8), dict(relu, ldgo=0)):
+        assert linear(**kw) == NM_ERR_SHAPE and b"stride" in lib.nm_last_error(), kw

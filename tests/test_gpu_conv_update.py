@@ -109,3 +109,35 @@ def test_a_binary32_weight_gets_unrounded_sums():
     b = _conv_update_shifted(gy, x, 3, NMConfig(seed=4), torch.bfloat16)
     assert a.dtype == torch.float32 and b.dtype == torch.bfloat16
     assert torch.equal(a.to(torch.bfloat16), b) and not torch.equal(a.to(torch.bfloat16).float(), a)
+
+
+@pytest.mark.parametrize("N,C,O,H,W,k", [(1, 16, 8, 5, 3, 3), (2, 16, 72, 7, 7, 3), (1, 80, 64, 14, 14, 3), (3, 64, 136, 9, 11, 5), (4, 32, 24, 8, 8, 1),
+                                         (3, 96, 48, 9, 13, 3), (24, 64, 64, 28, 28, 3)])
+@pytest.mark.parametrize("q8", [False, True])
+@pytest.mark.parametrize("channels_last", [False, True])
+def test_conv_update_with_the_approximate_estimator_matches_the_oracle(oracle, N, C, O, H, W, k, q8, channels_last):
+    """approx-MVUE: two selection words per block, in the 8-bit form dealt to the two lanes of a pair in another way than the
+    optimal estimator's"""
+    from paper_2203_10991_amd import api
+    torch.manual_seed(N + C + O)
+    fmt = torch.channels_last if channels_last else torch.contiguous_format
+    gy = (torch.randn(N, O, H, W, device=DEV) * torch.exp(2 * torch.randn(N, O, H, W, device=DEV))).to(torch.bfloat16).contiguous(memory_format=fmt)
+    x = torch.relu(torch.randn(N, C, H, W, device=DEV)).to(torch.bfloat16).contiguous(memory_format=fmt)
+    got = api.nm_conv_update(gy, x, k, q8=q8, mode=1, seed=17, stream_id=3).double().cpu().numpy()
+    pad, wp, gt = k // 2, W + 2 * (k // 2), 32 if q8 else 16
+    gg, xg = _grid(gy, pad), _grid(x, pad)
+    rows, margin = gg.shape[0], pad * wp + pad
+    T = (rows + gt - 1) // gt * gt
+    g2, xf = np.pad(gg, ((0, T - rows), (0, 0))), np.pad(xg, ((margin, margin + T - rows), (0, 0)))
+    shifts = [(ky - pad) * wp + (kx - pad) for ky in range(k) for kx in range(k)]
+    if q8:
+        sg, sh = oracle.pow2_scale(g2, 57344.0 / 4.0), oracle.pow2_scale(xf, 448.0)
+        v, m = oracle.prune_2of4_q8(g2, 17, 3, 1, sg)
+        want, wabs = oracle.update_gemm_q8_shifted(v, m, oracle.cast_e4m3(xf, sh), margin, shifts, alpha=1.0 / (sg * sh))
+    else:
+        v, m, _ = oracle.prune_2of4_approx(g2, 17, 3)
+        want, wabs = oracle.update_gemm_shifted(v, m, xf, margin, shifts)
+    want, wabs = (a.reshape(O, k, k, C).transpose(0, 3, 1, 2) for a in (want, wabs))
+    # the sums' tolerances as above, half a unit in the last place of the bf16 result, a wrong mask in one group
+    assert (np.abs(got - want) <= (1e-3 if q8 else 1e-5) * wabs + 2.0 ** -8 * np.abs(want) + 1e-30).all()
+    assert np.linalg.norm(got - want) <= 3e-3 * np.linalg.norm(want)

@@ -180,3 +180,34 @@ def test_the_bias_gradient_stays_differentiable_under_create_graph(cls, precisio
     # both sums are in binary32 and rounded once to bf16
     for b in (db, plain[1]):
         assert bool(((b.double() - g.sum(0)).abs() <= 2.0 ** -8 * g.sum(0).abs() + 1e-5 * g.abs().sum(0)).all())
+
+
+@pytest.mark.parametrize("q8,nmode,mode,relu", [(True, "2:4", 1, False), (True, "1:2", 0, False), (False, "2:4", 1, True), (False, "1:2", 0, True)])
+@pytest.mark.parametrize("T,O,I", SHAPES[:7])
+def test_linear_update_of_the_other_estimators_matches_the_oracle(oracle, q8, nmode, mode, relu, T, O, I):
+    """8-bit approx-MVUE and MVUE 1:2, and both behind a ReLU's derivative: masks through dW, and the bias gradient"""
+    from paper_2203_10991_amd import api
+    torch.manual_seed(T + 1)
+    g = (torch.randn(T, O, device=DEV) * torch.exp(2 * torch.randn(T, O, device=DEV))).to(torch.bfloat16)
+    g[torch.rand(T, O, device=DEV) < 0.2] = 0
+    h = torch.randn(T, I, device=DEV).to(torch.bfloat16)
+    act = torch.relu(torch.randn(T, O, device=DEV)).to(torch.bfloat16) if relu else None
+    dW, db, g_out = api.nm_linear_update(_behind_nan(g, O + 8), _behind_nan(h, I + 24), nm=nmode, mode=mode, q8=q8, seed=19, stream_id=5, bias=True,
+                                         act=None if act is None else _behind_nan(act, O + 16))
+    if relu:
+        g = g * (act > 0).to(torch.bfloat16)
+        assert torch.equal(g_out.view(torch.int16), g.view(torch.int16))
+    gp, hp = _bits(_padded(g, 32 if q8 else 16)), _bits(_padded(h, 32 if q8 else 16))
+    if q8:
+        sg, sh = oracle.pow2_scale(gp, 57344.0 / (4.0 if nmode == "2:4" else 2.0)), oracle.pow2_scale(hp, 448.0)
+        v, m = oracle.prune_1of2_q8(gp, 19, 5, sg) if nmode == "1:2" else oracle.prune_2of4_q8(gp, 19, 5, mode, sg)
+        want, wabs = oracle.update_gemm_q8(v, m, oracle.cast_e4m3(hp, sh), alpha=1.0 / (sg * sh))
+    else:
+        v, m, _ = (oracle.prune_1of2 if nmode == "1:2" else oracle.prune_2of4_approx)(gp, 19, 5)
+        want, wabs = oracle.update_gemm(v, m, hp)
+    got = dW.double().cpu().numpy()
+    # tolerances as in the first test of this file
+    assert (np.abs(got - want) <= (1e-3 if q8 else 1e-5) * wabs + 2.0 ** -8 * np.abs(want) + 1e-30).all()
+    assert np.linalg.norm(got - want) <= 3e-3 * np.linalg.norm(want)
+    gd = g.double()
+    assert bool(((db.double() - gd.sum(0)).abs() <= 1e-5 * gd.abs().sum(0) + 2.0 ** -8 * gd.sum(0).abs()).all())
