@@ -10,10 +10,9 @@
 // Masks and values are those of the ordinary prune on the materialised grid (same block index, same random words).
 //
 // Bound: HBM (one read of each tensor, one write of each result); alone, the pack is bound by it and the prune by its vector
-// arithmetic, so the two tasks alternate workgroup by
-// workgroup (256 x 64 x 56 x 56: 90 us in two launches, 87 in one and the layer 141 -> 132; 8-bit 14 x 14 stage 36.4 -> 33.2).  Streaming
-// loads or stores make the layer 4-11 % slower: the memory-side cache serves the next kernel.  Before, the layer
-// made the grid with tensor operations: a fill and a strided permuting copy per padding, a fill and a copy per margin --
+// arithmetic, so the two tasks alternate workgroup by workgroup (256 x 64 x 56 x 56: 90 us in two launches, 87 in one, the layer
+// 142 -> 140 with both sides timed in turn; 8-bit 14 x 14 stage 36.4 -> 33.2, the layer 87.2 -> 84.3).  Streaming loads or stores
+// make the layer 4-11 % slower: the memory-side cache serves the next kernel.  Before, the layer made the grid with tensor operations: a fill and a strided permuting copy per padding, a fill and a copy per margin --
 // 375 us for the two tensors of a 256 x 64 x 56 x 56 layer, whose bytes take 60 us, then the prune read the grid again.
 #include <hip/hip_runtime.h>
 #include <stdint.h>

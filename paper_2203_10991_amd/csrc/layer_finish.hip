@@ -13,8 +13,11 @@ namespace nm {
 // channels: R threads share a float4 of the partial sums (as in splitk_reduce_kernel: thread r sums slabs r, r+R, ... in
 // order, a fixed tree combines them), the results turn through LDS, and the CW x taps values leave contiguous.
 // Bound: launch latency and one read of the partial sums.  With many slabs a workgroup is 32 channels wide (128-byte reads), with 64 or
-// more -- few tiles, so few output channels to deal out -- 16, and has a thread for every sum of nine taps at once: 254 slabs of
-// 64 x 64 x 9 10.8 us at 32 channels and 8 threads a sum, 8.4 at 16 and 16.
+// more -- few tiles, so few output channels to deal out -- 16, and has a thread for every sum of nine taps at once.
+// The three forms over sizes that a plan makes (nine taps, partial sums in the caches, us; 64 channels and a thread a sum / 32 and 8 / 16
+// and 16): 64 x 64 channels, 254 slabs 23.7 / 10.8 / 7.5, 128 slabs 7.1 / 6.2 / 4.4, 64 slabs 4.3 / 4.2 / 3.4, 32 slabs 3.2 / 3.3 / 3.0;
+// 128 x 128, 64 slabs 8.0 / 6.6 / 7.1, 16 slabs 2.7 / 3.6 / 4.4; 256 x 256, 16 slabs 6.3 / 8.9 / 13.5, 12 slabs 3.6 / 7.9 / 13.0.
+// So both lines are right for narrow layers only: with 128 channels or more the wider forms are up to 4 us faster there.
 template <int R, int CW, int NT>
 __global__ __launch_bounds__(NT) void finish_conv_kernel(const float *__restrict__ part, int slabs, int64_t slab_stride, uint16_t *__restrict__ dW,
                                                          int C, int taps, AlphaArg al)

@@ -1,7 +1,7 @@
 // Fused MVUE prune + compress kernels for gfx950 (wave64).
 //
 // One thread owns one 16-token group of VEC columns (VEC = one 16-byte load: 8 bf16 or
-// 4 fp32 columns).  Blocks (pairs / quads) run along the token axis, i.e. down the rows of
+// 4 fp32 columns; 4 bf16 columns in the half-width, layer and 8-bit forms).  Blocks (pairs / quads) run along the token axis, i.e. down the rows of
 // the thread's own column, so no cross-lane exchange is needed: 16 coalesced 16-byte row
 // loads in, 128 contiguous bytes of kept values + VEC 16-bit index words out.
 //
