@@ -120,10 +120,14 @@ def _dtype_code(t: torch.Tensor) -> int:
     raise TypeError(f"nm_mvue tensors are float32 or bfloat16, got {t.dtype}")
 
 
+# (a Stream object made for every call costs 1.7 us; the function is not public: a torch without it takes the public way)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(t: torch.Tensor) -> int:
-    if t.is_cuda:
-        return torch._C._cuda_getCurrentRawStream(t.get_device())      # (a Stream object made for every call costs 1.7 us)
-    return torch.cuda.current_stream(t.device).cuda_stream             # raises: not a GPU tensor
+    if t.is_cuda and _raw_stream is not None:
+        return _raw_stream(t.get_device())
+    return torch.cuda.current_stream(t.device).cuda_stream             # raises where t is not a GPU tensor
 
 
 def _rowmajor(t: torch.Tensor, what: str) -> int:

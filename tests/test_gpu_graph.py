@@ -156,3 +156,15 @@ def test_independent_layers_replay_from_a_branched_graph():
         torch.cuda.synchronize()
         for j, x in zip(jobs, want):
             assert torch.equal(j["dW"], x), f"replay {i}"
+
+
+def test_stream_handle_with_and_without_the_raw_handle_function(monkeypatch):
+    """a torch without the private function: the same handle the public way"""
+    from paper_2203_10991_amd import api
+    t = torch.zeros(16, device=DEV)
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        assert api._stream(t) == side.cuda_stream
+        monkeypatch.setattr(api, "_raw_stream", None)
+        assert api._stream(t) == side.cuda_stream
+    assert api._stream(t) == torch.cuda.current_stream().cuda_stream
