@@ -168,3 +168,38 @@ def test_stream_handle_with_and_without_the_raw_handle_function(monkeypatch):
         monkeypatch.setattr(api, "_raw_stream", None)
         assert api._stream(t) == side.cuda_stream
     assert api._stream(t) == torch.cuda.current_stream().cuda_stream
+
+
+@pytest.mark.parametrize("form", ["linear", "linear q8", "linear relu", "conv", "conv q8"])
+def test_layer_calls_replay_from_a_graph(form):
+    """nm_linear_update (several slabs, ragged tokens, bias) and nm_conv_update captured once: new inputs and eager work between the
+    replays, every replay equal to the eager call on the same inputs"""
+    from paper_2203_10991_amd import api
+    q8 = "q8" in form
+    torch.manual_seed(9)
+    new = lambda *s: torch.randn(*s, device=DEV).to(torch.bfloat16)      # noqa: E731
+    if form.startswith("conv"):
+        ins = [new(6, 64, 28, 28), new(6, 64, 28, 28)]
+        call = lambda: (api.nm_conv_update(ins[0], ins[1], 3, q8=q8, seed=2),)      # noqa: E731
+    else:
+        ins = [new(3001, 128), new(3001, 64)] + ([new(3001, 128)] if "relu" in form else [])
+        call = lambda: api.nm_linear_update(ins[0], ins[1], q8=q8, seed=2, act=ins[2] if len(ins) > 2 else None, bias=True)      # noqa: E731
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        call()                                          # warm-up on the capture stream
+        side.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            out = call()
+    for i in range(4):
+        for t in ins:
+            t.copy_(new(*t.shape) * 2.0 ** (4 * i - 6))                  # (other scales in the 8-bit forms)
+        for o in out:
+            if o is not None:
+                o.fill_(float("nan"))
+        want = call()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(a is None and b is None or torch.equal(a, b) for a, b in zip(out, want)), f"replay {i}"
