@@ -309,6 +309,9 @@ __global__ __launch_bounds__(1024) void update_gemm_f32_small_kernel(
 // 10 us of fill; a token of a 64 x 64 tile 0.0169, 4.5 us per round and 5 per launch; the second pass as in the 16-bit
 // plan.  The smaller tile has the finer grain -- it fills the GPU without (or with a quarter of) the slabs -- and the
 // larger one needs a quarter of the operand bytes and pays no fill per tile: it keeps outputs of many tiles over few tokens.
+// A last round of few workgroups finds most of them alone on their CU: up to 72 of them 0.135 a token and 7 us (measured on 110 sizes
+// with 1 to 68 left over; 76 to 112 left over take 0.18-0.24 a token).  Priced as a whole round it sent 416 x 5232 x 3216, 533
+// workgroups, to the smaller tile: 184 -> 217 us, 448 x 4520 x 3952 190 -> 240.
 // Measured, 128 x 256 -> 64 x 64, second pass included: 1024 x 1024 x 1024 38.7 -> 27.0 us, 512 x 512 x 256 28 -> 14, 16384 x 256 x 256
 // 37.6 -> 29.3, 8192 x 1536 x 2048 677 (576 workgroups, a second round of 64) -> 436; the other way 512 x 4096 x 4096 138 against
 // 219, 4096 x 2048 x 2048 278 against 300.
@@ -323,9 +326,12 @@ static PlanF32 make_plan_f32(int64_t T, int64_t O, int64_t I)
     int64_t slabs = 1;
     auto consider = [&](bool small, int64_t z) {
         z = std::max<int64_t>(1, std::min<int64_t>(z, groups / (small ? 16 : 8)));       // at least 256 (128) tokens per slab
-        const int64_t wgs = z * (small ? fine : big), tokens = (groups + z - 1) / z * 16, per_round = small ? 256 : 512;
-        const double rounds = (double)((wgs + per_round - 1) / per_round);
-        double cost = small ? rounds * ((double)tokens * 0.0169 + 4.5) + 5.0 : rounds * (double)tokens * (wgs <= 256 ? 0.14 : 0.2425) + 10.0;
+        const int64_t wgs = z * (small ? fine : big), rest = wgs % 512;
+        const double tokens = (double)((groups + z - 1) / z * 16);
+        double cost;
+        if (small) cost = (double)((wgs + 255) / 256) * (tokens * 0.0169 + 4.5) + 5.0;
+        else if (wgs <= 256) cost = tokens * 0.14 + 10.0;
+        else cost = (double)(wgs / 512) * tokens * 0.2425 + (rest == 0 ? 0.0 : rest <= 72 && wgs > 512 ? tokens * 0.135 + 7.0 : tokens * 0.2425) + 10.0;
         if (z > 1) cost += 4.0 + (double)(z + 1) * (double)O * (double)I * 4.0 / 3.5e6;
         if (cost < best) { best = cost; p.small = small; slabs = z; }
     };

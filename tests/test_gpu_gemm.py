@@ -253,3 +253,9 @@ def test_binary32_kernels_on_both_sides_of_the_line(nm, oracle, T, O, I, beta):
 @pytest.mark.parametrize("T,O,I,beta", [(4096, 640, 1024, 0.0), (528, 200, 152, 1.0), (8816, 264, 2440, 0.0)])
 def test_binary32_as_three_terms_in_slabs(nm, oracle, T, O, I, beta):
     split_case(nm, oracle, T, O, I, seed=5, beta=beta, sample=None if beta else 4000)
+
+
+# 128 x 256 tiles in whole rounds of 512 workgroups and a few left over (the plan's price of that last round)
+@pytest.mark.parametrize("T,O,I,beta", [(416, 5232, 3216, 0.0), (48, 7232, 2312, 1.0), (1184, 2432, 6680, 0.0)])
+def test_update_gemm_f32_with_a_short_last_round(nm, oracle, T, O, I, beta):
+    run_case(nm, oracle, synth.Workload(f"f32_{T}x{O}x{I}", T, O, I, "f32", "2:4", 0.0, 2.0, 0.3), seed=T, beta=beta)
