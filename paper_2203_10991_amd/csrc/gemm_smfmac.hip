@@ -64,13 +64,15 @@ __device__ __forceinline__ int enter_window(int slab, const uint16_t *__restrict
 // SHIFTED: the dense operand is a set of row-shifted views of one [rows x cb] matrix (a convolution's im2col matrix
 // that is never materialised): column block j of h is x read sh.rows[j] rows further down, h[t][j*cb + c] =
 // x[(t + rows[j])*ldh + c].  Only a lane's constant source offset and the descriptor's extent change.
-template <int WM, int WN, int AB, int BB, bool SHIFTED = false, bool WINDOWS = false>
+// RAGGED: h ends inside the last token group (h_rows), the rows past it count as zeros.  An instance of its own: as a condition at run
+// time its arithmetic ahead of the first load cost every launch 0.2-0.4 us (512 x 512 x 256 and 70 other sizes that take under 14 us: 2 %).
+template <int WM, int WN, int AB, int BB, bool SHIFTED = false, bool WINDOWS = false, bool RAGGED = false>
 __global__ __launch_bounds__(WM * WN * 64) void update_gemm_smfmac_kernel(
     const uint16_t *__restrict__ vals, const uint16_t *__restrict__ meta, const uint16_t *__restrict__ h, int64_t ldh,
     float *__restrict__ out, int64_t ldo, int64_t slab_stride,       // out + z*slab_stride
     int64_t n_groups, int64_t groups_per_slab, int64_t O, int64_t I, int tiles_m, int tiles_n, int accumulate,
     int64_t o_first, int64_t o_end,          // the launch computes rows [o_first, o_end) of dW; tiles_m counts its M-tiles
-    int64_t h_rows,                          // rows h has: n_groups * 16, or up to 15 fewer (the rest count as zeros; not with SHIFTED)
+    int64_t h_rows,                          // (RAGGED only) rows h has: up to 15 fewer than n_groups * 16
     ShiftArg sh)                             // (SHIFTED only)
 {
     constexpr int TM = WM * AB * 32, TN = WN * BB * 32;
@@ -186,7 +188,7 @@ __global__ __launch_bounds__(WM * WN * 64) void update_gemm_smfmac_kernel(
         if constexpr (SHIFTED)       // rows -margin .. T+margin-1 of x are readable; offsets are relative to row t0 - margin
             rh = rsrc((const char *)h + (t0 - sh.margin) * ldh * 2, ((T - t0 - 1 + 2 * (int64_t)sh.margin) * ldh + sh.cb) * 2);
         else
-        rh = rsrc((const char *)h + t0 * ldh * 2, ((h_rows - t0 - 1) * ldh + I) * 2);
+        rh = rsrc((const char *)h + t0 * ldh * 2, (((RAGGED ? h_rows : T) - t0 - 1) * ldh + I) * 2);
         rv = rsrc((const char *)vals + Gs * O * 16, (n_groups - Gs) * O * 16);
         rm = rsrc((const char *)meta + Gs * O * 2, (n_groups - Gs) * O * 2);
     };
@@ -211,8 +213,11 @@ __global__ __launch_bounds__(WM * WN * 64) void update_gemm_smfmac_kernel(
     // first stage (relative to the slab) in which this wave's token group lies past the end of the tensor
     const int first_missing = (int)min((int64_t)0x7fffffff, (n_groups - g_begin - wgrp + 1) / 2);
     // stage in which this wave's token group has fewer than 16 rows of h (-1: none)
-    const int64_t last_group = h_rows / 16;
-    const int partial = !SHIFTED && h_rows < T && last_group >= g_begin && (last_group - g_begin) % 2 == wgrp ? (int)min((int64_t)0x7fffffff, (last_group - g_begin) / 2) : -1;
+    [[maybe_unused]] int partial = -1;
+    if constexpr (RAGGED) {
+        const int64_t last_group = h_rows / 16;
+        if (last_group >= g_begin && (last_group - g_begin) % 2 == wgrp) partial = (int)min((int64_t)0x7fffffff, (last_group - g_begin) / 2);
+    }
     // "stage `it` has landed" while the loads of the IN_FLIGHT stages fetched after it may still be on
     // their way ...
     auto stage_ready = [&](auto in_flight_c, int it, char *stage) {
@@ -227,7 +232,7 @@ __global__ __launch_bounds__(WM * WN * 64) void update_gemm_smfmac_kernel(
             for (int c = lane; c < M_SLOTS / 8; c += 64) *(uint4 *)(stage + M_OFF + wave * M_SLOTS * 2 + c * 16) = z;
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         }
-        if (!SHIFTED && it == partial) {             // the h rows past the last token of this wave's share
+        if (RAGGED && it == partial) {               // the h rows past the last token of this wave's share
             const int rows_left = (int)(h_rows % 16) - (wave * B_ROWS - 16 * wgrp);
             const uint4 z = make_uint4(0, 0, 0, 0);
             for (int c = lane; c < B_ROWS * CPR; c += 64)
@@ -822,13 +827,19 @@ static hipError_t run_plan(const Plan &p, const OutTarget &tg, const void *vals,
     if (p.tiles_m > 0) {
         dim3 grid((unsigned)(p.tiles_m * p.tiles_n), 1, (unsigned)p.slabs);
 #define NM_LAUNCH(WM, WN, AB, BB)                                                                                     \
-    hipLaunchKernelGGL((update_gemm_smfmac_kernel<WM, WN, AB, BB, false, WINDOWS>), grid, dim3(WM * WN * 64), 0, st, (const uint16_t *)vals, \
-                       meta, (const uint16_t *)h, ldh, tg.out, tg.ldo, tg.slab_stride, T / 16, p.groups_per_slab, O, I,         \
-                       p.tiles_m, p.tiles_n, tg.accumulate, p.tall_rows, O, h_rows, ShiftArg{})
-        if (p.shape == 0) NM_LAUNCH(2, 4, 4, 2);
-        else if (p.shape == 3) NM_LAUNCH(4, 2, 2, 2);
-        else NM_LAUNCH(2, 2, 2, 2);
+    hipLaunchKernelGGL((update_gemm_smfmac_kernel<WM, WN, AB, BB, false, WINDOWS, decltype(ragged)::value>), grid, dim3(WM * WN * 64), 0, st, \
+                       (const uint16_t *)vals, meta, (const uint16_t *)h, ldh, tg.out, tg.ldo, tg.slab_stride, T / 16,          \
+                       p.groups_per_slab, O, I, p.tiles_m, p.tiles_n, tg.accumulate, p.tall_rows, O, h_rows, ShiftArg{})
+        auto launch = [&](auto ragged) {
+            if (p.shape == 0) NM_LAUNCH(2, 4, 4, 2);
+            else if (p.shape == 3) NM_LAUNCH(4, 2, 2, 2);
+            else NM_LAUNCH(2, 2, 2, 2);
+        };
 #undef NM_LAUNCH
+        if constexpr (!WINDOWS) {
+            if (h_rows < T) { launch(std::true_type{}); return hipGetLastError(); }
+        }
+        launch(std::false_type{});
     }
     return hipGetLastError();
 }
