@@ -141,3 +141,16 @@ def test_conv_update_with_the_approximate_estimator_matches_the_oracle(oracle, N
     # the sums' tolerances as above, half a unit in the last place of the bf16 result, a wrong mask in one group
     assert (np.abs(got - want) <= (1e-3 if q8 else 1e-5) * wabs + 2.0 ** -8 * np.abs(want) + 1e-30).all()
     assert np.linalg.norm(got - want) <= 3e-3 * np.linalg.norm(want)
+
+
+@pytest.mark.parametrize("N,C,O,H,W,k", [(2, 16, 8, 5, 1, 3),          # images one pixel wide: no pixel pairs
+                                         (2, 24, 16, 1, 1, 3),
+                                         (3, 16, 24, 5, 3, 1),         # no border and an odd number of pixels: pairs would straddle images
+                                         (5, 16, 24, 3, 2, 1),         # ... an even number, the grid's end inside a tile
+                                         (2, 40, 72, 4, 2, 3),         # every pair of an image row is border beside a pixel
+                                         (1, 48, 40, 65, 3, 5)])       # pairs that start on the row's last pixel, odd and even rows in turn
+@pytest.mark.parametrize("q8", [False, True])
+def test_conv_update_pixel_pairs_at_the_edges(oracle, N, C, O, H, W, k, q8):
+    if q8 and C % 16:
+        C += 8
+    test_conv_update_matches_the_oracle(oracle, N, C, O, H, W, k, q8, (False, False))
