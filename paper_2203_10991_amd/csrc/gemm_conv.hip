@@ -56,15 +56,6 @@ union ConvB { bf16x16 v16; i32x8 v8; u32x2 q[4]; s16x4 h[4]; };
 union ConvI { u32x2 w2; uint32_t w[2]; };
 union ConvA { bf16x8 v16; i32x4 v8; u32x4 u4; };
 
-// one direct load to LDS: 16 (4) bytes per lane, lane offset + scalar offset from the descriptor's base, lanes side by side from `to` on
-__device__ __forceinline__ void load16_to_lds(__amdgpu_buffer_rsrc_t from, char *to, uint32_t offset, uint32_t scalar_offset)
-{
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(from, (lptr_t)to, 16, (int)offset, (int)scalar_offset, 0, 0);
-}
-__device__ __forceinline__ void load4_to_lds(__amdgpu_buffer_rsrc_t from, char *to, uint32_t offset, uint32_t scalar_offset)
-{
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(from, (lptr_t)to, 4, (int)offset, (int)scalar_offset, 0, 0);
-}
 __device__ __forceinline__ uint32_t add_u16(uint32_t s, uint32_t v)   // (s + v) mod 2^16
 {
     uint32_t r;

@@ -630,11 +630,9 @@ __global__ __launch_bounds__(512) void update_gemm_smfmac_tall_kernel(
     });
 }
 
-// out[o][i] = (accumulate ? out : 0) + alpha * sum_z part[z][o][i].  R threads share one float4 of the output
-// (R = 1 for a few slabs, 8 for many): thread r sums the slabs z = r, r+R, ... in ascending order, then the R partial
-// sums are combined in a fixed tree (neighbours at distance 1, 2, 4): the order of the additions depends on the slab
-// count only, never on timing.
-template <int R>
+// out[o][i] = (accumulate ? out : 0) + alpha * sum_z part[z][o][i]: R threads share one float4 of the output, a thread sums its slabs in CHAINS
+// chains (sum_of_slabs).  Deterministic: no atomics, an order that depends on the slab count only.
+template <int R, int CHAINS>
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *__restrict__ part, int slabs, int64_t slab_stride,
                                                            float *__restrict__ out, int64_t ldo, int64_t O, int64_t I, int accumulate,
                                                            AlphaArg al)
@@ -646,35 +644,35 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *__restr
     const bool valid = idx < n4;
     const int64_t o = valid ? idx / (I / 4) : 0, i = valid ? (idx % (I / 4)) * 4 : 0;
     float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (valid)
-        for (int z = r; z < slabs; z += R) {
-            const float4 v = *(const float4 *)(part + (int64_t)z * slab_stride + o * I + i);
-            s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
-        }
-#pragma unroll
-    for (int d = 1; d < R; d <<= 1) {
-        s.x += __shfl_xor(s.x, d); s.y += __shfl_xor(s.y, d); s.z += __shfl_xor(s.z, d); s.w += __shfl_xor(s.w, d);
-    }
+    if (valid) s = sum_of_slabs<R, CHAINS>(part + o * I + i, r, slabs, slab_stride);
+    s = sum_of_threads<R>(s);
     if (!valid || r != 0) return;
     s.x *= alpha; s.y *= alpha; s.z *= alpha; s.w *= alpha;
-    if (accumulate) {
-        const float4 d = *(const float4 *)(out + o * ldo + i);
-        s.x += d.x; s.y += d.y; s.z += d.z; s.w += d.w;
-    }
+    if (accumulate) add4(s, *(const float4 *)(out + o * ldo + i));
     *(float4 *)(out + o * ldo + i) = s;
 }
 
-// dW = (accumulate ? dW : 0) + alpha * sum over the slabs of [slabs][O][I] partial sums (row stride I), in slab order
+// A sum of up to 11 slabs is one chain of loads, from 12 on eight.  Eight threads to a sum only where there are too few sums to fill the GPU: a
+// thread with eight loads in flight is faster otherwise.
+SlabSum slab_sum_form(int64_t n4, int slabs)
+{
+    return slabs < 12 ? SlabSum::one_chain : n4 <= 18432 && slabs >= 64 ? SlabSum::shared : SlabSum::eight_chains;
+}
+
+// dW = (accumulate ? dW : 0) + alpha * sum over the slabs of [slabs][O][I] partial sums (row stride I)
 hipError_t launch_splitk_reduce(const float *part, int slabs, float *dW, int64_t lddw, int64_t O, int64_t I,
                                 int accumulate, AlphaArg alpha, hipStream_t st)
 {
     const int64_t n4 = O * (I / 4);
-    if (slabs >= 12)
-        hipLaunchKernelGGL(splitk_reduce_kernel<8>, dim3((unsigned)((n4 + 31) / 32)), dim3(256), 0, st, part, slabs, O * I,
-                           dW, lddw, O, I, accumulate, alpha);
-    else
-        hipLaunchKernelGGL(splitk_reduce_kernel<1>, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, st, part, slabs, O * I,
-                           dW, lddw, O, I, accumulate, alpha);
+#define NM_REDUCE(R, CHAINS)                                                                                                        \
+    hipLaunchKernelGGL((splitk_reduce_kernel<R, CHAINS>), dim3((unsigned)((n4 + 256 / R - 1) / (256 / R))), dim3(256), 0, st, part, \
+                       slabs, O * I, dW, lddw, O, I, accumulate, alpha)
+    switch (slab_sum_form(n4, slabs)) {
+    case SlabSum::one_chain: NM_REDUCE(1, 1); break;
+    case SlabSum::eight_chains: NM_REDUCE(1, 8); break;
+    case SlabSum::shared: NM_REDUCE(8, 1); break;
+    }
+#undef NM_REDUCE
     return hipGetLastError();
 }
 

@@ -12,13 +12,10 @@ namespace nm {
 // Convolution: dW[o][c][tap] (bf16) = alpha * sum_z part[z][o][tap][c].  A workgroup takes one output channel and CW input
 // channels: R threads share a float4 of the partial sums (as in splitk_reduce_kernel: thread r sums slabs r, r+R, ... in
 // order, a fixed tree combines them), the results turn through LDS, and the CW x taps values leave contiguous.
-// Bound: launch latency and one read of the partial sums.  With many slabs a workgroup is 32 channels wide (128-byte reads), with 64 or
-// more -- few tiles, so few output channels to deal out -- 16, and has a thread for every sum of nine taps at once.
-// The three forms over sizes that a plan makes (nine taps, partial sums in the caches, us; 64 channels and a thread a sum / 32 and 8 / 16
-// and 16): 64 x 64 channels, 254 slabs 23.7 / 10.8 / 7.5, 128 slabs 7.1 / 6.2 / 4.4, 64 slabs 4.3 / 4.2 / 3.4, 32 slabs 3.2 / 3.3 / 3.0;
-// 128 x 128, 64 slabs 8.0 / 6.6 / 7.1, 16 slabs 2.7 / 3.6 / 4.4; 256 x 256, 16 slabs 6.3 / 8.9 / 13.5, 12 slabs 3.6 / 7.9 / 13.0.
-// So both lines are right for narrow layers only: with 128 channels or more the wider forms are up to 4 us faster there.
-template <int R, int CW, int NT>
+// Bound: launch latency and one read of the partial sums.  A workgroup is 64 channels wide with a thread a sum, which fills the GPU from
+// 128 x 128 channels on; narrower layers have few output channels to deal out, and with many slabs a workgroup is 16 channels wide there
+// with 16 threads a sum, all sums of nine taps at once.
+template <int R, int CHAINS, int CW, int NT>
 __global__ __launch_bounds__(NT) void finish_conv_kernel(const float *__restrict__ part, int slabs, int64_t slab_stride, uint16_t *__restrict__ dW,
                                                          int C, int taps, AlphaArg al)
 {
@@ -33,18 +30,8 @@ __global__ __launch_bounds__(NT) void finish_conv_kernel(const float *__restrict
         const bool valid = t < tasks;
         const int tap = valid ? t / q4 : 0, c = valid ? (t % q4) * 4 : 0;
         float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (valid) {
-            const float *at = src + (int64_t)tap * C + c;
-#pragma unroll 4
-            for (int z = r; z < slabs; z += R) {
-                const float4 v = *(const float4 *)(at + (int64_t)z * slab_stride);
-                s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
-            }
-        }
-#pragma unroll
-        for (int d = 1; d < R; d <<= 1) {
-            s.x += __shfl_xor(s.x, d); s.y += __shfl_xor(s.y, d); s.z += __shfl_xor(s.z, d); s.w += __shfl_xor(s.w, d);
-        }
+        if (valid) s = sum_of_slabs<R, CHAINS>(src + (int64_t)tap * C + c, r, slabs, slab_stride);
+        s = sum_of_threads<R>(s);
         if (valid && r == 0) {
             const uint32_t a = pack_bf16_rne(s.x * alpha, s.y * alpha), b = pack_bf16_rne(s.z * alpha, s.w * alpha);
             turned[(c + 0) * taps + tap] = (uint16_t)a; turned[(c + 1) * taps + tap] = (uint16_t)(a >> 16);
@@ -58,12 +45,14 @@ __global__ __launch_bounds__(NT) void finish_conv_kernel(const float *__restrict
 
 hipError_t launch_finish_conv(const float *part, int slabs, void *dW, int64_t O, int C, int taps, AlphaArg alpha, hipStream_t st)
 {
-#define NM_FINISH(R, CW, NT)                                                                                                                      \
-    hipLaunchKernelGGL((finish_conv_kernel<R, CW, NT>), dim3((unsigned)O, (unsigned)((C + CW - 1) / CW)), dim3(NT), 0, st, part, slabs,            \
+#define NM_FINISH(R, CHAINS, CW, NT)                                                                                                              \
+    hipLaunchKernelGGL((finish_conv_kernel<R, CHAINS, CW, NT>), dim3((unsigned)O, (unsigned)((C + CW - 1) / CW)), dim3(NT), 0, st, part, slabs,    \
                        O * (int64_t)taps * C, (uint16_t *)dW, C, taps, alpha)
-    if (slabs >= 64) NM_FINISH(16, 16, 576);
-    else if (slabs >= 12) NM_FINISH(8, 32, 576);
-    else NM_FINISH(1, 64, 256);
+    const int64_t wide = O * C;
+    if (wide <= 128 * 128 && slabs >= (wide <= 64 * 64 ? 24 : 64)) NM_FINISH(16, 1, 16, 576);
+    else if (slabs >= 64) NM_FINISH(1, 16, 64, 256);
+    else if (slabs >= 12) NM_FINISH(1, 8, 64, 256);
+    else NM_FINISH(1, 1, 64, 256);
 #undef NM_FINISH
     return hipGetLastError();
 }
@@ -75,7 +64,7 @@ hipError_t launch_finish_conv(const float *part, int slabs, void *dW, int64_t O,
 // workgroups walk a chain of loads (1024 groups: 16 per thread), so they start first and keep four in flight: 16384 x 4096 x 1024
 // in four slabs 26 -> 18 us.
 constexpr int DB_COLS = 16;                                              // columns of a bias workgroup: 4 float4 x 64 groups in flight
-template <int R>
+template <int R, int CHAINS>
 __global__ __launch_bounds__(256) void finish_linear_kernel(const float *__restrict__ part, int slabs, int64_t O, int64_t I, uint16_t *__restrict__ dW,
                                                             AlphaArg al, int db_blocks, const float *__restrict__ csum, int64_t groups,
                                                             uint16_t *__restrict__ db)
@@ -87,15 +76,8 @@ __global__ __launch_bounds__(256) void finish_linear_kernel(const float *__restr
         const int r = threadIdx.x % R;
         const bool valid = idx < n4;
         float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (valid)
-            for (int z = r; z < slabs; z += R) {
-                const float4 v = *(const float4 *)(part + (int64_t)z * O * I + idx * 4);
-                s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
-            }
-#pragma unroll
-        for (int d = 1; d < R; d <<= 1) {
-            s.x += __shfl_xor(s.x, d); s.y += __shfl_xor(s.y, d); s.z += __shfl_xor(s.z, d); s.w += __shfl_xor(s.w, d);
-        }
+        if (valid) s = sum_of_slabs<R, CHAINS>(part + idx * 4, r, slabs, O * I);
+        s = sum_of_threads<R>(s);
         if (valid && r == 0) *(uint2 *)(dW + idx * 4) = make_uint2(pack_bf16_rne(s.x * alpha, s.y * alpha), pack_bf16_rne(s.z * alpha, s.w * alpha));
         return;
     }
@@ -126,14 +108,20 @@ __global__ __launch_bounds__(256) void finish_linear_kernel(const float *__restr
 hipError_t launch_finish_linear(const float *part, int slabs, int64_t O, int64_t I, void *dW, AlphaArg alpha, const float *csum, int64_t groups,
                                 void *db, hipStream_t st)
 {
-    const int R = slabs >= 12 ? 8 : 1;
+    const SlabSum form = slab_sum_form(O * I / 4, slabs);
+    const int R = form == SlabSum::shared ? 8 : 1;
     const int64_t dw_blocks = (O * I / 4 + 256 / R - 1) / (256 / R), db_blocks = db ? (O + DB_COLS - 1) / DB_COLS : 0;
     if (dw_blocks + db_blocks > 0x7fffffffll) return hipErrorInvalidConfiguration;
     const dim3 grid((unsigned)(dw_blocks + db_blocks));
-    if (R == 8)
-        hipLaunchKernelGGL(finish_linear_kernel<8>, grid, dim3(256), 0, st, part, slabs, O, I, (uint16_t *)dW, alpha, (int)db_blocks, csum, groups, (uint16_t *)db);
-    else
-        hipLaunchKernelGGL(finish_linear_kernel<1>, grid, dim3(256), 0, st, part, slabs, O, I, (uint16_t *)dW, alpha, (int)db_blocks, csum, groups, (uint16_t *)db);
+#define NM_FINISH(R, CHAINS)                                                                                                                  \
+    hipLaunchKernelGGL((finish_linear_kernel<R, CHAINS>), grid, dim3(256), 0, st, part, slabs, O, I, (uint16_t *)dW, alpha, (int)db_blocks, csum, \
+                       groups, (uint16_t *)db)
+    switch (form) {
+    case SlabSum::one_chain: NM_FINISH(1, 1); break;
+    case SlabSum::eight_chains: NM_FINISH(1, 8); break;
+    case SlabSum::shared: NM_FINISH(8, 1); break;
+    }
+#undef NM_FINISH
     return hipGetLastError();
 }
 

@@ -70,6 +70,10 @@ hipError_t launch_update_gemm_f32_split(const void *vals, const uint16_t *meta, 
                                         int64_t lddw, int64_t T, int64_t O, int64_t I, float beta, void *workspace,
                                         hipStream_t st);
 size_t update_gemm_f32_split_workspace(int64_t T, int64_t O, int64_t I);
+// A second pass over the slabs of n4 float4 sums: from 12 slabs on a sum runs as eight chains, which eight threads take (`shared`) or one thread
+// side by side; either way in the same order.
+enum class SlabSum { one_chain, eight_chains, shared };
+SlabSum slab_sum_form(int64_t n4, int slabs);
 hipError_t launch_splitk_reduce(const float *part, int slabs, float *dW, int64_t lddw, int64_t O, int64_t I,
                                 int accumulate, AlphaArg alpha, hipStream_t st);
 

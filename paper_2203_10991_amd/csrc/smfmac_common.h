@@ -158,6 +158,62 @@ template <int N> __device__ __forceinline__ void wait_vmcnt()
     __builtin_amdgcn_s_waitcnt((N & 0xF) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
 }
 
+// Sum of the float4s at `at` of the slabs r, r + R, ... : CHAINS partial sums, the slabs dealt to them in turn, then a fixed tree (neighbours
+// at distance 1, 2, 4, ...).  The order of the additions depends on the slab count only, and R * CHAINS threads-times-chains of eight give
+// the same bits however they are split.
+__device__ __forceinline__ void add4(float4 &s, const float4 &v) { s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w; }
+template <int R, int CHAINS>
+__device__ __forceinline__ float4 sum_of_slabs(const float *at, int r, int slabs, int64_t slab_stride)
+{
+    if constexpr (CHAINS == 1) {
+        float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 4
+        for (int z = r; z < slabs; z += R) add4(s, *(const float4 *)(at + (int64_t)z * slab_stride));
+        return s;
+    } else {
+        static_assert(R == 1, "one thread's chains");
+        float4 s[CHAINS];
+#pragma unroll
+        for (int c = 0; c < CHAINS; ++c) s[c] = make_float4(0.f, 0.f, 0.f, 0.f);
+        int z = 0;
+        for (; z + CHAINS <= slabs; z += CHAINS) {
+            float4 v[CHAINS];                                 // (a wave of loads, then the additions: left alone the compiler waits for every load)
+#pragma unroll
+            for (int c = 0; c < CHAINS; ++c) v[c] = *(const float4 *)(at + (int64_t)(z + c) * slab_stride);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int c = 0; c < CHAINS; ++c) add4(s[c], v[c]);
+        }
+#pragma unroll
+        for (int c = 0; c < CHAINS - 1; ++c)
+            if (z + c < slabs) add4(s[c], *(const float4 *)(at + (int64_t)(z + c) * slab_stride));
+#pragma unroll
+        for (int d = 1; d < CHAINS; d <<= 1)
+#pragma unroll
+            for (int c = 0; c < CHAINS; c += 2 * d) add4(s[c], s[c + d]);
+        return s[0];
+    }
+}
+// ... and over the R threads that share a sum, neighbours again
+template <int R> __device__ __forceinline__ float4 sum_of_threads(float4 s)
+{
+#pragma unroll
+    for (int d = 1; d < R; d <<= 1) {
+        s.x += __shfl_xor(s.x, d); s.y += __shfl_xor(s.y, d); s.z += __shfl_xor(s.z, d); s.w += __shfl_xor(s.w, d);
+    }
+    return s;
+}
+
+// one direct load to LDS: 16 (4) bytes per lane, lane offset + scalar offset from the descriptor's base, lanes side by side from `to` on
+__device__ __forceinline__ void load16_to_lds(__amdgpu_buffer_rsrc_t from, char *to, uint32_t offset, uint32_t scalar_offset)
+{
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(from, (lptr_t)to, 16, (int)offset, (int)scalar_offset, 0, 0);
+}
+__device__ __forceinline__ void load4_to_lds(__amdgpu_buffer_rsrc_t from, char *to, uint32_t offset, uint32_t scalar_offset)
+{
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(from, (lptr_t)to, 4, (int)offset, (int)scalar_offset, 0, 0);
+}
+
 // ---- tile assignment.  Workgroups are dealt round-robin to the 8 XCDs (workgroup id % 8), 32 CUs and one
 // L2 each; the 32 tiles resident on an XCD form a block of 8 M-tiles x 4 N-tiles (N fastest), so that
 // they share operand strips inside its L2 from the first stage on (8 vals strips + 4 h strips feed 32 tiles).

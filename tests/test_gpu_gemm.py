@@ -259,3 +259,13 @@ def test_binary32_as_three_terms_in_slabs(nm, oracle, T, O, I, beta):
 @pytest.mark.parametrize("T,O,I,beta", [(416, 5232, 3216, 0.0), (48, 7232, 2312, 1.0), (1184, 2432, 6680, 0.0)])
 def test_update_gemm_f32_with_a_short_last_round(nm, oracle, T, O, I, beta):
     run_case(nm, oracle, synth.Workload(f"f32_{T}x{O}x{I}", T, O, I, "f32", "2:4", 0.0, 2.0, 0.3), seed=T, beta=beta)
+
+
+@pytest.mark.parametrize("T,O,I", [(16 * 24 * 11, 64, 72),                # second pass over partial sums: one chain of eleven slabs
+                                   (16 * 24 * 12, 64, 72),                # ... eight chains, twelve slabs: four of them hold two
+                                   (16 * 24 * 23, 72, 264),               # ... a last trip of seven
+                                   (16 * 24 * 70, 64, 64),                # ... eight threads to a sum
+                                   (16 * 24 * 70, 296, 256)])             # ... too many sums for that
+def test_second_pass_over_partial_sums(nm, oracle, T, O, I):
+    run_case(nm, oracle, synth.Workload(f"slabs{T}x{O}x{I}", T, O, I, "bf16", "2:4", 0.0, 2.0, 0.3), seed=5)
+    run_case(nm, oracle, synth.Workload(f"slabs{T}x{O}x{I}", T, O, I, "bf16", "2:4", 0.0, 2.0, 0.3), seed=6, beta=1.0)
