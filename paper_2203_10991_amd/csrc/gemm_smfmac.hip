@@ -38,21 +38,6 @@ constexpr int KT = 32;            // tokens per LDS stage (one 32-token MFMA ste
 constexpr int NS = 6;             // LDS stages: one being consumed, one landed, four in flight
 constexpr int TALL_STAGES = 5;    // the same of the 384-row kernel
 
-// WINDOWS: one launch over two pairs of operands that are windows of longer stacks of planes (three planes to a window; binary32 as
-// bf16 terms, gemm_f32_split.hip).  The first half of the slabs multiplies the sparse stack from its third plane on with the
-// dense one from its first, the other half the sparse stack from its first with the dense one from its second.  Returns the slab's number inside its window.
-__device__ __forceinline__ int enter_window(int slab, const uint16_t *__restrict__ &vals, const uint16_t *__restrict__ &h, int64_t ldh, int64_t n_groups, int64_t O)
-{
-    const int half = (int)gridDim.z / 2;
-    const int64_t plane = n_groups / 3;                  // token groups
-    if (slab < half) {
-        vals += 2 * plane * O * 8;
-        return slab;
-    }
-    h += plane * 16 * ldh;
-    return slab - half;
-}
-
 // LDS image of one stage (all filled by direct loads, 64 consecutive lanes -> consecutive LDS bytes):
 //   [0, 64*TN)                h tile, [32 tokens][TN columns] bf16, rows unpadded.  Bank conflicts of the
 //                             transposing reads are avoided by a swizzle: 16-byte chunk c of row k sits at
@@ -66,7 +51,7 @@ __device__ __forceinline__ int enter_window(int slab, const uint16_t *__restrict
 // x[(t + rows[j])*ldh + c].  Only a lane's constant source offset and the descriptor's extent change.
 // RAGGED: h ends inside the last token group (h_rows), the rows past it count as zeros.  An instance of its own: as a condition at run
 // time its arithmetic ahead of the first load cost every launch 0.2-0.4 us (512 x 512 x 256 and 70 other sizes that take under 14 us: 2 %).
-template <int WM, int WN, int AB, int BB, bool SHIFTED = false, bool WINDOWS = false, bool RAGGED = false>
+template <int WM, int WN, int AB, int BB, bool SHIFTED = false, bool RAGGED = false>
 __global__ __launch_bounds__(WM * WN * 64) void update_gemm_smfmac_kernel(
     const uint16_t *__restrict__ vals, const uint16_t *__restrict__ meta, const uint16_t *__restrict__ h, int64_t ldh,
     float *__restrict__ out, int64_t ldo, int64_t slab_stride,       // out + z*slab_stride
@@ -125,7 +110,6 @@ __global__ __launch_bounds__(WM * WN * 64) void update_gemm_smfmac_kernel(
     const int64_t m0 = o_first + (int64_t)tm * TM;       // tile's first row of dW (= column of g)
     const int64_t n0 = (int64_t)tn * TN;                 // tile's first column of h / dW
     out += (int64_t)slab * slab_stride;
-    if constexpr (WINDOWS) slab = enter_window(slab, vals, h, ldh, n_groups, O);
     const int64_t g_begin = (int64_t)slab * groups_per_slab;
     const int64_t g_end = min(n_groups, g_begin + groups_per_slab);
 
@@ -383,7 +367,7 @@ __global__ __launch_bounds__(WM * WN * 64) void update_gemm_smfmac_kernel(
 // (slot 192*wm + 32*a + m) | meta [2 groups][384 rows] x 2 B; five stages rotate.
 // ------------------------------------------------------------------------------------
 // SLABS: launched with gridDim.z slabs; without, one slab and the same code with fewer scalar registers alive (one spill less)
-template <bool SLABS, bool WINDOWS>
+template <bool SLABS>
 __global__ __launch_bounds__(512) void update_gemm_smfmac_tall_kernel(
     const uint16_t *__restrict__ vals, const uint16_t *__restrict__ meta, const uint16_t *__restrict__ h, int64_t ldh,
     float *__restrict__ out, int64_t ldo, int64_t slab_stride, int64_t n_groups, int64_t groups_per_slab,
@@ -403,7 +387,6 @@ __global__ __launch_bounds__(512) void update_gemm_smfmac_tall_kernel(
     const int wm = wave / WN, wn = wave % WN;
     const int64_t m0 = o_first + (int64_t)tm * TM, n0 = (int64_t)tn * TN;
     out += (int64_t)slab * slab_stride;
-    if constexpr (WINDOWS) slab = enter_window(slab, vals, h, ldh, n_groups, O);
     const int64_t g_begin = (int64_t)slab * groups_per_slab;
     const int64_t g_end = min(n_groups, g_begin + groups_per_slab);
 
@@ -807,17 +790,16 @@ size_t update_gemm_smfmac_shifted_workspace(int64_t T, int64_t O, int64_t I)
 }
 
 // The kernels of a plan, into `tg`.  h_rows < T: only for plans without 384-row tiles
-template <bool WINDOWS = false>
 static hipError_t run_plan(const Plan &p, const OutTarget &tg, const void *vals, const uint16_t *meta, const void *h, int64_t ldh, int64_t h_rows,
                            int64_t T, int64_t O, int64_t I, hipStream_t st)
 {
     if (p.tall_rows > 0) {
         dim3 tall_grid((unsigned)(p.tall_tiles_m * p.tiles_n), 1, (unsigned)p.slabs);
 #define NM_TALL(SLABS)                                                                                                              \
-    hipLaunchKernelGGL((update_gemm_smfmac_tall_kernel<SLABS, WINDOWS>), tall_grid, dim3(512), 0, st, (const uint16_t *)vals, meta,   \
+    hipLaunchKernelGGL((update_gemm_smfmac_tall_kernel<SLABS>), tall_grid, dim3(512), 0, st, (const uint16_t *)vals, meta,   \
                        (const uint16_t *)h, ldh, tg.out, tg.ldo, tg.slab_stride, T / 16, p.groups_per_slab, O, I, p.tall_tiles_m,      \
                        p.tiles_n, tg.accumulate, (int64_t)0, p.tall_rows)
-        if (WINDOWS || p.slabs > 1) NM_TALL(true); else NM_TALL(WINDOWS);
+        if (p.slabs > 1) NM_TALL(true); else NM_TALL(false);
 #undef NM_TALL
         hipError_t e0 = hipGetLastError();
         if (e0 != hipSuccess) return e0;
@@ -825,7 +807,7 @@ static hipError_t run_plan(const Plan &p, const OutTarget &tg, const void *vals,
     if (p.tiles_m > 0) {
         dim3 grid((unsigned)(p.tiles_m * p.tiles_n), 1, (unsigned)p.slabs);
 #define NM_LAUNCH(WM, WN, AB, BB)                                                                                     \
-    hipLaunchKernelGGL((update_gemm_smfmac_kernel<WM, WN, AB, BB, false, WINDOWS, decltype(ragged)::value>), grid, dim3(WM * WN * 64), 0, st, \
+    hipLaunchKernelGGL((update_gemm_smfmac_kernel<WM, WN, AB, BB, false, decltype(ragged)::value>), grid, dim3(WM * WN * 64), 0, st, \
                        (const uint16_t *)vals, meta, (const uint16_t *)h, ldh, tg.out, tg.ldo, tg.slab_stride, T / 16,          \
                        p.groups_per_slab, O, I, p.tiles_m, p.tiles_n, tg.accumulate, p.tall_rows, O, h_rows, ShiftArg{})
         auto launch = [&](auto ragged) {
@@ -834,10 +816,7 @@ static hipError_t run_plan(const Plan &p, const OutTarget &tg, const void *vals,
             else NM_LAUNCH(2, 2, 2, 2);
         };
 #undef NM_LAUNCH
-        if constexpr (!WINDOWS) {
-            if (h_rows < T) { launch(std::true_type{}); return hipGetLastError(); }
-        }
-        launch(std::false_type{});
+        if (h_rows < T) launch(std::true_type{}); else launch(std::false_type{});
     }
     return hipGetLastError();
 }
@@ -852,26 +831,6 @@ hipError_t launch_update_gemm_smfmac(const void *vals, const uint16_t *meta, con
     hipError_t e = run_plan(p, tg, vals, meta, h, ldh, T, T, O, I, st);
     if (e != hipSuccess) return e;
     if (p.slabs > 1) e = launch_splitk_reduce((const float *)workspace, p.slabs, dW, lddw, O, I, accumulate, 1.0f, st);
-    return e;
-}
-
-// Operands that are windows of three planes over longer stacks (WINDOWS above): the plan is that of the 6T tokens the six planes
-// make, on an even number of slabs, half of them for each window.  0 slabs: the plan has an odd number
-int update_gemm_smfmac_window_slabs(int64_t T, int64_t O, int64_t I, size_t beside)
-{
-    const int slabs = make_plan(6 * T, O, I, false, true, beside).slabs;
-    return slabs % 2 ? 0 : slabs;
-}
-
-hipError_t launch_update_gemm_smfmac_windows(const void *vals, const uint16_t *meta, const void *h, float *dW, int64_t lddw, int64_t T, int64_t O,
-                                             int64_t I, float beta, void *workspace, hipStream_t st, size_t beside)
-{
-    Plan p = make_plan(6 * T, O, I, false, true, beside);
-    int half = p.slabs / 2;
-    p.groups_per_slab = slab_groups(3 * T / 16, half, p.tall_rows == O ? 2 * TALL_STAGES : 2 * NS);
-    p.slabs = 2 * half;
-    hipError_t e = run_plan<true>(p, OutTarget{(float *)workspace, I, O * I, 0}, vals, meta, h, I, 3 * T, 3 * T, O, I, st);
-    if (e == hipSuccess) e = launch_splitk_reduce((const float *)workspace, p.slabs, dW, lddw, O, I, beta != 0.f, 1.0f, st);
     return e;
 }
 

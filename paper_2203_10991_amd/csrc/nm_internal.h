@@ -49,11 +49,6 @@ hipError_t launch_update_gemm_smfmac(const void *vals, const uint16_t *meta, con
                                      int64_t lddw, int64_t T, int64_t O, int64_t I, float beta, void *workspace,
                                      hipStream_t st, size_t beside = 0);     // beside: workspace bytes of the call that are not this GEMM's
 size_t update_gemm_smfmac_workspace(int64_t T, int64_t O, int64_t I, size_t beside = 0);
-// the same over two windows of three planes of T tokens each, the first at vals plane 2 and h plane 0, the second at vals plane 0 and h
-// plane 1 (index words: the planes share them, three copies); only where window_slabs is not 0, workspace that of 6T tokens
-int update_gemm_smfmac_window_slabs(int64_t T, int64_t O, int64_t I, size_t beside);
-hipError_t launch_update_gemm_smfmac_windows(const void *vals, const uint16_t *meta, const void *h, float *dW, int64_t lddw, int64_t T, int64_t O,
-                                             int64_t I, float beta, void *workspace, hipStream_t st, size_t beside);
 size_t update_gemm_smfmac_shifted_workspace(int64_t T, int64_t O, int64_t I);
 // the same product with h given as n row-shifted views of one [rows x cb] matrix x (bf16): h[t][j*cb + c] = x[(t + rows[j])*ldx + c]
 hipError_t launch_update_gemm_smfmac_shifted(const void *vals, const uint16_t *meta, const void *x, int64_t ldx, int64_t cb,
@@ -64,8 +59,7 @@ hipError_t launch_update_gemm_f32(const void *vals, const uint16_t *meta, const 
                                   hipStream_t st);
 size_t update_gemm_f32_workspace(int64_t T, int64_t O, int64_t I);
 
-// binary32 operands split into three bf16 terms each, the six partial products as one run of the 16-bit sparse GEMM over
-// operands stacked along the token axis (gemm_f32_split.hip)
+// binary32 operands split into three bf16 terms each, six partial products on the sparse 16-bit path (gemm_f32_split.hip)
 hipError_t launch_update_gemm_f32_split(const void *vals, const uint16_t *meta, const void *h, int64_t ldh, float *dW,
                                         int64_t lddw, int64_t T, int64_t O, int64_t I, float beta, void *workspace,
                                         hipStream_t st);

@@ -269,3 +269,28 @@ def test_update_gemm_f32_with_a_short_last_round(nm, oracle, T, O, I, beta):
 def test_second_pass_over_partial_sums(nm, oracle, T, O, I):
     run_case(nm, oracle, synth.Workload(f"slabs{T}x{O}x{I}", T, O, I, "bf16", "2:4", 0.0, 2.0, 0.3), seed=5)
     run_case(nm, oracle, synth.Workload(f"slabs{T}x{O}x{I}", T, O, I, "bf16", "2:4", 0.0, 2.0, 0.3), seed=6, beta=1.0)
+
+
+@pytest.mark.parametrize("T,O,I", [(16, 128, 128), (32, 136, 8), (48, 8, 136), (16 * 5, 256, 264),           # one to three stages: the ring's edges
+                                   (16 * 41, 520, 128), (16 * 64, 1024, 1032),                              # ragged tiles, a last odd group, slabs
+                                   (16 * 512, 64, 72)])
+def test_three_bf16_terms_at_the_edges_of_the_narrow_tile(nm, oracle, T, O, I):
+    split_case(nm, oracle, T, O, I, seed=T + O, sigma=2.0)
+    split_case(nm, oracle, T, O, I, seed=T + I, sigma=2.0, beta=1.0)
+
+
+@pytest.mark.parametrize("T,O,I", [(16 * 515, 2056, 2056), (16 * 1030, 1024, 1032)])                        # one slab; eight
+def test_three_bf16_terms_on_the_wide_tile(nm, oracle, T, O, I):
+    split_case(nm, oracle, T, O, I, seed=T + O, sigma=2.0, sample=4000)
+
+
+@pytest.mark.parametrize("T,O,I", [(256, 64, 64), (1024, 512, 264), (4096, 256, 128)])
+def test_three_bf16_terms_are_as_near_as_binary32_products(nm, T, O, I):
+    """in the 2-norm against binary64: no further off than the dense binary32 kernels, whose products and sums are rounded once each"""
+    w = synth.Workload(f"near{T}x{O}x{I}", T, O, I, "f32", "2:4", 0.0, 2.0, 0.2)
+    g, h = to_dev(synth.make_g(w, 1)), to_dev(synth.make_h(w, 1))
+    v, m, theta = nm.mvue_prune_2of4(g, seed=1, stream_id=0, want_dense=True)
+    want = theta.double().cpu().t() @ h.double().cpu()
+    off = [float((nm.nm_update_gemm(v, m, h, f32_as_bf16x3=x3).double().cpu() - want).norm() / want.norm()) for x3 in (True, False)]
+    print(f"2-norm error, three terms {off[0]:.2e}, binary32 products {off[1]:.2e}", flush=True)
+    assert off[0] <= 1.1 * off[1]
