@@ -402,6 +402,17 @@ int nm_linear_update(const void *g, int64_t ldg, const void *act, int64_t lda, c
                      void *dW, void *db, void *workspace, size_t workspace_bytes, void *hip_stream);
 size_t nm_linear_update_workspace(int64_t T, int64_t O, int64_t I, int q8, int bias);
 
+/*
+ * The dense products of a linear layer (bf16 tensors, binary32 accumulation, one rounding):
+ *   nm_linear_forward      y [T x O] = x [T x I] w^T + bias, then max(., 0) where relu != 0 (a NaN stays one)
+ *   nm_linear_input_grad   dx [T x I] = g [T x O] w
+ * w [O x I], y, dx and bias [O] (NULL = none) contiguous, ldx and ldg row strides.  O % 8 == 0, I % 8 == 0, sizes and strides as in
+ * nm_linear_update; every base on a 16-byte boundary, strides multiples of 8.  No workspace.
+ */
+int nm_linear_forward(const void *x, int64_t ldx, const void *w, const void *bias, int64_t T, int64_t O, int64_t I, int relu,
+                      void *y, void *hip_stream);
+int nm_linear_input_grad(const void *g, int64_t ldg, const void *w, int64_t T, int64_t O, int64_t I, void *dx, void *hip_stream);
+
 /* Message of the last error on this thread ("" if none).  Static storage; do not free. */
 const char *nm_last_error(void);
 

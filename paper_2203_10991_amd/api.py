@@ -96,6 +96,10 @@ def load():
     lib.nm_linear_update.restype = i32
     lib.nm_linear_update_workspace.argtypes = [i64, i64, i64, i32, i32]
     lib.nm_linear_update_workspace.restype = sz
+    lib.nm_linear_forward.argtypes = [vp, i64, vp, vp, i64, i64, i64, i32, vp, vp]
+    lib.nm_linear_forward.restype = i32
+    lib.nm_linear_input_grad.argtypes = [vp, i64, vp, i64, i64, i64, vp, vp]
+    lib.nm_linear_input_grad.restype = i32
     for f in (lib.mvue_prune_1of2, lib.mvue_prune_2of4, lib.nm_compress, lib.nm_update_gemm, lib.mvue_prune_2of4_q8,
               lib.nm_update_gemm_q8):
         f.restype = i32
@@ -609,3 +613,29 @@ def nm_linear_update(g: torch.Tensor, h: torch.Tensor, nm: str = "2:4", mode: in
     _check(lib.nm_linear_update(_ptr(g), ldg, _ptr(act), lda, _ptr(h), ldh, T, O, I, 2 if nm == "1:2" else 4, 0 if nm == "1:2" else mode, q8,
                                 seed, stream_id, _ptr(g_out), O, _ptr(dW), _ptr(db), _ptr(workspace), need, _stream(g)))
     return dW, db, g_out
+
+
+def nm_linear_forward(x: torch.Tensor, weight: torch.Tensor, bias: Optional[torch.Tensor] = None, relu: bool = False) -> torch.Tensor:
+    """y [T x O] = x [T x I] weight^T + bias (bf16), with the ReLU behind it where asked, in one kernel."""
+    if any(t.dtype != torch.bfloat16 or not t.is_cuda for t in ((x, weight) if bias is None else (x, weight, bias))) or x.dim() != 2:
+        raise TypeError("nm_linear_forward takes bfloat16 tensors on the GPU, x with two dimensions")
+    (O, I), T = weight.shape, x.shape[0]
+    if x.shape[1] != I or (bias is not None and tuple(bias.shape) != (O,)) or not weight.is_contiguous() or (bias is not None and not bias.is_contiguous()):
+        raise ValueError(f"x {tuple(x.shape)}, weight {tuple(weight.shape)} and bias do not fit, or the weight is not contiguous")
+    x, ldx = _rows_of(x)
+    y = torch.empty((T, O), dtype=torch.bfloat16, device=x.device)
+    _check(load().nm_linear_forward(_ptr(x), ldx, _ptr(weight), _ptr(bias), T, O, I, relu, _ptr(y), _stream(x)))
+    return y
+
+
+def nm_linear_input_grad(g: torch.Tensor, weight: torch.Tensor) -> torch.Tensor:
+    """dx [T x I] = g [T x O] weight (bf16)."""
+    if g.dtype != torch.bfloat16 or weight.dtype != torch.bfloat16 or not (g.is_cuda and weight.is_cuda) or g.dim() != 2:
+        raise TypeError("nm_linear_input_grad takes bfloat16 tensors on the GPU, g with two dimensions")
+    (O, I), T = weight.shape, g.shape[0]
+    if g.shape[1] != O or not weight.is_contiguous():
+        raise ValueError(f"g {tuple(g.shape)} and weight {tuple(weight.shape)} do not fit, or the weight is not contiguous")
+    g, ldg = _rows_of(g)
+    dx = torch.empty((T, I), dtype=torch.bfloat16, device=g.device)
+    _check(load().nm_linear_input_grad(_ptr(g), ldg, _ptr(weight), T, O, I, _ptr(dx), _stream(g)))
+    return dx

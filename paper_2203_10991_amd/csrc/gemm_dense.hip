@@ -1,0 +1,299 @@
+// The dense products of a linear layer on bf16 tensors (T tokens, I inputs, O outputs), on the dense matrix cores:
+//     forward         y[T x O]  = x[T x I] W[O x I]^T + b, with or without the ReLU behind it
+//     input gradient  dx[T x I] = g[T x O] W[O x I]
+// binary32 accumulation, bias and ReLU before the one rounding.
+//
+// Instruction: v_mfma_f32_32x32x16_bf16.  Both operands have 32 rows or columns (lane % 32) and 16 steps of the reduction axis, eight
+// consecutive ones to a lane (8 * (lane / 32) on).  The weights are the first operand, so a lane holds four consecutive features of a
+// token and stores them together.
+//
+// Workgroup = WM x WN waves, each AM x AN blocks of 32 tokens x 32 features.  The reduction axis advances in stages of 64, NS of which rotate
+// through LDS, filled by direct loads.  A row that is contiguous along the reduction axis is eight chunks of 16 bytes, chunk c at position
+// c ^ (row / 2 % 8), which makes the 16-byte reads of consecutive rows free of bank conflicts; W of the input gradient is contiguous
+// along the features instead and is read with ds_read_b64_tr_b16 as the dense operand of the update GEMM is.
+// A stage is four MFMA steps.  Behind the second the next stage has to have landed (one barrier) and this stage's last fragments are in
+// registers, so its buffer is free and the loads of the stage NS later go there; the next stage's first fragments are read under the last two steps.
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include <algorithm>
+#include <type_traits>
+
+#include "nm_internal.h"
+#include "gemm_plan.h"
+#include "smfmac_common.h"
+#include "prune_common.h"        // pack_bf16_rne
+
+namespace nm {
+
+namespace {
+
+constexpr int DK = 64;           // reduction steps of a stage
+
+__device__ __forceinline__ void mfma_32x32x16(f32x16 &acc, const u32x4 &a, const u32x4 &b)
+{
+    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
+}
+
+union FragK { u32x4 u4; s16x4 q[2]; };
+
+struct DenseArg {
+    const uint16_t *x, *w, *bias;              // x [M][K], row stride ldx; w [N][K] or (NN) [K][N], contiguous
+    uint16_t *y;                               // [M][N], row stride ldy
+    int64_t ldx, ldy, M, N, K;
+    int tiles_m, tiles_n, relu;
+};
+
+template <int WM, int WN, int AM, int AN, bool NN, int NS>
+__global__ __launch_bounds__(WM * WN * 64) void dense_gemm_kernel(DenseArg p)
+{
+    constexpr int NW = WM * WN, TM = WM * AM * 32, TN = WN * AN * 32;
+    constexpr int X_BYTES = TM * DK * 2, STAGE = X_BYTES + TN * DK * 2;
+    constexpr int XL = TM / 8 / NW, WL = TN / 8 / NW, LPS = XL + WL;             // direct loads of a wave and stage
+    constexpr int CPR = TN / 8, W_ROWS = 64 / CPR;                               // (NN) chunks of a row, rows of a load
+    constexpr int PITCH = TN * 2 + 16;                                           // bytes of a row of the output tile in LDS
+    constexpr int LDS = NS * STAGE > TM * PITCH ? NS * STAGE : TM * PITCH;
+    static_assert(XL >= 1 && WL >= 1 && TM % (8 * NW) == 0 && TN % (8 * NW) == 0 && LDS <= 160 * 1024, "tile");
+    __shared__ __attribute__((aligned(1024))) char S[LDS];
+
+    int tm, tn;
+    tile_of_workgroup((int)blockIdx.x, p.tiles_m, p.tiles_n, tm, tn);
+    tm = __builtin_amdgcn_readfirstlane(tm); tn = __builtin_amdgcn_readfirstlane(tn);
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / WN, wn = wave % WN, hi = lane >> 5, l32 = lane & 31;
+    const int64_t m0 = (int64_t)tm * TM, n0 = (int64_t)tn * TN;
+    const int n = (int)((p.K + DK - 1) / DK), k_last = (int)(p.K - (int64_t)(n - 1) * DK);      // stages; reduction steps of the last one
+
+    f32x16 acc[AM][AN];
+#pragma unroll
+    for (int a = 0; a < AM; ++a)
+#pragma unroll
+        for (int b = 0; b < AN; ++b) acc_zero(acc[a][b]);
+
+    // ---- direct loads: load d of a wave covers 1 KB of the stage's image at (wave * XL + d) KB, resp. (wave * WL + d) KB behind the x tile.  Rows past
+    // the end are clamped to the last one, their results are not stored; chunks (NN: rows) past the end of the reduction axis are
+    // sent out of range, which drops them, and zeroed when the stage has landed.
+    const int r8 = lane >> 3, pos = lane & 7;
+    uint32_t x_src[XL], w_src[WL];
+    int x_k[2], w_k[2];                                                          // first reduction step of a lane's chunk in even and odd loads; NN: w_k[0] its row in load 0
+    auto chunk_of = [&](int row) { return pos ^ ((row >> 1) & 7); };
+#pragma unroll
+    for (int d = 0; d < XL; ++d) {
+        const int row = (wave * XL + d) * 8 + r8;
+        x_src[d] = (uint32_t)((min(m0 + row, p.M - 1) - m0) * p.ldx * 2 + chunk_of(row) * 16);
+    }
+#pragma unroll
+    for (int d = 0; d < 2; ++d) { x_k[d] = chunk_of((wave * XL + d) * 8 + r8) * 8; w_k[d] = chunk_of((wave * WL + d) * 8 + r8) * 8; }
+    const int w_row = lane / CPR, w_pos = lane % CPR;
+#pragma unroll
+    for (int d = 0; d < WL; ++d) {
+        if constexpr (NN) {
+            const int row = (wave * WL + d) * W_ROWS + w_row, swz = TN >= 128 ? 4 * (row & 3) : 4 * ((row >> 1) & 1);
+            w_src[d] = (uint32_t)((row * p.N + min(n0 + 8 * (w_pos ^ swz), p.N - 8)) * 2);
+        } else {
+            const int row = (wave * WL + d) * 8 + r8;
+            w_src[d] = (uint32_t)((min(n0 + row, p.N - 1) - n0) * p.K * 2 + chunk_of(row) * 16);
+        }
+    }
+    const char *xp = (const char *)(p.x + m0 * p.ldx), *wp = (const char *)(NN ? p.w : p.w + n0 * p.K);
+    const int64_t w_step = NN ? DK * p.N * 2 : DK * 2;
+    int ahead = 0;                                                               // stage whose loads are being issued
+    auto next_stage = [&]() { xp += DK * 2; wp += w_step; ++ahead; };
+    auto rsrc = [](const char *base, bool there) { return __builtin_amdgcn_make_buffer_rsrc((void *)base, 0, there ? 0x7fffffff : 0, 0x00020000); };
+    auto fetch_one = [&](auto k_c, int buf) {
+        constexpr int K = decltype(k_c)::value;
+        char *stage = S + buf * STAGE;
+        const int left = ahead == n - 1 ? k_last : DK;                           // reduction steps the stage has
+        if constexpr (K < XL) {
+            const uint32_t src = x_k[K & 1] < left ? x_src[K] : 0xffffffffu;
+            load16_to_lds(rsrc(xp, ahead < n), stage + (wave * XL + K) * 1024, src, 0);
+        } else {
+            constexpr int d = K - XL;
+            const int at = NN ? (wave * WL + d) * W_ROWS + w_row : w_k[d & 1];
+            const uint32_t src = at < left ? w_src[d] : 0xffffffffu;
+            load16_to_lds(rsrc(wp, ahead < n), stage + X_BYTES + (wave * WL + d) * 1024, src, 0);
+        }
+    };
+    // zeros where a wave's loads of the last stage were out of range
+    auto clear_tail = [&](int buf) {
+        char *stage = S + buf * STAGE;
+        const uint4 z = make_uint4(0, 0, 0, 0);
+        for (int d = 0; d < XL; ++d)
+            if (x_k[d & 1] >= k_last) *(uint4 *)(stage + (wave * XL + d) * 1024 + lane * 16) = z;
+        for (int d = 0; d < WL; ++d)
+            if ((NN ? (wave * WL + d) * W_ROWS + w_row : w_k[d & 1]) >= k_last) *(uint4 *)(stage + X_BYTES + (wave * WL + d) * 1024 + lane * 16) = z;
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    };
+
+    // ---- LDS reads
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(lptr_t)S;
+    const int key = (l32 >> 1) & 7, li = lane & 15;
+    uint32_t rd_k[4];                                                            // a row's chunk of MFMA step kk
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) rd_k[kk] = lds0 + (uint32_t)(l32 * (DK * 2) + ((2 * kk + hi) ^ key) * 16);
+    const uint32_t x_base = (uint32_t)(wm * AM * 32 * DK * 2), w_base = (uint32_t)(X_BYTES + wn * AN * 32 * DK * 2);
+    uint32_t rd_w[AN];
+    if constexpr (NN) {
+#pragma unroll
+        for (int b = 0; b < AN; ++b) {
+            const int swz = TN >= 128 ? 4 * (li >> 2) : 4 * ((li >> 3) & 1);
+            const int chunk = ((wn * AN + b) * 4 + 2 * ((lane >> 4) & 1) + ((li & 3) >> 1)) ^ swz;
+            rd_w[b] = lds0 + (uint32_t)(X_BYTES + (8 * hi + (li >> 2)) * (TN * 2) + chunk * 16 + (li & 1) * 8);
+        }
+    }
+    FragK xf[2][AM], wf[2][AN];
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+#pragma unroll
+        for (int a = 0; a < AM; ++a) xf[s][a].u4 = u32x4{0, 0, 0, 0};
+#pragma unroll
+        for (int b = 0; b < AN; ++b) wf[s][b].u4 = u32x4{0, 0, 0, 0};
+    }
+    constexpr int READS = AM + AN * (NN ? 2 : 1);
+    static_assert(READS <= 15, "counter of LDS reads");
+    auto read = [&](auto kk_c, int buf) {                                        // fragments of MFMA step kk, into set kk % 2
+        constexpr int kk = decltype(kk_c)::value, set = kk % 2;
+        const uint32_t so = (uint32_t)(buf * STAGE);
+        const uint32_t xa = rd_k[kk] + so + x_base;
+        static_for<AM>([&](auto a_c) { constexpr int a = decltype(a_c)::value; lds_refill_b128<a * 32 * DK * 2>(xf[set][a].u4, xa); });
+        if constexpr (NN)
+            static_for<AN>([&](auto b_c) {
+                constexpr int b = decltype(b_c)::value, R = TN * 2;
+                const uint32_t at = rd_w[b] + so;
+                lds_refill_tr16<(16 * kk) * R>(wf[set][b].q[0], at);
+                lds_refill_tr16<(16 * kk + 4) * R>(wf[set][b].q[1], at);
+            });
+        else {
+            const uint32_t wa = rd_k[kk] + so + w_base;
+            static_for<AN>([&](auto b_c) { constexpr int b = decltype(b_c)::value; lds_refill_b128<b * 32 * DK * 2>(wf[set][b].u4, wa); });
+        }
+    };
+    // MFMA step kk; the loads [lo, hi) of a stage are spread behind its MFMAs
+    auto step = [&](auto kk_c, auto lo_c, auto hi_c, int buf) {
+        constexpr int set = decltype(kk_c)::value % 2, lo = decltype(lo_c)::value, n_l = decltype(hi_c)::value - lo, NM = AM * AN;
+        static_for<NM>([&](auto i_c) {
+            constexpr int i = decltype(i_c)::value, a = i / AN, b = i % AN;
+            mfma_32x32x16(acc[a][b], wf[set][b].u4, xf[set][a].u4);
+            static_for<LPS>([&](auto k_c) {
+                constexpr int k = decltype(k_c)::value;
+                if constexpr (k >= lo && k < lo + n_l && (k - lo) * NM / n_l == i) fetch_one(k_c, buf);
+            });
+        });
+    };
+    using std::integral_constant;
+    using I0 = integral_constant<int, 0>; using I1 = integral_constant<int, 1>; using I2 = integral_constant<int, 2>; using I3 = integral_constant<int, 3>;
+
+    static_for<NS>([&](auto s_c) {
+        static_for<LPS>([&](auto k_c) { fetch_one(k_c, decltype(s_c)::value); });
+        next_stage();
+    });
+    wait_vmcnt<(NS - 1) * LPS>();
+    if (n == 1 && k_last < DK) clear_tail(0);
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    read(I0{}, 0);
+    read(I1{}, 0);
+    int buf = 0;
+    for (int s = 0; s < n; ++s) {
+        const int next = buf == NS - 1 ? 0 : buf + 1;
+        asm volatile("s_waitcnt lgkmcnt(%0)" : : "n"(READS) : "memory");
+        step(I0{}, I0{}, I0{}, 0);
+        read(I2{}, buf);
+        asm volatile("s_waitcnt lgkmcnt(%0)" : : "n"(READS) : "memory");
+        step(I1{}, I0{}, I0{}, 0);
+        read(I3{}, buf);
+        // the next stage has landed, and every wave has read all of this one
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" : : "n"((NS - 2) * LPS) : "memory");
+        if (s == n - 2 && k_last < DK) clear_tail(next);
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        step(I2{}, I0{}, integral_constant<int, LPS / 2>{}, buf);
+        read(I0{}, next);
+        step(I3{}, integral_constant<int, LPS / 2>{}, integral_constant<int, LPS>{}, buf);
+        read(I1{}, next);
+        next_stage();
+        buf = next;
+    }
+    // what ran ahead has landed, and the matrix pipeline is done, before the tile goes where the stages were
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");
+#pragma unroll
+    for (int a = 0; a < AM; ++a)
+#pragma unroll
+        for (int b = 0; b < AN; ++b) acc_settled(acc[a][b]);
+    __syncthreads();
+#pragma unroll
+    for (int b = 0; b < AN; ++b) {
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const int f = (wn * AN + b) * 32 + 8 * g + 4 * hi;                   // the lane's four features
+            float add[4] = {0.f, 0.f, 0.f, 0.f};
+            if (p.bias) {
+                const uint2 v = *(const uint2 *)(p.bias + min(n0 + f, p.N - 4));
+                add[0] = __uint_as_float(v.x << 16); add[1] = __uint_as_float(v.x & 0xffff0000u);
+                add[2] = __uint_as_float(v.y << 16); add[3] = __uint_as_float(v.y & 0xffff0000u);
+            }
+#pragma unroll
+            for (int a = 0; a < AM; ++a) {
+                float v[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    v[j] = acc[a][b][4 * g + j] + add[j];
+                    if (p.relu) v[j] = v[j] <= 0.f ? 0.f : v[j];                 // (a NaN stays one)
+                }
+                *(uint2 *)(S + ((wm * AM + a) * 32 + l32) * PITCH + f * 2) = make_uint2(pack_bf16_rne(v[0], v[1]), pack_bf16_rne(v[2], v[3]));
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    __syncthreads();
+    for (int i = tid; i < TM * (TN / 8); i += NW * 64) {
+        const int row = i / (TN / 8), c = (i % (TN / 8)) * 8;
+        if (m0 + row < p.M && n0 + c < p.N) *(uint4 *)(p.y + (m0 + row) * p.ldy + n0 + c) = *(const uint4 *)(S + row * PITCH + c * 2);
+    }
+}
+
+}  // namespace
+
+// Tiles of 64 x 64, 128 x 64, 128 x 128 (4 waves, two workgroups on a CU) or 256 x 256 (8 waves), the cheapest by what they were measured to take:
+// microseconds per stage of a tile alone on its CU and with a second one, of the largest by the share of the CUs that are busy, and per round.
+// Back to back from a graph, these / the vendor library's choice, us: 2048 x 1024 -> 1024 10 / 10.5 (input gradient 10 / 12), 1576 x 768 -> 3072 17.5 / 13.8
+// (20 / 22), 197 x 1024 -> 1024 8.0 / 6.0 (7.4 / 8.1), 12608 x 3072 -> 768 67 / 60 (78 / 72), 16384 x 1024 -> 4096 137 / 112 (112 / 106).  The small
+// tiles are bound by the path from the L2s to the CUs (24 KB a stage in 0.33 us on all of them: 18 TB/s), the largest by the matrix
+// pipes plus fill and drain of a round (5 us).
+hipError_t launch_dense_gemm(bool nn, const void *x, int64_t ldx, const void *w, const void *bias, void *y, int64_t ldy, int64_t M, int64_t N, int64_t K,
+                             bool relu, hipStream_t st)
+{
+    DenseArg p{(const uint16_t *)x, (const uint16_t *)w, (const uint16_t *)bias, (uint16_t *)y, ldx, ldy, M, N, K, 0, 0, relu};
+    struct Tile { int tm, tn, per_cu; double alone, shared, round; };
+    constexpr Tile tiles[4] = {{64, 64, 2, 0.25, 0.42, 0.7}, {128, 64, 2, 0.33, 0.70, 1.0}, {128, 128, 2, 0.85, 1.0, 1.5}, {256, 256, 1, 0.6, 1.75, 5.0}};
+    const double stages = (double)((K + DK - 1) / DK);
+    int best = 0;
+    double least = 1e300;
+    for (int i = 0; i < 4; ++i) {
+        const Tile &t = tiles[i];
+        const int64_t n = ((M + t.tm - 1) / t.tm) * ((N + t.tn - 1) / t.tn), round = (int64_t)t.per_cu * NM_CUS, left = n % round;
+        const double part = t.per_cu == 1 ? t.alone + (t.shared - t.alone) * (double)left / NM_CUS : left <= NM_CUS ? t.alone : t.shared;
+        const double cost = (double)(n / round) * (stages * t.shared + t.round) + (left ? stages * part + t.round : 0.0);
+        if (cost < least) { least = cost; best = i; }
+    }
+    p.tiles_m = (int)((M + tiles[best].tm - 1) / tiles[best].tm);
+    p.tiles_n = (int)((N + tiles[best].tn - 1) / tiles[best].tn);
+    const int64_t wgs = (int64_t)p.tiles_m * p.tiles_n;
+    if (wgs > 0x7fffffffll) return hipErrorInvalidConfiguration;
+#define NM_DENSE(WM, WN, AM, AN, NS)                                                                                                          \
+    do {                                                                                                                                      \
+        if (nn) hipLaunchKernelGGL((dense_gemm_kernel<WM, WN, AM, AN, true, NS>), dim3((unsigned)wgs), dim3(WM * WN * 64), 0, st, p);          \
+        else hipLaunchKernelGGL((dense_gemm_kernel<WM, WN, AM, AN, false, NS>), dim3((unsigned)wgs), dim3(WM * WN * 64), 0, st, p);            \
+    } while (0)
+    switch (best) {
+    case 0: NM_DENSE(2, 2, 1, 1, 4); break;
+    case 1: NM_DENSE(2, 2, 2, 1, 3); break;
+    case 2: NM_DENSE(2, 2, 2, 2, 2); break;
+    default: NM_DENSE(2, 4, 4, 2, 2); break;
+    }
+#undef NM_DENSE
+    return hipGetLastError();
+}
+
+}  // namespace nm

@@ -148,6 +148,11 @@ hipError_t launch_update_gemm_q8_parts(const uint8_t *vals8, const uint32_t *met
 hipError_t launch_finish_linear(const float *part, int slabs, int64_t O, int64_t I, void *dW, AlphaArg alpha, const float *csum, int64_t groups,
                                 void *db, hipStream_t st);
 
+// The dense products of a linear layer (gemm_dense.hip): y[M x N] = x[M x K] w^T + bias, w [N][K] contiguous, bias and ReLU optional; nn: w is
+// [K][N] and y = x w.  bf16, N and K multiples of 8
+hipError_t launch_dense_gemm(bool nn, const void *x, int64_t ldx, const void *w, const void *bias, void *y, int64_t ldy, int64_t M, int64_t N, int64_t K,
+                             bool relu, hipStream_t st);
+
 // The library's static device scratch array (nm_static.hip): its size, and its address on the current device
 // (looked up once per device; no allocation).
 size_t static_scratch_bytes();

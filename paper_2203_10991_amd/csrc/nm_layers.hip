@@ -113,7 +113,32 @@ const char *bad_linear_shape(int64_t T, int64_t O, int64_t I, int q8)
 
 }  // namespace
 
+// y = x w^T (+ bias, ReLU) or, nn, y = x w: checks of the two dense products of a linear layer
+static int dense_checked(const char *fn, bool nn, const void *x, int64_t ldx, const void *w, const void *bias, void *y, int64_t M, int64_t N, int64_t K,
+                         bool relu, void *hip_stream)
+{
+    const int64_t T = M, O = nn ? K : N, I = nn ? N : K;
+    if (const char *why = bad_linear_shape(T, O, I, 0)) return fail(NM_ERR_SHAPE, "%s: %s", fn, why);
+    if (!x || !w || !y) return fail(NM_ERR_NULL, "%s: a tensor is NULL", fn);
+    if (ldx < K || ldx > nm::LAYER_LD_MOST) return fail(NM_ERR_SHAPE, "%s: a row stride is smaller than its row or beyond 2^21", fn);
+    if (!aligned16(x) || !aligned16(w) || !aligned16(bias) || !aligned16(y) || ldx % 8)
+        return fail(NM_ERR_ALIGN, "%s: bases and row strides need 16-byte alignment", fn);
+    const size_t yb = (size_t)M * N * 2, xb = (size_t)((M - 1) * ldx + K) * 2, wb = (size_t)O * I * 2, bb = bias ? (size_t)N * 2 : 0;
+    if (overlap(y, yb, x, xb) || overlap(y, yb, w, wb) || overlap(y, yb, bias, bb)) return fail(NM_ERR_ALIAS, "%s: the output overlaps an input", fn);
+    return launched(fn, nm::launch_dense_gemm(nn, x, ldx, w, bias, y, N, M, N, K, relu, (hipStream_t)hip_stream));
+}
+
 extern "C" {
+
+int nm_linear_forward(const void *x, int64_t ldx, const void *w, const void *bias, int64_t T, int64_t O, int64_t I, int relu, void *y, void *hip_stream)
+{
+    return dense_checked("nm_linear_forward", false, x, ldx, w, bias, y, T, O, I, relu != 0, hip_stream);
+}
+
+int nm_linear_input_grad(const void *g, int64_t ldg, const void *w, int64_t T, int64_t O, int64_t I, void *dx, void *hip_stream)
+{
+    return dense_checked("nm_linear_input_grad", true, g, ldg, w, nullptr, dx, T, I, O, false, hip_stream);
+}
 
 size_t nm_linear_update_workspace(int64_t T, int64_t O, int64_t I, int q8, int bias)
 {

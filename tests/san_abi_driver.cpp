@@ -66,6 +66,7 @@ hipError_t launch_update_gemm_smfmac_parts(const void *, const uint16_t *, const
 size_t update_gemm_q8_parts_bytes(int64_t, int64_t O, int64_t I) { return (size_t)(2 * O * I * 4); }
 hipError_t launch_update_gemm_q8_parts(const uint8_t *, const uint32_t *, const uint8_t *, int64_t, int64_t, int64_t, int64_t, float *, int *slabs,
                                        hipStream_t) { *slabs = 2; ++g_launches; return hipSuccess; }
+hipError_t launch_dense_gemm(bool, const void *, int64_t, const void *, const void *, void *, int64_t, int64_t, int64_t, int64_t, bool, hipStream_t) { ++g_launches; return hipSuccess; }
 hipError_t launch_finish_linear(const float *, int, int64_t, int64_t, void *, AlphaArg, const float *, int64_t, void *, hipStream_t) { ++g_launches; return hipSuccess; }
 hipError_t launch_grid(const ConvShape &, const void *, int64_t, int64_t, const float *, void *, int, const void *, int64_t, uint64_t, uint32_t, const float *, void *,
                        void *, hipStream_t) { ++g_launches; return hipSuccess; }
