@@ -17,6 +17,7 @@ LIB_PATH = os.path.join(_HERE, "libnm_mvue.so")
 
 NM_F32, NM_BF16, NM_F32_BF16X3 = 0, 1, 2
 _lib = None
+_native = None            # the common forms of the hot calls in C++ (csrc/nm_torch.cpp)
 
 
 class NmError(RuntimeError):
@@ -107,8 +108,23 @@ def load():
     lib.nm_update_gemm_q8_workspace.restype = sz
     lib.nm_last_error.restype = C.c_char_p
     lib.nm_version.restype = C.c_char_p
-    _lib = lib
+    try:
+        from . import _nm_torch
+    except ImportError as e:
+        raise ImportError(f"_nm_torch.so is not built for this torch ({e}): run `python -m paper_2203_10991_amd.build`") from e
+    _nm_torch.bind({f: C.cast(getattr(lib, f), vp).value for f in (
+        "mvue_prune_1of2", "mvue_prune_2of4", "nm_update_gemm", "nm_update_gemm_workspace", "nm_linear_update", "nm_linear_update_workspace",
+        "nm_linear_forward", "nm_linear_input_grad")}, _raw_stream or (lambda d: torch.cuda.current_stream(d).cuda_stream))
+    global _native
+    _native, _lib = _nm_torch, lib
     return lib
+
+
+def _native_result(r):
+    """What a call of _native gave: its outputs, None where api.py's own way is to be taken, or an error status that is raised here."""
+    if type(r) is int:
+        _check(r)
+    return r
 
 
 def _check(rc: int):
@@ -152,6 +168,10 @@ def alloc_compressed(T: int, O: int, dtype: torch.dtype, device) -> Tuple[torch.
 
 def _prune(which: str, g, seed, stream_id, mode, vals, meta, dense_out, want_dense):
     lib = load()
+    if vals is None and meta is None and dense_out is None and not want_dense and which != "1of4":
+        r = _native_result(_native.prune(2 if which == "1of2" else 4, g, seed, stream_id, mode))
+        if r is not None:
+            return r[0], r[1], None
     if not g.is_cuda:
         raise ValueError("g must live on the GPU")
     T, O = g.shape
@@ -304,6 +324,10 @@ def nm_update_gemm(vals: torch.Tensor, meta: torch.Tensor, h: torch.Tensor, dW: 
 
     f32_as_bf16x3 (binary32 tensors only): multiply through three bf16 terms per value on the sparse 16-bit path."""
     lib = load()
+    if dW is None and workspace is None and beta == 0.0:
+        r = _native_result(_native.update_gemm(vals, meta, h, f32_as_bf16x3))
+        if r is not None:
+            return r
     G, O, _ = vals.shape
     T, I = h.shape
     if T != G * 16:
@@ -598,6 +622,9 @@ def nm_linear_update(g: torch.Tensor, h: torch.Tensor, nm: str = "2:4", mode: in
     """(dW [O x I], db [O] or None, g_out or None) of a linear layer, bf16, from its gradient g [T x O] and input h [T x I], in one
     library call.  act: the output of a ReLU behind the layer; the gradient is then g * [act > 0], returned as g_out."""
     lib = load()
+    r = _native_result(_native.linear_update(g, h, 2 if nm == "1:2" else 4, 0 if nm == "1:2" else mode, q8, seed, stream_id, act, bias))
+    if r is not None:
+        return r
     if any(t.dtype != torch.bfloat16 or not t.is_cuda or t.dim() != 2 for t in ((g, h) if act is None else (g, h, act))):
         raise TypeError("nm_linear_update takes 2-D bfloat16 tensors on the GPU")
     (T, O), I = g.shape, h.shape[1]
@@ -639,3 +666,16 @@ def nm_linear_input_grad(g: torch.Tensor, weight: torch.Tensor) -> torch.Tensor:
     dx = torch.empty((T, I), dtype=torch.bfloat16, device=g.device)
     _check(load().nm_linear_input_grad(_ptr(g), ldg, _ptr(weight), T, O, I, _ptr(dx), _stream(g)))
     return dx
+
+
+def own_linear_forward(x: torch.Tensor, weight: torch.Tensor, bias: Optional[torch.Tensor] = None, relu: bool = False) -> Optional[torch.Tensor]:
+    """nm_linear_forward over the last dimension of x where that is the faster way and can take the place of the framework's operators (csrc/nm_torch.cpp
+    says when); None otherwise."""
+    load()
+    return _native_result(_native.linear_forward(x, weight, bias, relu))
+
+
+def own_linear_input_grad(g: torch.Tensor, weight: torch.Tensor) -> Optional[torch.Tensor]:
+    """The same of nm_linear_input_grad; None where gradients are recorded, too."""
+    load()
+    return _native_result(_native.linear_input_grad(g, weight))

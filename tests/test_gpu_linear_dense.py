@@ -1,5 +1,6 @@
 """nm_linear_forward and nm_linear_input_grad (the dense products of a linear layer) against binary64 sums of the same bf16 operands, at the
-edges of their tiles, of a stage of 64 reduction steps and of a chunk of 8, on views whose padding is NaN."""
+edges of their tiles, of a stage of 64 reduction steps and of a chunk of 8, on views whose padding is NaN; the layers that take
+them, and those that do not."""
 import pytest
 import torch
 
@@ -62,3 +63,102 @@ def test_special_values_stay_where_they_are():
     assert bool(y[7].isnan().all()) and bool((y[40] == float("inf")).all()) and bool((y[41] == 0).all())
     rest = [r for r in range(100) if r not in (7, 40, 41)]
     assert torch.equal(y[rest], clean[rest]) and not bool(torch.signbit(clean).any())
+
+
+@pytest.mark.parametrize("relu", [False, True])
+@pytest.mark.parametrize("shape", [(50, 72), (3, 17, 72)])
+def test_layers_agree_with_the_framework_products(monkeypatch, relu, shape):
+    from paper_2203_10991_amd import api, autograd as ag
+    torch.manual_seed(2)
+    layer = (ag.NMLinearReLU if relu else ag.NMLinear)(72, 136, cfg=ag.NMConfig(seed=3), device=DEV, dtype=torch.bfloat16)
+    x = torch.randn(*shape, device=DEV).to(torch.bfloat16).requires_grad_()
+    gy = torch.randn(*shape[:-1], 136, device=DEV).to(torch.bfloat16)
+    taken = []
+    for name in ("own_linear_forward", "own_linear_input_grad"):
+        own = getattr(api, name)
+        monkeypatch.setattr(api, name, lambda *a, own=own: (taken.append(own(*a)), taken[-1])[1])
+    y = layer(x)
+    got = (y,) + torch.autograd.grad(y, (x, layer.weight, layer.bias), gy)
+    assert len(taken) == 2 and all(t is not None for t in taken)
+    for name in ("own_linear_forward", "own_linear_input_grad"):
+        monkeypatch.setattr(api, name, lambda *a: None)
+    y = layer(x)
+    want = (y,) + torch.autograd.grad(y, (x, layer.weight, layer.bias), gy)
+    for a, b in zip(got, want):
+        a, b = a.detach(), b.detach()
+        assert a.shape == b.shape and a.dtype == b.dtype
+        # either side rounds the same sum once: a unit in the last place of bf16 apart
+        assert float((a.double() - b.double()).norm()) <= 4e-3 * float(b.double().norm())
+
+
+def test_what_stays_the_framework_s():
+    """autocast regions, operators that are watched, gradients of gradients, views the kernels cannot read, other types, sizes the other library is
+    faster at"""
+    from paper_2203_10991_amd import api, autograd as ag
+    from torch.utils._python_dispatch import TorchDispatchMode
+    torch.manual_seed(3)
+    w = torch.randn(64, 48, device=DEV).to(torch.bfloat16)
+    x = torch.randn(32, 48, device=DEV).to(torch.bfloat16)
+    assert api.own_linear_forward(x, w) is not None and api.own_linear_forward(x.view(4, 8, 48), w).shape == (4, 8, 64)
+    flat = torch.randn(32 * 48 + 8, device=DEV).to(torch.bfloat16)
+    for a in (x.float(), flat[1:1 + 32 * 48].view(32, 48), torch.randn(48, 32, device=DEV).to(torch.bfloat16).t(), x[:0], x[0], x.cpu(), x[:, :40]):
+        assert api.own_linear_forward(a, w) is None
+    assert api.own_linear_forward(x, w.t().contiguous().t()) is None and api.own_linear_forward(x, w, torch.zeros(64, device=DEV)) is None
+    assert api.own_linear_forward(torch.empty(65536, 512, dtype=torch.bfloat16, device=DEV), torch.empty(1024, 512, dtype=torch.bfloat16, device=DEV)) is None
+    with torch.autocast("cuda", dtype=torch.float16):
+        assert api.own_linear_forward(x, w) is None
+
+    class Watch(TorchDispatchMode):
+        def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+            return func(*args, **(kwargs or {}))
+    with Watch():
+        assert api.own_linear_forward(x, w) is None
+    with torch.no_grad():
+        assert api.own_linear_input_grad(torch.randn(32, 64, device=DEV).to(torch.bfloat16), w) is not None
+    layer = ag.NMLinear(48, 64, bias=False, device=DEV, dtype=torch.bfloat16)
+    x.requires_grad_()
+    gy = torch.randn(32, 64, device=DEV).to(torch.bfloat16).requires_grad_()
+    (dx,) = torch.autograd.grad(layer(x), (x,), gy, create_graph=True)
+    (ggy,) = torch.autograd.grad(dx, (gy,), torch.ones_like(dx))
+    assert torch.allclose(ggy.float(), torch.ones(32, 48, device=DEV) @ layer.weight.detach().float().t(), rtol=2e-2, atol=1e-2)
+
+
+def test_the_calls_in_cpp_give_what_the_python_ones_give(monkeypatch):
+    """prune, update GEMM and the layer's update through csrc/nm_torch.cpp and without it: same outputs, same exceptions"""
+    from paper_2203_10991_amd import api
+    torch.manual_seed(4)
+    forms = []
+    for dt in (torch.bfloat16, torch.float32):
+        g, h = (torch.randn(64, n, device=DEV).to(dt) for n in (48, 40))
+        wide = torch.randn(64, 56, device=DEV).to(dt)[:, :48]
+        for a in (g, wide):
+            forms += [lambda a=a: api.mvue_prune_2of4(a, seed=-3, stream_id=2, mode=1), lambda a=a: api.mvue_prune_1of2(a, seed=2 ** 64 + 5)]
+        v, m, _ = api.mvue_prune_2of4(g, seed=1)
+        forms += [lambda v=v, m=m, h=h: api.nm_update_gemm(v, m, h), lambda v=v, m=m, h=h: api.nm_update_gemm(v, m, h, f32_as_bf16x3=True),
+                  lambda v=v, m=m, h=h: api.nm_update_gemm(v, m, h[:48]), lambda v=v, m=m, h=h: api.nm_update_gemm(v, m, h.double()),
+                  lambda g=g: api.mvue_prune_2of4(g[:10]), lambda g=g: api.mvue_prune_2of4(g.t()), lambda g=g: api.mvue_prune_2of4(g.half()),
+                  lambda g=g: api.mvue_prune_2of4(g.cpu()), lambda g=g: api.mvue_prune_2of4(g, mode=7)]
+    g, h = (torch.randn(50, n, device=DEV).to(torch.bfloat16) for n in (48, 32))
+    for q8 in (False, True):
+        forms += [lambda q8=q8: api.nm_linear_update(g, h, q8=q8, seed=3, bias=True), lambda q8=q8: api.nm_linear_update(g, h, nm="1:2", q8=q8, seed=3),
+                  lambda q8=q8: api.nm_linear_update(g, h, q8=q8, act=torch.relu(g)), lambda q8=q8: api.nm_linear_update(g[:, 1:9], h, q8=q8)]
+    forms += [lambda: api.nm_linear_update(g, h[:40]), lambda: api.nm_linear_update(g.float(), h)]
+
+    def outcome(f):
+        try:
+            return f()
+        except Exception as e:
+            return type(e), str(e)
+    native = [outcome(f) for f in forms]
+
+    class Absent:
+        def __getattr__(self, name):
+            return lambda *a: None
+    monkeypatch.setattr(api, "_native", Absent())
+    for f, a in zip(forms, native):
+        b = outcome(f)
+        if isinstance(a, torch.Tensor):
+            a, b = (a,), (b,)
+        assert len(a) == len(b)
+        for s, t in zip(a, b):
+            assert torch.equal(s, t) if isinstance(s, torch.Tensor) else s == t
