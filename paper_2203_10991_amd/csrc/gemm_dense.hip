@@ -11,6 +11,8 @@
 // through LDS, filled by direct loads.  A row that is contiguous along the reduction axis is eight chunks of 16 bytes, chunk c at position
 // c ^ (row / 2 % 8), which makes the 16-byte reads of consecutive rows free of bank conflicts; W of the input gradient is contiguous
 // along the features instead and is read with ds_read_b64_tr_b16 as the dense operand of the update GEMM is.
+// A workgroup takes tiles one after the other, and the stages run on across them: while a tile is converted and stored the next one's first stages
+// are on their way (16384 x 1024 -> 4096, four tiles a workgroup: 137 us with a workgroup to a tile and the tile through LDS, now 128).
 // A stage is four MFMA steps.  Behind the second the next stage has to have landed (one barrier) and this stage's last fragments are in
 // registers, so its buffer is free and the loads of the stage NS later go there; the next stage's first fragments are read under the last two steps.
 #include <hip/hip_runtime.h>
@@ -35,6 +37,13 @@ __device__ __forceinline__ void mfma_32x32x16(f32x16 &acc, const u32x4 &a, const
     asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
 }
 
+// zeros into the registers the block lives in
+__device__ __forceinline__ void acc_clear(f32x16 &acc)
+{
+    const bf16x8 z = {0, 0, 0, 0, 0, 0, 0, 0};
+    asm volatile("s_nop 4\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %1, 0" : "+a"(acc) : "v"(z));
+}
+
 union FragK { u32x4 u4; s16x4 q[2]; };
 
 struct DenseArg {
@@ -51,18 +60,20 @@ __global__ __launch_bounds__(WM * WN * 64) void dense_gemm_kernel(DenseArg p)
     constexpr int X_BYTES = TM * DK * 2, STAGE = X_BYTES + TN * DK * 2;
     constexpr int XL = TM / 8 / NW, WL = TN / 8 / NW, LPS = XL + WL;             // direct loads of a wave and stage
     constexpr int CPR = TN / 8, W_ROWS = 64 / CPR;                               // (NN) chunks of a row, rows of a load
-    constexpr int PITCH = TN * 2 + 16;                                           // bytes of a row of the output tile in LDS
-    constexpr int LDS = NS * STAGE > TM * PITCH ? NS * STAGE : TM * PITCH;
+    constexpr int LDS = NS * STAGE;
     static_assert(XL >= 1 && WL >= 1 && TM % (8 * NW) == 0 && TN % (8 * NW) == 0 && LDS <= 160 * 1024, "tile");
     __shared__ __attribute__((aligned(1024))) char S[LDS];
 
-    int tm, tn;
-    tile_of_workgroup((int)blockIdx.x, p.tiles_m, p.tiles_n, tm, tn);
-    tm = __builtin_amdgcn_readfirstlane(tm); tn = __builtin_amdgcn_readfirstlane(tn);
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WN, wn = wave % WN, hi = lane >> 5, l32 = lane & 31;
-    const int64_t m0 = (int64_t)tm * TM, n0 = (int64_t)tn * TN;
-    const int n = (int)((p.K + DK - 1) / DK), k_last = (int)(p.K - (int64_t)(n - 1) * DK);      // stages; reduction steps of the last one
+    const int n = (int)((p.K + DK - 1) / DK), k_last = (int)(p.K - (int64_t)(n - 1) * DK);      // stages of a tile; reduction steps of the last one
+    const int tiles = p.tiles_m * p.tiles_n;
+    auto place = [&](int tile, int64_t &m0, int64_t &n0) {
+        int tm, tn;
+        tile_of_workgroup(tile, p.tiles_m, p.tiles_n, tm, tn);
+        m0 = (int64_t)__builtin_amdgcn_readfirstlane(tm) * TM;
+        n0 = (int64_t)__builtin_amdgcn_readfirstlane(tn) * TN;
+    };
 
     f32x16 acc[AM][AN];
 #pragma unroll
@@ -78,40 +89,55 @@ __global__ __launch_bounds__(WM * WN * 64) void dense_gemm_kernel(DenseArg p)
     int x_k[2], w_k[2];                                                          // first reduction step of a lane's chunk in even and odd loads; NN: w_k[0] its row in load 0
     auto chunk_of = [&](int row) { return pos ^ ((row >> 1) & 7); };
 #pragma unroll
-    for (int d = 0; d < XL; ++d) {
-        const int row = (wave * XL + d) * 8 + r8;
-        x_src[d] = (uint32_t)((min(m0 + row, p.M - 1) - m0) * p.ldx * 2 + chunk_of(row) * 16);
-    }
-#pragma unroll
     for (int d = 0; d < 2; ++d) { x_k[d] = chunk_of((wave * XL + d) * 8 + r8) * 8; w_k[d] = chunk_of((wave * WL + d) * 8 + r8) * 8; }
     const int w_row = lane / CPR, w_pos = lane % CPR;
-#pragma unroll
-    for (int d = 0; d < WL; ++d) {
-        if constexpr (NN) {
-            const int row = (wave * WL + d) * W_ROWS + w_row, swz = TN >= 128 ? 4 * (row & 3) : 4 * ((row >> 1) & 1);
-            w_src[d] = (uint32_t)((row * p.N + min(n0 + 8 * (w_pos ^ swz), p.N - 8)) * 2);
-        } else {
-            const int row = (wave * WL + d) * 8 + r8;
-            w_src[d] = (uint32_t)((min(n0 + row, p.N - 1) - n0) * p.K * 2 + chunk_of(row) * 16);
-        }
-    }
-    const char *xp = (const char *)(p.x + m0 * p.ldx), *wp = (const char *)(NN ? p.w : p.w + n0 * p.K);
+    // the tile and stage whose loads are being issued
+    int f_tile = blockIdx.x, f_stage = 0;
+    const char *xp, *wp;
     const int64_t w_step = NN ? DK * p.N * 2 : DK * 2;
-    int ahead = 0;                                                               // stage whose loads are being issued
-    auto next_stage = [&]() { xp += DK * 2; wp += w_step; ++ahead; };
+    auto enter_tile = [&]() {
+        int64_t m0, n0;
+        place(f_tile, m0, n0);
+#pragma unroll
+        for (int d = 0; d < XL; ++d) {
+            const int row = (wave * XL + d) * 8 + r8;
+            x_src[d] = (uint32_t)((min(m0 + row, p.M - 1) - m0) * p.ldx * 2 + chunk_of(row) * 16);
+        }
+#pragma unroll
+        for (int d = 0; d < WL; ++d) {
+            if constexpr (NN) {
+                const int row = (wave * WL + d) * W_ROWS + w_row, swz = TN >= 128 ? 4 * (row & 3) : 4 * ((row >> 1) & 1);
+                w_src[d] = (uint32_t)((row * p.N + min(n0 + 8 * (w_pos ^ swz), p.N - 8)) * 2);
+            } else {
+                const int row = (wave * WL + d) * 8 + r8;
+                w_src[d] = (uint32_t)((min(n0 + row, p.N - 1) - n0) * p.K * 2 + chunk_of(row) * 16);
+            }
+        }
+        xp = (const char *)(p.x + m0 * p.ldx);
+        wp = (const char *)(NN ? p.w : p.w + n0 * p.K);
+    };
+    enter_tile();
+    auto next_stage = [&]() {
+        xp += DK * 2; wp += w_step;
+        if (++f_stage == n) {
+            f_stage = 0;
+            f_tile += gridDim.x;
+            if (f_tile < tiles) enter_tile();
+        }
+    };
     auto rsrc = [](const char *base, bool there) { return __builtin_amdgcn_make_buffer_rsrc((void *)base, 0, there ? 0x7fffffff : 0, 0x00020000); };
     auto fetch_one = [&](auto k_c, int buf) {
         constexpr int K = decltype(k_c)::value;
         char *stage = S + buf * STAGE;
-        const int left = ahead == n - 1 ? k_last : DK;                           // reduction steps the stage has
+        const int left = f_stage == n - 1 ? k_last : DK;                         // reduction steps the stage has
         if constexpr (K < XL) {
             const uint32_t src = x_k[K & 1] < left ? x_src[K] : 0xffffffffu;
-            load16_to_lds(rsrc(xp, ahead < n), stage + (wave * XL + K) * 1024, src, 0);
+            load16_to_lds(rsrc(xp, f_tile < tiles), stage + (wave * XL + K) * 1024, src, 0);
         } else {
             constexpr int d = K - XL;
             const int at = NN ? (wave * WL + d) * W_ROWS + w_row : w_k[d & 1];
             const uint32_t src = at < left ? w_src[d] : 0xffffffffu;
-            load16_to_lds(rsrc(wp, ahead < n), stage + X_BYTES + (wave * WL + d) * 1024, src, 0);
+            load16_to_lds(rsrc(wp, f_tile < tiles), stage + X_BYTES + (wave * WL + d) * 1024, src, 0);
         }
     };
     // zeros where a wave's loads of the last stage were out of range
@@ -183,10 +209,10 @@ __global__ __launch_bounds__(WM * WN * 64) void dense_gemm_kernel(DenseArg p)
     using std::integral_constant;
     using I0 = integral_constant<int, 0>; using I1 = integral_constant<int, 1>; using I2 = integral_constant<int, 2>; using I3 = integral_constant<int, 3>;
 
-    static_for<NS>([&](auto s_c) {
-        static_for<LPS>([&](auto k_c) { fetch_one(k_c, decltype(s_c)::value); });
+    for (int s = 0; s < NS; ++s) {
+        static_for<LPS>([&](auto k_c) { fetch_one(k_c, s); });
         next_stage();
-    });
+    }
     wait_vmcnt<(NS - 1) * LPS>();
     if (n == 1 && k_last < DK) clear_tail(0);
     __builtin_amdgcn_s_barrier();
@@ -194,73 +220,89 @@ __global__ __launch_bounds__(WM * WN * 64) void dense_gemm_kernel(DenseArg p)
     read(I0{}, 0);
     read(I1{}, 0);
     int buf = 0;
-    for (int s = 0; s < n; ++s) {
-        const int next = buf == NS - 1 ? 0 : buf + 1;
-        asm volatile("s_waitcnt lgkmcnt(%0)" : : "n"(READS) : "memory");
-        step(I0{}, I0{}, I0{}, 0);
-        read(I2{}, buf);
-        asm volatile("s_waitcnt lgkmcnt(%0)" : : "n"(READS) : "memory");
-        step(I1{}, I0{}, I0{}, 0);
-        read(I3{}, buf);
-        // the next stage has landed, and every wave has read all of this one
-        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" : : "n"((NS - 2) * LPS) : "memory");
-        if (s == n - 2 && k_last < DK) clear_tail(next);
-        __builtin_amdgcn_s_barrier();
+    for (int tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+        for (int s = 0; s < n; ++s) {
+            const int next = buf == NS - 1 ? 0 : buf + 1;
+            asm volatile("s_waitcnt lgkmcnt(%0)" : : "n"(READS) : "memory");
+            step(I0{}, I0{}, I0{}, 0);
+            read(I2{}, buf);
+            asm volatile("s_waitcnt lgkmcnt(%0)" : : "n"(READS) : "memory");
+            step(I1{}, I0{}, I0{}, 0);
+            read(I3{}, buf);
+            // the next stage (of this tile or the next) has landed, and every wave has read all of this one.  (Stores of the tile before count
+            // as loads do, and are older than any that is waited for.)
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" : : "n"((NS - 2) * LPS) : "memory");
+            if (k_last < DK && (s + 1 == n ? 0 : s + 1) == n - 1) clear_tail(next);
+            __builtin_amdgcn_s_barrier();
+            __builtin_amdgcn_sched_barrier(0);
+            step(I2{}, I0{}, integral_constant<int, LPS / 2>{}, buf);
+            read(I0{}, next);
+            step(I3{}, integral_constant<int, LPS / 2>{}, integral_constant<int, LPS>{}, buf);
+            read(I1{}, next);
+            next_stage();
+            buf = next;
+        }
+        // The tile leaves while the next one's first stages are on their way.  The matrix pipeline has to be done with it first.
+        int64_t m0, n0;
+        place(tile, m0, n0);
+        const int rows_left = (int)min(p.M - m0, (int64_t)TM);
         __builtin_amdgcn_sched_barrier(0);
-        step(I2{}, I0{}, integral_constant<int, LPS / 2>{}, buf);
-        read(I0{}, next);
-        step(I3{}, integral_constant<int, LPS / 2>{}, integral_constant<int, LPS>{}, buf);
-        read(I1{}, next);
-        next_stage();
-        buf = next;
-    }
-    // what ran ahead has landed, and the matrix pipeline is done, before the tile goes where the stages were
-    __builtin_amdgcn_sched_barrier(0);
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");
+        asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");
 #pragma unroll
-    for (int a = 0; a < AM; ++a)
+        for (int a = 0; a < AM; ++a)
 #pragma unroll
-        for (int b = 0; b < AN; ++b) acc_settled(acc[a][b]);
-    __syncthreads();
+            for (int b = 0; b < AN; ++b) acc_settled(acc[a][b]);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int b = 0; b < AN; ++b) {
+        for (int b = 0; b < AN; ++b) {
+            const int64_t f0 = n0 + (wn * AN + b) * 32;                          // a lane holds the features f0 + 8 g + 4 hi .. + 3 of a token
+            char *y0 = (char *)(p.y + m0 * p.ldy + f0);
+            // (through the scalar cache: a vector load would wait for the stages' loads, which are older)
+            uint2 add[4];
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            const int f = (wn * AN + b) * 32 + 8 * g + 4 * hi;                   // the lane's four features
-            float add[4] = {0.f, 0.f, 0.f, 0.f};
-            if (p.bias) {
-                const uint2 v = *(const uint2 *)(p.bias + min(n0 + f, p.N - 4));
-                add[0] = __uint_as_float(v.x << 16); add[1] = __uint_as_float(v.x & 0xffff0000u);
-                add[2] = __uint_as_float(v.y << 16); add[3] = __uint_as_float(v.y & 0xffff0000u);
+            for (int g = 0; g < 4; ++g) {
+                u32x4 v = {0u, 0u, 0u, 0u};
+                if (p.bias) v = *(const __attribute__((address_space(4))) u32x4 *)(uintptr_t)(p.bias + min(f0 + 8 * g, p.N - 8));
+                add[g] = hi ? make_uint2(v[2], v[3]) : make_uint2(v[0], v[1]);
             }
 #pragma unroll
             for (int a = 0; a < AM; ++a) {
-                float v[4];
+                const uint32_t row = (uint32_t)((wm * AM + a) * 32 + l32), at = row * (uint32_t)p.ldy * 2u + (uint32_t)hi * 16u;
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    v[j] = acc[a][b][4 * g + j] + add[j];
-                    if (p.relu) v[j] = v[j] <= 0.f ? 0.f : v[j];                 // (a NaN stays one)
+                for (int g = 0; g < 4; g += 2) {
+                    uint32_t w[2][2];
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) {
+                        float v[4];
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) {
+                            const uint32_t bits = j < 2 ? add[g + i].x : add[g + i].y;
+                            v[j] = acc[a][b][4 * (g + i) + j] + __uint_as_float(j & 1 ? bits & 0xffff0000u : bits << 16);
+                            if (p.relu) v[j] = v[j] <= 0.f ? 0.f : v[j];         // (a NaN stays one)
+                        }
+                        w[i][0] = pack_bf16_rne(v[0], v[1]);
+                        w[i][1] = pack_bf16_rne(v[2], v[3]);
+                    }
+                    // the two halves of the wave exchange, so that a lane holds eight features in a row: 8 g .. 8 g + 7, the upper half the eight behind
+                    const auto lo = __builtin_amdgcn_permlane32_swap(w[0][0], w[1][0], false, false), up = __builtin_amdgcn_permlane32_swap(w[0][1], w[1][1], false, false);
+                    if ((int)row < rows_left && f0 + 8 * g + 8 * hi < p.N) *(uint4 *)(y0 + at + 16u * g) = make_uint4(lo[0], up[0], lo[1], up[1]);
                 }
-                *(uint2 *)(S + ((wm * AM + a) * 32 + l32) * PITCH + f * 2) = make_uint2(pack_bf16_rne(v[0], v[1]), pack_bf16_rne(v[2], v[3]));
+                acc_clear(acc[a][b]);
+                __builtin_amdgcn_sched_barrier(0);
             }
-            __builtin_amdgcn_sched_barrier(0);
         }
     }
-    __syncthreads();
-    for (int i = tid; i < TM * (TN / 8); i += NW * 64) {
-        const int row = i / (TN / 8), c = (i % (TN / 8)) * 8;
-        if (m0 + row < p.M && n0 + c < p.N) *(uint4 *)(p.y + (m0 + row) * p.ldy + n0 + c) = *(const uint4 *)(S + row * PITCH + c * 2);
-    }
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");                  // what ran ahead
 }
 
 }  // namespace
 
 // Tiles of 64 x 64, 128 x 64, 128 x 128 (4 waves, two workgroups on a CU) or 256 x 256 (8 waves), the cheapest by what they were measured to take:
 // microseconds per stage of a tile alone on its CU and with a second one, of the largest by the share of the CUs that are busy, and per round.
-// Back to back from a graph, these / the vendor library's choice, us: 2048 x 1024 -> 1024 10 / 10.5 (input gradient 10 / 12), 1576 x 768 -> 3072 17.5 / 13.8
-// (20 / 22), 197 x 1024 -> 1024 8.0 / 6.0 (7.4 / 8.1), 12608 x 3072 -> 768 67 / 60 (78 / 72), 16384 x 1024 -> 4096 137 / 112 (112 / 106).  The small
-// tiles are bound by the path from the L2s to the CUs (24 KB a stage in 0.33 us on all of them: 18 TB/s), the largest by the matrix
-// pipes plus fill and drain of a round (5 us).
+// Back to back from a graph, these / the vendor library's choice, us: 2048 x 1024 -> 1024 10.3 / 10.2 (input gradient 10.4 / 11.8), 1576 x 768 -> 3072
+// 17.5 / 13.5 (21 / 22), 197 x 1024 -> 1024 8.5 / 5.9 (8.3 / 8.0), 6304 x 768 -> 3072 41 / 51 (43 / 38), 12608 x 3072 -> 768 65 / 59 (73 / 69),
+// 16384 x 1024 -> 4096 128 / 106 (112 / 103), with the ReLU 128 / 149.  The small tiles are bound by the path from the L2s to the CUs (24 KB a stage in
+// 0.33 us on all of them: 18 TB/s), the largest by the matrix pipes at the clock the power limit leaves.
 hipError_t launch_dense_gemm(bool nn, const void *x, int64_t ldx, const void *w, const void *bias, void *y, int64_t ldy, int64_t M, int64_t N, int64_t K,
                              bool relu, hipStream_t st)
 {
@@ -279,8 +321,8 @@ hipError_t launch_dense_gemm(bool nn, const void *x, int64_t ldx, const void *w,
     }
     p.tiles_m = (int)((M + tiles[best].tm - 1) / tiles[best].tm);
     p.tiles_n = (int)((N + tiles[best].tn - 1) / tiles[best].tn);
-    const int64_t wgs = (int64_t)p.tiles_m * p.tiles_n;
-    if (wgs > 0x7fffffffll) return hipErrorInvalidConfiguration;
+    const int64_t n_tiles = (int64_t)p.tiles_m * p.tiles_n, wgs = std::min<int64_t>(n_tiles, (int64_t)tiles[best].per_cu * NM_CUS);
+    if (n_tiles > 0x7fffffffll - 1024) return hipErrorInvalidConfiguration;
 #define NM_DENSE(WM, WN, AM, AN, NS)                                                                                                          \
     do {                                                                                                                                      \
         if (nn) hipLaunchKernelGGL((dense_gemm_kernel<WM, WN, AM, AN, true, NS>), dim3((unsigned)wgs), dim3(WM * WN * 64), 0, st, p);          \

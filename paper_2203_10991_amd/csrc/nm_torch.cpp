@@ -171,12 +171,12 @@ PyObject *linear_update(PyObject *, PyObject *const *a, Py_ssize_t n)
 }
 
 // ---- the dense products of a layer.  Which of them are the library's: plain bf16 tensors on the current device that the kernels read as they are, at
-// sizes at which they are the faster way.  Up to DENSE_MOST multiply-adds they take what the vendor library's take (0.7 to 1.2 of it from
-// size to size), and the call 6 us of the host's time instead of 20, which bounds layers of that size.  With a ReLU behind the
+// sizes at which they are the faster way.  Up to DENSE_MOST multiply-adds they take what the vendor library's take (0.7 to 1.4 of it from
+// size to size: gemm_dense.hip), and the call 6 us of the host's time instead of 20, which bounds layers of that size.  With a ReLU behind the
 // product, whatever its size, up to the reduction width DENSE_RELU_WIDTH: the pass over the output that is saved outweighs what the product may
-// lose (16384 x 1024 -> 4096 137 us against 112 and 44, 12608 x 3072 -> 768 67 against 60 and 8).  The framework's stay: autocast
-// regions, and operators that something watches.
-constexpr int64_t DENSE_MOST = 5000000000, DENSE_RELU_WIDTH = 2048;
+// lose (16384 x 1024 -> 4096 128 us against 106 and 43, 12608 x 768 -> 3072 73 against 60 and 24, but 16384 x 2048 -> 2048 122 against 95 and 23).
+// The framework's stay: autocast regions, and operators that something watches.
+constexpr int64_t DENSE_MOST = 5000000000, DENSE_RELU_WIDTH = 1536;
 
 bool dense_takes(const at::Tensor &a, const at::Tensor &w, const at::Tensor *bias, bool relu, int64_t width, int64_t &rows, int64_t &ld)
 {

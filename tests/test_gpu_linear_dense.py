@@ -33,7 +33,7 @@ SHAPES = [(1, 8, 8), (33, 40, 72), (64, 64, 64), (65, 72, 56), (197, 264, 256), 
           (5000, 2056, 264)]                                                                       # 256 x 256
 
 
-@pytest.mark.parametrize("T,O,I", SHAPES)
+@pytest.mark.parametrize("T,O,I", SHAPES + [(9000, 3080, 72), (9000, 4104, 200)])                       # several tiles to a workgroup, one and four stages long
 def test_linear_forward(T, O, I):
     from paper_2203_10991_amd import api
     torch.manual_seed(T + O)
