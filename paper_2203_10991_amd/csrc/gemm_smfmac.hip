@@ -664,7 +664,9 @@ hipError_t launch_splitk_reduce(const float *part, int slabs, float *dW, int64_t
 // ------------------------------------------------------------------------------------
 // tall_rows: rows [0, tall_rows) of dW are computed by the 384 x 256 kernel (tall_tiles_m tile rows), the rest by the
 // kernel of `shape` (tiles_m tile rows); 0 = that kernel alone.
-struct Plan { int shape; int tm, tn; int tiles_m, tiles_n; int slabs; int64_t groups_per_slab; int64_t tall_rows; int tall_tiles_m; };
+// us: predicted time where the plan weighs tiles against each other, else 0
+struct Plan { int shape; int tm, tn; int tiles_m, tiles_n; int slabs; int64_t groups_per_slab; int64_t tall_rows; int tall_tiles_m; double us; };
+constexpr int SMALL = 4;            // shape: 64 x 64 tiles, the tokens split over the waves (small_plan)
 
 // shifted: the dense operand is row-shifted views of one matrix (it stays in the caches: few-row problems are then
 // bound by the tile's own work, and the 64 x 256 tile wastes none of it; streamed from HBM, as a materialised
@@ -676,7 +678,7 @@ static Plan make_plan(int64_t T, int64_t O, int64_t I, bool shifted = false, boo
     Plan p;
     const int64_t groups = T / 16;
     const int CUS = 256;
-    p.tall_rows = 0; p.tall_tiles_m = 0;
+    p.tall_rows = 0; p.tall_tiles_m = 0; p.us = 0.0;
     // shape 0: 256x256 (8 waves), shape 1: 128x128 (4 waves, two workgroups fit a CU), shape 2: 64x256 (4 waves, one per CU),
     // shape 3: 256x128 (8 waves, one per CU)
     bool small = false;
@@ -761,6 +763,7 @@ static Plan make_plan(int64_t T, int64_t O, int64_t I, bool shifted = false, boo
             const int64_t tiles4 = (O + 383) / 384 * ((I + 255) / 256);
             const double cost4 = one_per_cu(tiles4, 0.60, 0.76, 0.0, s4), best = take0 ? std::min(cost0, take3 ? cost3 : cost0) : take3 ? cost3 : cost1;
             auto fits = [&](int64_t sl) { return beside + splitk_workspace_bytes((int)sl, O, I) <= static_scratch_bytes(); };
+            p.us = best;
             if (!shifted && whole_rows && s4 > 1 && cost4 < 0.83 * best && fits(s4) == fits(slabs)) {
                 p.shape = 0; p.tm = 256; p.tn = 256;
                 p.tall_rows = O; p.tall_tiles_m = (int)((O + 383) / 384);
@@ -774,6 +777,38 @@ static Plan make_plan(int64_t T, int64_t O, int64_t I, bool shifted = false, boo
     p.slabs = slabs;
     // whole trips of the kernel's LDS stages (2 groups each; one slab has no next one to run into)
     p.groups_per_slab = slab_groups(groups, p.slabs, p.tall_rows == O ? 2 * TALL_STAGES : 2 * NS);
+    return p;
+}
+
+// Small problems: the plan of the tile kernels, or 64 x 64 tiles with the tokens split over a workgroup's eight waves (gemm_smfmac_small.hip) and, for
+// long reductions, over at most eight slabs: never more than the tile kernels' plan, whose workspace a call is asked for whichever runs.  At most one
+// workgroup per CU (its LDS).  Up to 768 tokens it always measures faster (7.3-12.5 -> 4.7-8 us over sizes from 64 x 64 to 2400 x 250); beyond that by its
+// model -- 4.9 us, then per step of 32 tokens a wave 0.5 us, up to 0.75 with all CUs busy, or the tiles' operands at 6 TB/s, and the second pass --
+// against that of the tile kernels, which is 3 us short at these sizes.  Over 230 sizes, cold operands: taken by 133, none slower, 1024^3 17 -> 7.6 us,
+// 8192 x 256 x 256 15 -> 10.3; on average 4 % from the best choice.  Lines past it: 4480 x 320 x 440 14.0 -> 14.7, 24688 x 72 x 944 18.7 -> 30.
+// (The offsets of its loads are 32 bits wide: 32 rows of h.)
+static Plan small_plan(Plan p, int64_t T, int64_t O, int64_t I, int64_t ldh)
+{
+    const int64_t groups = T / 16, tiles = (O + 63) / 64 * ((I + 63) / 64);
+    if (groups == 0 || tiles > NM_CUS || ldh > (1 << 24)) return p;
+    int slabs = 0;
+    double best = groups < 48 ? 1e300 : p.us + 3.0;
+    for (const int s : {1, 2, 3, 4, 6, 8}) {
+        if (s > p.slabs || s * tiles > NM_CUS) break;
+        const int64_t steps = ((groups + s - 1) / s + 15) / 16;
+        const double loop = std::max((double)steps * (0.5 + 0.25 * (double)(s * tiles) / NM_CUS), (double)tiles * (double)T * 200.0 / 6e6);
+        const double us = 4.9 + loop + (s > 1 ? 2.6 + (double)(s + 1) * (double)O * (double)I * 4.0 / 3.5e6 : 0.0);
+        if (us < best) {
+            best = us;
+            slabs = s;
+        }
+    }
+    if (slabs > 0) {
+        p.shape = SMALL;
+        p.slabs = slabs;
+        p.groups_per_slab = slab_groups(groups, p.slabs, 2);
+        p.tall_rows = 0; p.tall_tiles_m = 0;
+    }
     return p;
 }
 
@@ -793,6 +828,8 @@ size_t update_gemm_smfmac_shifted_workspace(int64_t T, int64_t O, int64_t I)
 static hipError_t run_plan(const Plan &p, const OutTarget &tg, const void *vals, const uint16_t *meta, const void *h, int64_t ldh, int64_t h_rows,
                            int64_t T, int64_t O, int64_t I, hipStream_t st)
 {
+    if (p.shape == SMALL)
+        return launch_update_gemm_smfmac_small(vals, meta, h, ldh, h_rows, tg.out, tg.ldo, tg.slab_stride, p.slabs, p.groups_per_slab, T, O, I, tg.accumulate, st);
     if (p.tall_rows > 0) {
         dim3 tall_grid((unsigned)(p.tall_tiles_m * p.tiles_n), 1, (unsigned)p.slabs);
 #define NM_TALL(SLABS)                                                                                                              \
@@ -825,7 +862,7 @@ hipError_t launch_update_gemm_smfmac(const void *vals, const uint16_t *meta, con
                                      int64_t lddw, int64_t T, int64_t O, int64_t I, float beta, void *workspace,
                                      hipStream_t st, size_t beside)
 {
-    const Plan p = make_plan(T, O, I, false, true, beside);
+    const Plan p = small_plan(make_plan(T, O, I, false, true, beside), T, O, I, ldh);
     const int accumulate = beta != 0.f;
     const OutTarget tg = splitk_target(p.slabs, dW, lddw, workspace, O, I, accumulate);
     hipError_t e = run_plan(p, tg, vals, meta, h, ldh, T, T, O, I, st);
@@ -845,7 +882,7 @@ size_t update_gemm_smfmac_parts_bytes(int64_t h_rows, int64_t T, int64_t O, int6
 hipError_t launch_update_gemm_smfmac_parts(const void *vals, const uint16_t *meta, const void *h, int64_t ldh, int64_t h_rows, int64_t T,
                                            int64_t O, int64_t I, bool whole_rows, float *part, int *slabs, hipStream_t st)
 {
-    const Plan p = make_plan(T, O, I, false, whole_rows);
+    const Plan p = small_plan(make_plan(T, O, I, false, whole_rows), T, O, I, ldh);
     *slabs = p.slabs;
     return run_plan(p, OutTarget{part, I, O * I, 0}, vals, meta, h, ldh, h_rows, T, O, I, st);
 }

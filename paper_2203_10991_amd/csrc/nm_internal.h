@@ -49,6 +49,9 @@ hipError_t launch_update_gemm_smfmac(const void *vals, const uint16_t *meta, con
                                      int64_t lddw, int64_t T, int64_t O, int64_t I, float beta, void *workspace,
                                      hipStream_t st, size_t beside = 0);     // beside: workspace bytes of the call that are not this GEMM's
 size_t update_gemm_smfmac_workspace(int64_t T, int64_t O, int64_t I, size_t beside = 0);
+// small problems (gemm_smfmac_small.hip): slabs partial sums of groups_per_slab (even) token groups each, slab_stride apart; h_rows rows of h (at most T, the rest count as zeros)
+hipError_t launch_update_gemm_smfmac_small(const void *vals, const uint16_t *meta, const void *h, int64_t ldh, int64_t h_rows, float *out, int64_t ldo,
+                                           int64_t slab_stride, int slabs, int64_t groups_per_slab, int64_t T, int64_t O, int64_t I, int accumulate, hipStream_t st);
 size_t update_gemm_smfmac_shifted_workspace(int64_t T, int64_t O, int64_t I);
 // the same product with h given as n row-shifted views of one [rows x cb] matrix x (bf16): h[t][j*cb + c] = x[(t + rows[j])*ldx + c]
 hipError_t launch_update_gemm_smfmac_shifted(const void *vals, const uint16_t *meta, const void *x, int64_t ldx, int64_t cb,

@@ -135,6 +135,16 @@ template <int OFFSET> __device__ __forceinline__ u32x2 lds_read_b64(uint32_t add
     return r;
 }
 
+// waits for all LDS reads on their way; the fragments are operands, so that nothing made of them is placed above it
+__device__ __forceinline__ void wait_for_fragments(Frag8 (&a)[2], Frag16 (&b)[2], uint32_t &ix)
+{
+    asm volatile("s_waitcnt lgkmcnt(0)"
+                 : "+v"(a[0].u4), "+v"(a[1].u4), "+v"(b[0].q[0]), "+v"(b[0].q[1]), "+v"(b[0].q[2]), "+v"(b[0].q[3]), "+v"(b[1].q[0]), "+v"(b[1].q[1]),
+                   "+v"(b[1].q[2]), "+v"(b[1].q[3]), "+v"(ix)
+                 :
+                 : "memory");
+}
+
 // the 8-bit forms
 template <bool IN_VGPR = false>
 __device__ __forceinline__ void smfmac_32x32x64_bf8_fp8(f32x16 &acc, const i32x4 &a, const i32x8 &b, uint32_t idx)

@@ -261,14 +261,32 @@ def test_update_gemm_f32_with_a_short_last_round(nm, oracle, T, O, I, beta):
     run_case(nm, oracle, synth.Workload(f"f32_{T}x{O}x{I}", T, O, I, "f32", "2:4", 0.0, 2.0, 0.3), seed=T, beta=beta)
 
 
-@pytest.mark.parametrize("T,O,I", [(16 * 24 * 11, 64, 72),                # second pass over partial sums: one chain of eleven slabs
-                                   (16 * 24 * 12, 64, 72),                # ... eight chains, twelve slabs: four of them hold two
-                                   (16 * 24 * 23, 72, 264),               # ... a last trip of seven
-                                   (16 * 24 * 70, 64, 64),                # ... eight threads to a sum
-                                   (16 * 24 * 70, 296, 256)])             # ... too many sums for that
-def test_second_pass_over_partial_sums(nm, oracle, T, O, I):
-    run_case(nm, oracle, synth.Workload(f"slabs{T}x{O}x{I}", T, O, I, "bf16", "2:4", 0.0, 2.0, 0.3), seed=5)
-    run_case(nm, oracle, synth.Workload(f"slabs{T}x{O}x{I}", T, O, I, "bf16", "2:4", 0.0, 2.0, 0.3), seed=6, beta=1.0)
+@pytest.mark.parametrize("T,O,I", [(16, 8, 8), (16 * 9, 72, 56), (16 * 16, 64, 64), (16 * 17, 136, 64),     # fewer steps than waves; an odd group; one step each
+                                   (16 * 47, 1024, 1016), (16 * 49, 64, 2048),                              # every CU a tile; either side of 768 tokens
+                                   (1024, 1024, 1024), (16 * 131, 200, 72),                                 # past it, one slab
+                                   (16 * 24 * 11, 64, 72), (16 * 513, 256, 264), (16 * 1030, 72, 64)])      # in slabs, a shorter last one
+def test_small_tiles_with_the_tokens_split_over_waves(nm, oracle, T, O, I):
+    run_case(nm, oracle, synth.Workload(f"small{T}x{O}x{I}", T, O, I, "bf16", "2:4", 0.0, 2.0, 0.3), seed=5)
+    run_case(nm, oracle, synth.Workload(f"small{T}x{O}x{I}", T, O, I, "bf16", "1:2", 0.0, 2.0, 0.3), seed=6, beta=1.0)
+
+
+def test_small_tiles_leave_everything_beside_them_alone(nm):
+    """strides past the widths: NaN behind h's columns is not read, dW's own behind its columns is not written; sums of whole numbers are exact"""
+    T, O, I = 16 * 21, 72, 136
+    g = torch.randint(-3, 4, (T, O), device=DEV).to(torch.bfloat16)
+    g[:, 1::2] = 0                                                          # at most two of a block: kept as they are
+    gb = torch.zeros_like(g).view(T // 4, 4, O)
+    gb[:, 0::2] = g.view(T // 4, 4, O)[:, 0::2]
+    g = gb.view(T, O)
+    h = torch.randint(-3, 4, (T, I), device=DEV).to(torch.bfloat16)
+    wide_h = torch.full((T, I + 24), float("nan"), dtype=torch.bfloat16, device=DEV)
+    wide_h[:, :I] = h
+    wide_dW = torch.full((O, I + 8), 77.0, device=DEV)
+    v, m, _ = nm.mvue_prune_2of4(g, seed=1)
+    nm.nm_update_gemm(v, m, wide_h[:, :I], dW=wide_dW[:, :I])
+    torch.cuda.synchronize()
+    assert torch.equal(wide_dW[:, :I].double().cpu(), g.double().cpu().t() @ h.double().cpu())
+    assert (wide_dW[:, I:] == 77.0).all()
 
 
 @pytest.mark.parametrize("T,O,I", [(16, 128, 128), (32, 136, 8), (48, 8, 136), (16 * 5, 256, 264),           # one to three stages: the ring's edges

@@ -152,6 +152,19 @@ def test_update_gemm_q8_mid_sized_plans(nm, oracle, T, O, I, slabs, beta):
     gemm_case(nm, oracle, T, O, I, seed=T, beta=beta, sample=10)
 
 
+@pytest.mark.parametrize("T,O,I,slabs", [(32 * 132, 64, 64, 11),             # second pass over partial sums: one chain of eleven slabs
+                                         (32 * 280, 64, 80, 12),             # ... eight chains, twelve slabs: four of them hold two
+                                         (32 * 552, 72, 272, 46),            # ... a last trip of six
+                                         (32 * 1680, 64, 64, 140),           # ... eight threads to a sum
+                                         (32 * 1680, 296, 256, 70)])         # ... too many sums for that
+def test_second_pass_over_partial_sums(nm, oracle, T, O, I, slabs):
+    from paper_2203_10991_amd import api
+    assert api.nm_update_gemm_q8_workspace(T, O, I) == slabs * O * I * 4
+    sample = 16 if O > 64 else None
+    gemm_case(nm, oracle, T, O, I, seed=5, sample=sample)
+    gemm_case(nm, oracle, T, O, I, seed=6, beta=1.0, sample=sample)
+
+
 def test_update_gemm_q8_beta_one_large_tile(nm, oracle):
     gemm_case(nm, oracle, 128, 16 * 256, 16 * 256, seed=3, beta=1.0, sample=8)
 
