@@ -23,6 +23,7 @@
 #include "smfmac_common.h"       // static_for
 #include "prune_common.h"
 #include "prune_select.h"
+#include "q8_scale.h"
 
 namespace nm {
 
@@ -141,14 +142,17 @@ __device__ __forceinline__ uint32_t e4m3_of_words(uint32_t a, uint32_t b, float 
 
 template <bool Q8>
 __device__ __forceinline__ void grid_pack(uint32_t *tile, int64_t *offs, const uint16_t *__restrict__ x, const GridGeom &gg, bool cl, int64_t margin,
-                                          int64_t out_rows, const float *__restrict__ rec, void *__restrict__ out_, int64_t bx, int by)
+                                          int64_t out_rows, const LayerScale &ls, void *__restrict__ out_, int64_t bx, int by)
 {
     const int64_t r0 = bx * TILE_ROWS;                                  // out row
     const int c0 = by * TILE_COLS;
+    [[maybe_unused]] uint4 peaks;
+    if constexpr (Q8) peaks = layer_peaks(ls);
     load_tile(tile, offs, x, gg, cl, r0 - margin, c0);
+    float s = 1.0f;
+    if constexpr (Q8) s = layer_scale(ls, peaks, bx == 0 && by == 0);
     constexpr int PER = Q8 ? 16 : 8;                                    // channels of a 16-byte piece
     constexpr int PR = TILE_COLS / PER;                                 // pieces per row
-    const float s = Q8 ? rec[0] : 1.0f;
 #pragma unroll
     for (int k = 0; k < TILE_ROWS * PR / 256; ++k) {
         const int p = k * 256 + threadIdx.x, row = p / PR, piece = p % PR;
@@ -263,13 +267,14 @@ __device__ __forceinline__ void prune_grid(uint32_t *tile, int64_t *offs, const 
 
 template <int EST, bool HI0>
 __device__ __forceinline__ void prune_grid_q8(uint32_t *tile, int64_t *offs, const uint16_t *__restrict__ g, const GridGeom &gg, bool cl, int64_t n_groups,
-                                              uint32_t key0, uint32_t key1, uint32_t stream_id, const float *__restrict__ rec,
+                                              uint32_t key0, uint32_t key1, uint32_t stream_id, const LayerScale &ls,
                                               uint8_t *__restrict__ vals8, uint32_t *__restrict__ meta32, int64_t bx, int by)
 {
     const int64_t r0 = bx * TILE_ROWS;
     const int c0 = by * TILE_COLS, O = gg.C;
-    const float scale = rec[0];
+    const uint4 peaks = layer_peaks(ls);
     load_tile(tile, offs, g, gg, cl, r0, c0);
+    const float scale = layer_scale(ls, peaks, bx == 0 && by == 0);
 
     const int tid = threadIdx.x, cp = tid & 31, gi = tid >> 5;          // columns 2cp, 2cp+1 of token group gi (8 groups in the tile)
     const bool odd = cp & 1;
@@ -324,8 +329,8 @@ __device__ __forceinline__ void prune_grid_q8(uint32_t *tile, int64_t *offs, con
     if (col < O && G < n_groups) *(uint2 *)(meta32 + G * O + col) = make_uint2(md[0], md[1]);
 }
 
-struct PackTask { const uint16_t *x; GridGeom gg; bool cl; int64_t margin, out_rows; const float *rec; void *out; int64_t rows, blocks; };
-struct PruneTask { const uint16_t *g; GridGeom gg; bool cl; int64_t n_groups; const float *rec; void *vals, *meta; int64_t rows, blocks; };
+struct PackTask { const uint16_t *x; GridGeom gg; bool cl; int64_t margin, out_rows; LayerScale ls; void *out; int64_t rows, blocks; };
+struct PruneTask { const uint16_t *g; GridGeom gg; bool cl; int64_t n_groups; LayerScale ls; void *vals, *meta; int64_t rows, blocks; };
 
 // `rows` workgroups along the grid's rows (fastest) and the rest along the channels, for either task
 template <bool Q8, int EST, bool HI0>
@@ -336,11 +341,11 @@ __global__ __launch_bounds__(256) void grid_kernel(PackTask a, PruneTask b, uint
     // workgroup n is a pack where the running share of packs, n * blocks / total, steps at n+1
     const int64_t total = a.blocks + b.blocks, n = blockIdx.x, packs = n * a.blocks / total;
     if ((n + 1) * a.blocks / total != packs) {
-        grid_pack<Q8>(tile, offs, a.x, a.gg, a.cl, a.margin, a.out_rows, a.rec, a.out, packs % a.rows, (int)(packs / a.rows));
+        grid_pack<Q8>(tile, offs, a.x, a.gg, a.cl, a.margin, a.out_rows, a.ls, a.out, packs % a.rows, (int)(packs / a.rows));
     } else {
         const int64_t p = n - packs;
         if constexpr (Q8)
-            prune_grid_q8<EST, HI0>(tile, offs, b.g, b.gg, b.cl, b.n_groups, key0, key1, stream_id, b.rec, (uint8_t *)b.vals, (uint32_t *)b.meta,
+            prune_grid_q8<EST, HI0>(tile, offs, b.g, b.gg, b.cl, b.n_groups, key0, key1, stream_id, b.ls, (uint8_t *)b.vals, (uint32_t *)b.meta,
                                     p % b.rows, (int)(p / b.rows));
         else
             prune_grid<EST, HI0>(tile, offs, b.g, b.gg, b.cl, b.n_groups, key0, key1, stream_id, (uint16_t *)b.vals, (uint16_t *)b.meta,
@@ -348,14 +353,14 @@ __global__ __launch_bounds__(256) void grid_kernel(PackTask a, PruneTask b, uint
     }
 }
 
-// x, margin, out_rows, rec_x, x_out: the activations' rows [-margin, out_rows - margin), as bf16 (rec_x == nullptr) or e4m3.
-// est: 0 optimal MVUE 2:4, 1 approx-MVUE 2:4; T: the gradient's grid rows rounded up to whole groups (16 tokens, or 32 with rec_g: 8-bit)
-hipError_t launch_grid(const ConvShape &cs, const void *x, int64_t margin, int64_t out_rows, const float *rec_x, void *x_out, int est,
-                       const void *gy, int64_t T, uint64_t seed, uint32_t stream_id, const float *rec_g, void *vals, void *meta, hipStream_t st)
+// x, margin, out_rows, sx, x_out: the activations' rows [-margin, out_rows - margin), as bf16 (sx == nullptr) or e4m3.
+// est: 0 optimal MVUE 2:4, 1 approx-MVUE 2:4; T: the gradient's grid rows rounded up to whole groups (16 tokens, or 32 with sg: 8-bit)
+hipError_t launch_grid(const ConvShape &cs, const void *x, int64_t margin, int64_t out_rows, const LayerScale *sx, void *x_out, int est,
+                       const void *gy, int64_t T, uint64_t seed, uint32_t stream_id, const LayerScale *sg, void *vals, void *meta, hipStream_t st)
 {
-    const bool q8 = rec_g != nullptr;
-    PackTask a{(const uint16_t *)x, grid_geom(cs, cs.C), cs.x_channels_last, margin, out_rows, rec_x, x_out, (out_rows + TILE_ROWS - 1) / TILE_ROWS, 0};
-    PruneTask b{(const uint16_t *)gy, grid_geom(cs, cs.O), cs.g_channels_last, T / (q8 ? 32 : 16), rec_g, vals, meta, (T + TILE_ROWS - 1) / TILE_ROWS, 0};
+    const bool q8 = sg != nullptr;
+    PackTask a{(const uint16_t *)x, grid_geom(cs, cs.C), cs.x_channels_last, margin, out_rows, q8 ? *sx : LayerScale{}, x_out, (out_rows + TILE_ROWS - 1) / TILE_ROWS, 0};
+    PruneTask b{(const uint16_t *)gy, grid_geom(cs, cs.O), cs.g_channels_last, T / (q8 ? 32 : 16), q8 ? *sg : LayerScale{}, vals, meta, (T + TILE_ROWS - 1) / TILE_ROWS, 0};
     a.blocks = a.rows * ((cs.C + TILE_COLS - 1) / TILE_COLS);
     b.blocks = b.rows * ((cs.O + TILE_COLS - 1) / TILE_COLS);
     if (a.blocks + b.blocks > 0x7fffffffll) return hipErrorInvalidConfiguration;

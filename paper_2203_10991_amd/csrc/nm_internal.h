@@ -95,9 +95,13 @@ size_t update_gemm_q8_shifted_workspace(int64_t T, int64_t O, int64_t I);
 // 8-bit path, per-tensor scale and activation cast (q8_scale.hip).  rec: device float[4] = {s, 1/s, bits of max|t|, 0}
 // with s the largest power of two such that s * max|t| <= top (1 for an all-zero or non-finite tensor).
 hipError_t launch_q8_scale(int dt, const void *t, int64_t R, int64_t C, int64_t ld, float top, float *rec, hipStream_t st);
-// the scales of a layer's two bf16 tensors (R x C, row stride ld; not empty) in one pass of launches
-hipError_t launch_q8_scale_pair(const void *t0, int64_t R0, int64_t C0, int64_t ld0, float top0, float *rec0,
-                                const void *t1, int64_t R1, int64_t C1, int64_t ld1, float top1, float *rec1, hipStream_t st);
+// A tensor's scale inside a layer's call: the maxima of the n workgroups that passed over it (LAYER_PEAKS words of workspace, aligned to 16
+// bytes), the format's top, and the record that the first kernel to use the scale leaves for those behind it
+constexpr int LAYER_PEAKS = 256;
+struct LayerScale { uint32_t *peaks; int n; float top; float *rec; };
+// the maxima of a layer's two bf16 tensors (R x C, row stride ld; not empty) in one launch, into s0 and s1, whose n it sets
+hipError_t launch_layer_peaks(const void *t0, int64_t R0, int64_t C0, int64_t ld0, LayerScale &s0, const void *t1, int64_t R1, int64_t C1, int64_t ld1,
+                              LayerScale &s1, hipStream_t st);
 // h8 = e4m3(h * rec[0]), round to nearest even, magnitudes beyond 448 saturate
 hipError_t launch_cast_e4m3(int dt, const void *h, int64_t R, int64_t C, int64_t ld, const float *rec, uint8_t *h8, int64_t ld8,
                             hipStream_t st);
@@ -107,11 +111,11 @@ hipError_t launch_rw_mix_probe(const void *src, void *dst, int64_t n_blocks, hip
 // ---- layers (nm_layers.hip): a k x k, stride-1, "same" convolution on bf16 tensors [N, C, H, W] / [N, O, H, W], each stored
 // as channel planes or channels last
 struct ConvShape { int N, C, O, H, W, k; bool x_channels_last, g_channels_last; };
-// one launch: rows [-margin, out_rows - margin) of the zero-padded channels-last grid of the activations, as bf16 (rec_x == nullptr) or
-// e4m3(x * rec_x[0]), and the 2:4 prune (est 0 optimal, 1 approx-MVUE) of the gradient on that grid, T rows; rec_g: 8-bit
+// one launch: rows [-margin, out_rows - margin) of the zero-padded channels-last grid of the activations, as bf16 (sx == nullptr) or
+// e4m3(x * its scale), and the 2:4 prune (est 0 optimal, 1 approx-MVUE) of the gradient on that grid, T rows; sg: 8-bit
 // output in 32-token groups
-hipError_t launch_grid(const ConvShape &cs, const void *x, int64_t margin, int64_t out_rows, const float *rec_x, void *x_out, int est,
-                       const void *gy, int64_t T, uint64_t seed, uint32_t stream_id, const float *rec_g, void *vals, void *meta, hipStream_t st);
+hipError_t launch_grid(const ConvShape &cs, const void *x, int64_t margin, int64_t out_rows, const LayerScale *sx, void *x_out, int est,
+                       const void *gy, int64_t T, uint64_t seed, uint32_t stream_id, const LayerScale *sg, void *vals, void *meta, hipStream_t st);
 
 // The update GEMMs without their second pass: binary32 partial sums part[slabs][O][I], at most parts_bytes of them (one
 // slab where the plan has no split); the caller sums them with launch_finish.
@@ -137,9 +141,9 @@ constexpr int64_t LAYER_LD_MOST = (int64_t)1 << 21;       // largest row stride,
 hipError_t launch_prune_layer(int m, int est, const void *g, int64_t ldg, const void *act, int64_t lda, int64_t T, int64_t O, uint64_t seed,
                               uint32_t stream_id, void *gout, int64_t ldgo, void *vals, uint16_t *meta, float *csum, hipStream_t st);
 hipError_t launch_prune_q8_layer(int est, const void *g, int64_t ldg, int64_t T, int64_t O, uint64_t seed, uint32_t stream_id,
-                                 const float *rec, uint8_t *vals8, uint32_t *meta32, float *csum, hipStream_t st);
-hipError_t launch_cast_e4m3_rows(int dt, const void *h, int64_t R, int64_t C, int64_t ld, const float *rec, uint8_t *h8, int64_t ld8,
-                                 int64_t out_rows, hipStream_t st);
+                                 const LayerScale &ls, uint8_t *vals8, uint32_t *meta32, float *csum, hipStream_t st);
+hipError_t launch_cast_e4m3_layer(const void *h, int64_t R, int64_t C, int64_t ld, const LayerScale &ls, uint8_t *h8, int64_t ld8, int64_t out_rows,
+                                  hipStream_t st);
 hipError_t launch_pad_rows(const void *h, int64_t rows, int64_t C, int64_t ld, void *out, int64_t out_rows, hipStream_t st);
 size_t update_gemm_smfmac_parts_bytes(int64_t h_rows, int64_t T, int64_t O, int64_t I, bool *needs_whole_rows);
 hipError_t launch_update_gemm_smfmac_parts(const void *vals, const uint16_t *meta, const void *h, int64_t ldh, int64_t h_rows, int64_t T,

@@ -38,6 +38,13 @@ struct Carver {
     size_t take(size_t bytes) { const size_t at = used; used += (bytes + 255) / 256 * 256; return at; }
 };
 
+// the two scales of a call with 8-bit operands: maxima, then the records
+constexpr size_t SCALES = 2 * nm::LAYER_PEAKS * 4 + 32;
+nm::LayerScale scale_at(char *scales, int which, float top)
+{
+    return nm::LayerScale{(uint32_t *)scales + which * nm::LAYER_PEAKS, 0, top, (float *)(scales + 2 * nm::LAYER_PEAKS * 4) + which * 4};
+}
+
 struct ConvPlan {
     nm::ConvShape cs;
     int64_t T, margin, I;
@@ -56,7 +63,7 @@ ConvPlan plan_conv(const nm::ConvShape &cs, bool q8)
     p.margin = pad * Wp + pad;
     p.I = (int64_t)cs.C * cs.k * cs.k;
     Carver c;
-    p.recs = c.take(32);
+    p.recs = c.take(q8 ? SCALES : 0);
     p.x_full = c.take((size_t)(p.taps ? p.gemm.x_rows : p.T + 2 * p.margin) * cs.C * (q8 ? 1 : 2));
     p.vals = c.take((size_t)(p.T / 2) * cs.O * (q8 ? 1 : 2));
     p.meta = c.take((size_t)(p.T / gt) * cs.O * (q8 ? 4 : 2));
@@ -93,7 +100,7 @@ LinearPlan plan_linear(int64_t T, int64_t O, int64_t I, bool q8, bool bias)
     const size_t part = q8 ? nm::update_gemm_q8_parts_bytes(p.Tp, O, I) : nm::update_gemm_smfmac_parts_bytes(T, p.Tp, O, I, &whole);
     p.copy_h = !q8 && whole && p.Tp != T;
     Carver c;
-    p.recs = c.take(q8 ? 32 : 0);
+    p.recs = c.take(q8 ? SCALES : 0);
     p.h = c.take(q8 ? (size_t)p.Tp * I : p.copy_h ? (size_t)p.Tp * I * 2 : 0);
     p.vals = c.take((size_t)(p.Tp / 2) * O * (q8 ? 1 : 2));
     p.meta = c.take((size_t)p.groups * O * (q8 ? 4 : 2));
@@ -181,15 +188,15 @@ int nm_linear_update(const void *g, int64_t ldg, const void *act, int64_t lda, c
     int slabs = 1;
     nm::AlphaArg alpha(1.0f);
     if (q8) {
-        float *rec_g = (float *)(w + p.recs), *rec_h = rec_g + 4;
-        e = nm::launch_q8_scale_pair(g, T, O, ldg, 57344.0f / (float)m, rec_g, h, T, I, ldh, 448.0f, rec_h, st);
-        if (e == hipSuccess) e = nm::launch_cast_e4m3_rows(NM_DT_BF16, h, T, I, ldh, rec_h, (uint8_t *)(w + p.h), I, p.Tp, st);
+        nm::LayerScale sg = scale_at(w + p.recs, 0, 57344.0f / (float)m), sh = scale_at(w + p.recs, 1, 448.0f);
+        e = nm::launch_layer_peaks(g, T, O, ldg, sg, h, T, I, ldh, sh, st);
+        if (e == hipSuccess) e = nm::launch_cast_e4m3_layer(h, T, I, ldh, sh, (uint8_t *)(w + p.h), I, p.Tp, st);
         if (e == hipSuccess)
-            e = nm::launch_prune_q8_layer(m == 2 ? 3 : mode, g, ldg, T, O, seed, stream_id, rec_g, (uint8_t *)(w + p.vals), (uint32_t *)(w + p.meta), csum, st);
+            e = nm::launch_prune_q8_layer(m == 2 ? 3 : mode, g, ldg, T, O, seed, stream_id, sg, (uint8_t *)(w + p.vals), (uint32_t *)(w + p.meta), csum, st);
         if (e == hipSuccess)
             e = nm::launch_update_gemm_q8_parts((const uint8_t *)(w + p.vals), (const uint32_t *)(w + p.meta), (const uint8_t *)(w + p.h), I, p.Tp, O, I,
                                                 part, &slabs, st);
-        alpha = nm::AlphaArg(1.0f, rec_g, rec_h);
+        alpha = nm::AlphaArg(1.0f, sg.rec, sh.rec);
     } else {
         if (p.copy_h) e = nm::launch_pad_rows(h, T, I, ldh, w + p.h, p.Tp, st);
         if (e == hipSuccess)
@@ -230,7 +237,8 @@ int nm_conv_update(const void *gy, int gy_channels_last, const void *x, int x_ch
 
     hipStream_t st = (hipStream_t)hip_stream;
     char *w = (char *)workspace;
-    float *rec_g = (float *)(w + p.recs), *rec_x = rec_g + 4, *part = (float *)(w + p.part);
+    nm::LayerScale sg = scale_at(w + p.recs, 0, 57344.0f / 4.0f), sx = scale_at(w + p.recs, 1, 448.0f);
+    float *part = (float *)(w + p.part);
     int64_t shifts[32];
     const int pad = k / 2, Wp = (int)W + 2 * pad;
     for (int ky = 0; ky < k; ++ky)
@@ -240,12 +248,12 @@ int nm_conv_update(const void *gy, int gy_channels_last, const void *x, int x_ch
     nm::AlphaArg alpha(1.0f);
     if (q8) {
         // (the border's zeros do not change a maximum: the scales are those of the tensors as they are)
-        e = nm::launch_q8_scale_pair(gy, 1, gn, gn, 57344.0f / 4.0f, rec_g, x, 1, xn, xn, 448.0f, rec_x, st);
-        alpha = nm::AlphaArg(1.0f, rec_g, rec_x);
+        e = nm::launch_layer_peaks(gy, 1, gn, gn, sg, x, 1, xn, xn, sx, st);
+        alpha = nm::AlphaArg(1.0f, sg.rec, sx.rec);
     }
     if (e == hipSuccess)
-        e = nm::launch_grid(cs, x, p.margin, p.T + 2 * p.margin, q8 ? rec_x : nullptr, w + p.x_full, mode, gy, p.T, seed, stream_id,
-                            q8 ? rec_g : nullptr, w + p.vals, w + p.meta, st);
+        e = nm::launch_grid(cs, x, p.margin, p.T + 2 * p.margin, q8 ? &sx : nullptr, w + p.x_full, mode, gy, p.T, seed, stream_id,
+                            q8 ? &sg : nullptr, w + p.vals, w + p.meta, st);
     const char *x0 = w + p.x_full + p.margin * C * (q8 ? 1 : 2);
     if (e == hipSuccess && p.taps) {
         slabs = p.gemm.slabs;

@@ -19,6 +19,7 @@
 #include "smfmac_common.h"       // static_for
 #include "prune_common.h"
 #include "prune_select.h"
+#include "q8_scale.h"
 
 namespace nm {
 
@@ -40,7 +41,7 @@ struct ProdArg { const void *d; int64_t ldd; void *gout; int64_t ldgo; };
 // Offsets are 32 bits wide, from the first token group of the thread's WAVE: its 64 threads of four columns reach over 32 groups at
 // O = 8 and over fewer at any larger O, which at strides up to LAYER_LD_MOST is less than 2^32 bytes.  (From the WORKGROUP's first
 // group they would wrap at O = 8 beyond a stride of 2^20, with 32-token groups beyond 2^19.)
-struct LayerArg { int64_t T; float *csum; };
+struct LayerArg { int64_t T; float *csum; LayerScale scale; };       // scale: the 8-bit form's
 static_assert(32 * 32 * LAYER_LD_MOST * 2 <= (int64_t)1 << 32, "32-bit offsets inside a wave: 32 groups of 32 tokens, bf16");
 // first token group of the wave's threads
 __device__ __forceinline__ int64_t wave_first_group(int64_t ncg)
@@ -402,7 +403,9 @@ __global__ __launch_bounds__(256) void prune_compress_q8_kernel(
     const void *__restrict__ g_, int64_t n_groups, int64_t O, int64_t ldg, uint32_t key0, uint32_t key1, uint32_t stream_id,
     float scale, const float *__restrict__ scale_dev, uint8_t *__restrict__ vals8, uint32_t *__restrict__ meta32, LayerArg la)
 {
-    if (scale_dev) scale = scale_dev[0];            // the scale as a device value (element 0 of a scale record)
+    [[maybe_unused]] uint4 peaks;
+    if constexpr (LAYER) peaks = layer_peaks(la.scale);
+    else if (scale_dev) scale = scale_dev[0];       // the scale as a device value (element 0 of a scale record)
     auto philox = [&](uint64_t ctr, uint32_t domain, uint32_t (&w4)[4]) {
         if constexpr (HI0) philox4x32_10_uniform_c123((uint32_t)ctr, 0u, stream_id, domain, key0, key1, w4);
         else philox4x32_10((uint32_t)ctr, (uint32_t)(ctr >> 32), stream_id, domain, key0, key1, w4);
@@ -410,7 +413,8 @@ __global__ __launch_bounds__(256) void prune_compress_q8_kernel(
     constexpr int ESZ = DT == NM_DT_F32 ? 4 : 2, RB = VEC * ESZ;
     const int64_t ncg = O / VEC;
     const int64_t n = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (n >= n_groups * ncg) return;
+    // (LAYER: the last wave's threads past the end stay until it has its scale; what they load is past the last token and reads as zeros)
+    if ((LAYER ? n - (int64_t)(threadIdx.x & 63) : n) >= n_groups * ncg) return;
     const int64_t G = n / ncg;
     const int64_t col0 = (n - G * ncg) * VEC;
     const char *gp = (const char *)g_ + ((G * 32) * ldg + col0) * ESZ;
@@ -440,6 +444,10 @@ __global__ __launch_bounds__(256) void prune_compress_q8_kernel(
         }
     };
     fetch_rows(0);
+    if constexpr (LAYER) {
+        scale = layer_scale(la.scale, peaks, blockIdx.x == 0);
+        if (n >= n_groups * ncg) return;
+    }
 
     auto add_column = [&](auto b_c, int c) {             // the four rows of quad row b into the column's sum
         if constexpr (LAYER) {
@@ -564,14 +572,14 @@ static hipError_t launch_prune_q8_t(const void *g, int64_t T, int64_t O, int64_t
 // a layer's 8-bit prune (bf16, T tokens, T not necessarily a multiple of 32; T * O <= 2^34): est 0 optimal 2:4, 1 approx-MVUE 2:4,
 // 3 MVUE 1:2; csum (may be null): [ceil(T/32)][O] column sums of g per token group
 hipError_t launch_prune_q8_layer(int est, const void *g, int64_t ldg, int64_t T, int64_t O, uint64_t seed, uint32_t stream_id,
-                                 const float *rec, uint8_t *vals8, uint32_t *meta32, float *csum, hipStream_t st)
+                                 const LayerScale &ls, uint8_t *vals8, uint32_t *meta32, float *csum, hipStream_t st)
 {
     const int64_t groups = (T + 31) / 32, threads = groups * (O / 4), blocks = (threads + 255) / 256;
     if (threads == 0) return hipSuccess;
     if (blocks > 0x7fffffffll) return hipErrorInvalidConfiguration;
 #define NM_Q8L(EST)                                                                                                                     \
     hipLaunchKernelGGL((prune_compress_q8_kernel<NM_DT_BF16, EST, true, 4, true>), dim3((unsigned)blocks), dim3(256), 0, st, g, groups, O, \
-                       ldg, (uint32_t)seed, (uint32_t)(seed >> 32), stream_id, 1.0f, rec, vals8, meta32, LayerArg{T, csum})
+                       ldg, (uint32_t)seed, (uint32_t)(seed >> 32), stream_id, 1.0f, (const float *)nullptr, vals8, meta32, LayerArg{T, csum, ls})
     if (est == 3) NM_Q8L(3); else if (est == 1) NM_Q8L(1); else NM_Q8L(0);
 #undef NM_Q8L
     return hipGetLastError();

@@ -211,3 +211,27 @@ def test_linear_update_of_the_other_estimators_matches_the_oracle(oracle, q8, nm
     assert np.linalg.norm(got - want) <= 3e-3 * np.linalg.norm(want)
     gd = g.double()
     assert bool(((db.double() - gd.sum(0)).abs() <= 1e-5 * gd.abs().sum(0) + 2.0 ** -8 * gd.sum(0).abs()).all())
+
+
+# the layer's scales come from the maxima that each workgroup of the pass over its tensors leaves: 1, 2, a few and nearly all 256 of them a tensor, the
+# maximum in the first, in the last and in neither workgroup's share, no maximum (zeros), none that is finite
+@pytest.mark.parametrize("T,O,I", [(32, 8, 16), (1056, 64, 144), (4096, 512, 64), (40960, 64, 512)])
+def test_layer_scales_are_those_of_the_scale_records(T, O, I):
+    from paper_2203_10991_amd import api
+    torch.manual_seed(T)
+    g0 = torch.randn(T, O, device=DEV).to(torch.bfloat16).clamp(-3, 3)
+    h0 = torch.randn(T, I, device=DEV).to(torch.bfloat16).clamp(-3, 3)
+    for spot in ("first", "last", "middle", "zeros", "infinite"):
+        g, h = g0.clone(), h0.clone()
+        if spot == "zeros":
+            h.zero_()
+        else:
+            r = {"first": 0, "last": T - 1, "middle": T // 2, "infinite": T // 3}[spot]
+            h[r, -1 if spot == "last" else 0] = -1000.0
+            g[r, -1 if spot == "last" else 0] = float("inf") if spot == "infinite" else 3000.0
+        rg, rh = api.nm_q8_scale(g, 57344.0 / 4.0), api.nm_q8_scale(h, 448.0)
+        v, m = api.mvue_prune_2of4_q8(g, seed=3, stream_id=2, scale=rg)
+        want = api.nm_update_gemm_q8(v, m, api.nm_cast_e4m3(h, rh), alpha=float(rg[1] * rh[1]))
+        got = api.nm_linear_update(g, h, q8=True, seed=3, stream_id=2)[0]
+        # the same operands on the same plan, summed in the same order: one rounding to bf16 apart
+        assert torch.equal(got.view(torch.int16), want.to(torch.bfloat16).view(torch.int16)), spot
