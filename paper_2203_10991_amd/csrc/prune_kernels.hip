@@ -344,10 +344,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((DT == NM_D
 // Four bf16 columns per thread instead of eight: half the registers and LDS (seven or eight waves per SIMD instead of four or
 // five), twice the waves, half the chain of instructions between a wave's loads and its stores.  MVUE 1:2, whose arithmetic is
 // light, takes it at every size (32768 x 28672: 495 -> 463 us, 6.3 TB/s; 12608 x 2304: 18.3 -> 16.7; 512 x 512: 5.7 -> 4.0).
-// The two 2:4 estimators are bound by their arithmetic on large tensors, where the address and index work that two threads do
-// instead of one costs 1-2 % (32768 x 28672 optimal 530 -> 541 us); on small ones the launch is a wave or two deep per SIMD and
-// what counts is how long one wave takes: optimal 512 x 512 8.3 -> 5.3 us, 12608 x 768 12.7 -> 9.8, 12608 x 2304 22.3 -> 19.8,
-// 16384 x 4096 41.6 -> 41.0; approx-MVUE 17.7 -> 9.8, 26.3 -> 19.1, 44 -> 39, 81.3 -> 80.6.  Hence the line at 16384 x 4096.
+// The optimal 2:4 estimator is bound by its arithmetic on large tensors, where the address and index work that two threads do
+// instead of one costs 1-2 % (32768 x 28672 530 -> 541 us); below that the launch is a wave or two deep per SIMD and
+// what counts is how long one wave takes: 12608 x 768 12.7 -> 9.8, 12608 x 2304 22.3 -> 19.8, 16384 x 4096 41.6 -> 41.0.  Hence the line at 16384 x 4096.
+// (Approx-MVUE 2:4 and small tensors: the kernel below.)
 constexpr int64_t HALF_MOST = (int64_t)16384 * 4096;        // elements
 template <int M, int EST, bool HI0>
 __global__ __launch_bounds__(256) void prune_compress_half_kernel(
@@ -355,6 +355,118 @@ __global__ __launch_bounds__(256) void prune_compress_half_kernel(
     void *__restrict__ vals, uint16_t *__restrict__ meta)
 {
     prune_compress_body<NM_DT_BF16, M, EST, false, 0, HI0, true, 4>(g, n_groups, O, ldg, key0, key1, stream_id, vals, meta, nullptr, 0);
+}
+// The value of the lane at distance 1 or 2 among four lanes, and that of the Kth of them
+template <int D> __device__ __forceinline__ uint32_t lane_xor(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, D == 1 ? 0xB1 : 0x4E, 0xF, 0xF, true);      // quad_perm [1, 0, 3, 2] or [2, 3, 0, 1]
+}
+template <int K> __device__ __forceinline__ float lane_of_four(float v)
+{
+    return __uint_as_float((uint32_t)__builtin_amdgcn_mov_dpp((int)__float_as_uint(v), K * 0x55, 0xF, 0xF, true));
+}
+
+// Four lanes to a token group and four columns, a quad of each column to a lane (bf16, the two 2:4 estimators): four times the waves of the kernel
+// above and a quarter of its chain from a wave's loads to its stores, which is what a launch takes that is a few waves deep.  The kept pairs
+// are turned among the four lanes, so that a lane stores the eight values of one column.  Call indices below 2^32.
+// Graph replays over rotating buffers, the kernel above -> this: optimal 512 x 512 5.3 -> 3.0 us, 1584 x 3072 7.9 -> 6.2, 12608 x 768 10.3 -> 9.7, and past
+// the line 8192 x 2048 13.1 -> 13.8, 16384 x 4096 40.7 -> 44.1 (address and index work of four threads instead of one); approx-MVUE,
+// whose arithmetic is four times as long, 9.8 -> 4.1, 14.9 -> 9.4, 19.6 -> 15.8, 25 -> 23, 82 -> 79: at every size that the kernel above would take.
+// LAYER, PROD: as in prune_compress_body.
+constexpr int64_t QUAD_MOST = (int64_t)10 << 20, QUAD_MOST_APPROX = HALF_MOST;        // elements
+template <int EST> constexpr int64_t quad_most() { return EST == 1 ? QUAD_MOST_APPROX : QUAD_MOST; }
+template <int EST, int PROD = 0, bool LAYER = false>
+__global__ __launch_bounds__(256) void prune_compress_quad_kernel(
+    const void *__restrict__ g, int64_t n_groups, int64_t O, int64_t ldg, uint32_t key0, uint32_t key1, uint32_t stream_id,
+    void *__restrict__ vals, uint16_t *__restrict__ meta, ProdArg pa, LayerArg la)
+{
+    static_assert(PROD == 0 || LAYER, "the producer form of a layer");
+    const int64_t n = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (n >= n_groups * O) return;                                       // (O is a multiple of 8: the four lanes leave together)
+    const int b = (int)(n & 3);                                          // quad
+    const uint32_t cell = (uint32_t)(n >> 2), ncg = (uint32_t)(O / 4);
+    const uint32_t G = cell / ncg, col0 = (cell - G * ncg) * 4;
+    uint4 rows[4];
+    // LAYER: the wave's first token group, which the offsets count from (its 16 cells reach over 8 groups at O = 8), as in prune_compress_body
+    [[maybe_unused]] const uint32_t G0 = LAYER ? (uint32_t)__builtin_amdgcn_readfirstlane((int)G) : 0u;
+    if constexpr (LAYER) {
+        const int64_t t0 = (int64_t)G0 * 16;
+        auto rows_rsrc = [&](const void *p, int64_t ld) {
+            const int64_t bytes = (la.T - t0) * ld * 2;                  // (positive: the wave's first thread has a token)
+            return __builtin_amdgcn_make_buffer_rsrc((char *)p + t0 * ld * 2, 0, (int)(uint32_t)(bytes > 0xffffffffll ? 0xffffffffll : bytes), 0x00020000);
+        };
+        const uint32_t token = (G - G0) * 16 + 4 * b;
+        const auto rg = rows_rsrc(g, ldg);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) rows[r] = buffer_piece<8>(rg, ((token + r) * (uint32_t)ldg + col0) * 2u);
+        if constexpr (PROD != 0) {
+            const auto rd = rows_rsrc(pa.d, pa.ldd), ro = rows_rsrc(pa.gout, pa.ldgo);
+            uint4 f[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) f[r] = buffer_piece<8>(rd, ((token + r) * (uint32_t)pa.ldd + col0) * 2u);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                rows[r] = producer_row<NM_DT_BF16, PROD>(rows[r], f[r]);
+                buffer_put_piece<8>(ro, ((token + r) * (uint32_t)pa.ldgo + col0) * 2u, rows[r]);
+            }
+        }
+    } else {
+        const char *gp = (const char *)g + (((int64_t)G * 16 + 4 * b) * ldg + col0) * 2;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) rows[r] = load_global8(gp + (int64_t)r * ldg * 2);
+    }
+    constexpr int CALLS = EST == 1 ? 2 : 1;
+    const uint32_t call0 = ((G * 4 + b) * ncg + col0 / 4) * CALLS;
+    uint32_t words[4 * CALLS];
+#pragma unroll
+    for (int q = 0; q < CALLS; ++q) {
+        uint32_t w4[4];
+        philox4x32_10_uniform_c123(call0 + q, 0u, stream_id, EST == 1 ? 1u : 0u, key0, key1, w4);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) words[4 * q + j] = w4[j];
+    }
+    uint32_t w[4], nib[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        float v0, v1;
+        if constexpr (EST == 1)
+            select_2of4_approx(Row<NM_DT_BF16>::get(rows[0], c), Row<NM_DT_BF16>::get(rows[1], c), Row<NM_DT_BF16>::get(rows[2], c),
+                               Row<NM_DT_BF16>::get(rows[3], c), words[2 * c], words[2 * c + 1], v0, v1, nib[c]);
+        else
+            select_2of4<NM_DT_BF16>(Key<NM_DT_BF16>::make(rows[0], c, 0), Key<NM_DT_BF16>::make(rows[1], c, 1), Key<NM_DT_BF16>::make(rows[2], c, 2),
+                                    Key<NM_DT_BF16>::make(rows[3], c, 3), words[c], v0, v1, nib[c]);
+        w[c] = pack_bf16_rne(v0, v1);
+    }
+    if constexpr (LAYER) {                                               // column sums: quads in order, as one thread adds them
+        float cs[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            float q = Row<NM_DT_BF16>::get(rows[0], c) + Row<NM_DT_BF16>::get(rows[1], c);
+            q += Row<NM_DT_BF16>::get(rows[2], c) + Row<NM_DT_BF16>::get(rows[3], c);
+            cs[c] = lane_of_four<0>(q) + lane_of_four<1>(q);
+            cs[c] += lane_of_four<2>(q);
+            cs[c] += lane_of_four<3>(q);
+        }
+        if (b == 0) put_csum(la, G0, G, O, col0, cs);
+    }
+    // lane b, word c -> lane c, word b
+#pragma unroll
+    for (int i = 0; i < 4; i += 2) {
+        const uint32_t t = lane_xor<1>(b & 1 ? w[i] : w[i + 1]);
+        w[i] = b & 1 ? t : w[i];
+        w[i + 1] = b & 1 ? w[i + 1] : t;
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const uint32_t t = lane_xor<2>(b & 2 ? w[i] : w[i + 2]);
+        w[i] = b & 2 ? t : w[i];
+        w[i + 2] = b & 2 ? w[i + 2] : t;
+    }
+    *(uint4 *)((char *)vals + n * 16) = make_uint4(w[0], w[1], w[2], w[3]);      // ((G O + col0 + b) * 16)
+    uint32_t lo = (nib[0] | (nib[1] << 16)) << (4 * b), hi = (nib[2] | (nib[3] << 16)) << (4 * b);
+    lo |= lane_xor<1>(lo); hi |= lane_xor<1>(hi);
+    lo |= lane_xor<2>(lo); hi |= lane_xor<2>(hi);
+    if (b == 0) *(uint2 *)(meta + n) = make_uint2(lo, hi);
 }
 // the form of a layer's backward pass (bf16; see LayerArg): PROD = 2 with the ReLU's derivative in front, else 0
 template <int M, int EST, int PROD, bool NT>
@@ -999,13 +1111,17 @@ static hipError_t launch_prune_t(const void *g, int64_t T, int64_t O, int64_t ld
     // hi0: every call index (block / 4, or block / 2 for approx-MVUE's two words per block) lies below 2^32
     const bool hi0 = EST != 4 && (uint64_t)(T / M) * (uint64_t)O <= ((uint64_t)1 << (EST == 1 ? 33 : 34));
     const dim3 grid((unsigned)blocks);
-    const bool half = DT == NM_DT_BF16 && (EST == 0 || EST == 1) && threads % 32 == 0 && 2 * blocks <= 0x7fffffffll &&
+    const bool half = DT == NM_DT_BF16 && EST == 0 && threads % 32 == 0 && 2 * blocks <= 0x7fffffffll &&
                       (M == 2 || T * O <= HALF_MOST);             // (M = 4: hi0 holds at these sizes)
 #define NM_ARGS g, groups, O, ldg, (uint32_t)seed, (uint32_t)(seed >> 32), stream_id, vals, meta
     if (dense)
         hipLaunchKernelGGL((prune_compress_kernel<DT, M, EST, true>), grid, dim3(256), 0, st, NM_ARGS, dense, ldd);
-    else if (half) {
-        if constexpr (DT == NM_DT_BF16 && (EST == 0 || EST == 1)) {
+    else if (DT == NM_DT_BF16 && M == 4 && (EST == 0 || EST == 1) && T * O <= quad_most<EST>()) {
+        if constexpr (DT == NM_DT_BF16 && M == 4 && (EST == 0 || EST == 1))
+            hipLaunchKernelGGL((prune_compress_quad_kernel<EST>), dim3((unsigned)((groups * O + 255) / 256)), dim3(256), 0, st, NM_ARGS,
+                               ProdArg{}, LayerArg{});
+    } else if (half) {
+        if constexpr (DT == NM_DT_BF16 && EST == 0) {
             const dim3 half_grid((unsigned)((2 * threads + 255) / 256));
             if (hi0) hipLaunchKernelGGL((prune_compress_half_kernel<M, EST, true>), half_grid, dim3(256), 0, st, NM_ARGS);
             else if constexpr (M == 2) hipLaunchKernelGGL((prune_compress_half_kernel<M, EST, false>), half_grid, dim3(256), 0, st, NM_ARGS);
@@ -1072,8 +1188,14 @@ hipError_t launch_prune_layer(int m, int est, const void *g, int64_t ldg, const 
             hipLaunchKernelGGL((prune_layer_kernel<M, EST, PROD, false>), dim3((unsigned)blocks), dim3(256), 0, st, g, groups, O, ldg,  \
                                (uint32_t)seed, (uint32_t)(seed >> 32), stream_id, vals, meta, pa, la);                                  \
     } while (0)
-    if (act) { if (m == 2) NM_LAYER(2, 0, 2); else if (est == 1) NM_LAYER(4, 1, 2); else NM_LAYER(4, 0, 2); }
+#define NM_QUAD(EST, PROD)                                                                                                              \
+    hipLaunchKernelGGL((prune_compress_quad_kernel<EST, PROD, true>), dim3((unsigned)((groups * O + 255) / 256)), dim3(256), 0, st, g, groups, O, \
+                       ldg, (uint32_t)seed, (uint32_t)(seed >> 32), stream_id, vals, meta, pa, la)
+    if (m == 4 && est == 1 && T * O <= quad_most<1>()) { if (act) NM_QUAD(1, 2); else NM_QUAD(1, 0); }
+    else if (m == 4 && est == 0 && T * O <= quad_most<0>()) { if (act) NM_QUAD(0, 2); else NM_QUAD(0, 0); }
+    else if (act) { if (m == 2) NM_LAYER(2, 0, 2); else if (est == 1) NM_LAYER(4, 1, 2); else NM_LAYER(4, 0, 2); }
     else { if (m == 2) NM_LAYER(2, 0, 0); else if (est == 1) NM_LAYER(4, 1, 0); else NM_LAYER(4, 0, 0); }
+#undef NM_QUAD
 #undef NM_LAYER
     return hipGetLastError();
 }

@@ -235,3 +235,10 @@ def test_layer_scales_are_those_of_the_scale_records(T, O, I):
         got = api.nm_linear_update(g, h, q8=True, seed=3, stream_id=2)[0]
         # the same operands on the same plan, summed in the same order: one rounding to bf16 apart
         assert torch.equal(got.view(torch.int16), want.to(torch.bfloat16).view(torch.int16)), spot
+
+
+# the prune with a quad to a lane up to 10 * 2^20 elements (approx-MVUE 16384 * 4096), the one with a token group to a lane beyond it
+@pytest.mark.parametrize("form,T,O,I", [("2:4", 4096, 2560, 16), ("2:4", 4097, 2560, 16), ("relu", 4095, 2560, 16), ("relu", 5001, 2104, 16),
+                                        ("approx", 16380, 4096, 16), ("approx", 16385, 4104, 16)])
+def test_layers_on_either_side_of_the_prunes_lines(oracle, form, T, O, I):
+    test_linear_update_matches_the_oracle(oracle, form, T, O, I)

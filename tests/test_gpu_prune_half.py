@@ -50,3 +50,16 @@ def test_either_side_of_the_line_matches_the_oracle(oracle, T, which):
         v, m, _ = nm.mvue_prune_2of4(gd, seed=9, stream_id=1, mode=mode)
         ov, om, _ = (oracle.prune_2of4_approx if mode else oracle.prune_2of4)(g, 9, 1)
     assert np.array_equal(to_host(m), om) and np.array_equal(to_host(v), ov)
+
+
+@pytest.mark.parametrize("T", [4096, 4112])
+def test_either_side_of_a_quad_to_a_lane_matches_the_oracle(oracle, T):
+    """the optimal estimator with one quad to a lane up to 4096 x 2560, a padded stride"""
+    import paper_2203_10991_amd as nm
+    O = 2560
+    g = _g(T, O, 6)
+    d = torch.zeros((T, O + 24), dtype=torch.bfloat16, device=DEV)
+    d[:, :O] = to_dev(g)
+    v, m, _ = nm.mvue_prune_2of4(d[:, :O], seed=(5 << 32) + 9, stream_id=1)
+    ov, om, _ = oracle.prune_2of4(g, (5 << 32) + 9, 1)
+    assert np.array_equal(to_host(m), om) and np.array_equal(to_host(v), ov)
