@@ -52,13 +52,14 @@ size_t update_gemm_q8_shifted_workspace(int64_t T, int64_t O, int64_t I) { retur
 // the layer entry points (nm_layers.hip); the nine-tap plan as the real one's for images it takes
 struct ConvShape { int N, C, O, H, W, k; bool x_channels_last, g_channels_last; };
 struct ConvGemmPlan { int64_t T, x_rows; int slabs; };
-hipError_t launch_q8_scale_pair(const void *, int64_t, int64_t, int64_t, float, float *, const void *, int64_t, int64_t, int64_t, float, float *,
-                                hipStream_t) { ++g_launches; return hipSuccess; }
-hipError_t launch_cast_e4m3_rows(int, const void *, int64_t, int64_t, int64_t, const float *, uint8_t *, int64_t, int64_t, hipStream_t) { ++g_launches; return hipSuccess; }
+struct LayerScale { uint32_t *peaks; int n; float top; float *rec; };
+hipError_t launch_layer_peaks(const void *, int64_t, int64_t, int64_t, LayerScale &, const void *, int64_t, int64_t, int64_t, LayerScale &,
+                              hipStream_t) { ++g_launches; return hipSuccess; }
+hipError_t launch_cast_e4m3_layer(const void *, int64_t, int64_t, int64_t, const LayerScale &, uint8_t *, int64_t, int64_t, hipStream_t) { ++g_launches; return hipSuccess; }
 hipError_t launch_pad_rows(const void *, int64_t, int64_t, int64_t, void *, int64_t, hipStream_t) { ++g_launches; return hipSuccess; }
 hipError_t launch_prune_layer(int, int, const void *, int64_t, const void *, int64_t, int64_t, int64_t, uint64_t, uint32_t, void *, int64_t, void *, uint16_t *,
                               float *, hipStream_t) { ++g_launches; return hipSuccess; }
-hipError_t launch_prune_q8_layer(int, const void *, int64_t, int64_t, int64_t, uint64_t, uint32_t, const float *, uint8_t *, uint32_t *, float *,
+hipError_t launch_prune_q8_layer(int, const void *, int64_t, int64_t, int64_t, uint64_t, uint32_t, const LayerScale &, uint8_t *, uint32_t *, float *,
                                  hipStream_t) { ++g_launches; return hipSuccess; }
 size_t update_gemm_smfmac_parts_bytes(int64_t h_rows, int64_t T, int64_t O, int64_t I, bool *whole) { *whole = h_rows != T && O >= 1024; return (size_t)(2 * O * I * 4); }
 hipError_t launch_update_gemm_smfmac_parts(const void *, const uint16_t *, const void *, int64_t, int64_t, int64_t, int64_t, int64_t, bool, float *, int *slabs,
@@ -68,7 +69,7 @@ hipError_t launch_update_gemm_q8_parts(const uint8_t *, const uint32_t *, const 
                                        hipStream_t) { *slabs = 2; ++g_launches; return hipSuccess; }
 hipError_t launch_dense_gemm(bool, const void *, int64_t, const void *, const void *, void *, int64_t, int64_t, int64_t, int64_t, bool, hipStream_t) { ++g_launches; return hipSuccess; }
 hipError_t launch_finish_linear(const float *, int, int64_t, int64_t, void *, AlphaArg, const float *, int64_t, void *, hipStream_t) { ++g_launches; return hipSuccess; }
-hipError_t launch_grid(const ConvShape &, const void *, int64_t, int64_t, const float *, void *, int, const void *, int64_t, uint64_t, uint32_t, const float *, void *,
+hipError_t launch_grid(const ConvShape &, const void *, int64_t, int64_t, const LayerScale *, void *, int, const void *, int64_t, uint64_t, uint32_t, const LayerScale *, void *,
                        void *, hipStream_t) { ++g_launches; return hipSuccess; }
 bool conv_gemm_plan(const ConvShape &cs, bool, ConvGemmPlan &p)
 {
