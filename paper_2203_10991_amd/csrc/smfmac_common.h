@@ -177,8 +177,13 @@ __device__ __forceinline__ float4 sum_of_slabs(const float *at, int r, int slabs
 {
     if constexpr (CHAINS == 1) {
         float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+        if constexpr (R == 1) {             // few slabs of large outputs: four loads ahead measured 1 % slower (16384 x 4096 x 1024, 4 slabs: 89.8 -> 90.7 us a call)
+#pragma unroll 1
+            for (int z = r; z < slabs; z += R) add4(s, *(const float4 *)(at + (int64_t)z * slab_stride));
+        } else {
 #pragma unroll 4
-        for (int z = r; z < slabs; z += R) add4(s, *(const float4 *)(at + (int64_t)z * slab_stride));
+            for (int z = r; z < slabs; z += R) add4(s, *(const float4 *)(at + (int64_t)z * slab_stride));
+        }
         return s;
     } else {
         static_assert(R == 1, "one thread's chains");
