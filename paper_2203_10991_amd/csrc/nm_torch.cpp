@@ -173,10 +173,11 @@ PyObject *linear_update(PyObject *, PyObject *const *a, Py_ssize_t n)
 // ---- the dense products of a layer.  Which of them are the library's: plain bf16 tensors on the current device that the kernels read as they are, at
 // sizes at which they are the faster way.  Up to DENSE_MOST multiply-adds they take what the vendor library's take (0.7 to 1.4 of it from
 // size to size: gemm_dense.hip), and the call 6 us of the host's time instead of 20, which bounds layers of that size.  With a ReLU behind the
-// product, whatever its size, up to the reduction width DENSE_RELU_WIDTH: the pass over the output that is saved outweighs what the product may
-// lose (16384 x 1024 -> 4096 128 us against 106 and 43, 12608 x 768 -> 3072 73 against 60 and 24, but 16384 x 2048 -> 2048 122 against 95 and 23).
+// product, up to DENSE_RELU_MOST of them and the reduction width DENSE_RELU_WIDTH: the pass over the output that is saved outweighs what the product
+// may lose (a layer of 6143 x 640 -> 1320 157 us -> 126; 9143 x 1088 -> 2000 203.8 -> 202.9; alone 16384 x 2048 -> 2048 is 122 against 95 and 23).  Beyond,
+// the power limit takes the gain back: 16384 x 1024 -> 4096 alone 128 us against 106 and 43, inside its layer 445-462 us against 450-456.
 // The framework's stay: autocast regions, and operators that something watches.
-constexpr int64_t DENSE_MOST = 5000000000, DENSE_RELU_WIDTH = 1536;
+constexpr int64_t DENSE_MOST = 5000000000, DENSE_RELU_MOST = 20000000000, DENSE_RELU_WIDTH = 1536;
 
 bool dense_takes(const at::Tensor &a, const at::Tensor &w, const at::Tensor *bias, bool relu, int64_t width, int64_t &rows, int64_t &ld)
 {
@@ -184,7 +185,7 @@ bool dense_takes(const at::Tensor &a, const at::Tensor &w, const at::Tensor *bia
     const int64_t O = w.size(0), I = w.size(1);
     rows = width ? a.numel() / width : 0;
     if (rows < 1 || O < 1 || I < 1 || O % 8 || I % 8 || O > (1 << 21) || I > (1 << 21) || rows > ((int64_t)1 << 34) / O || rows > ((int64_t)1 << 36) / I) return false;
-    if (rows * O > DENSE_MOST / I && !(relu && I <= DENSE_RELU_WIDTH)) return false;
+    if (rows * O > (relu && I <= DENSE_RELU_WIDTH ? DENSE_RELU_MOST : DENSE_MOST) / I) return false;
     if (a.dim() == 2) ld = rows > 1 ? a.stride(0) : width;
     else if (a.is_contiguous()) ld = width;
     else return false;
