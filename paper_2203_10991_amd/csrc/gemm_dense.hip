@@ -194,6 +194,29 @@ __global__ __launch_bounds__(WM * WN * 64) void dense_gemm_kernel(DenseArg p)
             static_for<AN>([&](auto b_c) { constexpr int b = decltype(b_c)::value; lds_refill_b128<b * 32 * DK * 2>(wf[set][b].u4, wa); });
         }
     };
+    // The fragments on their way are in their registers.  Stands wherever compiled code lies between a read and the wait for it, which at a loop's head
+    // moves fragments to other registers (and would move what was there before); the empty statements keep the registers theirs until then.
+    auto reads_landed = [&]() {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+#pragma unroll
+            for (int a = 0; a < AM; ++a) asm volatile("" : : "v"(xf[s][a].u4));
+#pragma unroll
+            for (int b = 0; b < AN; ++b) asm volatile("" : : "v"(wf[s][b].u4));
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // the same of the accumulators and the matrix pipeline
+    auto sums_settled = [&]() {
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");
+#pragma unroll
+        for (int a = 0; a < AM; ++a)
+#pragma unroll
+            for (int b = 0; b < AN; ++b) acc_settled(acc[a][b]);
+        __builtin_amdgcn_sched_barrier(0);
+    };
     // MFMA step kk; the loads [lo, hi) of a stage are spread behind its MFMAs
     auto step = [&](auto kk_c, auto lo_c, auto hi_c, int buf) {
         constexpr int set = decltype(kk_c)::value % 2, lo = decltype(lo_c)::value, n_l = decltype(hi_c)::value - lo, NM = AM * AN;
@@ -219,78 +242,86 @@ __global__ __launch_bounds__(WM * WN * 64) void dense_gemm_kernel(DenseArg p)
     __builtin_amdgcn_sched_barrier(0);
     read(I0{}, 0);
     read(I1{}, 0);
-    int buf = 0;
-    for (int tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
-        for (int s = 0; s < n; ++s) {
-            const int next = buf == NS - 1 ? 0 : buf + 1;
-            asm volatile("s_waitcnt lgkmcnt(%0)" : : "n"(READS) : "memory");
-            step(I0{}, I0{}, I0{}, 0);
-            read(I2{}, buf);
-            asm volatile("s_waitcnt lgkmcnt(%0)" : : "n"(READS) : "memory");
-            step(I1{}, I0{}, I0{}, 0);
-            read(I3{}, buf);
-            // the next stage (of this tile or the next) has landed, and every wave has read all of this one.  (Stores of the tile before count
-            // as loads do, and are older than any that is waited for.)
-            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" : : "n"((NS - 2) * LPS) : "memory");
-            if (k_last < DK && (s + 1 == n ? 0 : s + 1) == n - 1) clear_tail(next);
-            __builtin_amdgcn_s_barrier();
-            __builtin_amdgcn_sched_barrier(0);
-            step(I2{}, I0{}, integral_constant<int, LPS / 2>{}, buf);
-            read(I0{}, next);
-            step(I3{}, integral_constant<int, LPS / 2>{}, integral_constant<int, LPS>{}, buf);
-            read(I1{}, next);
-            next_stage();
-            buf = next;
-        }
-        // The tile leaves while the next one's first stages are on their way.  The matrix pipeline has to be done with it first.
-        int64_t m0, n0;
-        place(tile, m0, n0);
-        const int rows_left = (int)min(p.M - m0, (int64_t)TM);
+    int buf = 0, s = 0, tile = blockIdx.x;                                       // the stage that is multiplied: its buffer, its number in its tile
+    // a stage's first half; behind it every read has landed, so that the loop below closes with none on its way
+    auto open = [&]() {
+        const int next = buf == NS - 1 ? 0 : buf + 1;
+        asm volatile("s_waitcnt lgkmcnt(%0)" : : "n"(READS) : "memory");
+        step(I0{}, I0{}, I0{}, 0);
+        read(I2{}, buf);
+        asm volatile("s_waitcnt lgkmcnt(%0)" : : "n"(READS) : "memory");
+        step(I1{}, I0{}, I0{}, 0);
+        read(I3{}, buf);
+        // the next stage (of this tile or the next) has landed, and every wave has read all of this one.  (Loads are counted down in the order they
+        // were issued, and the stores of the tile before with them.  At a tile's first stage those are younger than the loads that are
+        // waited for, so that more has to have landed than is needed; from then on they are older.)
+        wait_vmcnt<(NS - 2) * LPS>();
+        reads_landed();
+        if (k_last < DK && (s + 1 == n ? 0 : s + 1) == n - 1) clear_tail(next);
+        __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
-        asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");
+    };
+    open();
+    for (;;) {
+        const int next = buf == NS - 1 ? 0 : buf + 1;
+        step(I2{}, I0{}, integral_constant<int, LPS / 2>{}, buf);
+        read(I0{}, next);
+        step(I3{}, integral_constant<int, LPS / 2>{}, integral_constant<int, LPS>{}, buf);
+        read(I1{}, next);
+        next_stage();
+        buf = next;
+        if (++s == n) {
+            // The tile leaves while the next one's first stages are on their way.  The matrix pipeline has to be done with it first, and the reads of the
+            // next tile's first fragments with their registers.
+            s = 0;
+            int64_t m0, n0;
+            place(tile, m0, n0);
+            const int rows_left = (int)min(p.M - m0, (int64_t)TM);
+            reads_landed();
+            sums_settled();
 #pragma unroll
-        for (int a = 0; a < AM; ++a)
+            for (int b = 0; b < AN; ++b) {
+                const int64_t f0 = n0 + (wn * AN + b) * 32;                          // a lane holds the features f0 + 8 g + 4 hi .. + 3 of a token
+                char *y0 = (char *)(p.y + m0 * p.ldy + f0);
+                // (through the scalar cache: a vector load would wait for the stages' loads, which are older)
+                uint2 add[4];
 #pragma unroll
-            for (int b = 0; b < AN; ++b) acc_settled(acc[a][b]);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int b = 0; b < AN; ++b) {
-            const int64_t f0 = n0 + (wn * AN + b) * 32;                          // a lane holds the features f0 + 8 g + 4 hi .. + 3 of a token
-            char *y0 = (char *)(p.y + m0 * p.ldy + f0);
-            // (through the scalar cache: a vector load would wait for the stages' loads, which are older)
-            uint2 add[4];
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                u32x4 v = {0u, 0u, 0u, 0u};
-                if (p.bias) v = *(const __attribute__((address_space(4))) u32x4 *)(uintptr_t)(p.bias + min(f0 + 8 * g, p.N - 8));
-                add[g] = hi ? make_uint2(v[2], v[3]) : make_uint2(v[0], v[1]);
-            }
-#pragma unroll
-            for (int a = 0; a < AM; ++a) {
-                const uint32_t row = (uint32_t)((wm * AM + a) * 32 + l32), at = row * (uint32_t)p.ldy * 2u + (uint32_t)hi * 16u;
-#pragma unroll
-                for (int g = 0; g < 4; g += 2) {
-                    uint32_t w[2][2];
-#pragma unroll
-                    for (int i = 0; i < 2; ++i) {
-                        float v[4];
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) {
-                            const uint32_t bits = j < 2 ? add[g + i].x : add[g + i].y;
-                            v[j] = acc[a][b][4 * (g + i) + j] + __uint_as_float(j & 1 ? bits & 0xffff0000u : bits << 16);
-                            if (p.relu) v[j] = v[j] <= 0.f ? 0.f : v[j];         // (a NaN stays one)
-                        }
-                        w[i][0] = pack_bf16_rne(v[0], v[1]);
-                        w[i][1] = pack_bf16_rne(v[2], v[3]);
-                    }
-                    // the two halves of the wave exchange, so that a lane holds eight features in a row: 8 g .. 8 g + 7, the upper half the eight behind
-                    const auto lo = __builtin_amdgcn_permlane32_swap(w[0][0], w[1][0], false, false), up = __builtin_amdgcn_permlane32_swap(w[0][1], w[1][1], false, false);
-                    if ((int)row < rows_left && f0 + 8 * g + 8 * hi < p.N) *(uint4 *)(y0 + at + 16u * g) = make_uint4(lo[0], up[0], lo[1], up[1]);
+                for (int g = 0; g < 4; ++g) {
+                    u32x4 v = {0u, 0u, 0u, 0u};
+                    if (p.bias) v = *(const __attribute__((address_space(4))) u32x4 *)(uintptr_t)(p.bias + min(f0 + 8 * g, p.N - 8));
+                    add[g] = hi ? make_uint2(v[2], v[3]) : make_uint2(v[0], v[1]);
                 }
-                acc_clear(acc[a][b]);
-                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int a = 0; a < AM; ++a) {
+                    const uint32_t row = (uint32_t)((wm * AM + a) * 32 + l32), at = row * (uint32_t)p.ldy * 2u + (uint32_t)hi * 16u;
+#pragma unroll
+                    for (int g = 0; g < 4; g += 2) {
+                        uint32_t w[2][2];
+#pragma unroll
+                        for (int i = 0; i < 2; ++i) {
+                            float v[4];
+#pragma unroll
+                            for (int j = 0; j < 4; ++j) {
+                                const uint32_t bits = j < 2 ? add[g + i].x : add[g + i].y;
+                                v[j] = acc[a][b][4 * (g + i) + j] + __uint_as_float(j & 1 ? bits & 0xffff0000u : bits << 16);
+                                if (p.relu) v[j] = v[j] <= 0.f ? 0.f : v[j];         // (a NaN stays one)
+                            }
+                            w[i][0] = pack_bf16_rne(v[0], v[1]);
+                            w[i][1] = pack_bf16_rne(v[2], v[3]);
+                        }
+                        // the two halves of the wave exchange, so that a lane holds eight features in a row: 8 g .. 8 g + 7, the upper half the eight behind
+                        const auto lo = __builtin_amdgcn_permlane32_swap(w[0][0], w[1][0], false, false), up = __builtin_amdgcn_permlane32_swap(w[0][1], w[1][1], false, false);
+                        if ((int)row < rows_left && f0 + 8 * g + 8 * hi < p.N) *(uint4 *)(y0 + at + 16u * g) = make_uint4(lo[0], up[0], lo[1], up[1]);
+                    }
+                    acc_clear(acc[a][b]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
             }
+            sums_settled();                                                          // (of the zeros)
+            tile += gridDim.x;
         }
+        if (tile >= tiles) break;
+        open();
     }
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");                  // what ran ahead
 }

@@ -26,3 +26,14 @@ def to_host(t: torch.Tensor) -> np.ndarray:
 def first_mismatch(a: np.ndarray, b: np.ndarray):
     ne = np.argwhere(a != b)
     return None if len(ne) == 0 else tuple(int(v) for v in ne[0])
+
+
+def kernels_of(call):
+    """names of the kernels that `call` launches, in order, so that a test can assert the route it means to take"""
+    from torch.profiler import ProfilerActivity, profile
+    call()
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CPU, ProfilerActivity.CUDA]) as p:
+        call()
+        torch.cuda.synchronize()
+    return [e.name for e in sorted(p.events(), key=lambda e: e.time_range.start) if e.device_type == torch.autograd.DeviceType.CUDA]

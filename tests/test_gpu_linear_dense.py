@@ -4,7 +4,7 @@ them, and those that do not."""
 import pytest
 import torch
 
-from gpu_util import DEV
+from gpu_util import DEV, kernels_of
 
 pytestmark = pytest.mark.gpu
 
@@ -33,7 +33,31 @@ SHAPES = [(1, 8, 8), (33, 40, 72), (64, 64, 64), (65, 72, 56), (197, 264, 256), 
           (5000, 2056, 264)]                                                                       # 256 x 256
 
 
-@pytest.mark.parametrize("T,O,I", SHAPES + [(9000, 3080, 72), (9000, 4104, 200)])                       # several tiles to a workgroup, one and four stages long
+# several tiles to a workgroup: stages that run on from one into the next, stores on their way with them, accumulators cleared in place, a reduction axis that
+# ends inside a stage every time
+SEVERAL_FORWARD = [(2130, 1400, 1440, "2, 2, 1, 1, false, 4"), (5116, 1568, 416, "2, 2, 2, 1, false, 3"), (9000, 3080, 72, "2, 2, 2, 2, false, 2"),
+                   (9000, 4104, 200, "2, 2, 2, 2, false, 2"), (13357, 2016, 736, "2, 4, 4, 2, false, 2")]
+SEVERAL_GRAD = [(3886, 864, 720, "2, 2, 1, 1, true, 4"), (16251, 440, 528, "2, 2, 2, 1, true, 3"), (6390, 264, 2544, "2, 2, 2, 2, true, 2"),
+                (13357, 736, 2016, "2, 4, 4, 2, true, 2")]
+
+
+@pytest.mark.parametrize("T,O,I,kernel", SEVERAL_FORWARD)
+def test_linear_forward_of_several_tiles_to_a_workgroup(T, O, I, kernel):
+    from paper_2203_10991_amd import api
+    test_linear_forward(T, O, I)
+    x, w = torch.zeros(T, I, device=DEV, dtype=torch.bfloat16), torch.zeros(O, I, device=DEV, dtype=torch.bfloat16)
+    assert any(f"dense_gemm_kernel<{kernel}>" in k for k in kernels_of(lambda: api.nm_linear_forward(x, w)))
+
+
+@pytest.mark.parametrize("T,O,I,kernel", SEVERAL_GRAD)
+def test_linear_input_grad_of_several_tiles_to_a_workgroup(T, O, I, kernel):
+    from paper_2203_10991_amd import api
+    test_linear_input_grad(T, O, I)
+    g, w = torch.zeros(T, O, device=DEV, dtype=torch.bfloat16), torch.zeros(O, I, device=DEV, dtype=torch.bfloat16)
+    assert any(f"dense_gemm_kernel<{kernel}>" in k for k in kernels_of(lambda: api.nm_linear_input_grad(g, w)))
+
+
+@pytest.mark.parametrize("T,O,I", SHAPES)
 def test_linear_forward(T, O, I):
     from paper_2203_10991_amd import api
     torch.manual_seed(T + O)
