@@ -229,6 +229,17 @@ __global__ __launch_bounds__(CG_WAVES * 64) void conv_gemm_kernel(
     // the matrix pipeline may still write the last accumulators; loads and reads that ran ahead must not land in the exchange
     __builtin_amdgcn_sched_barrier(0);
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");
+    // (the fragments are not used any more, but their registers are theirs until here: a read that ran ahead writes to them)
+#pragma unroll
+    for (int set = 0; set < 2; ++set) {
+        asm volatile("" : : "v"(ix[set].w2));
+#pragma unroll
+        for (int a = 0; a < 2; ++a) asm volatile("" : : "v"(af[set][a].u4));
+    }
+#pragma unroll
+    for (int b = 0; b < 3; ++b)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) asm volatile("" : : "v"(bf[b].q[j]));
 #pragma unroll
     for (int a = 0; a < 2; ++a)
 #pragma unroll

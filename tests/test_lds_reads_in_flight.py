@@ -12,7 +12,7 @@ import pytest
 
 from paper_2203_10991_amd import build
 
-SOURCES = ["gemm_dense", "gemm_f32_split", "gemm_smfmac", "gemm_smfmac_q8", "gemm_smfmac_small"]
+SOURCES = ["gemm_conv", "gemm_dense", "gemm_f32_split", "gemm_smfmac", "gemm_smfmac_q8", "gemm_smfmac_small"]
 REGISTER = re.compile(r"\b([va])(?:\[(\d+):(\d+)\]|(\d+)\b)")
 MFMA_WAIT_STATES = 20                # instructions (s_nop n: n + 1) behind the longest MFMA, of 16 passes, until its result may be read or overwritten
 
