@@ -39,12 +39,12 @@ struct NoGil {                                                       // as a cty
     ~NoGil() { PyEval_RestoreThread(state); }
 };
 
-// a tensor (or parameter, no other subclass) on the GPU, or nullptr
+// a tensor (or parameter, no other subclass) on the GPU with memory of its own (a batch of gradients under vmap has none), or nullptr
 const at::Tensor *gpu_tensor(PyObject *o)
 {
     if (!THPVariable_CheckExact(o)) return nullptr;
     const at::Tensor &t = THPVariable_Unpack(o);
-    return t.defined() && t.is_cuda() && t.layout() == at::kStrided ? &t : nullptr;
+    return t.defined() && t.is_cuda() && t.layout() == at::kStrided && t.has_storage() ? &t : nullptr;
 }
 // rows of a 2-D tensor with unit column stride: the row stride, or -1
 int64_t row_stride(const at::Tensor &t)

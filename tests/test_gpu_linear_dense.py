@@ -186,3 +186,18 @@ def test_the_calls_in_cpp_give_what_the_python_ones_give(monkeypatch):
         assert len(a) == len(b)
         for s, t in zip(a, b):
             assert torch.equal(s, t) if isinstance(s, torch.Tensor) else s == t
+
+
+@pytest.mark.parametrize("relu", [False, True])
+def test_batches_of_gradients_through_a_layer_that_is_not_trained(relu):
+    """torch.autograd.grad(..., is_grads_batched=True): the gradient that reaches the layer has no storage of its own"""
+    from paper_2203_10991_amd import autograd as ag
+    torch.manual_seed(6)
+    layer = (ag.NMLinearReLU if relu else ag.NMLinear)(48, 64, bias=False, device=DEV, dtype=torch.bfloat16).requires_grad_(False)
+    x = torch.randn(32, 48, device=DEV).to(torch.bfloat16).requires_grad_()
+    g = torch.randn(5, 32, 64, device=DEV).to(torch.bfloat16)
+    y = layer(x)
+    (got,) = torch.autograd.grad(y, (x,), g, is_grads_batched=True)
+    for k in range(5):
+        want = (g[k].double() * (y > 0) if relu else g[k].double()) @ layer.weight.double()
+        assert float((got[k].double() - want).norm()) <= 4e-3 * float(want.norm())
