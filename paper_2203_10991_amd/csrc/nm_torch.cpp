@@ -7,6 +7,7 @@
 // worker thread of a backward pass, with cold caches, half as much again.
 #include <Python.h>
 
+#include <ATen/PythonTorchFunctionTLS.h>
 #include <ATen/autocast_mode.h>
 #include <ATen/core/Tensor.h>
 #include <ATen/ops/empty.h>
@@ -176,7 +177,7 @@ PyObject *linear_update(PyObject *, PyObject *const *a, Py_ssize_t n)
 // product, up to DENSE_RELU_MOST of them and the reduction width DENSE_RELU_WIDTH: the pass over the output that is saved outweighs what the product
 // may lose (a layer of 6143 x 640 -> 1320 157 us -> 126; 9143 x 1088 -> 2000 203.8 -> 202.9; alone 16384 x 2048 -> 2048 is 122 against 95 and 23).  Beyond,
 // the power limit takes the gain back: 16384 x 1024 -> 4096 alone 128 us against 106 and 43, inside its layer 445-462 us against 450-456.
-// The framework's stay: autocast regions, and operators that something watches.
+// The framework's stay: autocast regions, and operators that a mode of functions or of dispatch watches.
 constexpr int64_t DENSE_MOST = 5000000000, DENSE_RELU_MOST = 20000000000, DENSE_RELU_WIDTH = 1536;
 
 bool dense_takes(const at::Tensor &a, const at::Tensor &w, const at::Tensor *bias, bool relu, int64_t width, int64_t &rows, int64_t &ld)
@@ -194,7 +195,7 @@ bool dense_takes(const at::Tensor &a, const at::Tensor &w, const at::Tensor *bia
     if (bias && (bias->dim() != 1 || bias->size(0) != O || bias->scalar_type() != at::kBFloat16 || !bias->is_contiguous() || (uintptr_t)bias->data_ptr() % 16 ||
                  bias->device() != a.device()))
         return false;
-    return !at::autocast::is_autocast_enabled(at::kCUDA) && !c10::impl::TorchDispatchModeTLS::any_modes_set();
+    return !at::autocast::is_autocast_enabled(at::kCUDA) && !c10::impl::TorchDispatchModeTLS::any_modes_set() && !at::impl::torch_function_mode_enabled();
 }
 at::Tensor rows_like(const at::Tensor &a, int64_t width)
 {

@@ -201,3 +201,18 @@ def test_batches_of_gradients_through_a_layer_that_is_not_trained(relu):
     for k in range(5):
         want = (g[k].double() * (y > 0) if relu else g[k].double()) @ layer.weight.double()
         assert float((got[k].double() - want).norm()) <= 4e-3 * float(want.norm())
+
+
+def test_a_function_mode_sees_the_layers_product():
+    from paper_2203_10991_amd import autograd as ag
+    from torch.overrides import TorchFunctionMode
+    seen = []
+
+    class Watch(TorchFunctionMode):
+        def __torch_function__(self, func, types, args=(), kwargs=None):
+            seen.append(func)
+            return func(*args, **(kwargs or {}))
+    layer = ag.NMLinear(48, 64, device=DEV, dtype=torch.bfloat16)
+    with Watch():
+        layer(torch.randn(32, 48, device=DEV).to(torch.bfloat16))
+    assert torch.nn.functional.linear in seen
