@@ -114,7 +114,8 @@ def load():
         raise ImportError(f"_nm_torch.so is not built for this torch ({e}): run `python -m paper_2203_10991_amd.build`") from e
     _nm_torch.bind({f: C.cast(getattr(lib, f), vp).value for f in (
         "mvue_prune_1of2", "mvue_prune_2of4", "nm_update_gemm", "nm_update_gemm_workspace", "nm_linear_update", "nm_linear_update_workspace",
-        "nm_linear_forward", "nm_linear_input_grad")}, _raw_stream or (lambda d: torch.cuda.current_stream(d).cuda_stream))
+        "nm_linear_forward", "nm_linear_input_grad")}, _raw_stream or (lambda d: torch.cuda.current_stream(d).cuda_stream),
+                   torch.cuda.is_current_stream_capturing)
     global _native
     _native, _lib = _nm_torch, lib
     return lib

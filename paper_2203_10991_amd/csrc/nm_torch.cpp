@@ -18,13 +18,14 @@
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <cstdint>
+#include <utility>
 
 #include "../../include/nm_mvue.h"
 
 namespace {
 
-// The library's functions, by the addresses that ctypes resolved (the library is loaded once, by api.py), and the callable that gives a
-// device's current stream as an int
+// The library's functions, by the addresses that ctypes resolved (the library is loaded once, by api.py), and the callables that give a
+// device's current stream as an int and say whether the current device's is being captured
 decltype(&mvue_prune_1of2) p_prune_1of2;
 decltype(&mvue_prune_2of4) p_prune_2of4;
 decltype(&nm_update_gemm) p_update_gemm;
@@ -33,7 +34,7 @@ decltype(&nm_linear_update) p_linear_update;
 decltype(&nm_linear_update_workspace) p_linear_update_workspace;
 decltype(&nm_linear_forward) p_linear_forward;
 decltype(&nm_linear_input_grad) p_linear_input_grad;
-PyObject *stream_of = nullptr;
+PyObject *stream_of = nullptr, *is_capturing = nullptr;
 
 struct NoGil {                                                       // as a ctypes call does: a launch may wait for the queue
     PyThreadState *state = PyEval_SaveThread();
@@ -71,6 +72,14 @@ bool stream(const at::Tensor &t, void *&out)
     out = PyLong_AsVoidPtr(s);
     Py_DECREF(s);
     return !PyErr_Occurred();
+}
+bool capturing()
+{
+    PyObject *yes = PyObject_CallNoArgs(is_capturing);
+    if (!yes) PyErr_Clear();                                         // (the framework's operators will say what is wrong)
+    const bool r = !yes || PyObject_IsTrue(yes) != 0;
+    Py_XDECREF(yes);
+    return r;
 }
 bool whole_number(PyObject *o) { return PyLong_Check(o) && !PyBool_Check(o); }
 at::Tensor empty(at::IntArrayRef size, at::ScalarType type, const at::Tensor &like) { return at::empty(size, like.options().dtype(type).requires_grad(false)); }
@@ -177,8 +186,11 @@ PyObject *linear_update(PyObject *, PyObject *const *a, Py_ssize_t n)
 // product, up to DENSE_RELU_MOST of them and the reduction width DENSE_RELU_WIDTH: the pass over the output that is saved outweighs what the product
 // may lose (a layer of 6143 x 640 -> 1320 157 us -> 126; 9143 x 1088 -> 2000 203.8 -> 202.9; alone 16384 x 2048 -> 2048 is 122 against 95 and 23).  Beyond,
 // the power limit takes the gain back: 16384 x 1024 -> 4096 alone 128 us against 106 and 43, inside its layer 445-462 us against 450-456.
+// That is a rule for calls that the host makes one by one.  In a captured graph there is only the kernels' time: over 150 sizes the forward kernel takes up to
+// twice the vendor library's time (0.88 of it in the mean) and the input gradient's up to 1.6 times, so both stay the framework's there; with the ReLU and
+// up to DENSE_GRAPH_WIDTH inputs it was never more than 3 % behind product and pass, 0.57 of them in the mean.
 // The framework's stay: autocast regions, and operators that a mode of functions or of dispatch watches.
-constexpr int64_t DENSE_MOST = 5000000000, DENSE_RELU_MOST = 20000000000, DENSE_RELU_WIDTH = 1536;
+constexpr int64_t DENSE_MOST = 5000000000, DENSE_RELU_MOST = 20000000000, DENSE_RELU_WIDTH = 1536, DENSE_GRAPH_WIDTH = 1024;
 
 bool dense_takes(const at::Tensor &a, const at::Tensor &w, const at::Tensor *bias, bool relu, int64_t width, int64_t &rows, int64_t &ld)
 {
@@ -195,7 +207,8 @@ bool dense_takes(const at::Tensor &a, const at::Tensor &w, const at::Tensor *bia
     if (bias && (bias->dim() != 1 || bias->size(0) != O || bias->scalar_type() != at::kBFloat16 || !bias->is_contiguous() || (uintptr_t)bias->data_ptr() % 16 ||
                  bias->device() != a.device()))
         return false;
-    return !at::autocast::is_autocast_enabled(at::kCUDA) && !c10::impl::TorchDispatchModeTLS::any_modes_set() && !at::impl::torch_function_mode_enabled();
+    return !at::autocast::is_autocast_enabled(at::kCUDA) && !c10::impl::TorchDispatchModeTLS::any_modes_set() && !at::impl::torch_function_mode_enabled() &&
+           ((relu && I <= DENSE_GRAPH_WIDTH) || !capturing());
 }
 at::Tensor rows_like(const at::Tensor &a, int64_t width)
 {
@@ -253,10 +266,10 @@ PyObject *linear_input_grad(PyObject *, PyObject *const *a, Py_ssize_t n)
     END_HANDLE_TH_ERRORS
 }
 
-// bind({name: address}, stream_of)
+// bind({name: address}, stream_of, is_capturing)
 PyObject *bind(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
-    if (n != 2 || !PyDict_Check(a[0])) { PyErr_SetString(PyExc_TypeError, "bind(functions, stream_of)"); return nullptr; }
+    if (n != 3 || !PyDict_Check(a[0])) { PyErr_SetString(PyExc_TypeError, "bind(functions, stream_of, is_capturing)"); return nullptr; }
     struct { const char *name; void **at; } all[] = {
         {"mvue_prune_1of2", (void **)&p_prune_1of2}, {"mvue_prune_2of4", (void **)&p_prune_2of4}, {"nm_update_gemm", (void **)&p_update_gemm},
         {"nm_update_gemm_workspace", (void **)&p_update_gemm_workspace}, {"nm_linear_update", (void **)&p_linear_update},
@@ -268,9 +281,11 @@ PyObject *bind(PyObject *, PyObject *const *a, Py_ssize_t n)
         *f.at = PyLong_AsVoidPtr(address);
         if (PyErr_Occurred()) return nullptr;
     }
-    Py_INCREF(a[1]);
-    Py_XDECREF(stream_of);
-    stream_of = a[1];
+    for (const auto &[to, from] : {std::pair{&stream_of, a[1]}, std::pair{&is_capturing, a[2]}}) {
+        Py_INCREF(from);
+        Py_XDECREF(*to);
+        *to = from;
+    }
     Py_RETURN_NONE;
 }
 

@@ -216,3 +216,21 @@ def test_a_function_mode_sees_the_layers_product():
     with Watch():
         layer(torch.randn(32, 48, device=DEV).to(torch.bfloat16))
     assert torch.nn.functional.linear in seen
+
+
+def test_a_captured_step_takes_the_products_by_their_kernels_time():
+    """the host's time does not count in a graph: plain products are the framework's there, the ones with the ReLU behind them the library's"""
+    from paper_2203_10991_amd import api
+    x, w, g = (torch.randn(*s, device=DEV).to(torch.bfloat16) for s in ((197, 1024), (1024, 1024), (197, 1024)))
+    with torch.no_grad():
+        eager = [api.own_linear_forward(x, w), api.own_linear_forward(x, w, relu=True), api.own_linear_input_grad(g, w)]
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            captured = [api.own_linear_forward(x, w), api.own_linear_forward(x, w, relu=True), api.own_linear_input_grad(g, w)]
+    assert all(t is not None for t in eager)
+    assert captured[0] is None and captured[2] is None
+    for _ in range(3):
+        captured[1].zero_()
+        graph.replay()
+        assert torch.equal(captured[1], eager[1])
