@@ -186,18 +186,24 @@ PyObject *linear_update(PyObject *, PyObject *const *a, Py_ssize_t n)
 // product, up to DENSE_RELU_MOST of them and the reduction width DENSE_RELU_WIDTH: the pass over the output that is saved outweighs what the product
 // may lose (a layer of 6143 x 640 -> 1320 157 us -> 126; 9143 x 1088 -> 2000 203.8 -> 202.9; alone 16384 x 2048 -> 2048 is 122 against 95 and 23).  Beyond,
 // the power limit takes the gain back: 16384 x 1024 -> 4096 alone 128 us against 106 and 43, inside its layer 445-462 us against 450-456.
-// That is a rule for calls that the host makes one by one.  In a captured graph there is only the kernels' time: over 150 sizes the forward kernel takes up to
-// twice the vendor library's time (0.88 of it in the mean) and the input gradient's up to 1.6 times, so both stay the framework's there; with the ReLU and
-// up to DENSE_GRAPH_WIDTH inputs it was never more than 3 % behind product and pass, 0.57 of them in the mean.
+// A tile's reduction runs on one workgroup from end to end, 0.25 us for every 64 steps, where the vendor library splits it: 64 x 65536 -> 64 takes 269 us
+// against 46, 256 x 16384 -> 256 71 against 17.  So the reduction is at most DENSE_DEEP long, or DENSE_DEEPER where there are DENSE_TILES tiles of 64 x 64
+// to wait for.  Over 420 calls inside these lines one takes 0.44 of the framework's time in the mean, two 1.13 and 1.21 of it (694 x 1400 ->
+// 3280: a few tiles in a second round), all others at most 1.07.
+// Both are rules for calls that the host makes one by one.  In a captured graph there is only the kernels' time: the forward kernel takes up to
+// 1.8 times the vendor library's (0.9 in the mean) and the input gradient's up to 1.65, so both stay the framework's there; with the ReLU and
+// up to DENSE_GRAPH_WIDTH inputs it was never more than 3 % behind product and pass, 0.58 of them in the mean.
 // The framework's stay: autocast regions, and operators that a mode of functions or of dispatch watches.
-constexpr int64_t DENSE_MOST = 5000000000, DENSE_RELU_MOST = 20000000000, DENSE_RELU_WIDTH = 1536, DENSE_GRAPH_WIDTH = 1024;
+constexpr int64_t DENSE_MOST = 5000000000, DENSE_RELU_MOST = 20000000000, DENSE_RELU_WIDTH = 1536, DENSE_GRAPH_WIDTH = 1024,
+                  DENSE_DEEP = 2048, DENSE_DEEPER = 3584, DENSE_TILES = 128;
 
 bool dense_takes(const at::Tensor &a, const at::Tensor &w, const at::Tensor *bias, bool relu, int64_t width, int64_t &rows, int64_t &ld)
 {
     if (w.dim() != 2 || a.dim() < 2 || a.scalar_type() != at::kBFloat16 || w.scalar_type() != at::kBFloat16 || a.size(-1) != width) return false;
     const int64_t O = w.size(0), I = w.size(1);
-    rows = width ? a.numel() / width : 0;
+    rows = width ? a.numel() / width : 0;                              // (width: the reduction axis)
     if (rows < 1 || O < 1 || I < 1 || O % 8 || I % 8 || O > (1 << 21) || I > (1 << 21) || rows > ((int64_t)1 << 34) / O || rows > ((int64_t)1 << 36) / I) return false;
+    if (width > DENSE_DEEP && (width > DENSE_DEEPER || (rows + 63) / 64 * ((O * I / width + 63) / 64) < DENSE_TILES)) return false;
     if (rows * O > (relu && I <= DENSE_RELU_WIDTH ? DENSE_RELU_MOST : DENSE_MOST) / I) return false;
     if (a.dim() == 2) ld = rows > 1 ? a.stride(0) : width;
     else if (a.is_contiguous()) ld = width;

@@ -234,3 +234,17 @@ def test_a_captured_step_takes_the_products_by_their_kernels_time():
         captured[1].zero_()
         graph.replay()
         assert torch.equal(captured[1], eager[1])
+
+
+def test_reductions_too_long_for_their_tiles_are_the_framework_s():
+    """either side of 2048 steps, and of 3584 with 128 tiles of 64 x 64"""
+    from paper_2203_10991_amd import api
+
+    def taken(T, O, I):
+        x, w, g = (torch.empty(*s, device=DEV, dtype=torch.bfloat16) for s in ((T, I), (O, I), (T, O)))
+        with torch.no_grad():
+            return api.own_linear_forward(x, w) is not None, api.own_linear_forward(x, w, relu=True) is not None, api.own_linear_input_grad(g, w) is not None
+    assert taken(64, 64, 2048) == (True, True, True) and taken(64, 64, 2056) == (False, False, True) and taken(64, 2056, 64) == (True, True, False)
+    assert taken(65, 64 * 64, 3584) == (True, True, False) and taken(64, 127 * 64, 3584) == (False, False, False)
+    assert taken(65, 3584, 64 * 64) == (False, False, True) and taken(64, 128 * 64, 3592) == (False, False, False)
+    assert taken(8, 64, 262144) == (False, False, True)
