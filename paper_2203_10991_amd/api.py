@@ -8,6 +8,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import warnings
 from typing import Optional, Tuple
 
 import torch
@@ -109,16 +110,23 @@ def load():
     lib.nm_last_error.restype = C.c_char_p
     lib.nm_version.restype = C.c_char_p
     try:
-        from . import _nm_torch
+        from . import _nm_torch as native
+        native.bind({f: C.cast(getattr(lib, f), vp).value for f in (
+            "mvue_prune_1of2", "mvue_prune_2of4", "nm_update_gemm", "nm_update_gemm_workspace", "nm_linear_update", "nm_linear_update_workspace",
+            "nm_linear_forward", "nm_linear_input_grad")}, _raw_stream or (lambda d: torch.cuda.current_stream(d).cuda_stream),
+            torch.cuda.is_current_stream_capturing)
     except ImportError as e:
-        raise ImportError(f"_nm_torch.so is not built for this torch ({e}): run `python -m paper_2203_10991_amd.build`") from e
-    _nm_torch.bind({f: C.cast(getattr(lib, f), vp).value for f in (
-        "mvue_prune_1of2", "mvue_prune_2of4", "nm_update_gemm", "nm_update_gemm_workspace", "nm_linear_update", "nm_linear_update_workspace",
-        "nm_linear_forward", "nm_linear_input_grad")}, _raw_stream or (lambda d: torch.cuda.current_stream(d).cuda_stream),
-                   torch.cuda.is_current_stream_capturing)
+        warnings.warn(f"_nm_torch.so is not built for this torch ({e}): every call takes the slower way through ctypes and linear layers take the "
+                      "framework's products until `python -m paper_2203_10991_amd.build` has run")
+        native = _NoNative
     global _native
-    _native, _lib = _nm_torch, lib
+    _native, _lib = native, lib
     return lib
+
+
+class _NoNative:
+    """In the place of _nm_torch: no call is its own."""
+    prune = update_gemm = linear_update = linear_forward = linear_input_grad = staticmethod(lambda *a: None)
 
 
 def _native_result(r):

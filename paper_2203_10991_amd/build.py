@@ -68,11 +68,11 @@ def build(force: bool = True, verbose: bool = False) -> str:
     with ThreadPoolExecutor(max_workers=min(8, len(srcs) + 1)) as ex:
         binding = ex.submit(build_torch_binding)
         objs = list(ex.map(compile_one, srcs))
-        binding.result()
     cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"link failed:\n{r.stdout}\n{r.stderr}")
+    binding.result()              # (the library stands without it)
     return LIB
 
 

@@ -271,3 +271,30 @@ def test_layer_calls_argument_errors(lib):
     relu = dict(act=far(4), lda=8, gout=far(5), ldgo=8)
     for kw in (dict(ldg=most + 8), dict(ldh=most + 8), dict(relu, lda=most + 8), dict(relu, ldgo=most + 8), dict(ldg=0), dict(ldh=8), dict(relu, ldgo=0)):
         assert linear(**kw) == NM_ERR_SHAPE and b"stride" in lib.nm_last_error(), kw
+
+
+def test_the_library_alone_serves_every_call(lib):
+    """without the C++ part of the binding (built for another torch, say) the library loads, with a warning, and calls take the way through ctypes"""
+    import subprocess
+    import sys
+    code = """
+import sys, warnings
+sys.modules['paper_2203_10991_amd._nm_torch'] = None
+import torch
+from paper_2203_10991_amd import api, autograd as ag
+with warnings.catch_warnings(record=True) as said:
+    warnings.simplefilter('always')
+    assert b'gfx950' in api.load().nm_version()
+assert any('_nm_torch' in str(w.message) for w in said)
+assert api.nm_update_gemm_workspace(16384, 1024, 1024, torch.bfloat16) > 0
+for call in (lambda g: api.mvue_prune_2of4(g), lambda g: api.nm_update_gemm(g.view(1, 16, 16), g, g), lambda g: api.nm_linear_update(g, g)):
+    try:
+        call(torch.zeros(16, 16))
+        raise SystemExit('a CPU tensor went through')
+    except (ValueError, TypeError, RuntimeError):
+        pass
+assert api.own_linear_forward(torch.zeros(3, 8), torch.zeros(8, 8)) is None
+assert ag.NMLinear(8, 8)(torch.zeros(3, 8)).shape == (3, 8)
+"""
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout + r.stderr
