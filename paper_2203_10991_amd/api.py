@@ -680,11 +680,15 @@ def nm_linear_input_grad(g: torch.Tensor, weight: torch.Tensor) -> torch.Tensor:
 def own_linear_forward(x: torch.Tensor, weight: torch.Tensor, bias: Optional[torch.Tensor] = None, relu: bool = False) -> Optional[torch.Tensor]:
     """nm_linear_forward over the last dimension of x where that is the faster way and can take the place of the framework's operators (csrc/nm_torch.cpp
     says when); None otherwise."""
+    if not x.is_cuda:
+        return None
     load()
     return _native_result(_native.linear_forward(x, weight, bias, relu))
 
 
 def own_linear_input_grad(g: torch.Tensor, weight: torch.Tensor) -> Optional[torch.Tensor]:
     """The same of nm_linear_input_grad; None where gradients are recorded, too."""
+    if not g.is_cuda:
+        return None
     load()
     return _native_result(_native.linear_input_grad(g, weight))

@@ -298,3 +298,14 @@ assert ag.NMLinear(8, 8)(torch.zeros(3, 8)).shape == (3, 8)
 """
     r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True)
     assert r.returncode == 0, r.stdout + r.stderr
+
+
+def test_the_forward_of_a_layer_on_the_cpu_needs_no_library(monkeypatch):
+    import torch
+    from paper_2203_10991_amd import api, autograd as ag
+
+    def missing():
+        raise ImportError("not built")
+    monkeypatch.setattr(api, "load", missing)
+    for layer in (ag.NMLinear(8, 16), ag.NMLinearReLU(8, 16, bias=False)):
+        assert layer(torch.zeros(3, 8)).shape == (3, 16)
