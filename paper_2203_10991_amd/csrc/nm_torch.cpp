@@ -18,14 +18,13 @@
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <cstdint>
-#include <utility>
 
 #include "../../include/nm_mvue.h"
 
 namespace {
 
-// The library's functions, by the addresses that ctypes resolved (the library is loaded once, by api.py), and the callables that give a
-// device's current stream as an int and say whether the current device's is being captured
+// The library's functions, by the addresses that ctypes resolved (the library is loaded once, by api.py), and the callable that gives a
+// device's current stream as an int
 decltype(&mvue_prune_1of2) p_prune_1of2;
 decltype(&mvue_prune_2of4) p_prune_2of4;
 decltype(&nm_update_gemm) p_update_gemm;
@@ -34,7 +33,7 @@ decltype(&nm_linear_update) p_linear_update;
 decltype(&nm_linear_update_workspace) p_linear_update_workspace;
 decltype(&nm_linear_forward) p_linear_forward;
 decltype(&nm_linear_input_grad) p_linear_input_grad;
-PyObject *stream_of = nullptr, *is_capturing = nullptr;
+PyObject *stream_of = nullptr;
 
 struct NoGil {                                                       // as a ctypes call does: a launch may wait for the queue
     PyThreadState *state = PyEval_SaveThread();
@@ -72,14 +71,6 @@ bool stream(const at::Tensor &t, void *&out)
     out = PyLong_AsVoidPtr(s);
     Py_DECREF(s);
     return !PyErr_Occurred();
-}
-bool capturing()
-{
-    PyObject *yes = PyObject_CallNoArgs(is_capturing);
-    if (!yes) PyErr_Clear();                                         // (the framework's operators will say what is wrong)
-    const bool r = !yes || PyObject_IsTrue(yes) != 0;
-    Py_XDECREF(yes);
-    return r;
 }
 bool whole_number(PyObject *o) { return PyLong_Check(o) && !PyBool_Check(o); }
 at::Tensor empty(at::IntArrayRef size, at::ScalarType type, const at::Tensor &like) { return at::empty(size, like.options().dtype(type).requires_grad(false)); }
@@ -190,11 +181,12 @@ PyObject *linear_update(PyObject *, PyObject *const *a, Py_ssize_t n)
 // against 46, 256 x 16384 -> 256 71 against 17.  So the reduction is at most DENSE_DEEP long, or DENSE_DEEPER where there are DENSE_TILES tiles of 64 x 64
 // to wait for.  Over 420 calls inside these lines one takes 0.44 of the framework's time in the mean, two 1.13 and 1.21 of it (694 x 1400 ->
 // 3280: a few tiles in a second round), all others at most 1.07.
-// Both are rules for calls that the host makes one by one.  In a captured graph there is only the kernels' time: the forward kernel takes up to
-// 1.8 times the vendor library's (0.9 in the mean) and the input gradient's up to 1.65, so both stay the framework's there; with the ReLU and
-// up to DENSE_GRAPH_WIDTH inputs it was never more than 3 % behind product and pass, 0.58 of them in the mean.
+// Both are rules for calls that the host makes one by one.  Where only the kernels' time counts, in a captured graph or behind a deep queue, the forward
+// kernel takes 0.9 of the vendor library's in the mean and up to 1.8 times it on few tiles, the input gradient's 0.84 and up to 1.65, and with the ReLU
+// 0.65 and up to 1.35 of product and pass.  A captured step takes the same way all the same: it has to find there what the step before it, run once to
+// warm up, has used, and the vendor library's first product of a process or thread cannot be captured.
 // The framework's stay: autocast regions, and operators that a mode of functions or of dispatch watches.
-constexpr int64_t DENSE_MOST = 5000000000, DENSE_RELU_MOST = 20000000000, DENSE_RELU_WIDTH = 1536, DENSE_GRAPH_WIDTH = 1024,
+constexpr int64_t DENSE_MOST = 5000000000, DENSE_RELU_MOST = 20000000000, DENSE_RELU_WIDTH = 1536,
                   DENSE_DEEP = 2048, DENSE_DEEPER = 3584, DENSE_TILES = 128;
 
 bool dense_takes(const at::Tensor &a, const at::Tensor &w, const at::Tensor *bias, bool relu, int64_t width, int64_t &rows, int64_t &ld)
@@ -213,8 +205,7 @@ bool dense_takes(const at::Tensor &a, const at::Tensor &w, const at::Tensor *bia
     if (bias && (bias->dim() != 1 || bias->size(0) != O || bias->scalar_type() != at::kBFloat16 || !bias->is_contiguous() || (uintptr_t)bias->data_ptr() % 16 ||
                  bias->device() != a.device()))
         return false;
-    return !at::autocast::is_autocast_enabled(at::kCUDA) && !c10::impl::TorchDispatchModeTLS::any_modes_set() && !at::impl::torch_function_mode_enabled() &&
-           ((relu && I <= DENSE_GRAPH_WIDTH) || !capturing());
+    return !at::autocast::is_autocast_enabled(at::kCUDA) && !c10::impl::TorchDispatchModeTLS::any_modes_set() && !at::impl::torch_function_mode_enabled();
 }
 at::Tensor rows_like(const at::Tensor &a, int64_t width)
 {
@@ -272,10 +263,10 @@ PyObject *linear_input_grad(PyObject *, PyObject *const *a, Py_ssize_t n)
     END_HANDLE_TH_ERRORS
 }
 
-// bind({name: address}, stream_of, is_capturing)
+// bind({name: address}, stream_of)
 PyObject *bind(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
-    if (n != 3 || !PyDict_Check(a[0])) { PyErr_SetString(PyExc_TypeError, "bind(functions, stream_of, is_capturing)"); return nullptr; }
+    if (n != 2 || !PyDict_Check(a[0])) { PyErr_SetString(PyExc_TypeError, "bind(functions, stream_of)"); return nullptr; }
     struct { const char *name; void **at; } all[] = {
         {"mvue_prune_1of2", (void **)&p_prune_1of2}, {"mvue_prune_2of4", (void **)&p_prune_2of4}, {"nm_update_gemm", (void **)&p_update_gemm},
         {"nm_update_gemm_workspace", (void **)&p_update_gemm_workspace}, {"nm_linear_update", (void **)&p_linear_update},
@@ -287,11 +278,9 @@ PyObject *bind(PyObject *, PyObject *const *a, Py_ssize_t n)
         *f.at = PyLong_AsVoidPtr(address);
         if (PyErr_Occurred()) return nullptr;
     }
-    for (const auto &[to, from] : {std::pair{&stream_of, a[1]}, std::pair{&is_capturing, a[2]}}) {
-        Py_INCREF(from);
-        Py_XDECREF(*to);
-        *to = from;
-    }
+    Py_INCREF(a[1]);
+    Py_XDECREF(stream_of);
+    stream_of = a[1];
     Py_RETURN_NONE;
 }
 
