@@ -635,11 +635,12 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *__restr
     *(float4 *)(out + o * ldo + i) = s;
 }
 
-// A sum of up to 11 slabs is one chain of loads, from 12 on eight.  Eight threads to a sum only where there are too few sums to fill the GPU: a
-// thread with eight loads in flight is faster otherwise.
+// A sum of up to 11 slabs is one chain of loads, from 12 on eight.  Eight threads to a sum where there are too few sums to fill the GPU otherwise: back to
+// back with the partial sums in the caches, a thread with eight loads in flight / eight threads, us: 2048 float4s of 12 slabs 2.7 / 2.3, of 46 4.0 / 2.8, of
+// 256 13.7 / 6.2; 18432 of 12 2.9 / 3.0, of 46 6.5 / 4.8; 32768 of 46 7.2 / 6.8, of 128 11.5 / 14.6; 65536 of 24 5.8 / 6.4, of 96 16.4 / 18.8.
 SlabSum slab_sum_form(int64_t n4, int slabs)
 {
-    return slabs < 12 ? SlabSum::one_chain : n4 <= 18432 && slabs >= 64 ? SlabSum::shared : SlabSum::eight_chains;
+    return slabs < 12 ? SlabSum::one_chain : n4 <= 18432 ? SlabSum::shared : SlabSum::eight_chains;
 }
 
 // dW = (accumulate ? dW : 0) + alpha * sum over the slabs of [slabs][O][I] partial sums (row stride I)

@@ -153,10 +153,11 @@ def test_update_gemm_q8_mid_sized_plans(nm, oracle, T, O, I, slabs, beta):
 
 
 @pytest.mark.parametrize("T,O,I,slabs", [(32 * 132, 64, 64, 11),             # second pass over partial sums: one chain of eleven slabs
-                                         (32 * 280, 64, 80, 12),             # ... eight chains, twelve slabs: four of them hold two
+                                         (32 * 280, 64, 80, 12),             # ... eight threads to a sum, twelve slabs: four of them hold two
                                          (32 * 552, 72, 272, 46),            # ... a last trip of six
-                                         (32 * 1680, 64, 64, 140),           # ... eight threads to a sum
-                                         (32 * 1680, 296, 256, 70)])         # ... too many sums for that
+                                         (32 * 1680, 64, 64, 140),           # ... a last trip of four
+                                         (32 * 280, 296, 256, 12),           # ... too many sums for that: eight chains to a thread
+                                         (32 * 1680, 296, 256, 70)])         # ... a last trip of six
 def test_second_pass_over_partial_sums(nm, oracle, T, O, I, slabs):
     from paper_2203_10991_amd import api
     assert api.nm_update_gemm_q8_workspace(T, O, I) == slabs * O * I * 4
