@@ -12,9 +12,12 @@ namespace nm {
 // Convolution: dW[o][c][tap] (bf16) = alpha * sum_z part[z][o][tap][c].  A workgroup takes one output channel and CW input
 // channels: R threads share a float4 of the partial sums (as in splitk_reduce_kernel: thread r sums slabs r, r+R, ... in
 // order, a fixed tree combines them), the results turn through LDS, and the CW x taps values leave contiguous.
-// Bound: launch latency and one read of the partial sums.  A workgroup is 64 channels wide with a thread a sum, which fills the GPU from
-// 128 x 128 channels on; narrower layers have few output channels to deal out, and with many slabs a workgroup is 16 channels wide there
-// with 16 threads a sum, all sums of nine taps at once.
+// Bound: launch latency and one read of the partial sums.  A sum of up to 11 slabs is one chain, of up to 63 eight, beyond that 16 (the order of the
+// additions depends on the slab count only).  Large layers have a thread to a sum, all its chains side by side, in workgroups 64 channels
+// wide; others would leave the GPU idle so and have a thread to a chain, in workgroups 32 (16) channels wide.  Partial sums in the caches, thread a sum /
+// thread a chain, us: 64 x 64 x 9 of 46 slabs 6.5 / 4.4, 128 x 128 x 9 of 24 4.7 / 4.8, of 46 7.7 / 6.6, 256 x 128 x 9 of 12 5.3 / 5.9, of 46 10.6 / 11.3, 256 x 256 x 9 of
+// 24 10.1 / 12.5, 96 x 256 x 1 in its layer 7.1 / 4.2, 256 x 256 x 1 of 24 4.0 / 7.2; 64 x 64 x 9 of 254 15.5 / 8.8, 128 x 256 x 9 of 96 17.6 / 19.7, 256 x 128 x 1 in its
+// layer 8.8 / 6.9.
 template <int R, int CHAINS, int CW, int NT>
 __global__ __launch_bounds__(NT) void finish_conv_kernel(const float *__restrict__ part, int slabs, int64_t slab_stride, uint16_t *__restrict__ dW,
                                                          int C, int taps, AlphaArg al)
@@ -30,7 +33,7 @@ __global__ __launch_bounds__(NT) void finish_conv_kernel(const float *__restrict
         const bool valid = t < tasks;
         const int tap = valid ? t / q4 : 0, c = valid ? (t % q4) * 4 : 0;
         float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (valid) s = sum_of_slabs<R, CHAINS>(src + (int64_t)tap * C + c, r, slabs, slab_stride);
+        if (valid) s = sum_of_slabs<R, CHAINS, 4>(src + (int64_t)tap * C + c, r, slabs, slab_stride);
         s = sum_of_threads<R>(s);
         if (valid && r == 0) {
             const uint32_t a = pack_bf16_rne(s.x * alpha, s.y * alpha), b = pack_bf16_rne(s.z * alpha, s.w * alpha);
@@ -48,10 +51,9 @@ hipError_t launch_finish_conv(const float *part, int slabs, void *dW, int64_t O,
 #define NM_FINISH(R, CHAINS, CW, NT)                                                                                                              \
     hipLaunchKernelGGL((finish_conv_kernel<R, CHAINS, CW, NT>), dim3((unsigned)O, (unsigned)((C + CW - 1) / CW)), dim3(NT), 0, st, part, slabs,    \
                        O * (int64_t)taps * C, (uint16_t *)dW, C, taps, alpha)
-    const int64_t wide = O * C;
-    if (wide <= 128 * 128 && slabs >= (wide <= 64 * 64 ? 24 : 64)) NM_FINISH(16, 1, 16, 576);
-    else if (slabs >= 64) NM_FINISH(1, 16, 64, 256);
-    else if (slabs >= 12) NM_FINISH(1, 8, 64, 256);
+    const bool large = O * C > 128 * 128 && O * C * taps >= 65536;
+    if (slabs >= 64) { if (large) NM_FINISH(1, 16, 64, 256); else NM_FINISH(16, 1, 16, 576); }
+    else if (slabs >= 12) { if (large) NM_FINISH(1, 8, 64, 256); else NM_FINISH(8, 1, 32, 576); }
     else NM_FINISH(1, 1, 64, 256);
 #undef NM_FINISH
     return hipGetLastError();

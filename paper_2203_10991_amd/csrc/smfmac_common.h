@@ -172,18 +172,15 @@ template <int N> __device__ __forceinline__ void wait_vmcnt()
 // at distance 1, 2, 4, ...).  The order of the additions depends on the slab count only, and R * CHAINS threads-times-chains of eight give
 // the same bits however they are split.
 __device__ __forceinline__ void add4(float4 &s, const float4 &v) { s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w; }
-template <int R, int CHAINS>
+// AHEAD: loads in flight of a thread with one chain.  Large outputs take one, four ahead measured 1 % slower (16384 x 4096 x 1024, 4 slabs: 89.8 -> 90.7 us
+// a call); convolution layers, whose outputs are small, four (11 slabs 1.2 times as fast in the mean over 90 sizes).
+template <int R, int CHAINS, int AHEAD = (R == 1 ? 1 : 4)>
 __device__ __forceinline__ float4 sum_of_slabs(const float *at, int r, int slabs, int64_t slab_stride)
 {
     if constexpr (CHAINS == 1) {
         float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-        if constexpr (R == 1) {             // few slabs of large outputs: four loads ahead measured 1 % slower (16384 x 4096 x 1024, 4 slabs: 89.8 -> 90.7 us a call)
-#pragma unroll 1
-            for (int z = r; z < slabs; z += R) add4(s, *(const float4 *)(at + (int64_t)z * slab_stride));
-        } else {
-#pragma unroll 4
-            for (int z = r; z < slabs; z += R) add4(s, *(const float4 *)(at + (int64_t)z * slab_stride));
-        }
+#pragma unroll AHEAD
+        for (int z = r; z < slabs; z += R) add4(s, *(const float4 *)(at + (int64_t)z * slab_stride));
         return s;
     } else {
         static_assert(R == 1, "one thread's chains");

@@ -154,3 +154,21 @@ def test_conv_update_pixel_pairs_at_the_edges(oracle, N, C, O, H, W, k, q8):
     if q8 and C % 16:
         C += 8
     test_conv_update_matches_the_oracle(oracle, N, C, O, H, W, k, q8, (False, False))
+
+
+@pytest.mark.parametrize("N,C,O,H,W,k,form", [(16, 144, 144, 14, 14, 3, "1, 1, 64, 256"),          # up to eleven slabs
+                                              (12, 48, 24, 28, 28, 3, "8, 1, 32, 576"),            # up to 63: a thread to a chain
+                                              (40, 272, 272, 14, 14, 1, "1, 8, 64, 256"),          # ... large: a thread to a sum
+                                              (24, 48, 376, 28, 28, 3, "1, 8, 64, 256"),
+                                              (32, 48, 24, 28, 28, 3, "16, 1, 16, 576"),           # 64 and more
+                                              (128, 128, 512, 56, 56, 1, "1, 16, 64, 256")])       # ... large
+def test_conv_update_second_pass_forms(N, C, O, H, W, k, form):
+    """against the same sums by separate calls, unrounded: what is left is the rounding to bf16, 2^-9 of a value at most"""
+    from gpu_util import kernels_of
+    from paper_2203_10991_amd import api, autograd as ag
+    torch.manual_seed(C)
+    x, gy = torch.randn(N, C, H, W, device=DEV).to(torch.bfloat16), torch.randn(N, O, H, W, device=DEV).to(torch.bfloat16)
+    got = api.nm_conv_update(gy, x, k, seed=3).double()
+    want = ag._conv_update_shifted(gy, x, k, ag.NMConfig(seed=3), torch.float32).double()
+    assert float((got - want).norm()) <= 2.0 ** -9 * float(want.norm()) * 1.01
+    assert any(f"finish_conv_kernel<{form}>" in name for name in kernels_of(lambda: api.nm_conv_update(gy, x, k, seed=3)))
