@@ -102,13 +102,17 @@ __device__ __forceinline__ void load_tile(uint32_t *tile, int64_t *offs, const u
         const uint16_t *p = src + (o < 0 ? 0 : o) + (int64_t)c0 * plane;      // (a border row reads image 0 and drops it)
         const uint32_t keep = o < 0 ? 0u : 0xffffffffu;
         uint32_t *w = tile + tid * TILE_LD;
-        for (int c = 0; c < cols; c += 8) {
-            uint32_t v[8];
+        auto channels = [&](int c, auto n_c_) {                       // n channels from c on, all loads in flight together (8 at a time: 57 x 256 x 27 x 29 17.4 -> 19.4 us)
+            constexpr int n = decltype(n_c_)::value;
+            uint32_t v[n];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) v[j] = (uint32_t)p[(int64_t)(c + j) * plane];
+            for (int j = 0; j < n; ++j) v[j] = (uint32_t)p[(int64_t)(c + j) * plane];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) w[c / 2 + j] = (v[2 * j] | (v[2 * j + 1] << 16)) & keep;
-        }
+            for (int j = 0; j < n / 2; ++j) w[c / 2 + j] = (v[2 * j] | (v[2 * j + 1] << 16)) & keep;
+        };
+        int c = 0;
+        for (; c + 32 <= cols; c += 32) channels(c, std::integral_constant<int, 32>{});
+        for (; c < cols; c += 8) channels(c, std::integral_constant<int, 8>{});
     } else {
         offs[tid] = o;
         __syncthreads();
