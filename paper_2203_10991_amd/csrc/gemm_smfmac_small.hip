@@ -1,10 +1,10 @@
 // Update GEMM for small problems: 64 x 64 tiles of dW, the tokens split over the eight waves of a workgroup.
 //
 // What a small problem takes on the tile kernels is latency: 512 x 512 x 256 is eight 128 x 128 tiles of 16 stages behind a barrier each, and
-// with more tokens slabs, whose partial sums cost a second launch (2048 x 1024 x 1024: 19 us, 5 of them in the loop).  Here a wave takes every
+// with more tokens slabs, whose partial sums cost a second launch (1024^3: 17 us, 3 of them in the loop).  Here a wave takes every
 // eighth MFMA step (32 tokens) of its workgroup's tile, brings the step's operands into LDS of its own -- so nothing in the loop waits for
 // another wave -- two steps ahead, and the eight waves' sums meet in LDS at the end, in a fixed tree.
-// 512 x 512 x 256 9.3 -> 5.6 us, 1024^3 17 -> 7.6, 2048 x 1024 x 1024 19 -> 10.  A wave's step is bound by the way to its operands: 0.5 us alone,
+// 512 x 512 x 256 9.3 -> 5.6 us, 1024^3 17 -> 7.6.  A wave's step is bound by the way to its operands: 0.5 us alone,
 // 0.6-0.7 with all CUs busy, which is why long reductions stay on the large tiles.
 //
 // LDS of a wave and step: h [32 tokens][64 columns] bf16, chunk c of row k at position c ^ 4 (k / 2 % 2) (a transposing read touches the same 32

@@ -8,7 +8,7 @@ import pytest
 import torch
 
 from paper_2203_10991_amd import synth
-from gpu_util import DEV, to_dev, to_host
+from gpu_util import DEV, kernels_of, to_dev, to_host
 
 pytestmark = pytest.mark.gpu
 TOL = {"f32": 1e-5, "bf16": 1e-2}
@@ -263,8 +263,8 @@ def test_update_gemm_f32_with_a_short_last_round(nm, oracle, T, O, I, beta):
 
 @pytest.mark.parametrize("T,O,I", [(16, 8, 8), (16 * 9, 72, 56), (16 * 16, 64, 64), (16 * 17, 136, 64),     # fewer steps than waves; an odd group; one step each
                                    (16 * 47, 1024, 1016), (16 * 49, 64, 2048),                              # every CU a tile; either side of 768 tokens
-                                   (1024, 1024, 1024), (16 * 131, 200, 72),                                 # past it, one slab
-                                   (16 * 24 * 11, 64, 72), (16 * 513, 256, 264), (16 * 1030, 72, 64)])      # in slabs, a shorter last one
+                                   (1024, 1024, 1024), (16 * 131, 200, 72),                                 # past it, one slab and three
+                                   (16 * 24 * 11, 64, 72), (16 * 513, 256, 264), (16 * 1030, 72, 64)])      # six; the sizes at which 128 x 128 tiles take over again
 def test_small_tiles_with_the_tokens_split_over_waves(nm, oracle, T, O, I):
     run_case(nm, oracle, synth.Workload(f"small{T}x{O}x{I}", T, O, I, "bf16", "2:4", 0.0, 2.0, 0.3), seed=5)
     run_case(nm, oracle, synth.Workload(f"small{T}x{O}x{I}", T, O, I, "bf16", "1:2", 0.0, 2.0, 0.3), seed=6, beta=1.0)
@@ -312,3 +312,24 @@ def test_three_bf16_terms_are_as_near_as_binary32_products(nm, T, O, I):
     off = [float((nm.nm_update_gemm(v, m, h, f32_as_bf16x3=x3).double().cpu() - want).norm() / want.norm()) for x3 in (True, False)]
     print(f"2-norm error, three terms {off[0]:.2e}, binary32 products {off[1]:.2e}", flush=True)
     assert off[0] <= 1.1 * off[1]
+
+
+@pytest.mark.parametrize("T,O,I,slabs", [(16, 8, 8, 1), (16 * 47, 1024, 1016, 1), (16 * 97, 264, 256, 1),       # the whole reduction in a workgroup
+                                         (16 * 129, 256, 264, 3), (16 * 193, 72, 64, 6), (16 * 385, 256, 264, 4),   # slabs, the last one shorter and odd
+                                         (16 * 512, 64, 64, 8)])
+@pytest.mark.parametrize("beta", [0.0, 1.0])
+def test_small_tiles_in_slabs(nm, oracle, T, O, I, slabs, beta):
+    w = synth.Workload(f"smallslabs{T}x{O}x{I}", T, O, I, "bf16", "2:4", 0.0, 2.0, 0.3)
+    run_case(nm, oracle, w, seed=T, beta=beta)
+    v, m, _ = nm.mvue_prune_2of4(to_dev(synth.make_g(w, 1)))
+    h, dW = to_dev(synth.make_h(w, 1)), torch.zeros(O, I, device=DEV)
+    names = kernels_of(lambda: nm.nm_update_gemm(v, m, h, dW=dW, beta=beta))
+    assert sum("update_gemm_smfmac_small_kernel" in n for n in names) == 1 and any("splitk_reduce" in n for n in names) == (slabs > 1)
+
+
+@pytest.mark.parametrize("T,O,I", [(16 * 333, 64, 3152), (16 * 262, 16, 5936)])
+def test_a_wide_operand_stays_on_the_tile_kernels(nm, oracle, T, O, I):
+    w = synth.Workload(f"wide{T}x{O}x{I}", T, O, I, "bf16", "2:4", 0.0, 2.0, 0.3)
+    v, m, _ = nm.mvue_prune_2of4(to_dev(synth.make_g(w, 1)))
+    h = to_dev(synth.make_h(w, 1))
+    assert not any("small_kernel" in n for n in kernels_of(lambda: nm.nm_update_gemm(v, m, h)))
