@@ -283,6 +283,46 @@ int main()
         EXPECT(linear((((int64_t)1 << 34) / lim) + 1, lim, 16, 4, 0, 0, nullptr, lim, 16, bias, lws), NM_ERR_SHAPE);
         if (!nm_linear_update_workspace(((int64_t)1 << 34) / lim, lim, 16, 0, 1) || !nm_linear_update_workspace((int64_t)1 << 31, 8, 32, 1, 1)) ++failures;
 
+        // the dense products: x [T x I] and g [T x O] at a, w at b, y and dx at out
+        auto forward = [&](int64_t T_, int64_t O_, int64_t I_, int64_t ldx, const void *x_, const void *bias_, void *y) {
+            return nm_linear_forward(x_, ldx, b, bias_, T_, O_, I_, 1, y, nullptr);
+        };
+        auto input_grad = [&](int64_t T_, int64_t O_, int64_t I_, int64_t ldg, const void *w_, void *dx) { return nm_linear_input_grad(a, ldg, w_, T_, O_, I_, dx, nullptr); };
+        for (int64_t T_ : {(int64_t)1, (int64_t)77, (int64_t)1 << 31}) {
+            EXPECT(forward(T_, 8, 16, 16, a, bias, out), NM_OK);
+            EXPECT(input_grad(T_, 8, 16, 8, b, out), NM_OK);
+            const int wide = T_ < 1024 ? NM_OK : NM_ERR_ALIAS;          // (2^31 rows of 4 MB reach over the other tensors)
+            EXPECT(forward(T_, 8, 16, ld_most, a, nullptr, out), wide);
+            EXPECT(input_grad(T_, 8, 16, ld_most, b, out), wide);
+        }
+        EXPECT(forward(((int64_t)1 << 34) / lim, lim, 8, 8, a, bias, out), NM_OK);
+        EXPECT(forward(((int64_t)1 << 34) / lim + 1, lim, 8, 8, a, bias, out), NM_ERR_SHAPE);
+        EXPECT(forward(64, 64, 128, 128, nullptr, bias, out), NM_ERR_NULL);
+        EXPECT(forward(64, 64, 128, 128, a, bias, nullptr), NM_ERR_NULL);
+        EXPECT(forward(64, 64, 128, 132, a, bias, out), NM_ERR_ALIGN);
+        EXPECT(forward(64, 64, 128, 128, (char *)a + 8, bias, out), NM_ERR_ALIGN);
+        EXPECT(forward(64, 64, 128, 128, a, (char *)bias + 2, out), NM_ERR_ALIGN);
+        EXPECT(forward(64, 64, 128, 128, a, bias, (char *)out + 4), NM_ERR_ALIGN);
+        EXPECT(forward(64, 64, 128, 128, a, bias, (char *)a + 64 * 128 * 2 - 16), NM_ERR_ALIAS);
+        EXPECT(forward(64, 64, 128, 128, a, bias, (char *)b + 64 * 128 * 2 - 16), NM_ERR_ALIAS);
+        EXPECT(forward(64, 64, 128, 128, a, (char *)out + 64 * 64 * 2 - 16, out), NM_ERR_ALIAS);
+        EXPECT(forward(64, 64, 128, 128, a, bias, (char *)a + 64 * 128 * 2), NM_OK);
+        EXPECT(input_grad(64, 64, 128, 64, nullptr, out), NM_ERR_NULL);
+        EXPECT(input_grad(64, 64, 128, 68, b, out), NM_ERR_ALIGN);
+        EXPECT(input_grad(64, 64, 128, 64, (char *)b + 2, out), NM_ERR_ALIGN);
+        EXPECT(input_grad(64, 64, 128, 64, b, (char *)a + 64 * 64 * 2 - 16), NM_ERR_ALIAS);
+        EXPECT(input_grad(64, 64, 128, 64, b, (char *)b - 64 * 128 * 2 + 16), NM_ERR_ALIAS);
+        for (int64_t bad : {(int64_t)0, (int64_t)-16, huge, INT64_MAX, INT64_MIN}) {
+            EXPECT(forward(bad, 64, 128, 128, a, bias, out), NM_ERR_SHAPE);
+            EXPECT(forward(64, bad, 128, 128, a, bias, out), NM_ERR_SHAPE);
+            EXPECT(forward(64, 64, bad, bad, a, bias, out), NM_ERR_SHAPE);
+            EXPECT(forward(64, 64, 128, bad, a, bias, out), NM_ERR_SHAPE);
+            EXPECT(input_grad(64, bad, 128, bad, b, out), NM_ERR_SHAPE);
+            EXPECT(input_grad(64, 64, 128, bad, b, out), NM_ERR_SHAPE);
+        }
+        EXPECT(forward(64, 60, 128, 128, a, bias, out), NM_ERR_SHAPE);
+        EXPECT(input_grad(64, 64, 100, 64, b, out), NM_ERR_SHAPE);
+
         auto conv = [&](int64_t N, int64_t C, int64_t O_, int64_t H, int64_t W, int k, int q8, int mode, const void *x_, void *dW_, void *w_) {
             return nm_conv_update(a, 0, x_, 1, N, C, O_, H, W, k, q8, mode, 1, 2, dW_, w_, nm_conv_update_workspace(N, C, O_, H, W, k, q8), nullptr);
         };

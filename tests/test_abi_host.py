@@ -273,6 +273,30 @@ def test_layer_calls_argument_errors(lib):
         assert linear(**kw) == NM_ERR_SHAPE and b"stride" in lib.nm_last_error(), kw
 
 
+def test_dense_product_argument_errors(lib):
+    far = lambda i: P + (i << 40)                               # noqa: E731
+    fwd = dict(x=far(0), ldx=128, w=far(1), bias=far(2), T=64, O=64, I=128, relu=0, y=far(3), st=None)
+    grad = dict(g=far(0), ldg=64, w=far(1), T=64, O=64, I=128, dx=far(3), st=None)
+
+    def forward(**kw):
+        return lib.nm_linear_forward(*{**fwd, **kw}.values())
+
+    def input_grad(**kw):
+        return lib.nm_linear_input_grad(*{**grad, **kw}.values())
+    for kw in (dict(T=0), dict(O=60), dict(I=100), dict(O=(1 << 21) + 8), dict(T=1 << 34, O=8)):
+        assert forward(**kw) == NM_ERR_SHAPE and input_grad(**kw) == NM_ERR_SHAPE, kw
+    assert forward(ldx=120) == NM_ERR_SHAPE and forward(ldx=(1 << 21) + 8) == NM_ERR_SHAPE and b"stride" in lib.nm_last_error()
+    assert input_grad(ldg=56) == NM_ERR_SHAPE and input_grad(ldg=(1 << 21) + 8) == NM_ERR_SHAPE
+    assert forward(x=None) == forward(w=None) == forward(y=None) == input_grad(g=None) == input_grad(w=None) == input_grad(dx=None) == NM_ERR_NULL
+    for kw in (dict(x=far(0) + 8), dict(w=far(1) + 2), dict(bias=far(2) + 8), dict(y=far(3) + 4), dict(ldx=132)):
+        assert forward(**kw) == NM_ERR_ALIGN, kw
+    for kw in (dict(g=far(0) + 8), dict(w=far(1) + 2), dict(dx=far(3) + 4), dict(ldg=68)):
+        assert input_grad(**kw) == NM_ERR_ALIGN, kw
+    for at in (far(0) + 64 * 128 * 2 - 16, far(1) + 64, far(2) + 112):
+        assert forward(y=at) == NM_ERR_ALIAS
+    assert input_grad(dx=far(0) - 64) == NM_ERR_ALIAS and input_grad(dx=far(1) + 64) == NM_ERR_ALIAS
+
+
 def test_the_library_alone_serves_every_call(lib):
     """without the C++ part of the binding (built for another torch, say) the library loads, with a warning, and calls take the way through ctypes"""
     import subprocess

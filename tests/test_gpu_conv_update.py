@@ -146,6 +146,7 @@ def test_conv_update_with_the_approximate_estimator_matches_the_oracle(oracle, N
 @pytest.mark.parametrize("N,C,O,H,W,k", [(2, 16, 8, 5, 1, 3),          # images one pixel wide: no pixel pairs
                                          (2, 24, 16, 1, 1, 3),
                                          (3, 16, 24, 5, 3, 1),         # no border and an odd number of pixels: pairs would straddle images
+                                         (3, 48, 40, 7, 5, 1),         # ... with 32 channels in flight
                                          (5, 16, 24, 3, 2, 1),         # ... an even number, the grid's end inside a tile
                                          (2, 40, 72, 4, 2, 3),         # every pair of an image row is border beside a pixel
                                          (1, 48, 40, 65, 3, 5)])       # pairs that start on the row's last pixel, odd and even rows in turn

@@ -136,8 +136,8 @@ def _random_shapes(n, seed, t_mult, i_mult):
 
 @pytest.mark.parametrize("T,O,I", _random_shapes(14, 2024, 16, 8))
 def test_update_gemm_random_shapes(nm, oracle, T, O, I):
-    """seeded random problem sizes: every branch of the split-K plan (slab counts, tile counts that are and are not
-    multiples of 8, ragged tiles, ragged last stages) against the oracle"""
+    """seeded random problem sizes (slab counts, tile counts that are and are not multiples of 8, ragged tiles, ragged last steps) against the
+    oracle: most on 64 x 64 tiles with the tokens split over the waves, long reductions on 128 x 128 tiles in slabs"""
     run_case(nm, oracle, synth.Workload(f"r{T}x{O}x{I}", T, O, I, "bf16", "2:4", 0.0, 2.0, 0.3), seed=T + O + I)
 
 
@@ -325,6 +325,18 @@ def test_small_tiles_in_slabs(nm, oracle, T, O, I, slabs, beta):
     h, dW = to_dev(synth.make_h(w, 1)), torch.zeros(O, I, device=DEV)
     names = kernels_of(lambda: nm.nm_update_gemm(v, m, h, dW=dW, beta=beta))
     assert sum("update_gemm_smfmac_small_kernel" in n for n in names) == 1 and any("splitk_reduce" in n for n in names) == (slabs > 1)
+
+
+# fewer stages than the ring of the 128 x 128 kernel holds (six of 32 tokens), and just as many and one more
+@pytest.mark.parametrize("T", [16, 48, 176, 192, 208])
+@pytest.mark.parametrize("beta", [0.0, 1.0])
+def test_short_reductions_on_128_x_128_tiles(nm, oracle, T, beta):
+    O, I = 2048, 1032                                           # too many tiles of 64 x 64 for one to a CU, too few of 256 x 256
+    w = synth.Workload(f"short{T}x{O}x{I}", T, O, I, "bf16", "2:4", 0.0, 2.0, 0.3)
+    run_case(nm, oracle, w, seed=T, beta=beta)
+    v, m, _ = nm.mvue_prune_2of4(to_dev(synth.make_g(w, 1)))
+    h = to_dev(synth.make_h(w, 1))
+    assert any("update_gemm_smfmac_kernel<2, 2, 2, 2, false, false>" in n for n in kernels_of(lambda: nm.nm_update_gemm(v, m, h)))
 
 
 @pytest.mark.parametrize("T,O,I", [(16 * 333, 64, 3152), (16 * 262, 16, 5936)])

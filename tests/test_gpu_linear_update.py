@@ -26,7 +26,8 @@ def _padded(t, m):
     return torch.nn.functional.pad(t, (0, 0, 0, (-t.shape[0]) % m))
 
 
-# T (ragged and not), O, I: 128x128 tiles in one pass and in slabs; 256x128 and 256x256 tiles (8 waves); many slabs
+# T (ragged and not), O, I: bf16 64x64 tiles with the tokens split over the waves, in one slab and in several; 256x128 and 256x256 tiles (8 waves); 8-bit
+# 128x128 tiles in one pass and in slabs
 SHAPES = [(1, 8, 16), (15, 72, 48), (16, 64, 64), (17, 136, 80), (33, 256, 128), (1576, 256, 128), (3001, 128, 64), (2047, 2048, 1024), (3183, 3072, 1536)]
 
 
@@ -242,3 +243,14 @@ def test_layer_scales_are_those_of_the_scale_records(T, O, I):
                                         ("approx", 16380, 4096, 16), ("approx", 16385, 4104, 16)])
 def test_layers_on_either_side_of_the_prunes_lines(oracle, form, T, O, I):
     test_linear_update_matches_the_oracle(oracle, form, T, O, I)
+
+
+# 128 x 128 tiles with the only, the first few or all stages of their ring ending inside a token group
+@pytest.mark.parametrize("form", ["2:4", "relu"])
+@pytest.mark.parametrize("T", [1, 17, 33, 200])
+def test_ragged_short_reductions_on_128_x_128_tiles(oracle, form, T):
+    from gpu_util import kernels_of
+    from paper_2203_10991_amd import api
+    test_linear_update_matches_the_oracle(oracle, form, T, 2048, 1032)
+    g, h = (torch.randn(T, n, device=DEV).to(torch.bfloat16) for n in (2048, 1032))
+    assert any("update_gemm_smfmac_kernel<2, 2, 2, 2, false, true>" in n for n in kernels_of(lambda: api.nm_linear_update(g, h)))
