@@ -1,8 +1,8 @@
 """Linear and Conv2d layers whose UPDATE phase runs through libnm_mvue.
 
 Only the weight-gradient GEMM dW = g^T h (eq. (3)) sees the pruned gradient; the forward GEMM (eq. (1)) and the
-backward GEMM that propagates g (eq. (2)) are torch's dense ones, as in the paper (Table 1: the neural-gradient
-column accelerates the update phase only).  The random source is a pure function of (seed, stream_id, block),
+backward GEMM that propagates g (eq. (2)) are dense, as in the paper (Table 1: the neural-gradient
+column accelerates the update phase only): torch's, or for linear layers the library's where that is the faster call.  The random source is a pure function of (seed, stream_id, block),
 so holding `seed` fixed for `reuse_every` iterations is the sample reuse of App. B.1 (up to 50 iterations
 without loss) at no extra cost.
 

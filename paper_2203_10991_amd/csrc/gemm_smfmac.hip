@@ -866,9 +866,9 @@ static hipError_t run_plan(const Plan &p, const OutTarget &tg, const void *vals,
 
 hipError_t launch_update_gemm_smfmac(const void *vals, const uint16_t *meta, const void *h, int64_t ldh, float *dW,
                                      int64_t lddw, int64_t T, int64_t O, int64_t I, float beta, void *workspace,
-                                     hipStream_t st, size_t beside)
+                                     hipStream_t st)
 {
-    const Plan p = small_plan(make_plan(T, O, I, false, true, beside), T, O, I, ldh, false);
+    const Plan p = small_plan(make_plan(T, O, I), T, O, I, ldh, false);
     const int accumulate = beta != 0.f;
     const OutTarget tg = splitk_target(p.slabs, dW, lddw, workspace, O, I, accumulate);
     hipError_t e = run_plan(p, tg, vals, meta, h, ldh, T, T, O, I, st);

@@ -47,8 +47,8 @@ size_t update_gemm_workspace(int dt, int64_t T, int64_t O, int64_t I);
 // axis into slabs for shapes with few output tiles and sum the partials with launch_splitk_reduce
 hipError_t launch_update_gemm_smfmac(const void *vals, const uint16_t *meta, const void *h, int64_t ldh, float *dW,
                                      int64_t lddw, int64_t T, int64_t O, int64_t I, float beta, void *workspace,
-                                     hipStream_t st, size_t beside = 0);     // beside: workspace bytes of the call that are not this GEMM's
-size_t update_gemm_smfmac_workspace(int64_t T, int64_t O, int64_t I, size_t beside = 0);
+                                     hipStream_t st);
+size_t update_gemm_smfmac_workspace(int64_t T, int64_t O, int64_t I, size_t beside = 0);     // beside: workspace bytes of the call that are not partial sums
 // small problems (gemm_smfmac_small.hip): slabs partial sums of groups_per_slab (even) token groups each, slab_stride apart; h_rows rows of h (at most T, the rest count as zeros)
 hipError_t launch_update_gemm_smfmac_small(const void *vals, const uint16_t *meta, const void *h, int64_t ldh, int64_t h_rows, float *out, int64_t ldo,
                                            int64_t slab_stride, int slabs, int64_t groups_per_slab, int64_t T, int64_t O, int64_t I, int accumulate, hipStream_t st);
