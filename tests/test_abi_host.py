@@ -333,3 +333,14 @@ def test_the_forward_of_a_layer_on_the_cpu_needs_no_library(monkeypatch):
     monkeypatch.setattr(api, "load", missing)
     for layer in (ag.NMLinear(8, 16), ag.NMLinearReLU(8, 16, bias=False)):
         assert layer(torch.zeros(3, 8)).shape == (3, 16)
+
+
+def test_the_binding_has_no_thread_local_storage(lib):
+    """a library with a TLS segment that is loaded late sends every later access of others to theirs through the loader's slow path (glibc before
+    2.39): 0.45 us on each kernel launch of the process, whoever makes it"""
+    import struct
+    from paper_2203_10991_amd import api
+    image = open(os.path.join(os.path.dirname(api.LIB_PATH), "_nm_torch.so"), "rb").read()
+    at, size, count = struct.unpack_from("<Q", image, 32)[0], *struct.unpack_from("<HH", image, 54)
+    kinds = [struct.unpack_from("<I", image, at + i * size)[0] for i in range(count)]
+    assert 1 in kinds and 7 not in kinds                        # PT_LOAD, PT_TLS
