@@ -33,7 +33,12 @@ def kernels_of(call):
     from torch.profiler import ProfilerActivity, profile
     call()
     torch.cuda.synchronize()
-    with profile(activities=[ProfilerActivity.CPU, ProfilerActivity.CUDA]) as p:
-        call()
-        torch.cuda.synchronize()
-    return [e.name for e in sorted(p.events(), key=lambda e: e.time_range.start) if e.device_type == torch.autograd.DeviceType.CUDA]
+    names = []
+    for _ in range(3):                                          # (the first trace of a process may come back empty)
+        with profile(activities=[ProfilerActivity.CPU, ProfilerActivity.CUDA], acc_events=True) as p:
+            call()
+            torch.cuda.synchronize()
+        names = [e.name for e in sorted(p.events(), key=lambda e: e.time_range.start) if e.device_type == torch.autograd.DeviceType.CUDA]
+        if names:
+            break
+    return names
