@@ -366,21 +366,30 @@ template <int K> __device__ __forceinline__ float lane_of_four(float v)
     return __uint_as_float((uint32_t)__builtin_amdgcn_mov_dpp((int)__float_as_uint(v), K * 0x55, 0xF, 0xF, true));
 }
 
-// Four lanes to a token group and four columns, a quad of each column to a lane (bf16, the two 2:4 estimators): four times the waves of the kernel
-// above and a quarter of its chain from a wave's loads to its stores, which is what a launch takes that is a few waves deep.  The kept pairs
-// are turned among the four lanes, so that a lane stores the eight values of one column.  Call indices below 2^32.
+// Four lanes to a token group and four columns, a quad of each column to a lane (the MVUE estimators 2:4 and 1:2, where a lane then has two pairs): four
+// times the waves of the kernels above and a quarter of their chain from a wave's loads to its stores, which is what a launch takes that is a few waves
+// deep.  The kept pairs are turned among the four lanes, so that a lane stores the eight values of one column.  Call indices below 2^32.
 // Graph replays over rotating buffers, the kernel above -> this: optimal 512 x 512 5.3 -> 3.0 us, 1584 x 3072 7.9 -> 6.2, 12608 x 768 10.3 -> 9.7, and past
 // the line 8192 x 2048 13.1 -> 13.8, 16384 x 4096 40.7 -> 44.1 (address and index work of four threads instead of one); approx-MVUE,
 // whose arithmetic is four times as long, 9.8 -> 4.1, 14.9 -> 9.4, 19.6 -> 15.8, 25 -> 23, 82 -> 79: at every size that the kernel above would take.
+// binary32 2:4 1024 x 1024 6.9 -> 3.9, 1376 x 1232 8.2 -> 5.1, 12608 x 768 14.0 -> 12.1, 12608 x 3072 42 -> 37, past the line 16384 x 4096 70.7 -> 74.6
+// (approx 10.6 -> 4.8, 11.7 -> 6.3, 20.9 -> 16.9, 58 -> 53, 93.8 -> 96.1); MVUE 1:2, whose chain is shorter, bf16 512 x 512 4.1 -> 2.7, 2288 x 656 7.0 -> 3.5,
+// 12608 x 768 9.2 -> 8.6, past the line 4096 x 4096 11.5 -> 11.9, 12608 x 2304 16.7 -> 18.6; binary32 1024 x 1024 4.5 -> 3.2, past it 4096 x 1024 6.0 -> 6.5,
+// 8192 x 1024 9.3 -> 10.2 (rows a multiple of 4 KB apart; other widths gain up to 10 % there).
 // LAYER, PROD: as in prune_compress_body.
-constexpr int64_t QUAD_MOST = (int64_t)10 << 20, QUAD_MOST_APPROX = HALF_MOST;        // elements
-template <int EST> constexpr int64_t quad_most() { return EST == 1 ? QUAD_MOST_APPROX : QUAD_MOST; }
-template <int EST, int PROD = 0, bool LAYER = false>
+template <int DT, int M, int EST> constexpr int64_t quad_most()          // elements
+{
+    if (DT == NM_DT_F32) return (int64_t)(M == 2 ? 2 : 40) << 20;
+    return EST == 1 ? HALF_MOST : (int64_t)10 << 20;
+}
+template <int DT, int M, int EST, int PROD = 0, bool LAYER = false>
 __global__ __launch_bounds__(256) void prune_compress_quad_kernel(
     const void *__restrict__ g, int64_t n_groups, int64_t O, int64_t ldg, uint32_t key0, uint32_t key1, uint32_t stream_id,
     void *__restrict__ vals, uint16_t *__restrict__ meta, ProdArg pa, LayerArg la)
 {
     static_assert(PROD == 0 || LAYER, "the producer form of a layer");
+    static_assert(!LAYER || DT == NM_DT_BF16, "layers are bf16");
+    constexpr int ESZ = DT == NM_DT_F32 ? 4 : 2, PW = ESZ / 2;           // words of a kept pair
     const int64_t n = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (n >= n_groups * O) return;                                       // (O is a multiple of 8: the four lanes leave together)
     const int b = (int)(n & 3);                                          // quad
@@ -411,58 +420,79 @@ __global__ __launch_bounds__(256) void prune_compress_quad_kernel(
             }
         }
     } else {
-        const char *gp = (const char *)g + (((int64_t)G * 16 + 4 * b) * ldg + col0) * 2;
+        const char *gp = (const char *)g + (((int64_t)G * 16 + 4 * b) * ldg + col0) * ESZ;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) rows[r] = load_global8(gp + (int64_t)r * ldg * 2);
+        for (int r = 0; r < 4; ++r) rows[r] = ESZ == 4 ? load_global(gp + (int64_t)r * ldg * ESZ) : load_global8(gp + (int64_t)r * ldg * ESZ);
     }
-    constexpr int CALLS = EST == 1 ? 2 : 1;
-    const uint32_t call0 = ((G * 4 + b) * ncg + col0 / 4) * CALLS;
+    // M = 4: the quad's one call (approx-MVUE: two, side by side); M = 2: one for each of its two rows of pairs
+    constexpr int CALLS = EST == 1 || M == 2 ? 2 : 1;
     uint32_t words[4 * CALLS];
 #pragma unroll
     for (int q = 0; q < CALLS; ++q) {
+        const uint32_t call = M == 2 ? (G * 8 + 2 * b + q) * ncg + col0 / 4 : ((G * 4 + b) * ncg + col0 / 4) * CALLS + q;
         uint32_t w4[4];
-        philox4x32_10_uniform_c123(call0 + q, 0u, stream_id, EST == 1 ? 1u : 0u, key0, key1, w4);
+        philox4x32_10_uniform_c123(call, 0u, stream_id, EST == 1 ? 1u : 0u, key0, key1, w4);
 #pragma unroll
         for (int j = 0; j < 4; ++j) words[4 * q + j] = w4[j];
     }
-    uint32_t w[4], nib[4];
+    uint32_t w[PW][4], nib[4];
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
         float v0, v1;
-        if constexpr (EST == 1)
-            select_2of4_approx(Row<NM_DT_BF16>::get(rows[0], c), Row<NM_DT_BF16>::get(rows[1], c), Row<NM_DT_BF16>::get(rows[2], c),
-                               Row<NM_DT_BF16>::get(rows[3], c), words[2 * c], words[2 * c + 1], v0, v1, nib[c]);
+        if constexpr (M == 2) {
+            uint32_t k0, k1;
+            select_1of2(Row<DT>::get(rows[0], c), Row<DT>::get(rows[1], c), words[c], k0, v0);
+            select_1of2(Row<DT>::get(rows[2], c), Row<DT>::get(rows[3], c), words[4 + c], k1, v1);
+            nib[c] = k0 | (2u | k1) << 2;
+        } else if constexpr (EST == 1)
+            select_2of4_approx(Row<DT>::get(rows[0], c), Row<DT>::get(rows[1], c), Row<DT>::get(rows[2], c),
+                               Row<DT>::get(rows[3], c), words[2 * c], words[2 * c + 1], v0, v1, nib[c]);
         else
-            select_2of4<NM_DT_BF16>(Key<NM_DT_BF16>::make(rows[0], c, 0), Key<NM_DT_BF16>::make(rows[1], c, 1), Key<NM_DT_BF16>::make(rows[2], c, 2),
-                                    Key<NM_DT_BF16>::make(rows[3], c, 3), words[c], v0, v1, nib[c]);
-        w[c] = pack_bf16_rne(v0, v1);
+            select_2of4<DT>(Key<DT>::make(rows[0], c, 0), Key<DT>::make(rows[1], c, 1), Key<DT>::make(rows[2], c, 2), Key<DT>::make(rows[3], c, 3),
+                            words[c], v0, v1, nib[c]);
+        if constexpr (DT == NM_DT_F32) { w[0][c] = __float_as_uint(v0); w[PW - 1][c] = __float_as_uint(v1); }
+        else w[0][c] = pack_bf16_rne(v0, v1);
     }
-    if constexpr (LAYER) {                                               // column sums: quads in order, as one thread adds them
+    if constexpr (LAYER) {                                               // column sums: quads (M = 2: pairs) in order, as one thread adds them
         float cs[4];
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-            float q = Row<NM_DT_BF16>::get(rows[0], c) + Row<NM_DT_BF16>::get(rows[1], c);
-            q += Row<NM_DT_BF16>::get(rows[2], c) + Row<NM_DT_BF16>::get(rows[3], c);
-            cs[c] = lane_of_four<0>(q) + lane_of_four<1>(q);
-            cs[c] += lane_of_four<2>(q);
-            cs[c] += lane_of_four<3>(q);
+            const float q0 = Row<DT>::get(rows[0], c) + Row<DT>::get(rows[1], c), q1 = Row<DT>::get(rows[2], c) + Row<DT>::get(rows[3], c);
+            if constexpr (M == 2) {
+                cs[c] = lane_of_four<0>(q0) + lane_of_four<0>(q1);
+                cs[c] += lane_of_four<1>(q0); cs[c] += lane_of_four<1>(q1);
+                cs[c] += lane_of_four<2>(q0); cs[c] += lane_of_four<2>(q1);
+                cs[c] += lane_of_four<3>(q0); cs[c] += lane_of_four<3>(q1);
+            } else {
+                const float q = q0 + q1;
+                cs[c] = lane_of_four<0>(q) + lane_of_four<1>(q);
+                cs[c] += lane_of_four<2>(q);
+                cs[c] += lane_of_four<3>(q);
+            }
         }
         if (b == 0) put_csum(la, G0, G, O, col0, cs);
     }
     // lane b, word c -> lane c, word b
 #pragma unroll
-    for (int i = 0; i < 4; i += 2) {
-        const uint32_t t = lane_xor<1>(b & 1 ? w[i] : w[i + 1]);
-        w[i] = b & 1 ? t : w[i];
-        w[i + 1] = b & 1 ? w[i + 1] : t;
-    }
+    for (int p = 0; p < PW; ++p) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const uint32_t t = lane_xor<2>(b & 2 ? w[i] : w[i + 2]);
-        w[i] = b & 2 ? t : w[i];
-        w[i + 2] = b & 2 ? w[i + 2] : t;
+        for (int i = 0; i < 4; i += 2) {
+            const uint32_t t = lane_xor<1>(b & 1 ? w[p][i] : w[p][i + 1]);
+            w[p][i] = b & 1 ? t : w[p][i];
+            w[p][i + 1] = b & 1 ? w[p][i + 1] : t;
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const uint32_t t = lane_xor<2>(b & 2 ? w[p][i] : w[p][i + 2]);
+            w[p][i] = b & 2 ? t : w[p][i];
+            w[p][i + 2] = b & 2 ? w[p][i + 2] : t;
+        }
     }
-    *(uint4 *)((char *)vals + n * 16) = make_uint4(w[0], w[1], w[2], w[3]);      // ((G O + col0 + b) * 16)
+    uint4 *vp = (uint4 *)((char *)vals + n * (8 * ESZ));                 // ((G O + col0 + b) 8 values)
+    if constexpr (DT == NM_DT_F32) {
+        vp[0] = make_uint4(w[0][0], w[PW - 1][0], w[0][1], w[PW - 1][1]);
+        vp[1] = make_uint4(w[0][2], w[PW - 1][2], w[0][3], w[PW - 1][3]);
+    } else *vp = make_uint4(w[0][0], w[0][1], w[0][2], w[0][3]);
     uint32_t lo = (nib[0] | (nib[1] << 16)) << (4 * b), hi = (nib[2] | (nib[3] << 16)) << (4 * b);
     lo |= lane_xor<1>(lo); hi |= lane_xor<1>(hi);
     lo |= lane_xor<2>(lo); hi |= lane_xor<2>(hi);
@@ -1116,9 +1146,9 @@ static hipError_t launch_prune_t(const void *g, int64_t T, int64_t O, int64_t ld
 #define NM_ARGS g, groups, O, ldg, (uint32_t)seed, (uint32_t)(seed >> 32), stream_id, vals, meta
     if (dense)
         hipLaunchKernelGGL((prune_compress_kernel<DT, M, EST, true>), grid, dim3(256), 0, st, NM_ARGS, dense, ldd);
-    else if (DT == NM_DT_BF16 && M == 4 && (EST == 0 || EST == 1) && T * O <= quad_most<EST>()) {
-        if constexpr (DT == NM_DT_BF16 && M == 4 && (EST == 0 || EST == 1))
-            hipLaunchKernelGGL((prune_compress_quad_kernel<EST>), dim3((unsigned)((groups * O + 255) / 256)), dim3(256), 0, st, NM_ARGS,
+    else if ((EST == 0 || EST == 1) && T * O <= quad_most<DT, M, EST>()) {
+        if constexpr (EST == 0 || EST == 1)
+            hipLaunchKernelGGL((prune_compress_quad_kernel<DT, M, EST>), dim3((unsigned)((groups * O + 255) / 256)), dim3(256), 0, st, NM_ARGS,
                                ProdArg{}, LayerArg{});
     } else if (half) {
         if constexpr (DT == NM_DT_BF16 && EST == 0) {
@@ -1188,11 +1218,12 @@ hipError_t launch_prune_layer(int m, int est, const void *g, int64_t ldg, const 
             hipLaunchKernelGGL((prune_layer_kernel<M, EST, PROD, false>), dim3((unsigned)blocks), dim3(256), 0, st, g, groups, O, ldg,  \
                                (uint32_t)seed, (uint32_t)(seed >> 32), stream_id, vals, meta, pa, la);                                  \
     } while (0)
-#define NM_QUAD(EST, PROD)                                                                                                              \
-    hipLaunchKernelGGL((prune_compress_quad_kernel<EST, PROD, true>), dim3((unsigned)((groups * O + 255) / 256)), dim3(256), 0, st, g, groups, O, \
+#define NM_QUAD(M, EST, PROD)                                                                                                           \
+    hipLaunchKernelGGL((prune_compress_quad_kernel<NM_DT_BF16, M, EST, PROD, true>), dim3((unsigned)((groups * O + 255) / 256)), dim3(256), 0, st, g, groups, O, \
                        ldg, (uint32_t)seed, (uint32_t)(seed >> 32), stream_id, vals, meta, pa, la)
-    if (m == 4 && est == 1 && T * O <= quad_most<1>()) { if (act) NM_QUAD(1, 2); else NM_QUAD(1, 0); }
-    else if (m == 4 && est == 0 && T * O <= quad_most<0>()) { if (act) NM_QUAD(0, 2); else NM_QUAD(0, 0); }
+    if (m == 4 && est == 1 && T * O <= quad_most<NM_DT_BF16, 4, 1>()) { if (act) NM_QUAD(4, 1, 2); else NM_QUAD(4, 1, 0); }
+    else if (m == 4 && est == 0 && T * O <= quad_most<NM_DT_BF16, 4, 0>()) { if (act) NM_QUAD(4, 0, 2); else NM_QUAD(4, 0, 0); }
+    else if (m == 2 && T * O <= quad_most<NM_DT_BF16, 2, 0>()) { if (act) NM_QUAD(2, 0, 2); else NM_QUAD(2, 0, 0); }
     else if (act) { if (m == 2) NM_LAYER(2, 0, 2); else if (est == 1) NM_LAYER(4, 1, 2); else NM_LAYER(4, 0, 2); }
     else { if (m == 2) NM_LAYER(2, 0, 0); else if (est == 1) NM_LAYER(4, 1, 0); else NM_LAYER(4, 0, 0); }
 #undef NM_QUAD

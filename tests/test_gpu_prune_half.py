@@ -63,3 +63,47 @@ def test_either_side_of_a_quad_to_a_lane_matches_the_oracle(oracle, T):
     v, m, _ = nm.mvue_prune_2of4(d[:, :O], seed=(5 << 32) + 9, stream_id=1)
     ov, om, _ = oracle.prune_2of4(g, (5 << 32) + 9, 1)
     assert np.array_equal(to_host(m), om) and np.array_equal(to_host(v), ov)
+
+
+def _f32(T, O, seed):
+    return synth.make_g(synth.Workload("t", T, O, 8, "f32", "2:4", 0.0, 2.0, 0.3), seed)
+
+
+# binary32 with a quad to a lane: a wave and less, a partly filled workgroup, a padded stride; either side of its lines (1:2 2 * 2^20 elements, 2:4 40 * 2^20)
+@pytest.mark.parametrize("T,O,ld", [(16, 8, 8), (16, 256, 256), (48, 72, 76), (1584, 96, 104), (528, 40, 40), (1024, 2048, 2048), (1040, 2048, 2048)])
+@pytest.mark.parametrize("which", ["1of2", "2of4", "approx"])
+def test_binary32_matches_the_oracle(oracle, T, O, ld, which):
+    import paper_2203_10991_amd as nm
+    g = _f32(T, O, T + O)
+    g[:4, :8] = np.array([0.0, -0.0, 3e37, 1.5, 2.0 ** -140, 1.5, -1.5, 0.0], dtype=np.float32)
+    d = torch.zeros((T, ld), dtype=torch.float32, device=DEV)
+    d[:, :O] = to_dev(g)
+    seed = (3 << 32) + 5
+    if which == "1of2":
+        v, m, _ = nm.mvue_prune_1of2(d[:, :O], seed=seed, stream_id=2)
+        ov, om, _ = oracle.prune_1of2(g, seed, 2)
+    else:
+        v, m, _ = nm.mvue_prune_2of4(d[:, :O], seed=seed, stream_id=2, mode=int(which == "approx"))
+        ov, om, _ = (oracle.prune_2of4_approx if which == "approx" else oracle.prune_2of4)(g, seed, 2)
+    assert np.array_equal(to_host(m), om) and np.array_equal(to_host(v).view(np.uint32), ov.view(np.uint32))
+
+
+@pytest.mark.parametrize("T", [10240, 10256])
+def test_either_side_of_a_binary32_quad_to_a_lane(oracle, T):
+    import paper_2203_10991_amd as nm
+    O = 4096
+    g = _f32(T, O, 4)
+    v, m, _ = nm.mvue_prune_2of4(to_dev(g), seed=9, stream_id=1)
+    ov, om, _ = oracle.prune_2of4(g, 9, 1)
+    assert np.array_equal(to_host(m), om) and np.array_equal(to_host(v).view(np.uint32), ov.view(np.uint32))
+
+
+@pytest.mark.parametrize("T", [4096, 4112])
+def test_either_side_of_a_pair_row_to_a_lane_matches_the_oracle(oracle, T):
+    """MVUE 1:2 in bf16 with four lanes to a group up to 4096 x 2560"""
+    import paper_2203_10991_amd as nm
+    O = 2560
+    g = _g(T, O, 8)
+    v, m, _ = nm.mvue_prune_1of2(to_dev(g), seed=9, stream_id=1)
+    ov, om, _ = oracle.prune_1of2(g, 9, 1)
+    assert np.array_equal(to_host(m), om) and np.array_equal(to_host(v), ov)
