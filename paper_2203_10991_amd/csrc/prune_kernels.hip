@@ -90,8 +90,9 @@ __device__ __forceinline__ void prune_compress_body(
     constexpr int ESZ = DT == NM_DT_F32 ? 4 : 2;
     constexpr int RB = VEC * ESZ;                     // bytes of a thread's piece of a row: 16 or 8
     const int64_t ncg = O / VEC;
-    const int64_t n = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (n >= n_groups * ncg) return;                 // (NT: the launcher has checked that the thread count is a multiple of 64: whole waves leave)
+    // (NT: the stores go through whole waves, and the last wave's threads past the end do what the last thread does)
+    const int64_t threads = n_groups * ncg, n_own = (int64_t)blockIdx.x * 256 + threadIdx.x, n = NT ? min(n_own, threads - 1) : n_own;
+    if ((NT ? n_own - (int64_t)(threadIdx.x & 63) : n) >= threads) return;
     const int64_t G = n / ncg;
     const int64_t col0 = (n - G * ncg) * VEC;
 
@@ -243,21 +244,23 @@ __device__ __forceinline__ void prune_compress_body(
         static_assert(VEC == 4, "the sums leave as one float4");
         put_csum(la, t0 / 16, G, O, col0, cs);
     }
-    // ---- kept values: 8 per column, VEC columns contiguous
-    [[maybe_unused]] char *vp = (char *)vals_ + ((G * O + col0) * 8) * ESZ;            // = vals_ + 16 PC n (below): a wave's 64 threads own one run of it
-    [[maybe_unused]] uint16_t *mp_late = nullptr;
+    // ---- kept values: 8 per column, VEC columns contiguous: 16 PC bytes of a thread (below), of which a wave's 64 threads own one run
     // Streaming stores want whole lines per instruction: the wave's pieces (8 KB at eight columns per thread) go through LDS of
     // its own, written as each thread holds them (PC 16-byte pieces; piece c of lane l at slot PC l + (c ^ l%PC), which spreads the
     // lanes over the banks) and read back so that store k covers bytes [1024 k, 1024 k + 1024).
-    // Every lane of the wave is here (the launcher sends only launches made of whole waves to the streaming kernels), and
-    // a wave's LDS operations execute in order, so the reads below see the writes above without a workgroup barrier.
+    // Every lane of the wave is here, and a wave's LDS operations execute in order, so the reads below see the writes above without a
+    // workgroup barrier.  The stores go through descriptors that end with the last thread's piece, so that thread counts need be no
+    // multiple of 64 (those had plain stores and loads: MVUE 1:2 4112 x 4104 16.9 us, now 12.2, binary32 12208 x 5344 85 -> 64; 2:4 12208 x 1336 17.4 -> 12.9).
     constexpr int PC = VEC * KW / 4;                                     // 16-byte pieces per thread
+    uint4 mw;                                                            // index words
+    mw.x = md[0] | (md[1] << 16); mw.y = md[2] | (md[3] << 16);
+    mw.z = md[4 % VEC] | (md[5 % VEC] << 16); mw.w = md[6 % VEC] | (md[7 % VEC] << 16);
     if constexpr (NT) {
         __shared__ __attribute__((aligned(1024))) char xs[4 * 1024 * PC];
         uint32_t tid = threadIdx.x;
         asm volatile("" : "+v"(tid) : "v"(kept[VEC - 1][KW - 1]));       // (the addresses below are formed here, after the last block, not carried through the kernel)
-        const uint32_t lane = tid & 63u, wave_lds = (tid >> 6) * (1024 * PC);
-        const int64_t n_late = (int64_t)blockIdx.x * 256 + tid;          // = n
+        const uint32_t lane = tid & 63u, wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6)), wave_lds = wave * (1024 * PC);
+        const int64_t n_wave = (int64_t)blockIdx.x * 256 + wave * 64, there = min(threads - n_wave, (int64_t)64);
         // byte address of piece p of this lane: 16 PC lane + 16 (p ^ lane%PC) = (16 PC lane + 16 (lane%PC)) ^ 16 p
         const uint32_t wr = wave_lds + lane * (16 * PC) + (lane % PC) * 16;
 #pragma unroll
@@ -269,33 +272,20 @@ __device__ __forceinline__ void prune_compress_body(
             }
         __builtin_amdgcn_wave_barrier();
         // store k, lane l: piece l%PC of the wave's thread (64/PC) k + l/PC, which sits at slot 64 k + PC (l/PC) + (l%PC ^ (l/PC)%PC)
-        char *wave_base = (char *)vals_ + (n_late - lane) * (16 * PC);
-        mp_late = meta_ + n_late * VEC;                                   // (G O + col0 = n VEC)
+        const auto rv = __builtin_amdgcn_make_buffer_rsrc((char *)vals_ + n_wave * (16 * PC), 0, (int)there * (16 * PC), 0x00020000);
+        const auto rm = __builtin_amdgcn_make_buffer_rsrc((char *)meta_ + n_wave * (2 * VEC), 0, (int)there * (2 * VEC), 0x00020000);
         const uint32_t rd = wave_lds + (PC * (lane / PC) + ((lane % PC) ^ ((lane / PC) % PC))) * 16;
 #pragma unroll
-        for (int k = 0; k < PC; ++k) store_stream(wave_base + (1024 * k + 16 * lane), *(const uint4 *)(xs + rd + 1024 * k));
+        for (int k = 0; k < PC; ++k) buffer_put_piece<16, true>(rv, 16 * lane + 1024 * k, *(const uint4 *)(xs + rd + 1024 * k));
+        buffer_put_piece<2 * VEC, true>(rm, 2 * VEC * lane, mw);
     } else {
+        uint4 *vp = (uint4 *)((char *)vals_ + n * (16 * PC));
 #pragma unroll
-    for (int c = 0; c < VEC; ++c)
+        for (int c = 0; c < VEC; ++c)
 #pragma unroll
-        for (int j = 0; j < KW / 4; ++j)
-            ((uint4 *)vp)[c * (KW / 4) + j] = make_uint4(kept[c][4 * j], kept[c][4 * j + 1], kept[c][4 * j + 2], kept[c][4 * j + 3]);
-    }
-    // ---- index words
-    uint16_t *mp = NT ? mp_late : meta_ + (G * O + col0);
-    if (VEC == 8) {
-        uint4 o;
-        o.x = md[0] | (md[1] << 16); o.y = md[2] | (md[3] << 16);
-        o.z = md[4 % VEC] | (md[5 % VEC] << 16); o.w = md[6 % VEC] | (md[7 % VEC] << 16);
-        if constexpr (NT) store_stream(mp, o);
-        else *(uint4 *)mp = o;
-    } else {
-        uint2 o;
-        o.x = md[0] | (md[1] << 16); o.y = md[2] | (md[3] << 16);
-        if constexpr (NT) {
-            const u32x2_t t = {o.x, o.y};
-            __builtin_nontemporal_store(t, (u32x2_t *)mp);
-        } else *(uint2 *)mp = o;
+            for (int j = 0; j < KW / 4; ++j) vp[c * (KW / 4) + j] = make_uint4(kept[c][4 * j], kept[c][4 * j + 1], kept[c][4 * j + 2], kept[c][4 * j + 3]);
+        if (VEC == 8) *(uint4 *)(meta_ + n * VEC) = mw;
+        else *(uint2 *)(meta_ + n * VEC) = make_uint2(mw.x, mw.y);
     }
 
     // ---- optional dense theta(g)
@@ -324,14 +314,15 @@ __device__ __forceinline__ void prune_compress_body(
     }
 }
 
-template <int DT, int M, int EST, bool DENSE>
-__global__ __launch_bounds__(256) void prune_compress_kernel(
+// with the dense output
+template <int DT, int M, int EST>
+__global__ __launch_bounds__(256) void prune_compress_dense_kernel(
     const void *__restrict__ g, int64_t n_groups, int64_t O, int64_t ldg, uint32_t key0, uint32_t key1, uint32_t stream_id,
     void *__restrict__ vals, uint16_t *__restrict__ meta, void *__restrict__ dense, int64_t ldd)
 {
-    prune_compress_body<DT, M, EST, DENSE>(g, n_groups, O, ldg, key0, key1, stream_id, vals, meta, dense, ldd);
+    prune_compress_body<DT, M, EST, true>(g, n_groups, O, ldg, key0, key1, stream_id, vals, meta, dense, ldd);
 }
-// The streaming form (no dense output): its 32 KB of LDS let five workgroups onto a CU, so five waves per SIMD is
+// Without it, the streaming form: its 32 KB of LDS let five workgroups onto a CU, so five waves per SIMD is
 // what the registers are budgeted for (four for the instances that need more than 96).
 // HI0: every Philox call index of the launch is below 2^32, which the launcher has checked.
 template <int DT, int M, int EST, bool HI0>
@@ -499,28 +490,22 @@ __global__ __launch_bounds__(256) void prune_compress_quad_kernel(
     if (b == 0) *(uint2 *)(meta + n) = make_uint2(lo, hi);
 }
 // the form of a layer's backward pass (bf16; see LayerArg): PROD = 2 with the ReLU's derivative in front, else 0
-template <int M, int EST, int PROD, bool NT>
+template <int M, int EST, int PROD>
 __global__ __launch_bounds__(256) void prune_layer_kernel(
     const void *__restrict__ g, int64_t n_groups, int64_t O, int64_t ldg, uint32_t key0, uint32_t key1, uint32_t stream_id,
     void *__restrict__ vals, uint16_t *__restrict__ meta, ProdArg pa, LayerArg la)
 {
-    prune_compress_body<NM_DT_BF16, M, EST, false, PROD, true, NT, 4, true>(g, n_groups, O, ldg, key0, key1, stream_id, vals, meta, nullptr, 0, pa, la);
+    prune_compress_body<NM_DT_BF16, M, EST, false, PROD, true, true, 4, true>(g, n_groups, O, ldg, key0, key1, stream_id, vals, meta, nullptr, 0, pa, la);
 }
-template <int DT, int M, int EST, bool NT>
+template <int DT, int M, int EST>
 __global__ __launch_bounds__(256) void prune_producer_kernel(
     const void *__restrict__ u, int64_t n_groups, int64_t O, int64_t ldu, uint32_t key0, uint32_t key1, uint32_t stream_id,
     void *__restrict__ vals, uint16_t *__restrict__ meta, ProdArg pa)
 {
-    prune_compress_body<DT, M, EST, false, 1, false, NT>(u, n_groups, O, ldu, key0, key1, stream_id, vals, meta, nullptr, 0, pa);
+    prune_compress_body<DT, M, EST, false, 1, false, true>(u, n_groups, O, ldu, key0, key1, stream_id, vals, meta, nullptr, 0, pa);
 }
-// The bf16 optimal-2:4 kernel without the dense output needs 98 registers as the compiler would have it, two more
-// than let a fifth wave onto each SIMD; asked for five waves it fits 96 without spilling.
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 5))) void prune_compress_bf16_2of4_kernel(
-    const void *__restrict__ g, int64_t n_groups, int64_t O, int64_t ldg, uint32_t key0, uint32_t key1, uint32_t stream_id,
-    void *__restrict__ vals, uint16_t *__restrict__ meta)
-{
-    prune_compress_body<NM_DT_BF16, 4, 0, false, 0, true>(g, n_groups, O, ldg, key0, key1, stream_id, vals, meta, nullptr, 0);
-}
+// The bf16 optimal-2:4 kernel needs 98 registers as the compiler would have it, two more than let a fifth wave onto
+// each SIMD; asked for five waves it fits 96 without spilling.
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 5))) void prune_compress_bf16_2of4_stream_kernel(
     const void *__restrict__ g, int64_t n_groups, int64_t O, int64_t ldg, uint32_t key0, uint32_t key1, uint32_t stream_id,
     void *__restrict__ vals, uint16_t *__restrict__ meta)
@@ -1137,38 +1122,34 @@ static hipError_t launch_prune_t(const void *g, int64_t T, int64_t O, int64_t ld
     if (threads == 0) return hipSuccess;
     const int64_t blocks = (threads + 255) / 256;
     if (blocks > 0x7fffffffll) return hipErrorInvalidConfiguration;
-    // The streaming kernels store through whole waves: they take the launches whose thread count is a multiple of 64.
     // hi0: every call index (block / 4, or block / 2 for approx-MVUE's two words per block) lies below 2^32
     const bool hi0 = EST != 4 && (uint64_t)(T / M) * (uint64_t)O <= ((uint64_t)1 << (EST == 1 ? 33 : 34));
     const dim3 grid((unsigned)blocks);
-    const bool half = DT == NM_DT_BF16 && EST == 0 && threads % 32 == 0 && 2 * blocks <= 0x7fffffffll &&
-                      (M == 2 || T * O <= HALF_MOST);             // (M = 4: hi0 holds at these sizes)
 #define NM_ARGS g, groups, O, ldg, (uint32_t)seed, (uint32_t)(seed >> 32), stream_id, vals, meta
-    if (dense)
-        hipLaunchKernelGGL((prune_compress_kernel<DT, M, EST, true>), grid, dim3(256), 0, st, NM_ARGS, dense, ldd);
-    else if ((EST == 0 || EST == 1) && T * O <= quad_most<DT, M, EST>()) {
-        if constexpr (EST == 0 || EST == 1)
+    if (dense) {
+        hipLaunchKernelGGL((prune_compress_dense_kernel<DT, M, EST>), grid, dim3(256), 0, st, NM_ARGS, dense, ldd);
+        return hipGetLastError();
+    }
+    if constexpr (EST == 0 || EST == 1)
+        if (T * O <= quad_most<DT, M, EST>()) {
             hipLaunchKernelGGL((prune_compress_quad_kernel<DT, M, EST>), dim3((unsigned)((groups * O + 255) / 256)), dim3(256), 0, st, NM_ARGS,
                                ProdArg{}, LayerArg{});
-    } else if (half) {
-        if constexpr (DT == NM_DT_BF16 && EST == 0) {
-            const dim3 half_grid((unsigned)((2 * threads + 255) / 256));
+            return hipGetLastError();
+        }
+    if constexpr (DT == NM_DT_BF16 && EST == 0) {
+        const dim3 half_grid((unsigned)((2 * threads + 255) / 256));
+        if (M == 2 && (2 * threads + 255) / 256 > 0x7fffffffll) return hipErrorInvalidConfiguration;
+        if (M == 2 || T * O <= HALF_MOST) {                       // (M = 4: hi0 holds at these sizes)
             if (hi0) hipLaunchKernelGGL((prune_compress_half_kernel<M, EST, true>), half_grid, dim3(256), 0, st, NM_ARGS);
             else if constexpr (M == 2) hipLaunchKernelGGL((prune_compress_half_kernel<M, EST, false>), half_grid, dim3(256), 0, st, NM_ARGS);
-        }
-    }
-    else if (DT == NM_DT_BF16 && M == 4 && EST == 0 && hi0 && threads % 64 == 0)
-        hipLaunchKernelGGL(prune_compress_bf16_2of4_stream_kernel, grid, dim3(256), 0, st, NM_ARGS);
-    else if (DT == NM_DT_BF16 && M == 4 && EST == 0 && hi0)
-        hipLaunchKernelGGL(prune_compress_bf16_2of4_kernel, grid, dim3(256), 0, st, NM_ARGS);
-    else if (threads % 64 == 0) {
-        if constexpr (!(DT == NM_DT_BF16 && M == 2 && EST == 0)) {             // (that one runs with half the columns)
-            if (hi0) hipLaunchKernelGGL((prune_compress_stream_kernel<DT, M, EST, true>), grid, dim3(256), 0, st, NM_ARGS);
+        } else if constexpr (M == 4) {
+            if (hi0) hipLaunchKernelGGL(prune_compress_bf16_2of4_stream_kernel, grid, dim3(256), 0, st, NM_ARGS);
             else hipLaunchKernelGGL((prune_compress_stream_kernel<DT, M, EST, false>), grid, dim3(256), 0, st, NM_ARGS);
-        } else
-            hipLaunchKernelGGL((prune_compress_kernel<DT, M, EST, false>), grid, dim3(256), 0, st, NM_ARGS, dense, ldd);
-    } else
-        hipLaunchKernelGGL((prune_compress_kernel<DT, M, EST, false>), grid, dim3(256), 0, st, NM_ARGS, dense, ldd);
+        }
+    } else {
+        if (hi0) hipLaunchKernelGGL((prune_compress_stream_kernel<DT, M, EST, true>), grid, dim3(256), 0, st, NM_ARGS);
+        else hipLaunchKernelGGL((prune_compress_stream_kernel<DT, M, EST, false>), grid, dim3(256), 0, st, NM_ARGS);
+    }
 #undef NM_ARGS
     return hipGetLastError();
 }
@@ -1182,16 +1163,9 @@ hipError_t launch_prune_producer(int dt, int m, int est, const void *u, int64_t 
     const int64_t blocks = (threads + 255) / 256;
     if (blocks > 0x7fffffffll) return hipErrorInvalidConfiguration;
     const ProdArg pa{d, ldd, gout, ldgo};
-    // whole waves only on the streaming form (its stores go through the whole wave)
-#define NM_PROD(DT, M, EST)                                                                                             \
-    do {                                                                                                                \
-        if (threads % 64 == 0)                                                                                          \
-            hipLaunchKernelGGL((prune_producer_kernel<DT, M, EST, true>), dim3((unsigned)blocks), dim3(256), 0, st, u, groups, O, ldu,  \
-                               (uint32_t)seed, (uint32_t)(seed >> 32), stream_id, vals, meta, pa);                      \
-        else                                                                                                            \
-            hipLaunchKernelGGL((prune_producer_kernel<DT, M, EST, false>), dim3((unsigned)blocks), dim3(256), 0, st, u, groups, O, ldu, \
-                               (uint32_t)seed, (uint32_t)(seed >> 32), stream_id, vals, meta, pa);                      \
-    } while (0)
+#define NM_PROD(DT, M, EST)                                                                                                     \
+    hipLaunchKernelGGL((prune_producer_kernel<DT, M, EST>), dim3((unsigned)blocks), dim3(256), 0, st, u, groups, O, ldu,        \
+                       (uint32_t)seed, (uint32_t)(seed >> 32), stream_id, vals, meta, pa)
     if (dt == NM_DT_F32) { if (m == 2) NM_PROD(NM_DT_F32, 2, 0); else if (est == 1) NM_PROD(NM_DT_F32, 4, 1); else NM_PROD(NM_DT_F32, 4, 0); }
     else { if (m == 2) NM_PROD(NM_DT_BF16, 2, 0); else if (est == 1) NM_PROD(NM_DT_BF16, 4, 1); else NM_PROD(NM_DT_BF16, 4, 0); }
 #undef NM_PROD
@@ -1209,15 +1183,9 @@ hipError_t launch_prune_layer(int m, int est, const void *g, int64_t ldg, const 
     if (blocks > 0x7fffffffll) return hipErrorInvalidConfiguration;
     const ProdArg pa{act, lda, gout, ldgo};
     const LayerArg la{T, csum};
-#define NM_LAYER(M, EST, PROD)                                                                                                         \
-    do {                                                                                                                                \
-        if (threads % 64 == 0)                                                                                                          \
-            hipLaunchKernelGGL((prune_layer_kernel<M, EST, PROD, true>), dim3((unsigned)blocks), dim3(256), 0, st, g, groups, O, ldg,   \
-                               (uint32_t)seed, (uint32_t)(seed >> 32), stream_id, vals, meta, pa, la);                                  \
-        else                                                                                                                            \
-            hipLaunchKernelGGL((prune_layer_kernel<M, EST, PROD, false>), dim3((unsigned)blocks), dim3(256), 0, st, g, groups, O, ldg,  \
-                               (uint32_t)seed, (uint32_t)(seed >> 32), stream_id, vals, meta, pa, la);                                  \
-    } while (0)
+#define NM_LAYER(M, EST, PROD)                                                                                                  \
+    hipLaunchKernelGGL((prune_layer_kernel<M, EST, PROD>), dim3((unsigned)blocks), dim3(256), 0, st, g, groups, O, ldg,         \
+                       (uint32_t)seed, (uint32_t)(seed >> 32), stream_id, vals, meta, pa, la)
 #define NM_QUAD(M, EST, PROD)                                                                                                           \
     hipLaunchKernelGGL((prune_compress_quad_kernel<NM_DT_BF16, M, EST, PROD, true>), dim3((unsigned)((groups * O + 255) / 256)), dim3(256), 0, st, g, groups, O, \
                        ldg, (uint32_t)seed, (uint32_t)(seed >> 32), stream_id, vals, meta, pa, la)

@@ -273,10 +273,11 @@ template <int BYTES> __device__ __forceinline__ uint4 buffer_piece(__amdgpu_buff
         return make_uint4(t.x, t.y, 0u, 0u);
     }
 }
-template <int BYTES> __device__ __forceinline__ void buffer_put_piece(__amdgpu_buffer_rsrc_t r, uint32_t offset, const uint4 &v)
+// NT: the streaming form
+template <int BYTES, bool NT = false> __device__ __forceinline__ void buffer_put_piece(__amdgpu_buffer_rsrc_t r, uint32_t offset, const uint4 &v)
 {
-    if constexpr (BYTES == 16) { const u32x4_t t = {v.x, v.y, v.z, v.w}; __builtin_amdgcn_raw_buffer_store_b128(t, r, (int)offset, 0, 0); }
-    else { const u32x2_t t = {v.x, v.y}; __builtin_amdgcn_raw_buffer_store_b64(t, r, (int)offset, 0, 0); }
+    if constexpr (BYTES == 16) { const u32x4_t t = {v.x, v.y, v.z, v.w}; __builtin_amdgcn_raw_buffer_store_b128(t, r, (int)offset, 0, NT ? 2 : 0); }
+    else { const u32x2_t t = {v.x, v.y}; __builtin_amdgcn_raw_buffer_store_b64(t, r, (int)offset, 0, NT ? 2 : 0); }
 }
 __device__ __forceinline__ void store_stream(void *p, const uint4 &v)
 {

@@ -107,3 +107,17 @@ def test_either_side_of_a_pair_row_to_a_lane_matches_the_oracle(oracle, T):
     v, m, _ = nm.mvue_prune_1of2(to_dev(g), seed=9, stream_id=1)
     ov, om, _ = oracle.prune_1of2(g, 9, 1)
     assert np.array_equal(to_host(m), om) and np.array_equal(to_host(v), ov)
+
+
+# beyond the lines of four lanes to a group: a last wave that is not whole
+@pytest.mark.parametrize("T,O", [(4112, 2568), (10256, 1032), (16, 655368)])
+@pytest.mark.parametrize("which", ["1of2", "2of4", "f32"])
+def test_last_wave_partly_filled(oracle, T, O, which):
+    import paper_2203_10991_amd as nm
+    g = _f32(T, O, 3) if which == "f32" else _g(T, O, 3)
+    if which == "2of4":
+        (v, m, _), (ov, om, _) = nm.mvue_prune_2of4(to_dev(g), seed=2, stream_id=1), oracle.prune_2of4(g, 2, 1)
+    else:
+        (v, m, _), (ov, om, _) = nm.mvue_prune_1of2(to_dev(g), seed=2, stream_id=1), oracle.prune_1of2(g, 2, 1)
+    u = np.uint32 if which == "f32" else np.uint16
+    assert np.array_equal(to_host(m), om) and np.array_equal(to_host(v).view(u), ov.view(u))
