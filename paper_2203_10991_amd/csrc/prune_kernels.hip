@@ -673,6 +673,130 @@ __global__ __launch_bounds__(256) void prune_compress_q8_kernel(
     for (int c = 0; c < VEC / 4; ++c) mp[c] = make_uint4(md[4 * c], md[4 * c + 1], md[4 * c + 2], md[4 * c + 3]);
 }
 
+// The value of the lane at distance 4 among eight lanes: half of the row reversed, then four lanes reversed
+__device__ __forceinline__ uint32_t lane_xor4(uint32_t v)
+{
+    const int t = __builtin_amdgcn_mov_dpp((int)v, 0x141, 0xF, 0xF, true);                             // row_half_mirror: 7 - lane
+    return (uint32_t)__builtin_amdgcn_mov_dpp(t, 0x1B, 0xF, 0xF, true);                                // quad_perm [3, 2, 1, 0]
+}
+
+// Eight lanes to a token group and four columns, a quad of each column to a lane, as in prune_compress_quad_kernel: an eighth of the kernel above's
+// chain, which is what a launch takes that is a few waves deep.  Call indices below 2^32.
+// Graph replays, the kernel above -> this, us: optimal 512 x 512 9.8 -> 3.2, 2592 x 1928 11.1 -> 6.7, 12608 x 768 16.0 -> 11.3, 4096 x 4096 18.1 -> 15.3,
+// 12608 x 3072 33.4 -> 32.4, past the line 16384 x 4096 51.2 -> 54.4; approx-MVUE 19.1 -> 4.3, 20.8 -> 10.4, 30.4 -> 17.6, 32.6 -> 26.5, 62.6 -> 55.0,
+// at its line 92.4 -> 90.4; MVUE 1:2 7.9 -> 2.8, 9.4 -> 6.0, 14.5 -> 9.9, 16.2 -> 14.9, past its line 30.7 -> 30.7 and 45.9 -> 53.6.
+template <int EST> constexpr int64_t quad_q8_most() { return EST == 1 ? HALF_MOST : (int64_t)(EST == 3 ? 32 : 40) << 20; }      // elements
+template <int DT, int EST, bool LAYER = false>
+__global__ __launch_bounds__(256) void prune_compress_q8_quad_kernel(
+    const void *__restrict__ g, int64_t n_groups, int64_t O, int64_t ldg, uint32_t key0, uint32_t key1, uint32_t stream_id,
+    float scale, const float *__restrict__ scale_dev, uint8_t *__restrict__ vals8, uint32_t *__restrict__ meta32, LayerArg la)
+{
+    static_assert(!LAYER || DT == NM_DT_BF16, "layers are bf16");
+    constexpr int ESZ = DT == NM_DT_F32 ? 4 : 2, RB = 4 * ESZ;
+    [[maybe_unused]] uint4 peaks;
+    if constexpr (LAYER) peaks = layer_peaks(la.scale);
+    else if (scale_dev) scale = scale_dev[0];
+    const int64_t n = (int64_t)blockIdx.x * 256 + threadIdx.x, threads = n_groups * O * 2;
+    // (LAYER: the last wave's threads past the end stay until it has its scale; what they load is past the last token and reads as zeros)
+    if ((LAYER ? n - (int64_t)(threadIdx.x & 63) : n) >= threads) return;                              // (O is a multiple of 8: the eight lanes leave together)
+    const int b = (int)(n & 7);                                                                        // quad
+    const uint32_t cell = (uint32_t)(n >> 3), ncg = (uint32_t)(O / 4);
+    const uint32_t G = cell / ncg, col0 = (cell - G * ncg) * 4;
+    [[maybe_unused]] const uint32_t G0 = LAYER ? (uint32_t)__builtin_amdgcn_readfirstlane((int)G) : 0u;          // as in prune_compress_quad_kernel: at most 4 groups on
+    uint4 rows[4];
+    if constexpr (LAYER) {
+        const int64_t t0 = (int64_t)G0 * 32, bytes = (la.T - t0) * ldg * ESZ;
+        const auto rg = __builtin_amdgcn_make_buffer_rsrc((char *)g + t0 * ldg * ESZ, 0, (int)(uint32_t)(bytes > 0xffffffffll ? 0xffffffffll : bytes), 0x00020000);
+        const uint32_t token = (G - G0) * 32 + 4 * b;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) rows[r] = buffer_piece<RB>(rg, ((token + r) * (uint32_t)ldg + col0) * ESZ);
+        scale = layer_scale(la.scale, peaks, blockIdx.x == 0);
+        if (n >= threads) return;
+    } else {
+        const char *gp = (const char *)g + (((int64_t)G * 32 + 4 * b) * ldg + col0) * ESZ;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) rows[r] = RB == 16 ? load_global(gp + (int64_t)r * ldg * ESZ) : load_global8(gp + (int64_t)r * ldg * ESZ);
+    }
+    // calls of the selection and of the rounding; MVUE 1:2 has one of either for each of the quad's two rows of pairs
+    auto draw = [&](uint32_t call, uint32_t domain, uint32_t *words) {
+        uint32_t w4[4];
+        philox4x32_10_uniform_c123(call, 0u, stream_id, domain, key0, key1, w4);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) words[j] = w4[j];
+    };
+    uint32_t words[8], rnd[8];
+    const uint32_t quad_call = (G * 8 + b) * ncg + col0 / 4;
+    if constexpr (EST == 3) {
+#pragma unroll
+        for (int pr = 0; pr < 2; ++pr) {
+            const uint32_t call = (G * 16 + 2 * b + pr) * ncg + col0 / 4;
+            draw(call, 0u, words + 4 * pr);
+            draw(call, 2u, rnd + 4 * pr);
+        }
+    } else {
+        if constexpr (EST == 1) { draw(2 * quad_call, 1u, words); draw(2 * quad_call + 1, 1u, words + 4); }
+        else draw(quad_call, 0u, words);
+        draw(quad_call, 2u, rnd);
+    }
+    uint32_t w[4], nib[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        float v0, v1;
+        uint32_t r0 = rnd[c] << 16, r1 = rnd[c] & 0xffff0000u;
+        if constexpr (EST == 3) {
+            uint32_t k0, k1;
+            select_1of2(Row<DT>::get(rows[0], c), Row<DT>::get(rows[1], c), words[c], k0, v0);
+            select_1of2(Row<DT>::get(rows[2], c), Row<DT>::get(rows[3], c), words[4 + c], k1, v1);
+            nib[c] = k0 | (2u | k1) << 2;
+            r1 = rnd[4 + c] << 16;
+        } else if constexpr (EST == 1)
+            select_2of4_approx(Row<DT>::get(rows[0], c), Row<DT>::get(rows[1], c), Row<DT>::get(rows[2], c), Row<DT>::get(rows[3], c),
+                               words[2 * c], words[2 * c + 1], v0, v1, nib[c]);
+        else
+            select_2of4<DT>(Key<DT>::make(rows[0], c, 0), Key<DT>::make(rows[1], c, 1), Key<DT>::make(rows[2], c, 2), Key<DT>::make(rows[3], c, 3),
+                            words[c], v0, v1, nib[c]);
+        w[c] = sr_e5m2_into<1>(sr_e5m2_into<0>(0u, v0 * scale, r0), v1 * scale, r1);
+    }
+    if constexpr (LAYER) {                                               // column sums: quads in order, as one thread adds them
+        float cs[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const float q = (Row<DT>::get(rows[0], c) + Row<DT>::get(rows[1], c)) + (Row<DT>::get(rows[2], c) + Row<DT>::get(rows[3], c));
+            const float q4 = __uint_as_float(lane_xor4(__float_as_uint(q)));         // lanes 0-3: the quads of lanes 4-7
+            cs[c] = lane_of_four<0>(q) + lane_of_four<1>(q);
+            cs[c] += lane_of_four<2>(q); cs[c] += lane_of_four<3>(q);
+            cs[c] += lane_of_four<0>(q4); cs[c] += lane_of_four<1>(q4);
+            cs[c] += lane_of_four<2>(q4); cs[c] += lane_of_four<3>(q4);
+        }
+        if (b == 0) put_csum(la, G0, G, O, col0, cs);
+    }
+    // two lanes make a word of four codes; then lane pair i, word of column c -> lane pair c, word i
+#pragma unroll
+    for (int c = 0; c < 4; ++c) { const uint32_t t = lane_xor<1>(w[c]); w[c] = b & 1 ? t | w[c] << 16 : w[c] | t << 16; }
+#pragma unroll
+    for (int i = 0; i < 4; i += 2) {
+        const uint32_t t = lane_xor<2>(b & 2 ? w[i] : w[i + 1]);
+        w[i] = b & 2 ? t : w[i];
+        w[i + 1] = b & 2 ? w[i + 1] : t;
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const uint32_t t = lane_xor4(b & 4 ? w[i] : w[i + 2]);
+        w[i] = b & 4 ? t : w[i];
+        w[i + 2] = b & 4 ? w[i + 2] : t;
+    }
+    // each lane of a pair stores half of the column's 16 bytes: eight bytes a lane
+    *(uint2 *)(vals8 + n * 8) = b & 1 ? make_uint2(w[2], w[3]) : make_uint2(w[0], w[1]);              // ((G O + col0) 16 + 8 b)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        nib[c] <<= 4 * b;
+        nib[c] |= lane_xor<1>(nib[c]);
+        nib[c] |= lane_xor<2>(nib[c]);
+        nib[c] |= lane_xor4(nib[c]);
+    }
+    if (b == 0) *(uint4 *)(meta32 + (n >> 1)) = make_uint4(nib[0], nib[1], nib[2], nib[3]);          // (G O + col0)
+}
+
 template <int DT, int EST>
 static hipError_t launch_prune_q8_t(const void *g, int64_t T, int64_t O, int64_t ldg, uint64_t seed, uint32_t stream_id,
                                     float scale, const float *scale_dev, uint8_t *vals8, uint32_t *meta32, hipStream_t st)
@@ -685,6 +809,11 @@ static hipError_t launch_prune_q8_t(const void *g, int64_t T, int64_t O, int64_t
     const int64_t threads = groups * (O / VEC);
     if (threads == 0) return hipSuccess;
     if ((threads + 255) / 256 > 0x7fffffffll) return hipErrorInvalidConfiguration;
+    if (T * O <= quad_q8_most<EST>()) {
+        hipLaunchKernelGGL((prune_compress_q8_quad_kernel<DT, EST>), dim3((unsigned)((groups * O * 2 + 255) / 256)), dim3(256), 0, st,
+                           g, groups, O, ldg, (uint32_t)seed, (uint32_t)(seed >> 32), stream_id, scale, scale_dev, vals8, meta32, LayerArg{});
+        return hipGetLastError();
+    }
 #define NM_Q8(HI0)                                                                                                                   \
     hipLaunchKernelGGL((prune_compress_q8_kernel<DT, EST, HI0, VEC>), dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st,     \
                        g, groups, O, ldg, (uint32_t)seed, (uint32_t)(seed >> 32), stream_id, scale, scale_dev, vals8, meta32, LayerArg{})
@@ -705,8 +834,15 @@ hipError_t launch_prune_q8_layer(int est, const void *g, int64_t ldg, int64_t T,
     if (threads == 0) return hipSuccess;
     if (blocks > 0x7fffffffll) return hipErrorInvalidConfiguration;
 #define NM_Q8L(EST)                                                                                                                     \
-    hipLaunchKernelGGL((prune_compress_q8_kernel<NM_DT_BF16, EST, true, 4, true>), dim3((unsigned)blocks), dim3(256), 0, st, g, groups, O, \
-                       ldg, (uint32_t)seed, (uint32_t)(seed >> 32), stream_id, 1.0f, (const float *)nullptr, vals8, meta32, LayerArg{T, csum, ls})
+    do {                                                                                                                                \
+        if (T * O <= quad_q8_most<EST>())                                                                                               \
+            hipLaunchKernelGGL((prune_compress_q8_quad_kernel<NM_DT_BF16, EST, true>), dim3((unsigned)((groups * O * 2 + 255) / 256)), dim3(256), 0, st, g, \
+                               groups, O, ldg, (uint32_t)seed, (uint32_t)(seed >> 32), stream_id, 1.0f, (const float *)nullptr, vals8, meta32, \
+                               LayerArg{T, csum, ls});                                                                                  \
+        else                                                                                                                            \
+            hipLaunchKernelGGL((prune_compress_q8_kernel<NM_DT_BF16, EST, true, 4, true>), dim3((unsigned)blocks), dim3(256), 0, st, g, groups, O, \
+                               ldg, (uint32_t)seed, (uint32_t)(seed >> 32), stream_id, 1.0f, (const float *)nullptr, vals8, meta32, LayerArg{T, csum, ls}); \
+    } while (0)
     if (est == 3) NM_Q8L(3); else if (est == 1) NM_Q8L(1); else NM_Q8L(0);
 #undef NM_Q8L
     return hipGetLastError();

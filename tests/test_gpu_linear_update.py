@@ -245,6 +245,12 @@ def test_layers_on_either_side_of_the_prunes_lines(oracle, form, T, O, I):
     test_linear_update_matches_the_oracle(oracle, form, T, O, I)
 
 
+# MVUE 1:2 with four lanes to a group up to 10 * 2^20 elements, the 8-bit prune with eight up to 40 * 2^20; last waves that are not whole
+@pytest.mark.parametrize("form,T,O,I", [("1:2", 4095, 2560, 16), ("1:2", 4097, 2568, 16), ("q8", 10239, 4096, 16), ("q8", 10241, 4104, 16), ("q8", 33, 40, 16)])
+def test_layers_on_either_side_of_further_lines(oracle, form, T, O, I):
+    test_linear_update_matches_the_oracle(oracle, form, T, O, I)
+
+
 # 128 x 128 tiles with the only, the first few or all stages of their ring ending inside a token group
 @pytest.mark.parametrize("form", ["2:4", "relu"])
 @pytest.mark.parametrize("T", [1, 17, 33, 200])

@@ -58,6 +58,22 @@ def test_prune_q8_bit_exact(nm, oracle, dtype, mode, T, O):
     assert np.array_equal(v.cpu().numpy(), ov)
 
 
+# the largest launches with a quad to a lane (approx-MVUE 16384 x 4096, optimal 10240 x 4096, MVUE 1:2 8192 x 4096) and the first ones beyond, a padded stride
+@pytest.mark.parametrize("which,T", [("approx", 16384), ("approx", 16416), ("2of4", 10240), ("2of4", 10272), ("1of2", 8192), ("1of2", 8224)])
+def test_prune_q8_on_either_side_of_the_lines(nm, oracle, which, T):
+    O = 4096
+    g = synth.make_g(synth.Workload("q8", T, O, 16, "bf16", "2:4", 0.0, 2.5, 0.3), seed=T)
+    scale, seed = fit_scale(as_f32(g)), (1 << 40) + 7
+    d = torch.zeros((T, O + 8), dtype=torch.bfloat16, device=DEV)
+    d[:, :O] = to_dev(g)
+    if which == "1of2":
+        (ov, om), (v, m) = oracle.prune_1of2_q8(g, seed, 3, scale), nm.mvue_prune_1of2_q8(d[:, :O], seed=seed, stream_id=3, scale=scale)
+    else:
+        mode = int(which == "approx")
+        (ov, om), (v, m) = oracle.prune_2of4_q8(g, seed, 3, mode, scale), nm.mvue_prune_2of4_q8(d[:, :O], seed=seed, stream_id=3, mode=mode, scale=scale)
+    assert np.array_equal(m.cpu().numpy().view(np.uint32), om) and np.array_equal(v.cpu().numpy(), ov)
+
+
 def test_prune_q8_strided_input_small_and_large_scales(nm, oracle):
     """row stride larger than O; scales that push kept values into the subnormal range and into saturation"""
     T, O = 96, 40
