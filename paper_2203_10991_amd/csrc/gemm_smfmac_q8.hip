@@ -33,9 +33,6 @@ namespace nm {
 constexpr int KT8 = 64;           // tokens per LDS stage (one 64-token MFMA step, two 32-token groups)
 constexpr int NS8 = 6;            // LDS stages
 
-union FragB8 { i32x8 v; u32x2 q[4]; };
-union FragA8 { i32x4 v; u32x4 u4; };
-
 // alpha * (one accumulator element) to global memory: the element is copied out of its accumulation register, scaled
 // and stored inside one statement, so that the compiler never holds whole blocks in ordinary registers
 __device__ __forceinline__ void store_acc_scaled(float *p, float v, float alpha)
@@ -43,24 +40,6 @@ __device__ __forceinline__ void store_acc_scaled(float *p, float v, float alpha)
     float t;
     asm volatile("v_accvgpr_read_b32 %0, %2\n\tv_mul_f32 %0, %0, %3\n\tglobal_store_dword %1, %0, off"
                  : "=&v"(t) : "v"(p), "a"(v), "v"(alpha) : "memory");
-}
-// The (accumulate, alpha) argument pair of the kernels also carries the device-scale form without another kernel
-// argument (the 384 x 256 kernel has no register to spare for one): accumulate bit 0 = add to what is there, bit 1 =
-// "the scale is in device memory", and then the other 62 bits of the pair are the address of that binary32 value
-// (4-byte aligned: low 30 bits in accumulate[31:2], high 32 bits in alpha's bit pattern).  Decoded in the epilogue only.
-__device__ __forceinline__ float decode_alpha(int accumulate, float alpha)
-{
-    if (accumulate & 2) {
-        const uint64_t addr = ((uint64_t)__float_as_uint(alpha) << 32) | (uint32_t)(accumulate & ~3);
-        return *(const float *)addr;
-    }
-    return alpha;
-}
-template <int OFFSET> __device__ __forceinline__ u32x2 lds_read_tr8(uint32_t addr)
-{
-    u32x2 r;
-    asm volatile("ds_read_b64_tr_b8 %0, %1 offset:%2" : "=v"(r) : "v"(addr), "n"(OFFSET) : "memory");
-    return r;
 }
 
 // LDS image of one stage (all filled by direct loads, 64 consecutive lanes -> consecutive LDS bytes):
@@ -574,6 +553,7 @@ __global__ __launch_bounds__(512) void update_gemm_smfmac_q8_tall_kernel(
 // tall_rows: rows [0, tall_rows) of dW are computed by the 384 x 256 kernel (tall_tiles_m tile rows), the rest by the
 // kernel of `shape`
 struct PlanQ8 { int shape; int tm; int tiles_m, tiles_n; int slabs; int64_t groups_per_slab; int64_t tall_rows; int tall_tiles_m; };
+constexpr int SMALL8 = 4;           // shape: 64 x 64 tiles, the tokens split over the waves (small_plan_q8)
 
 static PlanQ8 make_plan_q8(int64_t T, int64_t O, int64_t I, bool shifted = false)
 {
@@ -639,6 +619,36 @@ static AlphaPair encode_alpha(int accumulate, const AlphaArg &al, hipStream_t st
     return p;
 }
 
+// Small problems: 64 x 64 tiles with the tokens split over a workgroup's eight waves (gemm_smfmac_small.hip), as in the 16-bit path, by two models in
+// microseconds.  The tile kernels: 10.5 and 1.6 for every trip of their ring, whatever the tile.  The small one: 4.7, then for a wave's step of 64 tokens
+// 0.45 alone, 0.85 from 48 workgroups on, never less than the tiles' operands at 12.5 TB/s or one pass over the operands at 3, and a round more for
+// every 256 workgroups.  Both: the second pass.  Within 15 % of what 77
+// sizes from 32 to 16384 tokens and from 64 x 64 to 4088 x 288 took (operands in no cache), so a margin of 10 %.  At most the tile kernels'
+// slabs, whose workspace a call is asked for whichever runs.  Tile kernels -> this, us: 256 x 512 x 512 12.8 -> 5.1, 1024^3 21.2 -> 7.6,
+// 2048 x 1024 x 1024 24.8 -> 9.3, 8192 x 512 x 512 23.2 -> 13 (4 slabs), 1024 x 2112 x 976 25.0 -> 18.4; stays: 4096 x 2112 x 976 28.6 (34.7).
+static PlanQ8 small_plan_q8(PlanQ8 p, int64_t T, int64_t O, int64_t I, int64_t ldh)
+{
+    const int64_t groups = T / 32, tiles = (O + 63) / 64 * ((I + 63) / 64);
+    if (groups == 0 || tiles > 4 * NM_CUS || p.tall_rows > 0 || ldh > (1 << 24)) return p;          // (offsets of 32 bits: 64 rows of h8)
+    auto second_pass = [&](int64_t sl) { return sl > 1 ? 2.6 + (double)(sl + 1) * (double)O * (double)I * 4.0 / 3.5e6 : 0.0; };
+    double least = 0.9 * (10.5 + 1.6 * (double)((p.groups_per_slab < groups ? p.groups_per_slab : groups) + 11) / 12.0 + second_pass(p.slabs));
+    int slabs = 0;
+    for (const int s : {1, 2, 3, 4, 6, 8}) {
+        const int64_t wgs = s * tiles, rounds = (wgs + NM_CUS - 1) / NM_CUS, steps = ((groups + s - 1) / s + 15) / 16;
+        if (s > p.slabs || (s > 1 && rounds > 1)) break;
+        const double loop = std::max({(double)(rounds * steps) * (0.45 + 0.4 * std::min(1.0, (double)wgs / 48.0)), (double)tiles * (double)T * 104.0 / 12.5e6,
+                                      (double)T * ((double)I + (double)O * 0.625) / 3e6});
+        const double us = 0.6 + 4.1 * (double)rounds + loop + second_pass(s);
+        if (us < least) { least = us; slabs = s; }
+    }
+    if (slabs > 0) {
+        p.shape = SMALL8;
+        p.slabs = slabs;
+        p.groups_per_slab = slab_groups(groups, p.slabs, 2);
+    }
+    return p;
+}
+
 size_t update_gemm_q8_workspace(int64_t T, int64_t O, int64_t I)
 {
     if (T <= 0 || O <= 0 || I <= 0) return 0;
@@ -649,6 +659,8 @@ size_t update_gemm_q8_workspace(int64_t T, int64_t O, int64_t I)
 static hipError_t run_q8_plan(const PlanQ8 &p, const OutTarget &tg, const AlphaPair &ap, const uint8_t *vals8, const uint32_t *meta32,
                               const uint8_t *h8, int64_t ldh, int64_t T, int64_t O, int64_t I, hipStream_t st)
 {
+    if (p.shape == SMALL8)
+        return launch_update_gemm_q8_small(vals8, meta32, h8, ldh, tg.out, tg.ldo, tg.slab_stride, p.slabs, p.groups_per_slab, T, O, I, ap.acc, ap.alpha, st);
     if (p.tall_rows > 0) {
         hipLaunchKernelGGL(update_gemm_smfmac_q8_tall_kernel, dim3((unsigned)(p.tall_tiles_m * p.tiles_n)), dim3(512), 0, st,
                            vals8, meta32, h8, ldh, tg.out, tg.ldo, T / 32, O, I, p.tall_tiles_m, p.tiles_n, ap.acc, ap.alpha, p.tall_rows);
@@ -673,7 +685,7 @@ hipError_t launch_update_gemm_q8(const uint8_t *vals8, const uint32_t *meta32, c
                                  hipStream_t st)
 {
     if (O == 0 || I == 0) return hipSuccess;
-    const PlanQ8 p = make_plan_q8(T, O, I);
+    const PlanQ8 p = small_plan_q8(make_plan_q8(T, O, I), T, O, I, ldh);
     const int accumulate = beta != 0.f;
     const OutTarget tg = splitk_target(p.slabs, dW, lddw, workspace, O, I, accumulate);
     // partial sums are scaled once, in the second pass; otherwise the kernels scale, by a host or a device value
@@ -692,7 +704,7 @@ size_t update_gemm_q8_parts_bytes(int64_t T, int64_t O, int64_t I)
 hipError_t launch_update_gemm_q8_parts(const uint8_t *vals8, const uint32_t *meta32, const uint8_t *h8, int64_t ldh, int64_t T, int64_t O,
                                        int64_t I, float *part, int *slabs, hipStream_t st)
 {
-    const PlanQ8 p = make_plan_q8(T, O, I);
+    const PlanQ8 p = small_plan_q8(make_plan_q8(T, O, I), T, O, I, ldh);
     *slabs = p.slabs;
     return run_q8_plan(p, OutTarget{part, I, O * I, 0}, AlphaPair{0, 1.0f}, vals8, meta32, h8, ldh, T, O, I, st);
 }

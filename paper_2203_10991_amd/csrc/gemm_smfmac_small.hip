@@ -29,6 +29,47 @@ constexpr int SM_SUMS = SM_WAVES * SM_TILE * SM_TILE * 4;
 constexpr int SM_LDS = SM_WAVES * SM_RING * SM_STEP > SM_SUMS ? SM_WAVES * SM_RING * SM_STEP : SM_SUMS;
 static_assert(SM_LDS <= 160 * 1024 && SM_STEP % 256 == 0, "LDS");
 
+// The eight waves' blocks are summed in a fixed tree, each sum goes through `scale`, and the tile is stored.  S: SM_SUMS bytes at least
+template <typename F>
+__device__ __forceinline__ void sum_and_store(f32x16 (&acc)[2][2], char *S, int wave, int64_t m0, int64_t n0, float *out, int64_t ldo, int64_t O, int64_t I,
+                                              bool accumulate, F scale)
+{
+    const int tid = threadIdx.x, lane = tid & 63;
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b) acc_settled(acc[a][b]);
+    __syncthreads();                                                    // every wave's ring is done with: the sums go there
+    float *sums = (float *)S;
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int r = 0; r < 16; ++r)                                // block a holds rows a, 2 + a, ...
+                sums[wave * (SM_TILE * SM_TILE) + (2 * (8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)) + a) * SM_TILE + b * 32 + (lane & 31)] = acc[a][b][r];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < SM_TILE * SM_TILE / 4 / (SM_WAVES * 64); ++k) {
+        const int at = (k * SM_WAVES * 64 + tid) * 4, row = at / SM_TILE, col = at % SM_TILE;
+        float4 v[SM_WAVES];
+#pragma unroll
+        for (int w = 0; w < SM_WAVES; ++w) v[w] = *(const float4 *)(sums + w * (SM_TILE * SM_TILE) + at);
+#pragma unroll
+        for (int d = 1; d < SM_WAVES; d <<= 1)
+#pragma unroll
+            for (int w = 0; w < SM_WAVES; w += 2 * d) add4(v[w], v[w + d]);
+        if (m0 + row < O && n0 + col < I) {
+            float4 *p = (float4 *)(out + (m0 + row) * ldo + n0 + col);
+            v[0] = make_float4(scale(v[0].x), scale(v[0].y), scale(v[0].z), scale(v[0].w));
+            if (accumulate) add4(v[0], *p);
+            *p = v[0];
+        }
+    }
+}
+
 // h_rows: rows h has, at most n_groups * 16; the rows past it and a token group past the end count as zeros
 __global__ __launch_bounds__(SM_WAVES * 64) void update_gemm_smfmac_small_kernel(const uint16_t *__restrict__ vals, const uint16_t *__restrict__ meta,
                                                                                const uint16_t *__restrict__ h, int64_t ldh, int64_t h_rows, float *__restrict__ out,
@@ -122,38 +163,105 @@ __global__ __launch_bounds__(SM_WAVES * 64) void update_gemm_smfmac_small_kernel
         fetch(slot);
         slot = slot == SM_RING - 1 ? 0 : slot + 1;
     }
-    __builtin_amdgcn_sched_barrier(0);
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");
+    sum_and_store(acc, S, wave, m0, n0, out, ldo, O, I, accumulate & 1, [](float v) { return v; });
+}
+
+// The same for 8-bit operands.  A step is 64 tokens: h8 [64 tokens][64 columns] bytes, chunk c (16 columns) of row k at position c ^ 2 (k / 4 % 2) (a transposing
+// read touches the same 32 bytes of eight consecutive rows, of which every fourth one shares the banks), vals8 as above, then the index words [2 groups][64 rows].
+// The tile kernels take 14 us for anything of up to 384 tokens (six stages and a barrier each, however few are needed):
+// 256 x 512 x 512 12.8 -> 5.1, 1024^3 21.2 -> 7.6.  A wave's step is bound by the way to its operands, 0.45 us alone and 0.8-1.15 with all CUs busy.
+constexpr int S8_A = 64 * SM_TILE, S8_M = S8_A + 2 * SM_TILE * 16, S8_STEP = S8_M + 2 * SM_TILE * 4, S8_LOADS = 8;       // direct loads of a step: 4 h8, 2 vals8, 2 index words
+constexpr int S8_LDS = SM_WAVES * SM_RING * S8_STEP > SM_SUMS ? SM_WAVES * SM_RING * S8_STEP : SM_SUMS;
+static_assert(S8_LDS <= 160 * 1024 && S8_STEP % 256 == 0, "LDS");
+
+__global__ __launch_bounds__(SM_WAVES * 64) void update_gemm_q8_small_kernel(const uint8_t *__restrict__ vals, const uint32_t *__restrict__ meta,
+                                                                            const uint8_t *__restrict__ h, int64_t ldh, float *__restrict__ out, int64_t ldo,
+                                                                            int64_t slab_stride, int64_t n_groups, int64_t groups_per_slab, int64_t O, int64_t I,
+                                                                            int tiles_m, int tiles_n, int accumulate, float alpha)
+{
+    const int64_t g0 = (int64_t)blockIdx.z * groups_per_slab;           // (even, below n_groups)
+    vals += g0 * O * 16; meta += g0 * O; h += g0 * 32 * ldh; out += (int64_t)blockIdx.z * slab_stride;
+    n_groups = min(n_groups - g0, groups_per_slab);
+
+    __shared__ __attribute__((aligned(1024))) char S[S8_LDS];
+    int tm, tn;
+    tile_of_workgroup((int)blockIdx.x, tiles_m, tiles_n, tm, tn);
+    tm = __builtin_amdgcn_readfirstlane(tm); tn = __builtin_amdgcn_readfirstlane(tn);
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t m0 = (int64_t)tm * SM_TILE, n0 = (int64_t)tn * SM_TILE;
+    const int steps = (int)((n_groups + 1) / 2), mine = (steps - wave + SM_WAVES - 1) / SM_WAVES;      // steps wave, wave + 8, ...
+
+    f32x16 acc[2][2];
 #pragma unroll
     for (int a = 0; a < 2; ++a)
 #pragma unroll
-        for (int b = 0; b < 2; ++b) acc_settled(acc[a][b]);
-    __syncthreads();                                                    // every wave's ring is done with: the sums go there
-    float *sums = (float *)S;
+        for (int b = 0; b < 2; ++b) acc_zero(acc[a][b]);
+
+    // ---- direct loads; columns and rows past the end are clamped (their sums are not stored), a second group past the end is sent out of range, which drops
+    // it: its h8 rows and kept values are zeroed when the step has landed (its index words may hold anything)
+    const int row16 = lane >> 2;
+    const uint32_t b_src = (uint32_t)(row16 * ldh + min(n0 + 16 * ((lane & 3) ^ (2 * ((row16 >> 2) & 1))), I - 16)), b_step = (uint32_t)(16 * ldh);
+    const uint32_t a_src = (uint32_t)min(m0 + 2 * (lane & 31) + (lane >> 5), O - 1) * 16u, m_src = (uint32_t)min(m0 + lane, O - 1) * 4u;
+    char *ring = S + wave * SM_RING * S8_STEP;
+    const char *hp = (const char *)(h + (int64_t)wave * 64 * ldh), *vp = (const char *)(vals + (int64_t)wave * 2 * O * 16), *mp = (const char *)(meta + (int64_t)wave * 2 * O);
+    const int64_t h_step = (int64_t)SM_WAVES * 64 * ldh, v_step = (int64_t)SM_WAVES * 2 * O * 16, m_step = (int64_t)SM_WAVES * 2 * O * 4;
+    int ahead = 0;                                                      // this wave's step whose loads are being issued
+    auto rsrc = [](const char *base, bool there) { return __builtin_amdgcn_make_buffer_rsrc((void *)base, 0, there ? 0x7fffffff : 0, 0x00020000); };
+    auto fetch = [&](int slot) {
+        char *to = ring + slot * S8_STEP;
+        const bool there = ahead < mine, both = there && !(wave + ahead * SM_WAVES == steps - 1 && n_groups % 2);
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+        for (int d = 0; d < 4; ++d) load16_to_lds(rsrc(hp, d < 2 ? there : both), to + d * 1024, b_src + d * b_step, 0);
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
+        for (int g = 0; g < 2; ++g) load16_to_lds(rsrc(vp, g ? both : there), to + S8_A + g * 1024, a_src, (uint32_t)(g * O * 16));
 #pragma unroll
-            for (int r = 0; r < 16; ++r)                                // block a holds rows a, 2 + a, ...
-                sums[wave * (SM_TILE * SM_TILE) + (2 * (8 * (r >> 2) + 4 * kg + (r & 3)) + a) * SM_TILE + b * 32 + (lane & 31)] = acc[a][b][r];
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < SM_TILE * SM_TILE / 4 / (SM_WAVES * 64); ++k) {
-        const int at = (k * SM_WAVES * 64 + tid) * 4, row = at / SM_TILE, col = at % SM_TILE;
-        float4 v[SM_WAVES];
-#pragma unroll
-        for (int w = 0; w < SM_WAVES; ++w) v[w] = *(const float4 *)(sums + w * (SM_TILE * SM_TILE) + at);
-#pragma unroll
-        for (int d = 1; d < SM_WAVES; d <<= 1)
-#pragma unroll
-            for (int w = 0; w < SM_WAVES; w += 2 * d) add4(v[w], v[w + d]);
-        if (m0 + row < O && n0 + col < I) {
-            float4 *p = (float4 *)(out + (m0 + row) * ldo + n0 + col);
-            if (accumulate) add4(v[0], *p);
-            *p = v[0];
-        }
+        for (int g = 0; g < 2; ++g) load4_to_lds(rsrc(mp, g ? both : there), to + S8_M + g * 256, m_src, (uint32_t)(g * O * 4));
+        hp += h_step; vp += v_step; mp += m_step;
+        ++ahead;
+    };
+    auto clear_second_group = [&](char *at) {
+        const uint4 z = make_uint4(0, 0, 0, 0);
+        *(uint4 *)(at + 2 * 1024 + lane * 16) = z;
+        *(uint4 *)(at + 3 * 1024 + lane * 16) = z;
+        *(uint4 *)(at + S8_A + 1024 + lane * 16) = z;
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    };
+
+    const int li = lane & 15, kg = lane >> 5;
+    const uint32_t base = (uint32_t)(uintptr_t)(lptr_t)ring;
+    const uint32_t rd_a = base + (uint32_t)(S8_A + kg * 1024 + (lane & 31) * 16), rd_m = base + (uint32_t)(S8_M + kg * 256 + (lane & 31) * 8);
+    const uint32_t rd_b = base + (uint32_t)((16 * kg + (li >> 1)) * SM_TILE + (((lane >> 4) & 1) ^ (2 * ((li >> 3) & 1))) * 16 + (li & 1) * 8);
+    const uint32_t rd_b1 = rd_b ^ 32u;                                  // column block 1: the chunks two on, which is bit 1 of a chunk's position
+    for (int s = 0; s < SM_RING; ++s) fetch(s);
+    int slot = 0;
+    for (int s = 0; s < mine; ++s) {
+        wait_vmcnt<(SM_RING - 1) * S8_LOADS>();
+        if (wave + s * SM_WAVES == steps - 1 && n_groups % 2) clear_second_group(ring + slot * S8_STEP);
+        __builtin_amdgcn_sched_barrier(0);
+        const uint32_t so = (uint32_t)(slot * S8_STEP);
+        FragA8 af[2];
+        FragB8 bf[2];
+        u32x2 ix = lds_read_b64<0>(rd_m + so);
+        af[0].u4 = lds_read_b128<0>(rd_a + so);
+        af[1].u4 = lds_read_b128<512>(rd_a + so);
+        static_for<4>([&](auto j_c) {
+            constexpr int j = decltype(j_c)::value, off = (32 * (j >> 1) + 8 * (j & 1)) * SM_TILE;
+            bf[0].q[j] = lds_read_tr8<off>(rd_b + so);
+        });
+        static_for<4>([&](auto j_c) {
+            constexpr int j = decltype(j_c)::value, off = (32 * (j >> 1) + 8 * (j & 1)) * SM_TILE;
+            bf[1].q[j] = lds_read_tr8<off>(rd_b1 + so);
+        });
+        wait_for_fragments(af, bf, ix);
+        smfmac_32x32x64_bf8_fp8(acc[0][0], af[0].v, bf[0].v, ix[0]);
+        smfmac_32x32x64_bf8_fp8(acc[1][0], af[1].v, bf[0].v, ix[1]);
+        smfmac_32x32x64_bf8_fp8(acc[0][1], af[0].v, bf[1].v, ix[0]);
+        smfmac_32x32x64_bf8_fp8(acc[1][1], af[1].v, bf[1].v, ix[1]);
+        fetch(slot);
+        slot = slot == SM_RING - 1 ? 0 : slot + 1;
     }
+    const float alpha_v = decode_alpha(accumulate, alpha);
+    sum_and_store(acc, S, wave, m0, n0, out, ldo, O, I, accumulate & 1, [&](float v) { return v * alpha_v; });
 }
 
 }  // namespace
@@ -164,6 +272,15 @@ hipError_t launch_update_gemm_smfmac_small(const void *vals, const uint16_t *met
     const int tiles_m = (int)((O + SM_TILE - 1) / SM_TILE), tiles_n = (int)((I + SM_TILE - 1) / SM_TILE);
     hipLaunchKernelGGL(update_gemm_smfmac_small_kernel, dim3((unsigned)(tiles_m * tiles_n), 1, (unsigned)slabs), dim3(SM_WAVES * 64), 0, st, (const uint16_t *)vals, meta,
                        (const uint16_t *)h, ldh, h_rows, out, ldo, slab_stride, T / 16, groups_per_slab, O, I, tiles_m, tiles_n, accumulate);
+    return hipGetLastError();
+}
+
+hipError_t launch_update_gemm_q8_small(const uint8_t *vals8, const uint32_t *meta32, const uint8_t *h8, int64_t ldh, float *out, int64_t ldo, int64_t slab_stride,
+                                       int slabs, int64_t groups_per_slab, int64_t T, int64_t O, int64_t I, int accumulate, float alpha, hipStream_t st)
+{
+    const int tiles_m = (int)((O + SM_TILE - 1) / SM_TILE), tiles_n = (int)((I + SM_TILE - 1) / SM_TILE);
+    hipLaunchKernelGGL(update_gemm_q8_small_kernel, dim3((unsigned)(tiles_m * tiles_n), 1, (unsigned)slabs), dim3(SM_WAVES * 64), 0, st, vals8, meta32, h8, ldh, out, ldo,
+                       slab_stride, T / 32, groups_per_slab, O, I, tiles_m, tiles_n, accumulate, alpha);
     return hipGetLastError();
 }
 

@@ -152,6 +152,35 @@ __device__ __forceinline__ void smfmac_32x32x64_bf8_fp8(f32x16 &acc, const i32x4
     if constexpr (IN_VGPR) asm volatile("v_smfmac_f32_32x32x64_bf8_fp8 %0, %1, %2, %3" : "+v"(acc) : "v"(a), "v"(b), "v"(idx));
     else                   asm volatile("v_smfmac_f32_32x32x64_bf8_fp8 %0, %1, %2, %3" : "+a"(acc) : "v"(a), "v"(b), "v"(idx));
 }
+template <int OFFSET> __device__ __forceinline__ u32x2 lds_read_tr8(uint32_t addr)
+{
+    u32x2 r;
+    asm volatile("ds_read_b64_tr_b8 %0, %1 offset:%2" : "=v"(r) : "v"(addr), "n"(OFFSET) : "memory");
+    return r;
+}
+union FragB8 { i32x8 v; u32x2 q[4]; };
+union FragA8 { i32x4 v; u32x4 u4; };
+// waits for all LDS reads on their way, as above
+__device__ __forceinline__ void wait_for_fragments(FragA8 (&a)[2], FragB8 (&b)[2], u32x2 &ix)
+{
+    asm volatile("s_waitcnt lgkmcnt(0)"
+                 : "+v"(a[0].u4), "+v"(a[1].u4), "+v"(b[0].q[0]), "+v"(b[0].q[1]), "+v"(b[0].q[2]), "+v"(b[0].q[3]), "+v"(b[1].q[0]), "+v"(b[1].q[1]),
+                   "+v"(b[1].q[2]), "+v"(b[1].q[3]), "+v"(ix)
+                 :
+                 : "memory");
+}
+// The (accumulate, alpha) argument pair of the kernels also carries the device-scale form without another kernel
+// argument (the 384 x 256 kernel has no register to spare for one): accumulate bit 0 = add to what is there, bit 1 =
+// "the scale is in device memory", and then the other 62 bits of the pair are the address of that binary32 value
+// (4-byte aligned: low 30 bits in accumulate[31:2], high 32 bits in alpha's bit pattern).  Decoded in the epilogue only.
+__device__ __forceinline__ float decode_alpha(int accumulate, float alpha)
+{
+    if (accumulate & 2) {
+        const uint64_t addr = ((uint64_t)__float_as_uint(alpha) << 32) | (uint32_t)(accumulate & ~3);
+        return *(const float *)addr;
+    }
+    return alpha;
+}
 template <int OFFSET> __device__ __forceinline__ void lds_refill_tr8(u32x2 &r, uint32_t addr)
 {
     asm volatile("ds_read_b64_tr_b8 %0, %1 offset:%2" : "+v"(r) : "v"(addr), "n"(OFFSET) : "memory");

@@ -151,6 +151,18 @@ def test_update_gemm_q8_beta_one_and_relu_activations(nm, oracle):
     gemm_case(nm, oracle, 4096, 64, 576, seed=6, beta=1.0)             # few rows, split-K
 
 
+# 64 x 64 tiles with the tokens split over the waves: one group, an odd number of groups in one and in many steps, ragged rows and columns, tiles for more
+# than one round, slabs (the last one shorter)
+@pytest.mark.parametrize("T,O,I,beta", [(32, 8, 16, 0.0), (32, 64, 80, 1.0), (96, 72, 64, 0.0), (544, 200, 112, 1.0), (992, 1016, 1008, 0.0), (1024, 2104, 976, 0.0),
+                                        (8224, 512, 512, 0.0), (8192, 264, 528, 1.0)])
+def test_update_gemm_q8_small_kernel(nm, oracle, T, O, I, beta):
+    from gpu_util import kernels_of
+    gemm_case(nm, oracle, T, O, I, seed=T + O, beta=beta)
+    v, m = nm.mvue_prune_2of4_q8(torch.randn(T, O, device=DEV).to(torch.bfloat16), seed=1, scale=16.0)
+    h8 = torch.from_numpy(h8_codes(T, I, 1)).to(DEV)
+    assert any("update_gemm_q8_small_kernel" in n for n in kernels_of(lambda: nm.nm_update_gemm_q8(v, m, h8, alpha=1.0)))
+
+
 @pytest.mark.parametrize("T,O,I", [(160, 16 * 256, 16 * 256),            # 16 x 16 tiles of 256 x 256: the 2 x 4 XCD grid; odd group count
                                    (96, 50 * 256 - 40, 8 * 256),         # banded map with a short last band, ragged rows
                                    (32 * 14, 33 * 256, 8 * 256 - 16)])   # more than two trips of stages, ragged columns
