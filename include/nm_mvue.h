@@ -331,7 +331,7 @@ int nm_rw_mix_probe(const void *src, void *dst, int64_t n_blocks, void *hip_stre
  *
  * The _ds ("device scale") forms of the 8-bit entry points read their scales from such records instead of host
  * arguments: mvue_prune_*_q8_ds multiplies kept values by rec[0]; nm_update_gemm_q8*_ds uses
- * alpha = rec_g[1] * rec_h[1], which a one-thread kernel of the call leaves in rec_h[3] for its GEMM kernels (so two
+ * alpha = rec_g[1] * rec_h[1], which a one-thread kernel of a large call leaves in rec_h[3] for its GEMM kernels (so two
  * GEMM calls that may run at the same time must not share an activation record).  Everything else as the
  * host-scale forms.
  */

@@ -33,6 +33,18 @@ namespace nm {
 constexpr int KT8 = 64;           // tokens per LDS stage (one 64-token MFMA step, two 32-token groups)
 constexpr int NS8 = 6;            // LDS stages
 
+// The (accumulate, alpha) argument pair of the 384 x 256 kernel also carries the device-scale form without another
+// argument (it has no register to spare for one): accumulate bit 0 = add to what is there, bit 1 =
+// "the scale is in device memory", and then the other 62 bits of the pair are the address of that binary32 value
+// (4-byte aligned: low 30 bits in accumulate[31:2], high 32 bits in alpha's bit pattern).  Decoded in the epilogue only.
+__device__ __forceinline__ float decode_alpha(int accumulate, float alpha)
+{
+    if (accumulate & 2) {
+        const uint64_t addr = ((uint64_t)__float_as_uint(alpha) << 32) | (uint32_t)(accumulate & ~3);
+        return *(const float *)addr;
+    }
+    return alpha;
+}
 // alpha * (one accumulator element) to global memory: the element is copied out of its accumulation register, scaled
 // and stored inside one statement, so that the compiler never holds whole blocks in ordinary registers
 __device__ __forceinline__ void store_acc_scaled(float *p, float v, float alpha)
@@ -53,7 +65,7 @@ template <int WM, int WN, int AB, int BB, bool SHIFTED = false>
 __global__ __launch_bounds__(WM * WN * 64) void update_gemm_smfmac_q8_kernel(
     const uint8_t *__restrict__ vals, const uint32_t *__restrict__ meta, const uint8_t *__restrict__ h, int64_t ldh,
     float *__restrict__ out, int64_t ldo, int64_t slab_stride,
-    int64_t n_groups, int64_t groups_per_slab, int64_t O, int64_t I, int tiles_m, int tiles_n, int accumulate, float alpha,
+    int64_t n_groups, int64_t groups_per_slab, int64_t O, int64_t I, int tiles_m, int tiles_n, int accumulate, AlphaArg alpha,
     int64_t o_first,                         // the launch computes rows [o_first, O) of dW; tiles_m counts its M-tiles
     ShiftArg sh)                             // (SHIFTED only)
 {
@@ -281,7 +293,7 @@ __global__ __launch_bounds__(WM * WN * 64) void update_gemm_smfmac_q8_kernel(
 #pragma unroll
         for (int b = 0; b < BB; ++b) acc_settled(acc[a][b]);
     __builtin_amdgcn_sched_barrier(0);
-    const float alpha_v = decode_alpha(accumulate, alpha);
+    const float alpha_v = alpha_of(alpha);
     const int64_t o0 = m0 + wm * (AB * 32);
 #pragma unroll
     for (int a = 0; a < AB; ++a)
@@ -598,13 +610,14 @@ static PlanQ8 make_plan_q8(int64_t T, int64_t O, int64_t I, bool shifted = false
     return p;
 }
 
-// alpha = rec_a[1] * rec_b[1], left in rec_b[3] (the consumer's scratch slot of a scale record) for the kernels
+// alpha = rec_a[1] * rec_b[1], left in rec_b[3] (the consumer's scratch slot of a scale record) for the 384 x 256 kernel; the others multiply the
+// two themselves (a launch in front of them cost 4 us, of 13.8 for the smallest products)
 __global__ void q8_alpha_product_kernel(const float *rec_a, float *rec_b)
 {
     if (threadIdx.x == 0) rec_b[3] = rec_a[1] * rec_b[1];
 }
 
-// the (accumulate, alpha) pair the kernels take: host scale, or the address of the device scale (see decode_alpha)
+// the (accumulate, alpha) pair that kernel takes: host scale, or the address of the device scale (see decode_alpha)
 struct AlphaPair { int acc; float alpha; };
 static AlphaPair encode_alpha(int accumulate, const AlphaArg &al, hipStream_t st)
 {
@@ -656,12 +669,13 @@ size_t update_gemm_q8_workspace(int64_t T, int64_t O, int64_t I)
 }
 
 // The kernels of a plan, into `tg`, scaled by `ap`
-static hipError_t run_q8_plan(const PlanQ8 &p, const OutTarget &tg, const AlphaPair &ap, const uint8_t *vals8, const uint32_t *meta32,
+static hipError_t run_q8_plan(const PlanQ8 &p, const OutTarget &tg, const AlphaArg &alpha, const uint8_t *vals8, const uint32_t *meta32,
                               const uint8_t *h8, int64_t ldh, int64_t T, int64_t O, int64_t I, hipStream_t st)
 {
     if (p.shape == SMALL8)
-        return launch_update_gemm_q8_small(vals8, meta32, h8, ldh, tg.out, tg.ldo, tg.slab_stride, p.slabs, p.groups_per_slab, T, O, I, ap.acc, ap.alpha, st);
+        return launch_update_gemm_q8_small(vals8, meta32, h8, ldh, tg.out, tg.ldo, tg.slab_stride, p.slabs, p.groups_per_slab, T, O, I, tg.accumulate, alpha, st);
     if (p.tall_rows > 0) {
+        const AlphaPair ap = encode_alpha(tg.accumulate, alpha, st);
         hipLaunchKernelGGL(update_gemm_smfmac_q8_tall_kernel, dim3((unsigned)(p.tall_tiles_m * p.tiles_n)), dim3(512), 0, st,
                            vals8, meta32, h8, ldh, tg.out, tg.ldo, T / 32, O, I, p.tall_tiles_m, p.tiles_n, ap.acc, ap.alpha, p.tall_rows);
         hipError_t e0 = hipGetLastError();
@@ -671,7 +685,7 @@ static hipError_t run_q8_plan(const PlanQ8 &p, const OutTarget &tg, const AlphaP
     dim3 grid((unsigned)(p.tiles_m * p.tiles_n), 1, (unsigned)p.slabs);
 #define NM_LAUNCH(WM, WN, AB, BB)                                                                                     \
     hipLaunchKernelGGL((update_gemm_smfmac_q8_kernel<WM, WN, AB, BB>), grid, dim3(WM * WN * 64), 0, st, vals8, meta32, h8,    \
-                       ldh, tg.out, tg.ldo, tg.slab_stride, T / 32, p.groups_per_slab, O, I, p.tiles_m, p.tiles_n, ap.acc, ap.alpha,  \
+                       ldh, tg.out, tg.ldo, tg.slab_stride, T / 32, p.groups_per_slab, O, I, p.tiles_m, p.tiles_n, tg.accumulate, alpha,  \
                        p.tall_rows, ShiftArg{})
     if (p.shape == 0) NM_LAUNCH(2, 4, 4, 2);
     else if (p.shape == 1) NM_LAUNCH(2, 4, 2, 2);
@@ -689,8 +703,7 @@ hipError_t launch_update_gemm_q8(const uint8_t *vals8, const uint32_t *meta32, c
     const int accumulate = beta != 0.f;
     const OutTarget tg = splitk_target(p.slabs, dW, lddw, workspace, O, I, accumulate);
     // partial sums are scaled once, in the second pass; otherwise the kernels scale, by a host or a device value
-    const AlphaPair ap = p.slabs > 1 ? AlphaPair{tg.accumulate, 1.0f} : encode_alpha(tg.accumulate, alpha, st);
-    hipError_t e = run_q8_plan(p, tg, ap, vals8, meta32, h8, ldh, T, O, I, st);
+    hipError_t e = run_q8_plan(p, tg, p.slabs > 1 ? AlphaArg{} : alpha, vals8, meta32, h8, ldh, T, O, I, st);
     if (e != hipSuccess) return e;
     if (p.slabs > 1) e = launch_splitk_reduce((const float *)workspace, p.slabs, dW, lddw, O, I, accumulate, alpha, st);
     return e;
@@ -706,7 +719,7 @@ hipError_t launch_update_gemm_q8_parts(const uint8_t *vals8, const uint32_t *met
 {
     const PlanQ8 p = small_plan_q8(make_plan_q8(T, O, I), T, O, I, ldh);
     *slabs = p.slabs;
-    return run_q8_plan(p, OutTarget{part, I, O * I, 0}, AlphaPair{0, 1.0f}, vals8, meta32, h8, ldh, T, O, I, st);
+    return run_q8_plan(p, OutTarget{part, I, O * I, 0}, AlphaArg{}, vals8, meta32, h8, ldh, T, O, I, st);
 }
 
 size_t update_gemm_q8_shifted_workspace(int64_t T, int64_t O, int64_t I)
@@ -716,7 +729,7 @@ size_t update_gemm_q8_shifted_workspace(int64_t T, int64_t O, int64_t I)
 }
 
 // The kernels of a plan on the shift table, into `tg`, scaled by `ap`
-static hipError_t run_q8_shifted(const PlanQ8 &p, const OutTarget &tg, const AlphaPair &ap, const uint8_t *vals8, const uint32_t *meta32,
+static hipError_t run_q8_shifted(const PlanQ8 &p, const OutTarget &tg, const AlphaArg &alpha, const uint8_t *vals8, const uint32_t *meta32,
                                  const uint8_t *x8, int64_t ldx, int64_t cb, const int64_t *rows, int n, int64_t T, int64_t O, hipStream_t st)
 {
     const int64_t I = cb * n;
@@ -724,7 +737,7 @@ static hipError_t run_q8_shifted(const PlanQ8 &p, const OutTarget &tg, const Alp
     dim3 grid((unsigned)(p.tiles_m * p.tiles_n), 1, (unsigned)p.slabs);
 #define NM_LAUNCH(WM, WN, AB, BB)                                                                                     \
     hipLaunchKernelGGL((update_gemm_smfmac_q8_kernel<WM, WN, AB, BB, true>), grid, dim3(WM * WN * 64), 0, st, vals8, meta32, x8, \
-                       ldx, tg.out, tg.ldo, tg.slab_stride, T / 32, p.groups_per_slab, O, I, p.tiles_m, p.tiles_n, ap.acc, ap.alpha,   \
+                       ldx, tg.out, tg.ldo, tg.slab_stride, T / 32, p.groups_per_slab, O, I, p.tiles_m, p.tiles_n, tg.accumulate, alpha,   \
                        (int64_t)0, sh)
     if (p.shape == 0) NM_LAUNCH(2, 4, 4, 2);
     else if (p.shape == 1) NM_LAUNCH(2, 4, 2, 2);
@@ -743,9 +756,7 @@ hipError_t launch_update_gemm_q8_shifted(const uint8_t *vals8, const uint32_t *m
     const PlanQ8 p = make_plan_q8(T, O, I, true);
     const int accumulate = beta != 0.f;
     const OutTarget tg = splitk_target(p.slabs, dW, lddw, workspace, O, I, accumulate);
-    // partial sums are scaled once, in the second pass; otherwise the kernels scale, by a host or a device value
-    const AlphaPair ap = p.slabs > 1 ? AlphaPair{tg.accumulate, 1.0f} : encode_alpha(tg.accumulate, alpha, st);
-    hipError_t e = run_q8_shifted(p, tg, ap, vals8, meta32, x8, ldx, cb, rows, n, T, O, st);
+    hipError_t e = run_q8_shifted(p, tg, p.slabs > 1 ? AlphaArg{} : alpha, vals8, meta32, x8, ldx, cb, rows, n, T, O, st);
     if (e != hipSuccess) return e;
     if (p.slabs > 1) e = launch_splitk_reduce((const float *)workspace, p.slabs, dW, lddw, O, I, accumulate, alpha, st);
     return e;
@@ -762,7 +773,7 @@ hipError_t launch_update_gemm_q8_shifted_parts(const uint8_t *vals8, const uint3
     const int64_t I = cb * n;
     const PlanQ8 p = make_plan_q8(T, O, I, true);
     *slabs = p.slabs;
-    return run_q8_shifted(p, OutTarget{part, I, O * I, 0}, AlphaPair{0, 1.0f}, vals8, meta32, x8, ldx, cb, rows, n, T, O, st);
+    return run_q8_shifted(p, OutTarget{part, I, O * I, 0}, AlphaArg{}, vals8, meta32, x8, ldx, cb, rows, n, T, O, st);
 }
 
 }  // namespace nm

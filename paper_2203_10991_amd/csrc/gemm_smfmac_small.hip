@@ -163,7 +163,7 @@ __global__ __launch_bounds__(SM_WAVES * 64) void update_gemm_smfmac_small_kernel
         fetch(slot);
         slot = slot == SM_RING - 1 ? 0 : slot + 1;
     }
-    sum_and_store(acc, S, wave, m0, n0, out, ldo, O, I, accumulate & 1, [](float v) { return v; });
+    sum_and_store(acc, S, wave, m0, n0, out, ldo, O, I, accumulate != 0, [](float v) { return v; });
 }
 
 // The same for 8-bit operands.  A step is 64 tokens: h8 [64 tokens][64 columns] bytes, chunk c (16 columns) of row k at position c ^ 2 (k / 4 % 2) (a transposing
@@ -177,7 +177,7 @@ static_assert(S8_LDS <= 160 * 1024 && S8_STEP % 256 == 0, "LDS");
 __global__ __launch_bounds__(SM_WAVES * 64) void update_gemm_q8_small_kernel(const uint8_t *__restrict__ vals, const uint32_t *__restrict__ meta,
                                                                             const uint8_t *__restrict__ h, int64_t ldh, float *__restrict__ out, int64_t ldo,
                                                                             int64_t slab_stride, int64_t n_groups, int64_t groups_per_slab, int64_t O, int64_t I,
-                                                                            int tiles_m, int tiles_n, int accumulate, float alpha)
+                                                                            int tiles_m, int tiles_n, int accumulate, AlphaArg alpha)
 {
     const int64_t g0 = (int64_t)blockIdx.z * groups_per_slab;           // (even, below n_groups)
     vals += g0 * O * 16; meta += g0 * O; h += g0 * 32 * ldh; out += (int64_t)blockIdx.z * slab_stride;
@@ -260,8 +260,8 @@ __global__ __launch_bounds__(SM_WAVES * 64) void update_gemm_q8_small_kernel(con
         fetch(slot);
         slot = slot == SM_RING - 1 ? 0 : slot + 1;
     }
-    const float alpha_v = decode_alpha(accumulate, alpha);
-    sum_and_store(acc, S, wave, m0, n0, out, ldo, O, I, accumulate & 1, [&](float v) { return v * alpha_v; });
+    const float alpha_v = alpha_of(alpha);
+    sum_and_store(acc, S, wave, m0, n0, out, ldo, O, I, accumulate != 0, [&](float v) { return v * alpha_v; });
 }
 
 }  // namespace
@@ -276,7 +276,7 @@ hipError_t launch_update_gemm_smfmac_small(const void *vals, const uint16_t *met
 }
 
 hipError_t launch_update_gemm_q8_small(const uint8_t *vals8, const uint32_t *meta32, const uint8_t *h8, int64_t ldh, float *out, int64_t ldo, int64_t slab_stride,
-                                       int slabs, int64_t groups_per_slab, int64_t T, int64_t O, int64_t I, int accumulate, float alpha, hipStream_t st)
+                                       int slabs, int64_t groups_per_slab, int64_t T, int64_t O, int64_t I, int accumulate, const AlphaArg &alpha, hipStream_t st)
 {
     const int tiles_m = (int)((O + SM_TILE - 1) / SM_TILE), tiles_n = (int)((I + SM_TILE - 1) / SM_TILE);
     hipLaunchKernelGGL(update_gemm_q8_small_kernel, dim3((unsigned)(tiles_m * tiles_n), 1, (unsigned)slabs), dim3(SM_WAVES * 64), 0, st, vals8, meta32, h8, ldh, out, ldo,

@@ -52,9 +52,9 @@ size_t update_gemm_smfmac_workspace(int64_t T, int64_t O, int64_t I, size_t besi
 // small problems (gemm_smfmac_small.hip): slabs partial sums of groups_per_slab (even) token groups each, slab_stride apart; h_rows rows of h (at most T, the rest count as zeros)
 hipError_t launch_update_gemm_smfmac_small(const void *vals, const uint16_t *meta, const void *h, int64_t ldh, int64_t h_rows, float *out, int64_t ldo,
                                            int64_t slab_stride, int slabs, int64_t groups_per_slab, int64_t T, int64_t O, int64_t I, int accumulate, hipStream_t st);
-// the same for 8-bit operands; groups of 32 tokens; accumulate, alpha: see decode_alpha
+// the same for 8-bit operands; groups of 32 tokens; alpha scales what is stored
 hipError_t launch_update_gemm_q8_small(const uint8_t *vals8, const uint32_t *meta32, const uint8_t *h8, int64_t ldh, float *out, int64_t ldo, int64_t slab_stride,
-                                       int slabs, int64_t groups_per_slab, int64_t T, int64_t O, int64_t I, int accumulate, float alpha, hipStream_t st);
+                                       int slabs, int64_t groups_per_slab, int64_t T, int64_t O, int64_t I, int accumulate, const AlphaArg &alpha, hipStream_t st);
 size_t update_gemm_smfmac_shifted_workspace(int64_t T, int64_t O, int64_t I);
 // the same product with h given as n row-shifted views of one [rows x cb] matrix x (bf16): h[t][j*cb + c] = x[(t + rows[j])*ldx + c]
 hipError_t launch_update_gemm_smfmac_shifted(const void *vals, const uint16_t *meta, const void *x, int64_t ldx, int64_t cb,

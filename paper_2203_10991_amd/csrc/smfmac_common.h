@@ -169,18 +169,6 @@ __device__ __forceinline__ void wait_for_fragments(FragA8 (&a)[2], FragB8 (&b)[2
                  :
                  : "memory");
 }
-// The (accumulate, alpha) argument pair of the kernels also carries the device-scale form without another kernel
-// argument (the 384 x 256 kernel has no register to spare for one): accumulate bit 0 = add to what is there, bit 1 =
-// "the scale is in device memory", and then the other 62 bits of the pair are the address of that binary32 value
-// (4-byte aligned: low 30 bits in accumulate[31:2], high 32 bits in alpha's bit pattern).  Decoded in the epilogue only.
-__device__ __forceinline__ float decode_alpha(int accumulate, float alpha)
-{
-    if (accumulate & 2) {
-        const uint64_t addr = ((uint64_t)__float_as_uint(alpha) << 32) | (uint32_t)(accumulate & ~3);
-        return *(const float *)addr;
-    }
-    return alpha;
-}
 template <int OFFSET> __device__ __forceinline__ void lds_refill_tr8(u32x2 &r, uint32_t addr)
 {
     asm volatile("ds_read_b64_tr_b8 %0, %1 offset:%2" : "+v"(r) : "v"(addr), "n"(OFFSET) : "memory");
