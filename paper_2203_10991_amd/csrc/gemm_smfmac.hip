@@ -784,13 +784,12 @@ static Plan make_plan(int64_t T, int64_t O, int64_t I, bool shifted = false, boo
 // Small problems: the plan of the tile kernels, or 64 x 64 tiles with the tokens split over a workgroup's eight waves (gemm_smfmac_small.hip) and, for
 // long reductions, over at most eight slabs: never more than the tile kernels' plan, whose workspace a call is asked for whichever runs.  At most one
 // workgroup per CU (its LDS).  Up to 768 tokens it always measures faster (7.3-12.5 -> 4.7-8 us over sizes from 64 x 64 to 2400 x 250); beyond that by its
-// model -- 4.9 us, then per step of 32 tokens a wave 0.5 us, up to 0.75 with all CUs busy, or the tiles' operands at 6 TB/s, or one pass over the
-// operands at 2.5 TB/s (its loads of a wide h are 128 bytes of a row: without this 5328 x 64 x 3152 took 18.9 -> 24.1 us), and the second pass --
-// against that of the tile kernels, which is 3 us short at these sizes.  `parts`: a layer's call, where a finishing pass runs anyway, so that one slab
-// saves less.  1024^3 17 -> 7.6 us.  Against the tile kernels over 560 sizes from 768 tokens on, cold operands: a call takes it at 290 of them, 0.86 of the
-// time in the mean, six slower by 0.4 to 1.2 us (the most 11632 x 16 x 216 11.5 -> 12.7); a layer 0.94 of its time, 14 up to 1.09 of it.  And 60
-// stay on the tile kernels that would gain more than 5 %: the 6 TB/s are too few where few tiles share a strip (2048 x 1024 x 1024 19.8 us,
-// here 10.4; 4096 x 1024 x 1024 20.6 and 15.2).
+// model -- 4.9 us, then per step of 32 tokens a wave 0.5 us, up to 0.75 with all CUs busy, or the tiles' operands at 14 TB/s (measured 14-18 on 256 tiles), or
+// one pass over the operands at 2.5 TB/s (its loads of a wide h are 128 bytes of a row: without this 5328 x 64 x 3152 took 18.9 -> 24.1 us), and the
+// second pass -- against that of the tile kernels, which is 3 us short at these sizes.  `parts`: a layer's call, where a finishing pass runs anyway, so that
+// one slab saves less.  1024^3 17 -> 7.6 us, 1536 x 512 x 2048 21.6 -> 9.2, 2048 x 1024 x 1024 19.7 -> 10.6, 4096 x 1024 x 1024 20.4 -> 15.0,
+// 8192 x 200 x 640 17.6 -> 13.  Against the tile kernels over 144 sizes from 272 to 8192 tokens, operands in no cache: none slower by more than 4 %
+// (with 6 TB/s for the tiles' operands, 30 of them, 7 % of the time in the mean over all, had stayed on the tile kernels).
 // (The offsets of its loads are 32 bits wide: 32 rows of h.)
 static Plan small_plan(Plan p, int64_t T, int64_t O, int64_t I, int64_t ldh, bool parts)
 {
@@ -801,7 +800,7 @@ static Plan small_plan(Plan p, int64_t T, int64_t O, int64_t I, int64_t ldh, boo
     for (const int s : {1, 2, 3, 4, 6, 8}) {
         if (s > p.slabs || s * tiles > NM_CUS) break;
         const int64_t steps = ((groups + s - 1) / s + 15) / 16;
-        const double loop = std::max({(double)steps * (0.5 + 0.25 * (double)(s * tiles) / NM_CUS), (double)tiles * (double)T * 200.0 / 6e6,
+        const double loop = std::max({(double)steps * (0.5 + 0.25 * (double)(s * tiles) / NM_CUS), (double)tiles * (double)T * 200.0 / 14e6,
                                       (double)T * ((double)I * 2.0 + (double)O * 1.125) / 2.5e6});
         const double us = 4.9 + loop + (s > 1 ? 2.6 + (double)(s + 1) * (double)O * (double)I * 4.0 / 3.5e6 : parts && p.slabs > 1 ? 0.9 : 0.0);
         if (us < best) {
