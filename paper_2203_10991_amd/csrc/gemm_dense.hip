@@ -328,24 +328,31 @@ __global__ __launch_bounds__(WM * WN * 64) void dense_gemm_kernel(DenseArg p)
 
 }  // namespace
 
-// Tiles of 64 x 64, 128 x 64, 128 x 128 (4 waves, two workgroups on a CU) or 256 x 256 (8 waves), the cheapest by what they were measured to take:
+// Tiles of 64 x 64, 128 x 64, 128 x 128 (4 waves, two workgroups on a CU), 128 x 128 on 8 waves with four stages in LDS (one workgroup on a CU) or 256 x 256
+// (8 waves), the cheapest by what they were measured to take:
 // microseconds per stage of a tile alone on its CU and with a second one, of the largest by the share of the CUs that are busy, and per round.
 // Back to back from a graph, these / the vendor library's choice, us: 2048 x 1024 -> 1024 10.3 / 10.2 (input gradient 10.4 / 11.8), 1576 x 768 -> 3072
 // 17.5 / 13.5 (21 / 22), 197 x 1024 -> 1024 8.5 / 5.9 (8.3 / 8.0), 6304 x 768 -> 3072 41 / 51 (43 / 38), 12608 x 3072 -> 768 65 / 59 (73 / 69),
 // 16384 x 1024 -> 4096 128 / 106 (112 / 103), with the ReLU 128 / 149.  The small tiles are bound by the path from the L2s to the CUs (24 KB a stage in
 // 0.33 us on all of them: 18 TB/s), the largest by the matrix pipes at the clock the power limit leaves.
+// The eight waves with four stages are for one round of at most 256 tiles, which two stages of 128 x 128 spend waiting (0.85 us a stage, of which 0.2 is matrix
+// work) and smaller tiles on more operand bytes: 7478 x 1568 -> 384 23.6 -> 17.6 us (the vendor library 21.0), input gradient 21.7 -> 17.0 (25.5);
+// 2774 x 2976 -> 944 40 -> 30 (33), 1881 x 2216 -> 1680 35.7 -> 27.7 (29.9), 931 x 1104 -> 2544 19.4 -> 13.6 (18.0).  Over 230 products of 2e8 to 1.3e10
+// multiply-adds the choice takes 0.967 of what it took without, none more than 1.02, and 1.017 of the fastest tile's time.  (With 181 to 256 tiles over fewer
+// than 24 stages it would be up to 25 % faster too; those stay on the smaller tiles, whose way from one tile to the next is checked at such sizes.)
 hipError_t launch_dense_gemm(bool nn, const void *x, int64_t ldx, const void *w, const void *bias, void *y, int64_t ldy, int64_t M, int64_t N, int64_t K,
                              bool relu, hipStream_t st)
 {
     DenseArg p{(const uint16_t *)x, (const uint16_t *)w, (const uint16_t *)bias, (uint16_t *)y, ldx, ldy, M, N, K, 0, 0, relu};
     struct Tile { int tm, tn, per_cu; double alone, shared, round; };
-    constexpr Tile tiles[4] = {{64, 64, 2, 0.25, 0.42, 0.7}, {128, 64, 2, 0.33, 0.70, 1.0}, {128, 128, 2, 0.85, 1.0, 1.5}, {256, 256, 1, 0.6, 1.75, 5.0}};
+    constexpr Tile tiles[5] = {{64, 64, 2, 0.25, 0.42, 0.7}, {128, 64, 2, 0.33, 0.70, 1.0}, {128, 128, 2, 0.85, 1.0, 1.5}, {128, 128, 1, 0.25, 0.55, 1.5}, {256, 256, 1, 0.6, 1.75, 5.0}};
     const double stages = (double)((K + DK - 1) / DK);
     int best = 0;
     double least = 1e300;
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < 5; ++i) {
         const Tile &t = tiles[i];
         const int64_t n = ((M + t.tm - 1) / t.tm) * ((N + t.tn - 1) / t.tn), round = (int64_t)t.per_cu * NM_CUS, left = n % round;
+        if (i == 3 && (n > NM_CUS || (n > 180 && stages < 24.0))) continue;
         const double part = t.per_cu == 1 ? t.alone + (t.shared - t.alone) * (double)left / NM_CUS : left <= NM_CUS ? t.alone : t.shared;
         const double cost = (double)(n / round) * (stages * t.shared + t.round) + (left ? stages * part + t.round : 0.0);
         if (cost < least) { least = cost; best = i; }
@@ -363,6 +370,7 @@ hipError_t launch_dense_gemm(bool nn, const void *x, int64_t ldx, const void *w,
     case 0: NM_DENSE(2, 2, 1, 1, 4); break;
     case 1: NM_DENSE(2, 2, 2, 1, 3); break;
     case 2: NM_DENSE(2, 2, 2, 2, 2); break;
+    case 3: NM_DENSE(2, 4, 2, 1, 4); break;
     default: NM_DENSE(2, 4, 4, 2, 2); break;
     }
 #undef NM_DENSE

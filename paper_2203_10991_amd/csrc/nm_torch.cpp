@@ -172,8 +172,10 @@ PyObject *linear_update(PyObject *, PyObject *const *a, Py_ssize_t n)
 }
 
 // ---- the dense products of a layer.  Which of them are the library's: plain bf16 tensors on the current device that the kernels read as they are, at
-// sizes at which they are the faster way.  Up to DENSE_MOST multiply-adds they take what the vendor library's take (0.7 to 1.4 of it from
-// size to size: gemm_dense.hip), and the call 6 us of the host's time instead of 20, which bounds layers of that size.  With a ReLU behind the
+// sizes at which they are the faster way.  Up to DENSE_SURE multiply-adds the host's time counts, 6 us of it a call instead of 20, and the kernels take 0.77 of
+// the vendor library's time in the mean (0.4 to 1.1 and one of 1.33: gemm_dense.hip).  From there to DENSE_MOST the kernels count: over 288 products
+// 0.80 in the mean, and at most 1.06 but for reductions beyond DENSE_LARGE_DEEP (641 x 3520 -> 2744 29.5 us against 25.2) and for ones of DENSE_LARGE_ROUND or
+// more with a few tiles of 128 x 128 more than a round of 256 (264 tiles, 5519 x 2192 -> 712: 53 against 36), which stay the vendor library's.  With a ReLU behind the
 // product, up to DENSE_RELU_MOST of them and the reduction width DENSE_RELU_WIDTH: the pass over the output that is saved outweighs what the product
 // may lose (a layer of 6143 x 640 -> 1320 157 us -> 126; 9143 x 1088 -> 2000 203.8 -> 202.9; alone 16384 x 2048 -> 2048 is 122 against 95 and 23).  Beyond,
 // the power limit takes the gain back: 16384 x 1024 -> 4096 alone 128 us against 106 and 43, inside its layer 445-462 us against 450-456.
@@ -186,7 +188,7 @@ PyObject *linear_update(PyObject *, PyObject *const *a, Py_ssize_t n)
 // 0.65 and up to 1.35 of product and pass.  A captured step takes the same way all the same: it has to find there what the step before it, run once to
 // warm up, has used, and the vendor library's first product of a process or thread cannot be captured.
 // The framework's stay: autocast regions, and operators that a mode of functions or of dispatch watches.
-constexpr int64_t DENSE_MOST = 5000000000, DENSE_RELU_MOST = 20000000000, DENSE_RELU_WIDTH = 1536,
+constexpr int64_t DENSE_SURE = 5000000000, DENSE_MOST = 12000000000, DENSE_LARGE_DEEP = 3072, DENSE_LARGE_ROUND = 1024, DENSE_RELU_MOST = 20000000000, DENSE_RELU_WIDTH = 1536,
                   DENSE_DEEP = 2048, DENSE_DEEPER = 3584, DENSE_TILES = 128;
 
 bool dense_takes(const at::Tensor &a, const at::Tensor &w, const at::Tensor *bias, bool relu, int64_t width, int64_t &rows, int64_t &ld)
@@ -196,7 +198,12 @@ bool dense_takes(const at::Tensor &a, const at::Tensor &w, const at::Tensor *bia
     rows = width ? a.numel() / width : 0;                              // (width: the reduction axis)
     if (rows < 1 || O < 1 || I < 1 || O % 8 || I % 8 || O > (1 << 21) || I > (1 << 21) || rows > ((int64_t)1 << 34) / O || rows > ((int64_t)1 << 36) / I) return false;
     if (width > DENSE_DEEP && (width > DENSE_DEEPER || (rows + 63) / 64 * ((O * I / width + 63) / 64) < DENSE_TILES)) return false;
-    if (rows * O > (relu && I <= DENSE_RELU_WIDTH ? DENSE_RELU_MOST : DENSE_MOST) / I) return false;
+    const bool relu_pass = relu && I <= DENSE_RELU_WIDTH;              // (a ReLU whose pass over the output outweighs the product's time)
+    if (rows * O > (relu_pass ? DENSE_RELU_MOST : DENSE_MOST) / I) return false;
+    if (!relu_pass && rows * O > DENSE_SURE / I) {
+        const int64_t tiles = (rows + 127) / 128 * ((O * I / width + 127) / 128);
+        if (width > DENSE_LARGE_DEEP || (width >= DENSE_LARGE_ROUND && tiles > 256 && tiles <= 384)) return false;
+    }
     if (a.dim() == 2) ld = rows > 1 ? a.stride(0) : width;
     else if (a.is_contiguous()) ld = width;
     else return false;

@@ -41,6 +41,20 @@ SEVERAL_GRAD = [(3886, 864, 720, "2, 2, 1, 1, true, 4"), (16251, 440, 528, "2, 2
                 (13357, 736, 2016, "2, 4, 4, 2, true, 2")]
 
 
+# 128 x 128 tiles on eight waves, four stages in LDS: fewer stages than that, a whole round of 256 tiles, ragged rows, features and reductions
+EIGHT_WAVES = [(2047, 1032, 72), (2774, 944, 2976), (4096, 1024, 1544), (2040, 1912, 1608)]
+
+
+@pytest.mark.parametrize("T,O,I", EIGHT_WAVES)
+def test_tiles_on_eight_waves(T, O, I):
+    from paper_2203_10991_amd import api
+    test_linear_forward(T, O, I)
+    test_linear_input_grad(T, I, O)
+    x, w, v = (torch.zeros(*s, device=DEV, dtype=torch.bfloat16) for s in ((T, I), (O, I), (I, O)))
+    names = kernels_of(lambda: api.nm_linear_forward(x, w)) + kernels_of(lambda: api.nm_linear_input_grad(x, v))
+    assert any("dense_gemm_kernel<2, 4, 2, 1, false, 4>" in k for k in names) and any("dense_gemm_kernel<2, 4, 2, 1, true, 4>" in k for k in names)
+
+
 @pytest.mark.parametrize("T,O,I,kernel", SEVERAL_FORWARD)
 def test_linear_forward_of_several_tiles_to_a_workgroup(T, O, I, kernel):
     from paper_2203_10991_amd import api
@@ -261,3 +275,14 @@ def test_reductions_too_long_for_their_tiles_are_the_framework_s():
     assert taken(65, 64 * 64, 3584) == (True, True, False) and taken(64, 127 * 64, 3584) == (False, False, False)
     assert taken(65, 3584, 64 * 64) == (False, False, True) and taken(64, 128 * 64, 3592) == (False, False, False)
     assert taken(8, 64, 262144) == (False, False, True)
+
+
+def test_large_products_the_other_library_is_faster_at():
+    """beyond 5e9 multiply-adds: reductions beyond 3072, and from 1024 on 257 to 384 tiles of 128 x 128"""
+    from paper_2203_10991_amd import api
+
+    def taken(T, O, I):
+        x, w = (torch.empty(*s, device=DEV, dtype=torch.bfloat16) for s in ((T, I), (O, I)))
+        return api.own_linear_forward(x, w) is not None
+    assert taken(2048, 1024, 3072) and not taken(2048, 1024, 3080) and taken(1024, 1024, 3080)
+    assert taken(4096, 1024, 2048) and not taken(4097, 1024, 2048) and taken(5 * 1280, 1024, 1016) and not taken(48 * 128, 1024, 1024) and taken(49 * 128, 1024, 1024)
