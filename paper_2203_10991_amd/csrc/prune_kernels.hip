@@ -79,8 +79,9 @@ __device__ __forceinline__ uint4 producer_row(const uint4 &u, const uint4 &d)
 
 // HI0: the caller guarantees that every Philox call index of the launch is below 2^32 (the launcher checks the
 // tensor's size): counter words 1-3 are then wave-uniform and the generator's first rounds run partly on the scalar unit.
+// CACHED: the streaming form with plain stores, for outputs that the GEMM behind still finds in the L2s
 // VEC: columns per thread: one 16-byte load, or half of it (bf16, for launches that would leave SIMDs without work)
-template <int DT, int M, int EST, bool DENSE, int PROD = 0, bool HI0 = false, bool NT = false, int VEC = Row<DT>::VEC, bool LAYER = false>
+template <int DT, int M, int EST, bool DENSE, int PROD = 0, bool HI0 = false, bool NT = false, int VEC = Row<DT>::VEC, bool LAYER = false, bool CACHED = false>
 __device__ __forceinline__ void prune_compress_body(
     const void *__restrict__ g_, int64_t n_groups, int64_t O, int64_t ldg,
     uint32_t key0, uint32_t key1, uint32_t stream_id,
@@ -276,8 +277,8 @@ __device__ __forceinline__ void prune_compress_body(
         const auto rm = __builtin_amdgcn_make_buffer_rsrc((char *)meta_ + n_wave * (2 * VEC), 0, (int)there * (2 * VEC), 0x00020000);
         const uint32_t rd = wave_lds + (PC * (lane / PC) + ((lane % PC) ^ ((lane / PC) % PC))) * 16;
 #pragma unroll
-        for (int k = 0; k < PC; ++k) buffer_put_piece<16, true>(rv, 16 * lane + 1024 * k, *(const uint4 *)(xs + rd + 1024 * k));
-        buffer_put_piece<2 * VEC, true>(rm, 2 * VEC * lane, mw);
+        for (int k = 0; k < PC; ++k) buffer_put_piece<16, !CACHED>(rv, 16 * lane + 1024 * k, *(const uint4 *)(xs + rd + 1024 * k));
+        buffer_put_piece<2 * VEC, !CACHED>(rm, 2 * VEC * lane, mw);
     } else {
         uint4 *vp = (uint4 *)((char *)vals_ + n * (16 * PC));
 #pragma unroll
@@ -340,12 +341,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((DT == NM_D
 // what counts is how long one wave takes: 12608 x 768 12.7 -> 9.8, 12608 x 2304 22.3 -> 19.8, 16384 x 4096 41.6 -> 41.0.  Hence the line at 16384 x 4096.
 // (Approx-MVUE 2:4 and small tensors: the kernel below.)
 constexpr int64_t HALF_MOST = (int64_t)16384 * 4096;        // elements
-template <int M, int EST, bool HI0>
+// Plain stores (CACHED) up to 20 Mi elements leave the kept values in the L2s for the GEMM behind, streaming ones leave there what else it reads.  Which is the better
+// depends on the program: prune and GEMM alone in a loop, streaming / plain, 2128 x 6496 x 1240 54.0 / 49.6 us, 4112 x 4104 x 1024 58.4 / 52.6,
+// 8192 x 1536 x 1536 51.8 / 48.8, 16384 x 1024 x 4096 109 / 112; four layers of a block one after the other, 4096 tokens of width 1024 167 / 174, 16384 of
+// 1024 411 / 417, 12208 of 1336 556 / 555.  So launches of whole waves stream, and those of a last wave that is not whole, which had plain
+// stores before they streamed at all (50.8, 55.7 and 576 us), keep them.
+constexpr int64_t CACHED_MOST = (int64_t)20 << 20;          // elements
+template <int M, int EST, bool HI0, bool CACHED = false>
 __global__ __launch_bounds__(256) void prune_compress_half_kernel(
     const void *__restrict__ g, int64_t n_groups, int64_t O, int64_t ldg, uint32_t key0, uint32_t key1, uint32_t stream_id,
     void *__restrict__ vals, uint16_t *__restrict__ meta)
 {
-    prune_compress_body<NM_DT_BF16, M, EST, false, 0, HI0, true, 4>(g, n_groups, O, ldg, key0, key1, stream_id, vals, meta, nullptr, 0);
+    prune_compress_body<NM_DT_BF16, M, EST, false, 0, HI0, true, 4, false, CACHED>(g, n_groups, O, ldg, key0, key1, stream_id, vals, meta, nullptr, 0);
 }
 // The value of the lane at distance 1 or 2 among four lanes, and that of the Kth of them
 template <int D> __device__ __forceinline__ uint32_t lane_xor(uint32_t v)
@@ -1276,7 +1283,8 @@ static hipError_t launch_prune_t(const void *g, int64_t T, int64_t O, int64_t ld
         const dim3 half_grid((unsigned)((2 * threads + 255) / 256));
         if (M == 2 && (2 * threads + 255) / 256 > 0x7fffffffll) return hipErrorInvalidConfiguration;
         if (M == 2 || T * O <= HALF_MOST) {                       // (M = 4: hi0 holds at these sizes)
-            if (hi0) hipLaunchKernelGGL((prune_compress_half_kernel<M, EST, true>), half_grid, dim3(256), 0, st, NM_ARGS);
+            if (threads % 32 && T * O <= CACHED_MOST) hipLaunchKernelGGL((prune_compress_half_kernel<M, EST, true, true>), half_grid, dim3(256), 0, st, NM_ARGS);
+            else if (hi0) hipLaunchKernelGGL((prune_compress_half_kernel<M, EST, true>), half_grid, dim3(256), 0, st, NM_ARGS);
             else if constexpr (M == 2) hipLaunchKernelGGL((prune_compress_half_kernel<M, EST, false>), half_grid, dim3(256), 0, st, NM_ARGS);
         } else if constexpr (M == 4) {
             if (hi0) hipLaunchKernelGGL(prune_compress_bf16_2of4_stream_kernel, grid, dim3(256), 0, st, NM_ARGS);
