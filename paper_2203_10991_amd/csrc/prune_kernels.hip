@@ -341,11 +341,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((DT == NM_D
 // what counts is how long one wave takes: 12608 x 768 12.7 -> 9.8, 12608 x 2304 22.3 -> 19.8, 16384 x 4096 41.6 -> 41.0.  Hence the line at 16384 x 4096.
 // (Approx-MVUE 2:4 and small tensors: the kernel below.)
 constexpr int64_t HALF_MOST = (int64_t)16384 * 4096;        // elements
-// Plain stores (CACHED) up to 20 Mi elements leave the kept values in the L2s for the GEMM behind, streaming ones leave there what else it reads.  Which is the better
-// depends on the program: prune and GEMM alone in a loop, streaming / plain, 2128 x 6496 x 1240 54.0 / 49.6 us, 4112 x 4104 x 1024 58.4 / 52.6,
-// 8192 x 1536 x 1536 51.8 / 48.8, 16384 x 1024 x 4096 109 / 112; four layers of a block one after the other, 4096 tokens of width 1024 167 / 174, 16384 of
-// 1024 411 / 417, 12208 of 1336 556 / 555.  So launches of whole waves stream, and those of a last wave that is not whole, which had plain
-// stores before they streamed at all (50.8, 55.7 and 576 us), keep them.
+// Plain stores (CACHED) leave the kept values in the caches for the GEMM behind, streaming ones leave there what else it reads.  Which is the better depends on
+// what the program holds there, and not on T and O alone: prune and GEMM in a loop over two sets of tensors, streaming / plain, 2128 x 6496 x 1240 56.7 / 52.6 us,
+// 5952 x 2152 x 2304 72 / 65, 8192 x 1536 x 1536 53.3 / 51.0, 9952 x 1760 x 5848 189.7 / 191.9, 16384 x 1024 x 4096 113.8 / 116.2; four layers of a block one after
+// the other, 8192 tokens of width 768 202 / 208, 4096 of 1024 171 / 177, 4112 of 1032 182.7 / 194.5, 12208 of 1336 570 / 566.  A launch is left with the
+// stores that it had before the streaming form took thread counts that are no multiple of a wave, since either change loses somewhere: whole waves stream,
+// and those of a last wave that is not whole store plainly up to 20 Mi elements.  (What the line costs: 4112 of 1032 above, which took 200 with plain
+// loads as well.)  A layer's backward pass the same, forward and backward of a layer, streaming / plain: 4531 x 1392 -> 3728 with the ReLU 265 / 254,
+// 3682 x 1744 -> 2896 197 / 189, 6058 x 1504 -> 2320 185 / 178, beyond the line 8892 x 496 -> 1976 132 / 133, 14555 x 320 -> 3816 250 / 255.
 constexpr int64_t CACHED_MOST = (int64_t)20 << 20;          // elements
 template <int M, int EST, bool HI0, bool CACHED = false>
 __global__ __launch_bounds__(256) void prune_compress_half_kernel(
@@ -497,12 +500,12 @@ __global__ __launch_bounds__(256) void prune_compress_quad_kernel(
     if (b == 0) *(uint2 *)(meta + n) = make_uint2(lo, hi);
 }
 // the form of a layer's backward pass (bf16; see LayerArg): PROD = 2 with the ReLU's derivative in front, else 0
-template <int M, int EST, int PROD>
+template <int M, int EST, int PROD, bool CACHED>
 __global__ __launch_bounds__(256) void prune_layer_kernel(
     const void *__restrict__ g, int64_t n_groups, int64_t O, int64_t ldg, uint32_t key0, uint32_t key1, uint32_t stream_id,
     void *__restrict__ vals, uint16_t *__restrict__ meta, ProdArg pa, LayerArg la)
 {
-    prune_compress_body<NM_DT_BF16, M, EST, false, PROD, true, true, 4, true>(g, n_groups, O, ldg, key0, key1, stream_id, vals, meta, nullptr, 0, pa, la);
+    prune_compress_body<NM_DT_BF16, M, EST, false, PROD, true, true, 4, true, CACHED>(g, n_groups, O, ldg, key0, key1, stream_id, vals, meta, nullptr, 0, pa, la);
 }
 template <int DT, int M, int EST>
 __global__ __launch_bounds__(256) void prune_producer_kernel(
@@ -1327,9 +1330,16 @@ hipError_t launch_prune_layer(int m, int est, const void *g, int64_t ldg, const 
     if (blocks > 0x7fffffffll) return hipErrorInvalidConfiguration;
     const ProdArg pa{act, lda, gout, ldgo};
     const LayerArg la{T, csum};
+    const bool cached = threads % 64 && T * O <= CACHED_MOST;
 #define NM_LAYER(M, EST, PROD)                                                                                                  \
-    hipLaunchKernelGGL((prune_layer_kernel<M, EST, PROD>), dim3((unsigned)blocks), dim3(256), 0, st, g, groups, O, ldg,         \
-                       (uint32_t)seed, (uint32_t)(seed >> 32), stream_id, vals, meta, pa, la)
+    do {                                                                                                                        \
+        if (cached)                                                                                                             \
+            hipLaunchKernelGGL((prune_layer_kernel<M, EST, PROD, true>), dim3((unsigned)blocks), dim3(256), 0, st, g, groups, O, ldg,  \
+                               (uint32_t)seed, (uint32_t)(seed >> 32), stream_id, vals, meta, pa, la);                          \
+        else                                                                                                                    \
+            hipLaunchKernelGGL((prune_layer_kernel<M, EST, PROD, false>), dim3((unsigned)blocks), dim3(256), 0, st, g, groups, O, ldg, \
+                               (uint32_t)seed, (uint32_t)(seed >> 32), stream_id, vals, meta, pa, la);                          \
+    } while (0)
 #define NM_QUAD(M, EST, PROD)                                                                                                           \
     hipLaunchKernelGGL((prune_compress_quad_kernel<NM_DT_BF16, M, EST, PROD, true>), dim3((unsigned)((groups * O + 255) / 256)), dim3(256), 0, st, g, groups, O, \
                        ldg, (uint32_t)seed, (uint32_t)(seed >> 32), stream_id, vals, meta, pa, la)

@@ -260,3 +260,15 @@ def test_ragged_short_reductions_on_128_x_128_tiles(oracle, form, T):
     test_linear_update_matches_the_oracle(oracle, form, T, 2048, 1032)
     g, h = (torch.randn(T, n, device=DEV).to(torch.bfloat16) for n in (2048, 1032))
     assert any("update_gemm_smfmac_kernel<2, 2, 2, 2, false, true>" in n for n in kernels_of(lambda: api.nm_linear_update(g, h)))
+
+
+# beyond the prunes' small forms, a last wave that is not whole: plain stores up to 20 * 2^20 elements, streaming ones beyond and for whole waves
+@pytest.mark.parametrize("form,T,O,cached", [("2:4", 5121, 2056, True), ("relu", 10199, 2056, True), ("1:2", 7085, 1608, True), ("relu", 10201, 2056, False),
+                                             ("2:4", 5121, 2048, False)])
+def test_the_stores_of_a_last_wave_that_is_not_whole(oracle, form, T, O, cached):
+    from gpu_util import kernels_of
+    from paper_2203_10991_amd import api
+    test_linear_update_matches_the_oracle(oracle, form, T, O, 16)
+    g, h = torch.zeros(T, O, dtype=torch.bfloat16, device=DEV), torch.zeros(T, 16, dtype=torch.bfloat16, device=DEV)
+    names = kernels_of(lambda: api.nm_linear_update(g, h, nm="1:2" if form == "1:2" else "2:4", act=g if form == "relu" else None))
+    assert any(f"prune_layer_kernel<{2 if form == '1:2' else 4}, 0, {2 if form == 'relu' else 0}, {str(cached).lower()}>" in n for n in names)
