@@ -507,12 +507,16 @@ __global__ __launch_bounds__(256) void prune_layer_kernel(
 {
     prune_compress_body<NM_DT_BF16, M, EST, false, PROD, true, true, 4, true, CACHED>(g, n_groups, O, ldg, key0, key1, stream_id, vals, meta, nullptr, 0, pa, la);
 }
-template <int DT, int M, int EST>
+// The producer's form.  With plain loads and stores (NT false) where the last wave is not whole, up to 32 Mi elements: with the streaming ones such launches took,
+// plain -> streaming, 656 x 1144 11.7 -> 14.5 us, 672 x 1264 11.7 -> 16.7, 3024 x 1144 15.8 -> 18.4, 5408 x 1704 20.5 -> 23.4, 6000 x 5352 49.5 -> 51.4, beyond the line
+// 8944 x 8088 124 -> 112 (MVUE 2:4 in bf16; approx-MVUE and binary32 alike, MVUE 1:2 up to 1.3 of the time and, at 14032 x 5216, 0.83).
+constexpr int64_t PRODUCER_PLAIN_MOST = (int64_t)32 << 20;  // elements
+template <int DT, int M, int EST, bool NT>
 __global__ __launch_bounds__(256) void prune_producer_kernel(
     const void *__restrict__ u, int64_t n_groups, int64_t O, int64_t ldu, uint32_t key0, uint32_t key1, uint32_t stream_id,
     void *__restrict__ vals, uint16_t *__restrict__ meta, ProdArg pa)
 {
-    prune_compress_body<DT, M, EST, false, 1, false, true>(u, n_groups, O, ldu, key0, key1, stream_id, vals, meta, nullptr, 0, pa);
+    prune_compress_body<DT, M, EST, false, 1, false, NT>(u, n_groups, O, ldu, key0, key1, stream_id, vals, meta, nullptr, 0, pa);
 }
 // The bf16 optimal-2:4 kernel needs 98 registers as the compiler would have it, two more than let a fifth wave onto
 // each SIMD; asked for five waves it fits 96 without spilling.
@@ -1310,9 +1314,16 @@ hipError_t launch_prune_producer(int dt, int m, int est, const void *u, int64_t 
     const int64_t blocks = (threads + 255) / 256;
     if (blocks > 0x7fffffffll) return hipErrorInvalidConfiguration;
     const ProdArg pa{d, ldd, gout, ldgo};
-#define NM_PROD(DT, M, EST)                                                                                                     \
-    hipLaunchKernelGGL((prune_producer_kernel<DT, M, EST>), dim3((unsigned)blocks), dim3(256), 0, st, u, groups, O, ldu,        \
-                       (uint32_t)seed, (uint32_t)(seed >> 32), stream_id, vals, meta, pa)
+    const bool plain = threads % 64 && T * O <= PRODUCER_PLAIN_MOST;
+#define NM_PROD(DT, M, EST)                                                                                                             \
+    do {                                                                                                                                \
+        if (plain)                                                                                                                      \
+            hipLaunchKernelGGL((prune_producer_kernel<DT, M, EST, false>), dim3((unsigned)blocks), dim3(256), 0, st, u, groups, O, ldu, \
+                               (uint32_t)seed, (uint32_t)(seed >> 32), stream_id, vals, meta, pa);                                      \
+        else                                                                                                                            \
+            hipLaunchKernelGGL((prune_producer_kernel<DT, M, EST, true>), dim3((unsigned)blocks), dim3(256), 0, st, u, groups, O, ldu,  \
+                               (uint32_t)seed, (uint32_t)(seed >> 32), stream_id, vals, meta, pa);                                      \
+    } while (0)
     if (dt == NM_DT_F32) { if (m == 2) NM_PROD(NM_DT_F32, 2, 0); else if (est == 1) NM_PROD(NM_DT_F32, 4, 1); else NM_PROD(NM_DT_F32, 4, 0); }
     else { if (m == 2) NM_PROD(NM_DT_BF16, 2, 0); else if (est == 1) NM_PROD(NM_DT_BF16, 4, 1); else NM_PROD(NM_DT_BF16, 4, 0); }
 #undef NM_PROD

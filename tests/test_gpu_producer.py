@@ -89,3 +89,16 @@ def test_fused_producer_argument_errors():
         nm.mvue_prune_producer(torch.zeros((24, 8), dtype=torch.bfloat16, device=DEV), torch.zeros((24, 8), dtype=torch.bfloat16, device=DEV),
                                vals=torch.zeros((1, 8, 8), dtype=torch.bfloat16, device=DEV), meta=torch.zeros((1, 8), dtype=torch.int16, device=DEV))
     assert ei.value.status == 2
+
+
+# plain loads and stores where the last wave is not whole, up to 32 * 2^20 elements; whole waves and what lies beyond stream
+@pytest.mark.parametrize("T,O,dtype,streams", [(528, 72, "bf16", False), (528, 1024, "bf16", True), (48, 40, "f32", False), (64, 64, "f32", True), (16, 8, "bf16", False),
+                                               (8160, 4104, "bf16", False), (8192, 4104, "bf16", True), (8208, 4104, "f32", True)])
+@pytest.mark.parametrize("nmode", ["2:4", "1:2"])
+def test_whole_and_partly_filled_last_waves(oracle, dtype, nmode, T, O, streams):
+    import paper_2203_10991_amd as nm
+    from gpu_util import kernels_of
+    test_fused_producer_prune_bit_exact(oracle, dtype, nmode, 0, (T, O))
+    u = torch.zeros((T, O), dtype=torch.float32 if dtype == "f32" else torch.bfloat16, device=DEV)
+    names = kernels_of(lambda: nm.mvue_prune_producer(u, u, nm=nmode))
+    assert any("prune_producer_kernel<" in n and f", {str(streams).lower()}>" in n for n in names), names
