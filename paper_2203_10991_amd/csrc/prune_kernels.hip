@@ -510,9 +510,12 @@ __global__ __launch_bounds__(256) void prune_layer_kernel(
 // The producer's form.  With plain loads and stores (NT false) where the last wave is not whole, up to 32 Mi elements: with the streaming ones such launches took,
 // plain -> streaming, 656 x 1144 11.7 -> 14.5 us, 672 x 1264 11.7 -> 16.7, 3024 x 1144 15.8 -> 18.4, 5408 x 1704 20.5 -> 23.4, 6000 x 5352 49.5 -> 51.4, beyond the line
 // 8944 x 8088 124 -> 112 (MVUE 2:4 in bf16; approx-MVUE and binary32 alike, MVUE 1:2 up to 1.3 of the time and, at 14032 x 5216, 0.83).
+// Three waves per SIMD are what the streaming form's loads in flight are worth for MVUE 1:2 in bf16 and approx-MVUE in binary32 (153 and 148 registers); left to
+// itself the compiler, with the clamped last wave, takes 131 and 96 and more trips to memory: 1536 x 7680 20.9 -> 22.8 us, 512 x 512 13.3 -> 13.9, 12832 x 1408 58.9 -> 63.7.
 constexpr int64_t PRODUCER_PLAIN_MOST = (int64_t)32 << 20;  // elements
+constexpr bool producer_few_waves(int dt, int m, int est, bool nt) { return nt && (dt == NM_DT_BF16 ? m == 2 : est == 1); }
 template <int DT, int M, int EST, bool NT>
-__global__ __launch_bounds__(256) void prune_producer_kernel(
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, producer_few_waves(DT, M, EST, NT) ? 3 : 8))) void prune_producer_kernel(
     const void *__restrict__ u, int64_t n_groups, int64_t O, int64_t ldu, uint32_t key0, uint32_t key1, uint32_t stream_id,
     void *__restrict__ vals, uint16_t *__restrict__ meta, ProdArg pa)
 {
