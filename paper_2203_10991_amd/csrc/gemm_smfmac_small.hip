@@ -70,22 +70,40 @@ __device__ __forceinline__ void sum_and_store(f32x16 (&acc)[2][2], char *S, int 
     }
 }
 
+// Slab and tile of a workgroup.  Up to eight rows of tiles an XCD (every eighth workgroup) takes a run of all slabs' tiles, a column of tiles after the other, so that
+// those which read the same columns of h find them in their L2.  As the tile kernels deal them, in turn unless their number divides by eight, every XCD
+// read all of h: 9600 x 184 x 5424 79.7 -> 42.2 us, 20032 x 400 x 576 in four slabs 39.0 -> 24.3, in 8 bits 11968 x 88 x 7536 71.5 -> 40.7 and
+// 31648 x 192 x 544 in eight 28.8 -> 17.4; 0.95 of the time in the mean over 2494 plans.  With more rows a run holds part of a column, and is up to 1.11 times slower in
+// 8 bits (1056 x 616 x 5120 22.2 -> 24.7).
+__device__ __forceinline__ int slab_and_tile(int tiles_m, int tiles_n, int &tm, int &tn)
+{
+    int slab = (int)blockIdx.z;
+    if (tiles_m <= 8) {
+        const int n_tiles = tiles_m * tiles_n, id = (int)(blockIdx.z * gridDim.x + blockIdx.x), all = (int)(gridDim.x * gridDim.z), xcd = id % 8;
+        const int at = xcd * (all / 8) + min(xcd, all % 8) + id / 8;
+        slab = at / n_tiles;
+        tn = (at - slab * n_tiles) / tiles_m;
+        tm = at - slab * n_tiles - tn * tiles_m;
+    } else tile_of_workgroup((int)blockIdx.x, tiles_m, tiles_n, tm, tn);
+    tm = __builtin_amdgcn_readfirstlane(tm); tn = __builtin_amdgcn_readfirstlane(tn);
+    return __builtin_amdgcn_readfirstlane(slab);
+}
+
 // h_rows: rows h has, at most n_groups * 16; the rows past it and a token group past the end count as zeros
 __global__ __launch_bounds__(SM_WAVES * 64) void update_gemm_smfmac_small_kernel(const uint16_t *__restrict__ vals, const uint16_t *__restrict__ meta,
                                                                                const uint16_t *__restrict__ h, int64_t ldh, int64_t h_rows, float *__restrict__ out,
                                                                                int64_t ldo, int64_t slab_stride, int64_t n_groups, int64_t groups_per_slab, int64_t O,
                                                                                int64_t I, int tiles_m, int tiles_n, int accumulate)
 {
-    // this slab's operands and sums: blockIdx.z * groups_per_slab (even) is below n_groups
-    const int64_t g0 = (int64_t)blockIdx.z * groups_per_slab;
-    vals += g0 * O * 8; meta += g0 * O; h += g0 * 16 * ldh; out += (int64_t)blockIdx.z * slab_stride;
+    // this slab's operands and sums: slab * groups_per_slab (even) is below n_groups
+    int tm, tn;
+    const int slab = slab_and_tile(tiles_m, tiles_n, tm, tn);
+    const int64_t g0 = slab * groups_per_slab;
+    vals += g0 * O * 8; meta += g0 * O; h += g0 * 16 * ldh; out += slab * slab_stride;
     if (n_groups - g0 > groups_per_slab) { n_groups = groups_per_slab; h_rows = groups_per_slab * 16; }
     else { n_groups -= g0; h_rows -= g0 * 16; }
 
     __shared__ __attribute__((aligned(1024))) char S[SM_LDS];
-    int tm, tn;
-    tile_of_workgroup((int)blockIdx.x, tiles_m, tiles_n, tm, tn);
-    tm = __builtin_amdgcn_readfirstlane(tm); tn = __builtin_amdgcn_readfirstlane(tn);
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t m0 = (int64_t)tm * SM_TILE, n0 = (int64_t)tn * SM_TILE;
     const int steps = (int)((n_groups + 1) / 2), mine = (steps - wave + SM_WAVES - 1) / SM_WAVES;      // steps wave, wave + 8, ...
@@ -179,14 +197,13 @@ __global__ __launch_bounds__(SM_WAVES * 64) void update_gemm_q8_small_kernel(con
                                                                             int64_t slab_stride, int64_t n_groups, int64_t groups_per_slab, int64_t O, int64_t I,
                                                                             int tiles_m, int tiles_n, int accumulate, AlphaArg alpha)
 {
-    const int64_t g0 = (int64_t)blockIdx.z * groups_per_slab;           // (even, below n_groups)
-    vals += g0 * O * 16; meta += g0 * O; h += g0 * 32 * ldh; out += (int64_t)blockIdx.z * slab_stride;
+    int tm, tn;
+    const int slab = slab_and_tile(tiles_m, tiles_n, tm, tn);
+    const int64_t g0 = slab * groups_per_slab;                          // (even, below n_groups)
+    vals += g0 * O * 16; meta += g0 * O; h += g0 * 32 * ldh; out += slab * slab_stride;
     n_groups = min(n_groups - g0, groups_per_slab);
 
     __shared__ __attribute__((aligned(1024))) char S[S8_LDS];
-    int tm, tn;
-    tile_of_workgroup((int)blockIdx.x, tiles_m, tiles_n, tm, tn);
-    tm = __builtin_amdgcn_readfirstlane(tm); tn = __builtin_amdgcn_readfirstlane(tn);
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t m0 = (int64_t)tm * SM_TILE, n0 = (int64_t)tn * SM_TILE;
     const int steps = (int)((n_groups + 1) / 2), mine = (steps - wave + SM_WAVES - 1) / SM_WAVES;      // steps wave, wave + 8, ...

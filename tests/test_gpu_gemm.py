@@ -345,3 +345,10 @@ def test_a_wide_operand_stays_on_the_tile_kernels(nm, oracle, T, O, I):
     v, m, _ = nm.mvue_prune_2of4(to_dev(synth.make_g(w, 1)))
     h = to_dev(synth.make_h(w, 1))
     assert not any("small_kernel" in n for n in kernels_of(lambda: nm.nm_update_gemm(v, m, h)))
+
+
+# up to eight rows of tiles, whose XCDs take runs of all slabs' tiles: numbers of tiles that do not divide by eight, fewer than eight, one slab and several; nine rows
+@pytest.mark.parametrize("T,O,I,slabs", [(16, 72, 136, 1), (2096, 72, 712, 3), (4112, 120, 456, 6), (6000, 200, 328, 8), (1040, 456, 1096, 1), (8016, 520, 136, 8)])
+@pytest.mark.parametrize("beta", [0.0, 1.0])
+def test_small_tiles_dealt_over_the_xcds(nm, oracle, T, O, I, slabs, beta):
+    test_small_tiles_in_slabs(nm, oracle, T, O, I, slabs, beta)

@@ -163,6 +163,12 @@ def test_update_gemm_q8_small_kernel(nm, oracle, T, O, I, beta):
     assert any("update_gemm_q8_small_kernel" in n for n in kernels_of(lambda: nm.nm_update_gemm_q8(v, m, h8, alpha=1.0)))
 
 
+# up to eight rows of those tiles, whose XCDs take runs of all slabs' tiles: numbers of tiles that do not divide by eight, one slab and several; nine rows
+@pytest.mark.parametrize("T,O,I,beta", [(96, 72, 144, 0.0), (2080, 72, 720, 1.0), (4128, 120, 464, 0.0), (6016, 200, 336, 1.0), (1056, 456, 1104, 0.0), (8032, 520, 144, 0.0)])
+def test_update_gemm_q8_small_kernel_over_the_xcds(nm, oracle, T, O, I, beta):
+    test_update_gemm_q8_small_kernel(nm, oracle, T, O, I, beta)
+
+
 @pytest.mark.parametrize("T,O,I", [(160, 16 * 256, 16 * 256),            # 16 x 16 tiles of 256 x 256: the 2 x 4 XCD grid; odd group count
                                    (96, 50 * 256 - 40, 8 * 256),         # banded map with a short last band, ragged rows
                                    (32 * 14, 33 * 256, 8 * 256 - 16)])   # more than two trips of stages, ragged columns
