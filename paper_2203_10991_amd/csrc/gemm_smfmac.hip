@@ -665,7 +665,7 @@ hipError_t launch_splitk_reduce(const float *part, int slabs, float *dW, int64_t
 // ------------------------------------------------------------------------------------
 // tall_rows: rows [0, tall_rows) of dW are computed by the 384 x 256 kernel (tall_tiles_m tile rows), the rest by the
 // kernel of `shape` (tiles_m tile rows); 0 = that kernel alone.
-// us: predicted time where the plan weighs tiles against each other, else 0
+// us: predicted time but for the second pass where the plan weighs tiles against each other, else 0
 struct Plan { int shape; int tm, tn; int tiles_m, tiles_n; int slabs; int64_t groups_per_slab; int64_t tall_rows; int tall_tiles_m; double us; };
 constexpr int SMALL = 4;            // shape: 64 x 64 tiles, the tokens split over the waves (small_plan)
 
@@ -764,7 +764,7 @@ static Plan make_plan(int64_t T, int64_t O, int64_t I, bool shifted = false, boo
             const int64_t tiles4 = (O + 383) / 384 * ((I + 255) / 256);
             const double cost4 = one_per_cu(tiles4, 0.60, 0.76, 0.0, s4), best = take0 ? std::min(cost0, take3 ? cost3 : cost0) : take3 ? cost3 : cost1;
             auto fits = [&](int64_t sl) { return beside + splitk_workspace_bytes((int)sl, O, I) <= static_scratch_bytes(); };
-            p.us = best;
+            p.us = best - second_pass(slabs);
             if (!shifted && whole_rows && s4 > 1 && cost4 < 0.83 * best && fits(s4) == fits(slabs)) {
                 p.shape = 0; p.tm = 256; p.tn = 256;
                 p.tall_rows = O; p.tall_tiles_m = (int)((O + 383) / 384);
@@ -784,25 +784,27 @@ static Plan make_plan(int64_t T, int64_t O, int64_t I, bool shifted = false, boo
 // Small problems: the plan of the tile kernels, or 64 x 64 tiles with the tokens split over a workgroup's eight waves (gemm_smfmac_small.hip) and, for
 // long reductions, over at most eight slabs: never more than the tile kernels' plan, whose workspace a call is asked for whichever runs.  At most one
 // workgroup per CU (its LDS).  Up to 768 tokens it always measures faster (7.3-12.5 -> 4.7-8 us over sizes from 64 x 64 to 2400 x 250); beyond that by its
-// model -- 4.9 us, then per step of 32 tokens a wave 0.5 us, up to 0.75 with all CUs busy, or the tiles' operands at 14 TB/s (measured 14-18 on 256 tiles), or
-// one pass over the operands at 2.5 TB/s (its loads of a wide h are 128 bytes of a row: without this 5328 x 64 x 3152 took 18.9 -> 24.1 us), and the
-// second pass -- against that of the tile kernels, which is 3 us short at these sizes.  `parts`: a layer's call, where a finishing pass runs anyway, so that
-// one slab saves less.  1024^3 17 -> 7.6 us, 1536 x 512 x 2048 21.6 -> 9.2, 2048 x 1024 x 1024 19.7 -> 10.6, 4096 x 1024 x 1024 20.4 -> 15.0,
-// 8192 x 200 x 640 17.6 -> 13.  Against the tile kernels over 144 sizes from 272 to 8192 tokens, operands in no cache: none slower by more than 4 %
-// (with 6 TB/s for the tiles' operands, 30 of them, 7 % of the time in the mean over all, had stayed on the tile kernels).
+// model -- 2.4 us, then per step of 32 tokens a wave 0.86 us, up to 1.13 with all CUs busy, or one pass over the operands at 1.9 TB/s -- against that of the
+// tile kernels, which is 7 us short at these sizes, each with its second pass: none for one slab of a call, while a layer's call (`parts`) has its finishing
+// pass either way, which reads the slabs and writes bf16.  1024^3 17 -> 7.6 us, 1536 x 512 x 2048 21.6 -> 9.2, 2048 x 1024 x 1024 19.7 -> 10.6,
+// 8192 x 200 x 640 17.6 -> 13.  Over 900 sizes of 64 to 32768 tokens, operands in no cache and in the last-level one, as a call and in a layer: 0.74 and 0.80 of the tile
+// kernels' time in the mean, 0.01 above the faster of the two, one in 1700 slower than them by more than 4 %, the most 8.  (Constants that had been set on 144 calls,
+// with 14 TB/s for what the tiles read and no finishing pass for the other side, let 3618 x 368 -> 1304 take 28.0 us in a layer, now 25.5.)
 // (The offsets of its loads are 32 bits wide: 32 rows of h.)
 static Plan small_plan(Plan p, int64_t T, int64_t O, int64_t I, int64_t ldh, bool parts)
 {
     const int64_t groups = T / 16, tiles = (O + 63) / 64 * ((I + 63) / 64);
     if (groups == 0 || tiles > NM_CUS || ldh > (1 << 24)) return p;
+    auto second_pass = [&](int64_t sl) {
+        const double mb = (double)O * (double)I * 4e-6;
+        return parts ? ((double)sl + 0.5) * mb / 4.8 + (sl > 1 ? 1.0 : 0.0) : sl > 1 ? 4.9 + (double)(sl + 1) * mb / 4.8 : 0.0;
+    };
     int slabs = 0;
-    double best = groups < 48 ? 1e300 : p.us + 3.0;
+    double best = groups < 48 ? 1e300 : p.us + 7.1 + second_pass(p.slabs);
     for (const int s : {1, 2, 3, 4, 6, 8}) {
         if (s > p.slabs || s * tiles > NM_CUS) break;
         const int64_t steps = ((groups + s - 1) / s + 15) / 16;
-        const double loop = std::max({(double)steps * (0.5 + 0.25 * (double)(s * tiles) / NM_CUS), (double)tiles * (double)T * 200.0 / 14e6,
-                                      (double)T * ((double)I * 2.0 + (double)O * 1.125) / 2.5e6});
-        const double us = 4.9 + loop + (s > 1 ? 2.6 + (double)(s + 1) * (double)O * (double)I * 4.0 / 3.5e6 : parts && p.slabs > 1 ? 0.9 : 0.0);
+        const double us = 2.4 + std::max((double)steps * (0.86 + 0.27 * (double)(s * tiles) / NM_CUS), (double)T * ((double)I * 2.0 + (double)O * 1.125) / 1.92e6) + second_pass(s);
         if (us < best) {
             best = us;
             slabs = s;

@@ -352,3 +352,8 @@ def test_a_wide_operand_stays_on_the_tile_kernels(nm, oracle, T, O, I):
 @pytest.mark.parametrize("beta", [0.0, 1.0])
 def test_small_tiles_dealt_over_the_xcds(nm, oracle, T, O, I, slabs, beta):
     test_small_tiles_in_slabs(nm, oracle, T, O, I, slabs, beta)
+
+
+@pytest.mark.parametrize("T,O,I", [(5056, 5928, 80), (6048, 288, 2128), (6752, 520, 1376)])
+def test_many_tiles_along_one_side_stay_on_the_tile_kernels(nm, oracle, T, O, I):
+    test_a_wide_operand_stays_on_the_tile_kernels(nm, oracle, T, O, I)

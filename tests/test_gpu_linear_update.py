@@ -272,3 +272,14 @@ def test_the_stores_of_a_last_wave_that_is_not_whole(oracle, form, T, O, cached)
     g, h = torch.zeros(T, O, dtype=torch.bfloat16, device=DEV), torch.zeros(T, 16, dtype=torch.bfloat16, device=DEV)
     names = kernels_of(lambda: api.nm_linear_update(g, h, nm="1:2" if form == "1:2" else "2:4", act=g if form == "relu" else None))
     assert any(f"prune_layer_kernel<{2 if form == '1:2' else 4}, 0, {2 if form == 'relu' else 0}, {str(cached).lower()}>" in n for n in names)
+
+
+# sizes at which a layer, whose finishing pass runs either way, is faster on the tile kernels than on 64 x 64 tiles with the tokens split over the waves
+@pytest.mark.parametrize("T,O,I", [(3104, 264, 1824), (4076, 1880, 352), (5470, 320, 3120)])
+def test_layers_that_stay_on_the_tile_kernels(oracle, T, O, I):
+    from gpu_util import kernels_of
+    from paper_2203_10991_amd import api
+    test_linear_update_matches_the_oracle(oracle, "2:4", T, O, I)
+    g, h = (torch.randn(T, n, device=DEV).to(torch.bfloat16) for n in (O, I))
+    names = kernels_of(lambda: api.nm_linear_update(g, h))
+    assert any("update_gemm" in n for n in names) and not any("small_kernel" in n for n in names)
