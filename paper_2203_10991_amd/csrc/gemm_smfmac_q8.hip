@@ -633,25 +633,28 @@ static AlphaPair encode_alpha(int accumulate, const AlphaArg &al, hipStream_t st
 }
 
 // Small problems: 64 x 64 tiles with the tokens split over a workgroup's eight waves (gemm_smfmac_small.hip), as in the 16-bit path, by two models in
-// microseconds.  The tile kernels: 10.5 and 1.6 for every trip of their ring, whatever the tile.  The small one: 4.7, then for a wave's step of 64 tokens
-// 0.45 alone, 0.85 from 48 workgroups on, never less than the tiles' operands at 12.5 TB/s or one pass over the operands at 3, and a round more for
-// every 256 workgroups.  Both: the second pass.  Within 15 % of what 77
-// sizes from 32 to 16384 tokens and from 64 x 64 to 4088 x 288 took (operands in no cache), so a margin of 10 %.  At most the tile kernels'
-// slabs, whose workspace a call is asked for whichever runs.  Tile kernels -> this, us: 256 x 512 x 512 12.8 -> 5.1, 1024^3 21.2 -> 7.6,
-// 2048 x 1024 x 1024 24.8 -> 9.3, 8192 x 512 x 512 23.2 -> 13 (4 slabs), 1024 x 2112 x 976 25.0 -> 18.4; stays: 4096 x 2112 x 976 28.6 (34.7).
-static PlanQ8 small_plan_q8(PlanQ8 p, int64_t T, int64_t O, int64_t I, int64_t ldh)
+// microseconds.  The tile kernels: 12.5 and 1.6 for every trip of their ring, whatever the tile.  The small one: 2.5, then for a wave's step of 64 tokens
+// 0.87 alone, 1.29 with all CUs busy, or one pass over the operands at 6.7 TB/s, and 5.2 more for every round of workgroups behind the first.  Both with their
+// second pass, as in the 16-bit path (`parts`: a layer's call).  At most the tile kernels' slabs, whose workspace a call is asked for whichever runs.
+// Tile kernels -> this, us: 256 x 512 x 512 12.8 -> 5.1, 1024^3 21.2 -> 7.4, 2048 x 1024 x 1024 24.8 -> 9.3, 8192 x 512 x 512 23.2 -> 13 (4 slabs),
+// 1024 x 2112 x 976 25.0 -> 18.4; stays: 4096 x 2112 x 976 28.6 (34.7).  Over 900 sizes of 64 to 32768 tokens, operands in no cache and in the last-level one, as a call and in
+// a layer: 0.67 and 0.74 of the tile kernels' time in the mean, 0.006 above the faster of the two, one in 300 slower by more than 4 %, the most 12
+// (7872 x 72 x 4432 24.0 -> 26.8).  (Without the finishing pass on both sides a layer of 1152 x 1712 -> 2240 took 45 us instead of 37, 2979 x 2080 -> 760 44 instead of 38.)
+static PlanQ8 small_plan_q8(PlanQ8 p, int64_t T, int64_t O, int64_t I, int64_t ldh, bool parts)
 {
     const int64_t groups = T / 32, tiles = (O + 63) / 64 * ((I + 63) / 64);
     if (groups == 0 || tiles > 4 * NM_CUS || p.tall_rows > 0 || ldh > (1 << 24)) return p;          // (offsets of 32 bits: 64 rows of h8)
-    auto second_pass = [&](int64_t sl) { return sl > 1 ? 2.6 + (double)(sl + 1) * (double)O * (double)I * 4.0 / 3.5e6 : 0.0; };
-    double least = 0.9 * (10.5 + 1.6 * (double)((p.groups_per_slab < groups ? p.groups_per_slab : groups) + 11) / 12.0 + second_pass(p.slabs));
+    auto second_pass = [&](int64_t sl) {
+        const double mb = (double)O * (double)I * 4e-6;
+        return parts ? ((double)sl + 0.5) * mb / 5.0 + (sl > 1 ? 1.0 : 0.0) : sl > 1 ? 4.25 + (double)(sl + 1) * mb / 5.0 : 0.0;
+    };
+    double least = 12.5 + 1.6 * (double)(((p.groups_per_slab < groups ? p.groups_per_slab : groups) + 11) / 12) + second_pass(p.slabs);
     int slabs = 0;
     for (const int s : {1, 2, 3, 4, 6, 8}) {
         const int64_t wgs = s * tiles, rounds = (wgs + NM_CUS - 1) / NM_CUS, steps = ((groups + s - 1) / s + 15) / 16;
         if (s > p.slabs || (s > 1 && rounds > 1)) break;
-        const double loop = std::max({(double)(rounds * steps) * (0.45 + 0.4 * std::min(1.0, (double)wgs / 48.0)), (double)tiles * (double)T * 104.0 / 12.5e6,
-                                      (double)T * ((double)I + (double)O * 0.625) / 3e6});
-        const double us = 0.6 + 4.1 * (double)rounds + loop + second_pass(s);
+        const double loop = std::max((double)(rounds * steps) * (0.87 + 0.42 * std::min(1.0, (double)wgs / NM_CUS)), (double)T * ((double)I + (double)O * 0.625) / 6.7e6);
+        const double us = 2.5 + 5.2 * (double)(rounds - 1) + loop + second_pass(s);
         if (us < least) { least = us; slabs = s; }
     }
     if (slabs > 0) {
@@ -699,7 +702,7 @@ hipError_t launch_update_gemm_q8(const uint8_t *vals8, const uint32_t *meta32, c
                                  hipStream_t st)
 {
     if (O == 0 || I == 0) return hipSuccess;
-    const PlanQ8 p = small_plan_q8(make_plan_q8(T, O, I), T, O, I, ldh);
+    const PlanQ8 p = small_plan_q8(make_plan_q8(T, O, I), T, O, I, ldh, false);
     const int accumulate = beta != 0.f;
     const OutTarget tg = splitk_target(p.slabs, dW, lddw, workspace, O, I, accumulate);
     // partial sums are scaled once, in the second pass; otherwise the kernels scale, by a host or a device value
@@ -717,7 +720,7 @@ size_t update_gemm_q8_parts_bytes(int64_t T, int64_t O, int64_t I)
 hipError_t launch_update_gemm_q8_parts(const uint8_t *vals8, const uint32_t *meta32, const uint8_t *h8, int64_t ldh, int64_t T, int64_t O,
                                        int64_t I, float *part, int *slabs, hipStream_t st)
 {
-    const PlanQ8 p = small_plan_q8(make_plan_q8(T, O, I), T, O, I, ldh);
+    const PlanQ8 p = small_plan_q8(make_plan_q8(T, O, I), T, O, I, ldh, true);
     *slabs = p.slabs;
     return run_q8_plan(p, OutTarget{part, I, O * I, 0}, AlphaArg{}, vals8, meta32, h8, ldh, T, O, I, st);
 }

@@ -283,3 +283,13 @@ def test_layers_that_stay_on_the_tile_kernels(oracle, T, O, I):
     g, h = (torch.randn(T, n, device=DEV).to(torch.bfloat16) for n in (O, I))
     names = kernels_of(lambda: api.nm_linear_update(g, h))
     assert any("update_gemm" in n for n in names) and not any("small_kernel" in n for n in names)
+
+
+@pytest.mark.parametrize("T,O,I", [(1152, 2240, 1712), (2979, 760, 2080), (1576, 768, 3072), (12162, 360, 1888)])
+def test_8_bit_layers_that_stay_on_the_tile_kernels(oracle, T, O, I):
+    from gpu_util import kernels_of
+    from paper_2203_10991_amd import api
+    test_linear_update_matches_the_oracle(oracle, "q8", T, O, I)
+    g, h = (torch.randn(T, n, device=DEV).to(torch.bfloat16) for n in (O, I))
+    names = kernels_of(lambda: api.nm_linear_update(g, h, q8=True))
+    assert any("update_gemm" in n for n in names) and not any("small_kernel" in n for n in names)

@@ -244,3 +244,20 @@ def test_prune_1of2_q8_feeds_the_8_bit_gemm(nm, oracle):
     rel = float((np.abs(got - want) / np.maximum(wabs, 1e-300)).max())
     print(f"1:2 q8 gemm: max |err|/sum|ab| = {rel:.3e}", flush=True)
     assert rel <= TOL
+
+
+# the tile kernels where the small one leaves them the call: 128 x 256 tiles in one pass, in two, five and ten slabs (one chain to a sum) and in more (eight threads or
+# eight chains to a sum), 64 x 256 tiles, of which no plan has a single slab
+@pytest.mark.parametrize("T,O,I,beta,tile,second", [
+    (32, 1168, 1680, 0.0, "2, 4, 2, 2", None), (32, 1176, 1680, 1.0, "2, 4, 2, 2", None), (768, 2208, 1488, 1.0, "2, 4, 2, 2", "1, 1"), (3104, 800, 1232, 0.0, "2, 4, 2, 2", "1, 1"),
+    (10976, 200, 2112, 0.0, "2, 4, 2, 2", "1, 1"), (3584, 176, 6368, 0.0, "2, 4, 2, 2", "1, 1"), (66496, 264, 16, 1.0, "2, 4, 2, 2", "8, 1"), (55296, 72, 16, 0.0, "2, 4, 2, 2", "8, 1"), (28576, 72, 1440, 1.0, "2, 4, 2, 2", "1, 8"),
+    (58496, 104, 736, 0.0, "2, 4, 2, 2", "1, 8"), (65888, 8, 528, 0.0, "1, 4, 2, 2", "8, 1"), (53376, 8, 16, 1.0, "1, 4, 2, 2", "8, 1"), (49664, 40, 2144, 0.0, "1, 4, 2, 2", "1, 8")])
+def test_update_gemm_q8_tile_kernels(nm, oracle, T, O, I, beta, tile, second):
+    from gpu_util import kernels_of
+    gemm_case(nm, oracle, T, O, I, seed=T + O, beta=beta)
+    v, m = nm.alloc_compressed_q8(T, O, DEV)
+    v.zero_(); m.fill_(0x44444444)
+    h8, dW = torch.zeros(T, I, dtype=torch.uint8, device=DEV), torch.zeros(O, I, device=DEV)
+    names = kernels_of(lambda: nm.nm_update_gemm_q8(v, m, h8, dW=dW, alpha=1.0, beta=beta))
+    assert any(f"update_gemm_smfmac_q8_kernel<{tile}, false>" in n for n in names), names
+    assert any("splitk_reduce" in n for n in names) == (second is not None) and (second is None or any(f"splitk_reduce_kernel<{second}>" in n for n in names))

@@ -122,6 +122,29 @@ def test_device_scale_entry_points_equal_the_host_scale_ones(oracle, nmode):
     assert torch.equal(a, b)
 
 
+# scales in device memory through every kernel that applies them: the small one, 128 x 256 and 256 x 256 tiles in one pass, tiles in slabs (the second pass scales), 384 x 256
+# tiles, which find the product of the two where a launch in front of them leaves it, beside 256 x 256 ones, which multiply them
+@pytest.mark.parametrize("T,O,I,kernels", [(640, 184, 144, ["q8_small"]), (32, 1168, 1680, ["q8_kernel<2, 4, 2, 2"]), (160, 4096, 4096, ["q8_kernel<2, 4, 4, 2"]),
+                                           (4128, 2040, 2000, ["q8_kernel<2, 4, 2, 2", "splitk_reduce"]), (65888, 8, 528, ["q8_kernel<1, 4, 2, 2", "splitk_reduce"]),
+                                           (96, 8240, 4096, ["alpha_product", "q8_tall", "q8_kernel<2, 4, 4, 2"])])
+@pytest.mark.parametrize("beta", [0.0, 1.0])
+def test_device_scales_in_every_gemm_kernel(T, O, I, kernels, beta):
+    import paper_2203_10991_amd as nm
+    from gpu_util import kernels_of
+    torch.manual_seed(T)
+    g, h = (torch.randn(T, n, device=DEV).to(torch.bfloat16) for n in (O, I))
+    rg, rh = nm.nm_q8_scale(g, 57344.0 / 4.0), nm.nm_q8_scale(h, 448.0)
+    v, m = nm.mvue_prune_2of4_q8(g, seed=1, scale=rg)
+    h8, prior = nm.nm_cast_e4m3(h, rh), torch.randn(O, I, device=DEV)
+    alpha = float(rg.cpu()[1]) * float(rh.cpu()[1])
+
+    def product(a):
+        return nm.nm_update_gemm_q8(v, m, h8, dW=prior.clone(), alpha=a, beta=beta)
+    assert alpha != 1.0 and torch.equal(product((rg, rh)), product(alpha))
+    names = kernels_of(lambda: product((rg, rh)))
+    assert all(any(k in n for n in names) for k in kernels), names
+
+
 def test_scale_and_cast_argument_errors():
     import paper_2203_10991_amd as nm
     t = torch.zeros((4, 12), dtype=torch.float32, device=DEV)
