@@ -338,8 +338,8 @@ __global__ __launch_bounds__(WM * WN * 64) void dense_gemm_kernel(DenseArg p)
 // The eight waves with four stages are for one round of at most 256 tiles, which two stages of 128 x 128 spend waiting (0.85 us a stage, of which 0.2 is matrix
 // work) and smaller tiles on more operand bytes: 7478 x 1568 -> 384 23.6 -> 17.6 us (the vendor library 21.0), input gradient 21.7 -> 17.0 (25.5);
 // 2774 x 2976 -> 944 40 -> 30 (33), 1881 x 2216 -> 1680 35.7 -> 27.7 (29.9), 931 x 1104 -> 2544 19.4 -> 13.6 (18.0).  Over 230 products of 2e8 to 1.3e10
-// multiply-adds the choice takes 0.967 of what it took without, none more than 1.02, and 1.017 of the fastest tile's time.  (With 181 to 256 tiles over fewer
-// than 24 stages it would be up to 25 % faster too; those stay on the smaller tiles, whose way from one tile to the next is checked at such sizes.)
+// multiply-adds the choice takes 0.967 of what it took without, none more than 1.02; over 226 of 181 to 256 tiles and fewer than 24 stages 0.928, none more than
+// 1.03 (2130 x 1440 -> 1400 22.8 -> 17.3 us, 935 x 1288 -> 3088 26.1 -> 17.4, 8096 x 1112 -> 376 20.2 -> 15.2, 7343 x 320 -> 496 11.4 -> 8.5).
 hipError_t launch_dense_gemm(bool nn, const void *x, int64_t ldx, const void *w, const void *bias, void *y, int64_t ldy, int64_t M, int64_t N, int64_t K,
                              bool relu, hipStream_t st)
 {
@@ -352,7 +352,7 @@ hipError_t launch_dense_gemm(bool nn, const void *x, int64_t ldx, const void *w,
     for (int i = 0; i < 5; ++i) {
         const Tile &t = tiles[i];
         const int64_t n = ((M + t.tm - 1) / t.tm) * ((N + t.tn - 1) / t.tn), round = (int64_t)t.per_cu * NM_CUS, left = n % round;
-        if (i == 3 && (n > NM_CUS || (n > 180 && stages < 24.0))) continue;
+        if (i == 3 && n > NM_CUS) continue;
         const double part = t.per_cu == 1 ? t.alone + (t.shared - t.alone) * (double)left / NM_CUS : left <= NM_CUS ? t.alone : t.shared;
         const double cost = (double)(n / round) * (stages * t.shared + t.round) + (left ? stages * part + t.round : 0.0);
         if (cost < least) { least = cost; best = i; }
