@@ -121,3 +121,30 @@ def test_last_wave_partly_filled(oracle, T, O, which):
         (v, m, _), (ov, om, _) = nm.mvue_prune_1of2(to_dev(g), seed=2, stream_id=1), oracle.prune_1of2(g, 2, 1)
     u = np.uint32 if which == "f32" else np.uint16
     assert np.array_equal(to_host(m), om) and np.array_equal(to_host(v).view(u), ov.view(u))
+
+
+# a last wave that is not whole, in each kernel that stores through descriptors: both forms of the one with four columns to a thread, the ones for large tensors of each
+# estimator, Greedy and MVUE 1:4 at any size; what lies behind the outputs stays as it is
+@pytest.mark.parametrize("which,T,O", [("2of4", 4112, 2568), ("1of2", 10256, 1032), ("2of4", 12208, 1736), ("1of2", 12208, 1736), ("2of4", 16400, 4104), ("approx", 16400, 4104),
+                                       ("1of4", 48, 72), ("1of4", 16, 8), ("greedy2of4", 48, 72), ("greedy1of2", 16, 8), ("f32_1of2", 1040, 2056), ("f32_2of4", 10256, 4104),
+                                       ("f32_approx", 10256, 4104), ("f32_1of4", 48, 72), ("f32_greedy2of4", 16, 8)])
+def test_nothing_behind_the_outputs_is_written(oracle, which, T, O):
+    import paper_2203_10991_amd as nm
+    f32, form = which.startswith("f32_"), which.split("_")[-1]
+    g = _f32(T, O, 3) if f32 else _g(T, O, 3)
+    n, dt = T // 2 * O, torch.float32 if f32 else torch.bfloat16
+    vb, mb = torch.full((n + 8192,), 7.0, dtype=dt, device=DEV), torch.full((T // 16 * O + 8192,), 0x1234, dtype=torch.int16, device=DEV)
+    out = {"vals": vb[:n].view(T // 16, O, 8), "meta": mb[:T // 16 * O].view(T // 16, O)}
+    if form.startswith("greedy"):
+        k, m = int(form[6]), int(form[-1])
+        nm.nm_prune_greedy(to_dev(g), k, m, **out)
+        ov, om, _ = oracle.prune_greedy(g, k, m)
+    elif form == "approx":
+        nm.mvue_prune_2of4(to_dev(g), seed=2, stream_id=1, mode=1, **out)
+        ov, om, _ = oracle.prune_2of4_approx(g, 2, 1)
+    else:
+        {"1of2": nm.mvue_prune_1of2, "2of4": nm.mvue_prune_2of4, "1of4": nm.mvue_prune_1of4}[form](to_dev(g), seed=2, stream_id=1, **out)
+        ov, om, _ = {"1of2": oracle.prune_1of2, "2of4": oracle.prune_2of4, "1of4": oracle.prune_1of4}[form](g, 2, 1)
+    u = np.uint32 if f32 else np.uint16
+    assert np.array_equal(to_host(out["meta"]), om) and np.array_equal(to_host(out["vals"]).view(u), ov.view(u))
+    assert bool((vb[n:] == 7.0).all()) and bool((mb[T // 16 * O:] == 0x1234).all())
