@@ -789,7 +789,7 @@ static Plan make_plan(int64_t T, int64_t O, int64_t I, bool shifted = false, boo
 // pass either way, which reads the slabs and writes bf16.  1024^3 17 -> 7.6 us, 1536 x 512 x 2048 21.6 -> 9.2, 2048 x 1024 x 1024 19.7 -> 10.6,
 // 8192 x 200 x 640 17.6 -> 13.  Over 900 sizes of 64 to 32768 tokens, operands in no cache and in the last-level one, as a call and in a layer: 0.74 and 0.80 of the tile
 // kernels' time in the mean, 0.01 above the faster of the two, one in 1700 slower than them by more than 4 %, the most 8.  (Constants that had been set on 144 calls,
-// with 14 TB/s for what the tiles read and no finishing pass for the other side, let 3618 x 368 -> 1304 take 28.0 us in a layer, now 25.5.)
+// with 14 TB/s for what the tiles read and no finishing pass for the other side, let 3618 x 368 -> 1304 take 27.9 us in a layer, 25.3 before and 23.7 now.)
 // (The offsets of its loads are 32 bits wide: 32 rows of h.)
 static Plan small_plan(Plan p, int64_t T, int64_t O, int64_t I, int64_t ldh, bool parts)
 {

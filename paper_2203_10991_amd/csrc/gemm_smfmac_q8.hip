@@ -611,7 +611,7 @@ static PlanQ8 make_plan_q8(int64_t T, int64_t O, int64_t I, bool shifted = false
 }
 
 // alpha = rec_a[1] * rec_b[1], left in rec_b[3] (the consumer's scratch slot of a scale record) for the 384 x 256 kernel; the others multiply the
-// two themselves (a launch in front of them cost 4 us, of 13.8 for the smallest products)
+// two themselves (a launch in front of them cost 1.5 to 2.5 us a call)
 __global__ void q8_alpha_product_kernel(const float *rec_a, float *rec_b)
 {
     if (threadIdx.x == 0) rec_b[3] = rec_a[1] * rec_b[1];
@@ -638,7 +638,7 @@ static AlphaPair encode_alpha(int accumulate, const AlphaArg &al, hipStream_t st
 // second pass, as in the 16-bit path (`parts`: a layer's call).  At most the tile kernels' slabs, whose workspace a call is asked for whichever runs.
 // Tile kernels -> this, us: 256 x 512 x 512 12.8 -> 5.1, 1024^3 21.2 -> 7.4, 2048 x 1024 x 1024 24.8 -> 9.3, 8192 x 512 x 512 23.2 -> 13 (4 slabs),
 // 1024 x 2112 x 976 25.0 -> 18.4; stays: 4096 x 2112 x 976 28.6 (34.7).  Over 900 sizes of 64 to 32768 tokens, operands in no cache and in the last-level one, as a call and in
-// a layer: 0.67 and 0.74 of the tile kernels' time in the mean, 0.006 above the faster of the two, one in 300 slower by more than 4 %, the most 12
+// a layer: 0.68 and 0.74 of the tile kernels' time in the mean, 0.006 above the faster of the two, one in 300 slower by more than 4 %, the most 12
 // (7872 x 72 x 4432 24.0 -> 26.8).  (Without the finishing pass on both sides a layer of 1152 x 1712 -> 2240 took 45 us instead of 37, 2979 x 2080 -> 760 44 instead of 38.)
 static PlanQ8 small_plan_q8(PlanQ8 p, int64_t T, int64_t O, int64_t I, int64_t ldh, bool parts)
 {
@@ -671,7 +671,7 @@ size_t update_gemm_q8_workspace(int64_t T, int64_t O, int64_t I)
     return splitk_workspace_bytes(make_plan_q8(T, O, I).slabs, O, I);
 }
 
-// The kernels of a plan, into `tg`, scaled by `ap`
+// The kernels of a plan, into `tg`, scaled by `alpha`
 static hipError_t run_q8_plan(const PlanQ8 &p, const OutTarget &tg, const AlphaArg &alpha, const uint8_t *vals8, const uint32_t *meta32,
                               const uint8_t *h8, int64_t ldh, int64_t T, int64_t O, int64_t I, hipStream_t st)
 {
@@ -731,7 +731,7 @@ size_t update_gemm_q8_shifted_workspace(int64_t T, int64_t O, int64_t I)
     return splitk_workspace_bytes(make_plan_q8(T, O, I, true).slabs, O, I);
 }
 
-// The kernels of a plan on the shift table, into `tg`, scaled by `ap`
+// The kernels of a plan on the shift table, into `tg`, scaled by `alpha`
 static hipError_t run_q8_shifted(const PlanQ8 &p, const OutTarget &tg, const AlphaArg &alpha, const uint8_t *vals8, const uint32_t *meta32,
                                  const uint8_t *x8, int64_t ldx, int64_t cb, const int64_t *rows, int n, int64_t T, int64_t O, hipStream_t st)
 {

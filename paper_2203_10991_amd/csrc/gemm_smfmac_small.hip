@@ -189,7 +189,7 @@ __global__ __launch_bounds__(SM_WAVES * 64) void update_gemm_smfmac_small_kernel
 // The same for 8-bit operands.  A step is 64 tokens: h8 [64 tokens][64 columns] bytes, chunk c (16 columns) of row k at position c ^ 2 (k / 4 % 2) (a transposing
 // read touches the same 32 bytes of eight consecutive rows, of which every fourth one shares the banks), vals8 as above, then the index words [2 groups][64 rows].
 // The tile kernels take 14 us for anything of up to 384 tokens (six stages and a barrier each, however few are needed):
-// 256 x 512 x 512 12.8 -> 5.1, 1024^3 21.2 -> 7.6.  A wave's step is bound by the way to its operands, 0.45 us alone and 0.8-1.15 with all CUs busy.
+// 256 x 512 x 512 12.8 -> 5.1, 1024^3 21.2 -> 7.4.  A wave's step is bound by the way to its operands, 0.45 us alone and 0.8-1.15 with all CUs busy.
 constexpr int S8_A = 64 * SM_TILE, S8_M = S8_A + 2 * SM_TILE * 16, S8_STEP = S8_M + 2 * SM_TILE * 4, S8_LOADS = 8;       // direct loads of a step: 4 h8, 2 vals8, 2 index words
 constexpr int S8_LDS = SM_WAVES * SM_RING * S8_STEP > SM_SUMS ? SM_WAVES * SM_RING * S8_STEP : SM_SUMS;
 static_assert(S8_LDS <= 160 * 1024 && S8_STEP % 256 == 0, "LDS");

@@ -10,8 +10,8 @@
 namespace nm {
 
 // Output scale of the 8-bit update GEMM: a host value, or (inv_a != nullptr) value * inv_a[1] * inv_b[1] with the two
-// factors read on the device -- element [1] of a scale record written by launch_q8_scale is the inverse scale; the
-// GEMM launchers leave that product in inv_b[3] (the record's scratch slot) for their kernels.
+// factors read on the device -- element [1] of a scale record written by launch_q8_scale is the inverse scale.  The kernels
+// multiply them; for the 384 x 256 one the launcher leaves the product in inv_b[3] (the record's scratch slot).
 struct AlphaArg {
     float value;
     const float *inv_a, *inv_b;
