@@ -26,8 +26,8 @@ def _padded(t, m):
     return torch.nn.functional.pad(t, (0, 0, 0, (-t.shape[0]) % m))
 
 
-# T (ragged and not), O, I: bf16 64x64 tiles with the tokens split over the waves, in one slab and in several; 256x128 and 256x256 tiles (8 waves); 8-bit
-# 128x128 tiles in one pass and in slabs
+# T (ragged and not), O, I: 64x64 tiles with the tokens split over the waves, in one slab and in several, in 8 bits up to two rounds of them; bf16 128x128 tiles in slabs
+# and 256x128 ones; 8-bit 128x256 tiles
 SHAPES = [(1, 8, 16), (15, 72, 48), (16, 64, 64), (17, 136, 80), (33, 256, 128), (1576, 256, 128), (3001, 128, 64), (2047, 2048, 1024), (3183, 3072, 1536)]
 
 

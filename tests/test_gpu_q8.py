@@ -148,7 +148,7 @@ def test_update_gemm_q8_matches_fp64_oracle(nm, oracle, T, O, I):
 
 def test_update_gemm_q8_beta_one_and_relu_activations(nm, oracle):
     gemm_case(nm, oracle, 32 * 9, 200, 272, seed=5, beta=1.0, relu=True)
-    gemm_case(nm, oracle, 4096, 64, 576, seed=6, beta=1.0)             # few rows, split-K
+    gemm_case(nm, oracle, 4096, 64, 576, seed=6, beta=1.0)             # few rows, slabs
 
 
 # 64 x 64 tiles with the tokens split over the waves: one group, an odd number of groups in one and in many steps, ragged rows and columns, tiles for more
@@ -186,12 +186,10 @@ def test_update_gemm_q8_mid_sized_plans(nm, oracle, T, O, I, slabs, beta):
     gemm_case(nm, oracle, T, O, I, seed=T, beta=beta, sample=10)
 
 
-@pytest.mark.parametrize("T,O,I,slabs", [(32 * 132, 64, 64, 11),             # second pass over partial sums: one chain of eleven slabs
-                                         (32 * 280, 64, 80, 12),             # ... eight threads to a sum, twelve slabs: four of them hold two
-                                         (32 * 552, 72, 272, 46),            # ... a last trip of six
-                                         (32 * 1680, 64, 64, 140),           # ... a last trip of four
-                                         (32 * 280, 296, 256, 12),           # ... too many sums for that: eight chains to a thread
-                                         (32 * 1680, 296, 256, 70)])         # ... a last trip of six
+# second passes over the partial sums of up to eight slabs of 64 x 64 tiles, and of 140 slabs of the tile kernels (eight threads to a sum); slabs: what the tile
+# kernels' plan asks for as workspace (the forms of the second pass that more slabs take: test_update_gemm_q8_tile_kernels)
+@pytest.mark.parametrize("T,O,I,slabs", [(32 * 132, 64, 64, 11), (32 * 280, 64, 80, 12), (32 * 552, 72, 272, 46), (32 * 1680, 64, 64, 140), (32 * 280, 296, 256, 12),
+                                         (32 * 1680, 296, 256, 70)])
 def test_second_pass_over_partial_sums(nm, oracle, T, O, I, slabs):
     from paper_2203_10991_amd import api
     assert api.nm_update_gemm_q8_workspace(T, O, I) == slabs * O * I * 4
@@ -211,7 +209,7 @@ def _random_shapes(n, seed):
 
 @pytest.mark.parametrize("T,O,I", _random_shapes(12, 77))
 def test_update_gemm_q8_random_shapes(nm, oracle, T, O, I):
-    """seeded random problem sizes through every branch of the 8-bit split-K plan"""
+    """seeded random problem sizes, which all run on 64 x 64 tiles, in one slab and in up to six"""
     gemm_case(nm, oracle, T, O, I, seed=T + O)
 
 
